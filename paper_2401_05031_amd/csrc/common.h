@@ -34,8 +34,15 @@ template <typename T> __device__ inline void store_vec(T* p, const Vec<T>& v) {
   *reinterpret_cast<Vec<T>*>(p) = v;
 }
 
+template <typename T> struct alignas(4 * sizeof(T)) Quad { T x[4]; };   // 4 consecutive elements, one load
+template <typename T> struct alignas(8 * sizeof(T)) Oct { T x[8]; };    // 8 consecutive elements, one load
+
 __device__ inline float to_float(float x) { return x; }
 __device__ inline float to_float(bf16_t x) { return (float)x; }
+template <typename T> __device__ inline floatx4 load4(const T* p) {   // four elements widened
+  const Quad<T> v = *reinterpret_cast<const Quad<T>*>(p);
+  return floatx4{to_float(v.x[0]), to_float(v.x[1]), to_float(v.x[2]), to_float(v.x[3])};
+}
 template <typename T> __device__ inline T from_float(float x);
 template <> __device__ inline float from_float<float>(float x) { return x; }
 template <> __device__ inline bf16_t from_float<bf16_t>(float x) { return (bf16_t)x; }

@@ -2,8 +2,8 @@
 // the concatenated heads, and the MLP):  Y[M,N] = epilogue(X[M,K] W[N,K]^T + bias[N]).
 //
 // Kernels:
-//   * gemm_valu_kernel  -- plain fp32 FMA tiles; the true-fp32 path (f32 models) and the fallback
-//                          for shapes the MFMA kernels do not take.
+//   * gemm_f32_kernel, gemm_f32_small_kernel -- true fp32 on the matrix cores: f32 models, and the fallback for bf16
+//                          shapes the bf16 kernels do not take.
 //   * bf16 MFMA (v_mfma_f32_32x32x16_bf16), fp32 accumulate, operand tiles loaded straight into
 //     swizzled LDS stages, fused bias / GELU / residual epilogue (bf16 models):
 //       gemm_mfma_k32_kernel     128 x 128, K step 32, three workgroups per CU (also split-K)
@@ -38,83 +38,263 @@ __device__ inline float epilogue_value(float acc, float bias, const float* res, 
   return v;
 }
 
-// ------------------------------------------------------------------------------ fp32 FMA tiles
-// 64x64 output tile, K step 16, 256 threads, 4x4 outputs per thread, operands converted to fp32
-// in LDS ([k][row] layout so that the inner product walks consecutive rows).
+// ------------------------------------------------------------------------------ true fp32 on the matrix cores
+// f32 models, and the fallback for bf16 shapes the bf16 MFMA kernels do not take (operands widened on the way in):
+// v_mfma_f32_16x16x4_f32, whose products and sums are fp32 (256 FLOP per clock and CU, 157 TFLOP/s on the chip; the
+// four lane groups of an operand hold neighbouring 16-byte pieces of a row, so a wave's load covers 64 bytes of 16 rows,
+// where the 32x32x2 form takes 32 bytes of 32 rows and twice as long).
+// Two kernels with the same arithmetic in the same order, so that a row's result does not depend on which one the
+// batch's row count picks: K is cut into four quarters (multiples of 32), each quarter is summed from zero in
+// ascending order, and the quarters are added as ((q0 + q1) + q2) + q3.
+//   gemm_f32_kernel        64 x 64 tile, eight waves of 32 x 32: four for each half of K, so that a CU with a single
+//                          workgroup has two waves per SIMD to cover LDS and barrier waits; operands through two LDS
+//                          stages of K step 32 per half.  Bound by the matrix pipe from about 256 tiles on.
+//   gemm_f32_small_kernel  32 x 32 tile, four waves, one quarter of K each, operands straight into registers, the four
+//                          sums added through LDS.  With few tiles a launch lasts as long as one wave's chain of
+//                          MFMAs (32 clocks per column of K); a quarter of K per wave makes that four times
+//                          shorter, at twice the operand bytes per FLOP.
+// Measured on MI355X against tiles of 4 x 4 FMAs per thread on the vector ALU, which these replace (us): 1206 x 768 x
+// 3072 205 -> 68, 1206 x 3072 x 768 90 -> 73, 402 x 192 x 768 51 -> 9, 402 x 576 x 192 16 -> 5.
+constexpr int kF32SmallTiles = 150;
+__host__ __device__ static inline int f32_quarter(int K) { return ((K + 3) / 4 + 31) & ~31; }
+
+// Four consecutive outputs of row m from column n (N % 8 == 0: inside or outside as a whole).
 template <typename T, int EPI>
-__global__ __launch_bounds__(256) void gemm_valu_kernel(const T* __restrict__ A, const T* __restrict__ W,
-                                                        const T* __restrict__ bias, const float* res,
-                                                        typename OutType<T, EPI>::type* Y, int64_t M, int N,
-                                                        int K) {
+__device__ inline void f32_epilogue4(floatx4 v, const T* __restrict__ bias, const float* res,
+                                     typename OutType<T, EPI>::type* Y, int64_t m, int n, int64_t M, int N) {
   typedef typename OutType<T, EPI>::type OT;
-  __shared__ float As[16][64 + 4];
-  __shared__ float Ws[16][64 + 4];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  if (m >= M || n >= N) return;
+  const size_t idx = (size_t)m * N + n;
+  const floatx4 b = load4<T>(bias + n);
+  Quad<OT> o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o.x[e] = from_float<OT>(epilogue_value<EPI>(v[e], b[e], res, idx + e));
+  *reinterpret_cast<Quad<OT>*>(Y + idx) = o;
+}
+
+constexpr int kF32Ld = 36;   // LDS row stride in floats
+constexpr size_t kF32Lds = sizeof(float) * 2 * 2 * 2 * 64 * kF32Ld;   // [K half][operand][stage][64][36]
+
+template <typename T, int EPI>
+__global__ __launch_bounds__(512) void gemm_f32_kernel(const T* __restrict__ A, const T* __restrict__ W,
+                                                       const T* __restrict__ bias, const float* res,
+                                                       typename OutType<T, EPI>::type* Y, int64_t M, int N, int K) {
+  // rows of 32 floats padded to 36: the 16 lanes served per clock read 16 bytes of 16 consecutive rows, 9 r mod 16
+  // sixteen-byte groups apart, i.e. all 64 banks once
+  constexpr int LD = kF32Ld;
+  extern __shared__ __attribute__((aligned(16))) float f32_lds[];
+  const int lane = threadIdx.x & 63, fr = lane & 15, fk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int half = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1, tid = threadIdx.x & 255;
+  float* As = f32_lds + half * (2 * 2 * 64 * LD);   // [2][64][LD]
+  float* Ws = As + 2 * 64 * LD;
   const int64_t m0 = (int64_t)blockIdx.y * 64;
   const int n0 = blockIdx.x * 64;
-  const int lr = threadIdx.x >> 2, lk = (threadIdx.x & 3) * 4;
-  float acc[4][4];
+  const int lr = tid >> 3, lk = (tid & 7) * 4;   // staging: rows lr, lr + 32; columns lk .. lk + 3
+  // K-tile kt is requested two k-tiles ahead (a k-tile is 0.43 us of MFMAs, less than a load takes), into
+  // registers slot kt & 1, and stored to LDS stage kt & 1 one k-tile ahead.
+  const int qt = f32_quarter(K) / 32, KT = 2 * qt, k_beg = half * KT * 32;
+  // Loads are never masked and the loop has no branch around one (the compiler would wait for all loads in flight):
+  // rows past the end repeat the last one, columns past K are read at K - 4 and zeroed on their way to LDS.
+  floatx4 ra[2][2], rw[2][2];
+  const T *pa[2], *pw[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < 2; ++j) {
+    pa[j] = A + (size_t)min(m0 + lr + 32 * j, M - 1) * K;
+    pw[j] = W + (size_t)min(n0 + lr + 32 * j, N - 1) * K;
+  }
+  auto fetch = [&](int slot, int kt) {
+    const int k = min(k_beg + kt * 32 + lk, K - 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    float a[4] = {0.f, 0.f, 0.f, 0.f}, w[4] = {0.f, 0.f, 0.f, 0.f};
-    if (m0 + lr < M && k0 + lk < K) {
-      const T* p = A + (size_t)(m0 + lr) * K + k0 + lk;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = to_float(p[i]);
+    for (int j = 0; j < 2; ++j) {
+      ra[slot][j] = load4<T>(pa[j] + k);
+      rw[slot][j] = load4<T>(pw[j] + k);
     }
-    if (n0 + lr < N && k0 + lk < K) {
-      const T* p = W + (size_t)(n0 + lr) * K + k0 + lk;
+  };
+  auto stage = [&](int slot, int kt) {
+    const bool in = k_beg + kt * 32 + lk < K;   // K % 8 == 0
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = to_float(p[i]);
+    for (int j = 0; j < 2; ++j) {
+      *reinterpret_cast<floatx4*>(As + (slot * 64 + lr + 32 * j) * LD + lk) = in ? ra[slot][j] : zero;
+      *reinterpret_cast<floatx4*>(Ws + (slot * 64 + lr + 32 * j) * LD + lk) = in ? rw[slot][j] : zero;
     }
+  };
+  floatx4 acc[2][2], first[2][2];   // [row block][column block] of 16 x 16: the quarter being summed, the half's first one
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = first[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  fetch(0, 0);
+  fetch(1, 1);
+  stage(0, 0);
+  __syncthreads();
+  auto step = [&](int st, int kt) {
+    floatx4 a[2][2], w[2][2];   // [block][16-column half of the k-tile]
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i][g] = *reinterpret_cast<const floatx4*>(As + (st * 64 + wm * 32 + 16 * i + fr) * LD + 16 * g + 4 * fk);
+        w[i][g] = *reinterpret_cast<const floatx4*>(Ws + (st * 64 + wn * 32 + 16 * i + fr) * LD + 16 * g + 4 * fk);
+      }
+    fetch(st, kt + 2);
+    __builtin_amdgcn_sched_barrier(0);   // else the loads sink below the MFMAs that are to cover them
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          acc[i >> 1][i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i & 1][g][u], a[i >> 1][g][u], acc[i >> 1][i & 1], 0, 0, 0);
+    if (kt + 1 == qt) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        first[i >> 1][i & 1] = acc[i >> 1][i & 1];
+        acc[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    stage(st ^ 1, kt + 1);   // everyone left that stage before the barrier of the previous k-tile
     __syncthreads();
+  };
+  for (int kt = 0; kt < KT; kt += 2) {
+    step(0, kt);
+    step(1, kt + 1);
+  }
+  // the second half's two quarters go to the first half's waves through LDS: [quarter][64][64 + 4]
+  constexpr int LDX = 68;
+  const int row = wm * 32 + fr, col = wn * 32 + 4 * fk;
+  if (half) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { As[lk + i][lr] = a[i]; Ws[lk + i][lr] = w[i]; }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], wv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = As[kk][ty * 4 + i]; wv[i] = Ws[kk][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], wv[j], acc[i][j]);
+    for (int i = 0; i < 4; ++i) {
+      float* p = f32_lds + (row + 16 * (i >> 1)) * LDX + col + 16 * (i & 1);
+      *reinterpret_cast<floatx4*>(p) = first[i >> 1][i & 1];
+      *reinterpret_cast<floatx4*>(p + 64 * LDX) = acc[i >> 1][i & 1];
     }
   }
+  __syncthreads();
+  if (half) return;
+  // W rows were the first operand: a lane holds, of output row fr, the columns 4 fk .. + 3 of every 16 x 16 block
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int64_t m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      const size_t idx = (size_t)m * N + n;
-      Y[idx] = from_float<OT>(epilogue_value<EPI>(acc[i][j], to_float(bias[n]), res, idx));
-    }
+    const float* p = f32_lds + (row + 16 * (i >> 1)) * LDX + col + 16 * (i & 1);
+    floatx4 v = first[i >> 1][i & 1] + acc[i >> 1][i & 1];
+    v += *reinterpret_cast<const floatx4*>(p);
+    v += *reinterpret_cast<const floatx4*>(p + 64 * LDX);
+    f32_epilogue4<T, EPI>(v, bias, res, Y, m0 + row + 16 * (i >> 1), n0 + col + 16 * (i & 1), M, N);
   }
 }
 
+template <typename T, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_small_kernel(const T* __restrict__ A, const T* __restrict__ W,
+                                                             const T* __restrict__ bias, const float* res,
+                                                             typename OutType<T, EPI>::type* Y, int64_t M, int N,
+                                                             int K) {
+  constexpr int LD = 36, NS = 4;   // batches of 32 columns, NS - 1 of them requested ahead
+  __shared__ __attribute__((aligned(16))) float part[4][32][LD];
+  const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: the loop below has scalar branches only
+  const int64_t m0 = (int64_t)blockIdx.y * 32;
+  const int n0 = blockIdx.x * 32;
+  const int KQ = f32_quarter(K), k_beg = wave * KQ, k_end = min(K, k_beg + KQ);
+  // rows past the end repeat the last one: their outputs are not stored
+  const T *pa[2], *pw[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    pa[i] = A + (size_t)min(m0 + 16 * i + fr, M - 1) * K + 4 * fk;
+    pw[i] = W + (size_t)min(n0 + 16 * i + fr, N - 1) * K + 4 * fk;
+  }
+  const int nb = k_end > k_beg ? (k_end - k_beg) / 32 : 0;   // whole batches; the last quarter may have 8, 16 or 24 more columns
+  floatx4 ra[NS][2][2], rw[NS][2][2];
+  auto fetch = [&](int slot, int b) {   // unmasked: batches past the last repeat it
+    const int k = k_beg + 32 * min(b, nb - 1);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        ra[slot][i][g] = load4<T>(pa[i] + k + 16 * g);
+        rw[slot][i][g] = load4<T>(pw[i] + k + 16 * g);
+      }
+  };
+  floatx4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto mfma16 = [&](const floatx4 (&w)[2], const floatx4 (&a)[2]) {   // 16 columns of K
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[i >> 1][i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i & 1][u], a[i >> 1][u], acc[i >> 1][i & 1], 0, 0, 0);
+  };
+  if (nb > 0) {
+#pragma unroll
+    for (int j = 0; j < NS - 1; ++j) fetch(j, j);
+    auto batch = [&](int j, int b) {   // j = b % NS
+      fetch((j + NS - 1) % NS, b + NS - 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const floatx4 w[2] = {rw[j][0][g], rw[j][1][g]}, a[2] = {ra[j][0][g], ra[j][1][g]};
+        mfma16(w, a);
+      }
+    };
+    int b = 0;
+    for (; b + NS <= nb; b += NS) {   // no branch inside: the compiler would wait for every load in flight at the join
+#pragma unroll
+      for (int j = 0; j < NS; ++j) batch(j, b + j);
+    }
+#pragma unroll
+    for (int j = 0; j < NS - 1; ++j)
+      if (b + j < nb) batch(j, b + j);
+  }
+  for (int k = k_beg + 32 * nb; k < k_end; k += 16) {   // columns past the end of K are zero, as in gemm_f32_kernel
+    const bool in = k + 4 * fk < k_end;
+    const int kk = in ? k : k_end - 4 - 4 * fk;
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    floatx4 w[2], a[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      w[i] = in ? load4<T>(pw[i] + kk) : zero;
+      a[i] = in ? load4<T>(pa[i] + kk) : zero;
+    }
+    mfma16(w, a);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<floatx4*>(&part[wave][16 * i + fr][16 * j + 4 * fk]) = acc[i][j];
+  __syncthreads();
+  const int r = tid >> 3, c = (tid & 7) * 4;
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const floatx4*>(&part[w][r][c]);
+  f32_epilogue4<T, EPI>(v, bias, res, Y, m0 + r, n0 + c, M, N);
+}
+
 template <typename T>
-static hipError_t linear_valu(const void* x, const void* w, const void* bias, const float* res, void* y,
-                              int64_t M, int N, int K, int epi, hipStream_t s) {
-  dim3 grid((N + 63) / 64, (unsigned)((M + 63) / 64)), block(256);
+static hipError_t linear_f32(const void* x, const void* w, const void* bias, const float* res, void* y,
+                             int64_t M, int N, int K, int epi, hipStream_t s) {
+  // Fewer than 256 tiles of 64 x 64 leave SIMDs without a wave; the small tiles then finish first as long as their
+  // own number (four times as many, a quarter of the MFMAs per wave) does not pile up.  Measured (us, small against
+  // large): 84 tiles of K = 3072 49 / 66, 156 tiles 73 / 68; 156 tiles of K = 768 21.7 / 20.9.
+  const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+  const bool small = tiles < kF32SmallTiles;
+  const int b = small ? 32 : 64;
+  dim3 grid((N + b - 1) / b, (unsigned)((M + b - 1) / b)), block(small ? 256 : 512);
 #define OTAS_GEMM(E)                                                                                        \
-  gemm_valu_kernel<T, E><<<grid, block, 0, s>>>((const T*)x, (const T*)w, (const T*)bias, res,           \
-                                                (typename OutType<T, E>::type*)y, M, N, K)
+  do {                                                                                                      \
+    auto kern = small ? gemm_f32_small_kernel<T, E> : gemm_f32_kernel<T, E>;                               \
+    if (!small) {                                                                                          \
+      hipError_t e = set_max_dynamic_lds((const void*)kern, (int)kF32Lds);                                 \
+      if (e != hipSuccess) return e;                                                                        \
+    }                                                                                                       \
+    kern<<<grid, block, small ? 0 : kF32Lds, s>>>((const T*)x, (const T*)w, (const T*)bias, res,                             \
+                                (typename OutType<T, E>::type*)y, M, N, K);                                 \
+  } while (0)
   if (epi == EPI_NONE) OTAS_GEMM(EPI_NONE);
   else if (epi == EPI_GELU) OTAS_GEMM(EPI_GELU);
   else OTAS_GEMM(EPI_RESIDUAL);
 #undef OTAS_GEMM
   return hipGetLastError();
 }
-
-
 
 // Epilogue shared by the MFMA kernels.  A lane's accumulators belong to ONE output row and to
 // scattered 4-column groups, so storing them directly would touch 32 rows with 16-byte pieces per
@@ -1014,10 +1194,10 @@ hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64
 hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,
                          int64_t M, int N, int K, int epi, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  if (dtype == 0) return linear_valu<float>(x, w, bias, res, y, M, N, K, epi, s);
+  if (dtype == 0) return linear_f32<float>(x, w, bias, res, y, M, N, K, epi, s);
   if (K % 32 == 0 && K >= 64 && N % 8 == 0)
     return linear_mfma_kernel(pick_mfma_kernel(M, N, K, epi), x, w, bias, res, y, M, N, K, epi, s);
-  return linear_valu<bf16_t>(x, w, bias, res, y, M, N, K, epi, s);
+  return linear_f32<bf16_t>(x, w, bias, res, y, M, N, K, epi, s);
 }
 
 // Whether the projection's launch has workgroup slots to spare for B list workgroups: they take a slot each (a
@@ -1057,8 +1237,8 @@ hipError_t launch_linear_kernel(int kernel, int dtype, const void* x, const void
   if (kernel == GK_AUTO) return launch_linear(dtype, x, w, bias, res, y, M, N, K, epi, s);
   if (M <= 0) return hipSuccess;
   if (kernel == GK_FMA)
-    return dtype == 0 ? linear_valu<float>(x, w, bias, res, y, M, N, K, epi, s)
-                      : linear_valu<bf16_t>(x, w, bias, res, y, M, N, K, epi, s);
+    return dtype == 0 ? linear_f32<float>(x, w, bias, res, y, M, N, K, epi, s)
+                      : linear_f32<bf16_t>(x, w, bias, res, y, M, N, K, epi, s);
   if (dtype == 0 || N % 8 != 0) return hipErrorInvalidValue;
   return linear_mfma_kernel(kernel, x, w, bias, res, y, M, N, K, epi, s);
 }

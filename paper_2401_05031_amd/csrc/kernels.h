@@ -59,7 +59,7 @@ hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bi
                          hipStream_t s);
 
 // The same with the kernel named by the caller (tests and profiling exercise every kernel at every
-// shape this way): GK_AUTO = launch_linear's own choice, GK_FMA = the plain-FMA kernel (any dtype),
+// shape this way): GK_AUTO = launch_linear's own choice, GK_FMA = fp32 arithmetic (any dtype),
 // the others bf16 MFMA kernels named by block tile (rows x columns) and K step.  Returns
 // hipErrorInvalidValue if the kernel does not take the shape (K % 32 / K % 64, N % 8).
 enum gemm_kernel_id {

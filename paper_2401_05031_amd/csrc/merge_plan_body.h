@@ -14,9 +14,6 @@ namespace otas {
 
 constexpr int kPlanThreads = 1024;
 
-template <typename T> struct alignas(4 * sizeof(T)) Quad { T x[4]; };   // 4 consecutive elements, one load
-template <typename T> struct alignas(8 * sizeof(T)) Oct { T x[8]; };    // 8 consecutive elements, one load
-
 // LDS layout of the plan kernel (4-byte words), n = query length, nA = ceil(n/2), nB = floor(n/2):
 //   mh [n][dm+4] normalised metric rows | best [nA] | bcol [nA] | merged [nA] | cnt [nB] |
 //   keep_pos [n] | ent_pos [n] | wave_tot [2][16] | part_v [512] | part_c [512]
