@@ -2,8 +2,8 @@
 //   O_h = softmax(Q_h K_h^T / sqrt(d_h) [+ ln size_j]) V_h,   heads concatenated into [T, D].
 // qkv is the packed [T, 3D] output of the QKV projection (columns Q | K | V, heads contiguous).
 //
-//   * attention_rows_kernel -- one wave per query row, fp32 arithmetic throughout (f32 models,
-//                              and the fallback for head widths the MFMA kernel does not take).
+//   * attention_f32_kernel  -- fp32 MFMA, fp32 arithmetic throughout (f32 models, and the fallback for head widths
+//                              the bf16 kernel does not take).
 //   * attention_mfma_kernel -- bf16 MFMA with one head's K and V staged in LDS (bf16 models).
 #include <algorithm>
 #include <cstdlib>
@@ -14,58 +14,159 @@
 
 namespace otas {
 
-// ------------------------------------------------------------------------------ one wave per row
-// grid (ceil(max_n / 4), H, B), 256 threads.  Dynamic LDS: per wave max_n scores + d_h query floats.
-template <typename T>
-__global__ __launch_bounds__(256) void attention_rows_kernel(const T* __restrict__ qkv,
-                                                             const int32_t* __restrict__ sizes,
-                                                             const int32_t* __restrict__ off, int D, int H,
-                                                             int max_n, float scale, T* __restrict__ o) {
-  extern __shared__ float lds[];
+// ------------------------------------------------------------------------------ true fp32 on the matrix cores
+// f32 models, and bf16 models of head widths the bf16 kernel is not built for: fp32 products, sums and exponentials
+// (v_mfma_f32_32x32x2_f32, expf).  grid (ceil(max_n / 32), H, B), four waves: a workgroup owns 32 query rows of one
+// head, wave w the key blocks w, w + 4, ... of 32 keys with an online softmax of its own; the four partial results
+// (row maximum, row sum, O) are combined through LDS in wave order, so a row's result depends on its own query alone.
+// Both products are computed transposed, as in the bf16 kernel below: a lane owns one query row, and the
+// accumulator element e of lane half h of the first product is key 8 (e / 4) + 4 h + (e & 3), which the second
+// product takes as k-slot h of its MFMA e straight from registers.  K, V and Q go from global memory to registers
+// (no wave shares a key block with another): what bounds it is the matrix pipe, 2 x 32 MFMAs of 64 clocks per key
+// block at head width 64, and, at few waves per SIMD, the chain load -> logits -> softmax -> product.
+// Measured on MI355X against one wave per query row on the vector ALU (us): 6 x 201 tokens, 12 heads of 64
+// 119 -> 21.6; 2 x 201 tokens, 3 heads 31 -> 12.
+template <typename T, int DT>
+__global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict__ qkv,
+                                                            const int32_t* __restrict__ sizes,
+                                                            const int32_t* __restrict__ off, int D, int H,
+                                                            float scale, T* __restrict__ o) {
+  constexpr int NG = 4 * DT;             // groups of 8 columns of a head, zero-filled past its width
+  constexpr int LDO = 32 * DT + 4;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float* ml = lds;                       // [4][2][32] row maximum and sum of every wave
+  float* osh = lds + 256;                // [4][32][LDO]
   const int dh = D / H;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, fr = lane & 31, fk = lane >> 5;
   const int q = blockIdx.z, h = blockIdx.y;
   const int base = off[q], n = off[q + 1] - base;
-  const int row = blockIdx.x * 4 + wave;
-  if (row >= n) return;
-  float* sc = lds + (size_t)wave * (max_n + dh);
-  float* qv = sc + max_n;
+  const int row0 = blockIdx.x * 32;
+  if (row0 >= n) return;                 // the whole workgroup
   const size_t ld = (size_t)3 * D;
-  const T* qrow = qkv + (size_t)(base + row) * ld + h * dh;
-  for (int d = lane; d < dh; d += 64) qv[d] = to_float(qrow[d]);
-  __builtin_amdgcn_wave_barrier();
-  // logits
-  float mx = -INFINITY;
-  for (int j = lane; j < n; j += 64) {
-    const T* kr = qkv + (size_t)(base + j) * ld + D + h * dh;
-    float s = 0.f;
-    for (int d = 0; d < dh; d += 4) {
+  const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+  floatx4 qf[NG];
+  {
+    const T* p = qkv + (size_t)(base + min(row0 + fr, n - 1)) * ld + h * dh + 4 * fk;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) s = fmaf(qv[d + k], to_float(kr[d + k]), s);
+    for (int g = 0; g < NG; ++g) qf[g] = 8 * g + 4 * fk < dh ? load4<T>(p + 8 * g) : zero;   // dh % 4 == 0
+  }
+  floatx16 oacc[DT];
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
+  float m_run = -INFINITY, l_part = 0.f;
+  const int nblk = (n + 31) >> 5;
+  for (int b = wave; b < nblk; b += 4) {
+    const int kb = b * 32;
+    // keys past the end repeat the last one: their logits become -inf
+    const T* pk = qkv + (size_t)(base + min(kb + fr, n - 1)) * ld + D + h * dh + 4 * fk;
+    floatx4 kf[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) kf[g] = 8 * g + 4 * fk < dh ? load4<T>(pk + 8 * g) : zero;
+    float vf[DT][16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = min(kb + 8 * (e >> 2) + 4 * fk + (e & 3), n - 1);
+      const T* pv = qkv + (size_t)(base + key) * ld + 2 * D + h * dh;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) vf[t][e] = to_float(pv[min(32 * t + fr, dh - 1)]);   // rows past dh are not stored
     }
-    s *= scale;
-    if (sizes) s += logf((float)sizes[base + j]);
-    sc[j] = s;
-    mx = fmaxf(mx, s);
+    floatx16 s;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      if (8 * g < dh) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[g][u], qf[g][u], s, 0, 0, 0);
+      }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = kb + 8 * (e >> 2) + 4 * fk + (e & 3);
+      float v = s[e] * scale;
+      if (sizes) v += logf((float)sizes[base + min(key, n - 1)]);
+      s[e] = key < n ? v : -INFINITY;
+      mx = fmaxf(mx, s[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    const float m_new = fmaxf(m_run, mx);
+    const float alpha = expf(m_run - m_new);   // 0 on the first block
+    m_run = m_new;
+    l_part *= alpha;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[t][e] *= alpha;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s[e] = expf(s[e] - m_new);
+      l_part += s[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+#pragma unroll
+      for (int t = 0; t < DT; ++t) oacc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t][e], s[e], oacc[t], 0, 0, 0);
   }
-  mx = wave_max(mx);
-  float sum = 0.f;
-  for (int j = lane; j < n; j += 64) {
-    const float e = expf(sc[j] - mx);
-    sc[j] = e;
-    sum += e;
+  const float l_run = l_part + __shfl_xor(l_part, 32, kWave);
+  if (fk == 0) {
+    ml[wave * 64 + fr] = m_run;
+    ml[wave * 64 + 32 + fr] = l_run;
   }
-  sum = wave_sum(sum);
-  __builtin_amdgcn_wave_barrier();
-  const float inv = 1.0f / sum;
-  for (int d = lane; d < dh; d += 64) {
-    const T* vc = qkv + (size_t)base * ld + 2 * D + h * dh + d;
-    float acc = 0.f;
-    for (int j = 0; j < n; ++j) acc = fmaf(sc[j], to_float(vc[(size_t)j * ld]), acc);
-    o[(size_t)(base + row) * D + h * dh + d] = from_float<T>(acc * inv);
+  __syncthreads();
+  float m_all = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) m_all = fmaxf(m_all, ml[w * 64 + fr]);   // wave 0 always has a key block
+  const float f = expf(m_run - m_all);                                 // 0 for a wave without one
+  float* mine = osh + (wave * 32 + fr) * LDO;
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<floatx4*>(mine + 32 * t + 8 * g + 4 * fk) =
+          floatx4{oacc[t][4 * g] * f, oacc[t][4 * g + 1] * f, oacc[t][4 * g + 2] * f, oacc[t][4 * g + 3] * f};
+  __syncthreads();
+  const int r = tid >> 3;                // 8 threads per row
+  if (row0 + r >= n) return;
+  float mr = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) mr = fmaxf(mr, ml[w * 64 + r]);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) l += ml[w * 64 + 32 + r] * expf(ml[w * 64 + r] - mr);
+  const float inv = 1.0f / l;
+  for (int d = (tid & 7) * 4; d < dh; d += 32) {
+    floatx4 v = zero;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const floatx4*>(osh + (w * 32 + r) * LDO + d);
+    Quad<T> out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out.x[e] = from_float<T>(v[e] * inv);
+    *reinterpret_cast<Quad<T>*>(o + (size_t)(base + row0 + r) * D + h * dh + d) = out;
   }
 }
 
+template <typename T>
+static hipError_t attention_f32(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int D,
+                                int H, float scale, void* o, hipStream_t s) {
+  const int dt = (D / H + 31) / 32;
+  dim3 grid((max_n + 31) / 32, H, B), block(256);
+  const size_t lds = sizeof(float) * (256 + 4 * 32 * (32 * (size_t)dt + 4));
+#define OTAS_ATTN(N)                                                                                              \
+  do {                                                                                                            \
+    auto kern = attention_f32_kernel<T, N>;                                                                       \
+    hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
+    if (e != hipSuccess) return e;                                                                                \
+    kern<<<grid, block, lds, s>>>((const T*)qkv, sz, d_off, D, H, scale, (T*)o);                                  \
+  } while (0)
+  if (dt <= 1) OTAS_ATTN(1);
+  else if (dt == 2) OTAS_ATTN(2);
+  else if (dt == 3) OTAS_ATTN(3);
+  else if (dt == 4) OTAS_ATTN(4);
+  else return hipErrorInvalidValue;
+#undef OTAS_ATTN
+  return hipGetLastError();
+}
 
 // ------------------------------------------------------------------------------ bf16 MFMA
 // grid (ceil(max_n / (32 NW)), H, B), NW waves (4 or 8): each wave owns 32 query rows of one (query, head).
@@ -425,20 +526,14 @@ hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes, co
   const int dh = D / H;
   const float scale = 1.0f / sqrtf((float)dh);
   const int32_t* sz = size_bias ? sizes : nullptr;
-  dim3 grid((max_n + 3) / 4, H, B), block(256);
-  const size_t lds = (size_t)4 * (max_n + dh) * sizeof(float);
   if (dtype != 0) {
     if (dh == 64) return attention_mfma<64>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
     if (dh == 80) return attention_mfma<80>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
     if (dh == 96) return attention_mfma<96>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
     if (dh == 128) return attention_mfma<128>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
   }
-  if (dtype == 0)
-    attention_rows_kernel<float><<<grid, block, lds, s>>>((const float*)qkv, sz, d_off, D, H, max_n, scale, (float*)o);
-  else
-    attention_rows_kernel<bf16_t><<<grid, block, lds, s>>>((const bf16_t*)qkv, sz, d_off, D, H, max_n, scale,
-                                                           (bf16_t*)o);
-  return hipGetLastError();
+  return dtype == 0 ? attention_f32<float>(qkv, sz, d_off, B, max_n, D, H, scale, o, s)
+                    : attention_f32<bf16_t>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
 }
 
 }  // namespace otas

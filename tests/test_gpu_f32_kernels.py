@@ -1,0 +1,76 @@
+"""The fp32 matrix-core kernels (GEMM tiles of 64 and of 32 rows, attention) at the edges of their tiles and of their
+range, against float64 arithmetic; and the two GEMM kernels against each other, bit for bit."""
+import numpy as np
+import pytest
+
+import otas_synth as synth
+from tests import harness as hz
+
+pytestmark = pytest.mark.gpu
+
+
+def _context(lib, D, H, dtype):
+    import torch
+    cfg = synth.Config("f32", L=1, D=D, H=H, F=8, dtype=dtype, B=1, n0=2)
+    return hz.make_context(cfg)[0], torch.float32 if dtype == "f32" else torch.bfloat16
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K", [(8, 8), (24, 40), (192, 768), (72, 1000), (2304, 136)])
+def test_fp32_gemm_tile_edges_and_row_independence(lib, dtype, N, K):
+    """Rows 0 .. m - 1 of a product must not depend on how many rows follow them: M = 1 .. 65 runs the small tiles,
+    M = 12000 the large ones for every N here.  Error of the sum: at most K roundings of 2^-24 each on terms of total
+    size sum |x w|, plus the rounding of the result (bf16: 2^-9 of it)."""
+    import torch
+    ctx, dt = _context(lib, 64, 1, dtype)
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    M = 12000
+    x = torch.randn((M, K), generator=g, device="cuda").to(dt)
+    w = torch.randn((N, K), generator=g, device="cuda").to(dt)
+    b = torch.randn(N, generator=g, device="cuda").to(dt)
+    res = torch.randn((M, N), generator=g, device="cuda")
+    out = {}
+    for m in (1, 31, 33, 64, 65, M):
+        y = torch.full((m, N), float("nan"), device="cuda")
+        ctx.otas_linear_kernel(1, x[:m].contiguous(), w, b, res[:m].contiguous(), m, N, K, 2, y)
+        out[m] = y
+    xd, wd = x.double(), w.double()
+    ref = xd @ wd.T + b.double() + res.double()
+    bound = (K + 8) * 2.0 ** -24 * (xd.abs() @ wd.abs().T + b.double().abs() + res.double().abs())
+    assert bool(((out[M].double() - ref).abs() <= bound).all())
+    for m in (1, 31, 33, 64, 65):
+        assert torch.equal(out[m], out[M][:m]), m
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,H", [(8, 2), (24, 2), (64, 1), (200, 2), (256, 2)])
+def test_fp32_attention_tile_edges(lib, dtype, D, H):
+    """Head widths 4, 12, 64, 100 and 128 (the bf16 model takes this kernel where it has no other), sequences around the
+    32-row and 32-key blocks and the four waves, with and without the size bias, in one ragged batch each."""
+    import torch
+    ctx, dt = _context(lib, D, H, dtype)
+    dh = D // H
+    if dtype == "bf16" and dh in (64, 80, 96, 128):
+        pytest.skip("the bf16 kernel takes this width")
+    ns = [1, 31, 32, 33, 128, 129, 300]
+    off = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
+    T = int(off[-1])
+    g = torch.Generator(device="cuda").manual_seed(D)
+    qkv = torch.randn((T, 3 * D), generator=g, device="cuda").to(dt)
+    sizes = torch.randint(1, 9, (T,), generator=g, device="cuda", dtype=torch.int32)
+    for flags in (0, lib.OTAS_FLAG_SIZE_BIAS):
+        o = torch.full((T, D), float("nan"), device="cuda", dtype=dt)
+        ctx.otas_attention(qkv, sizes, off, flags, o)
+        for q, n in enumerate(ns):
+            r = slice(int(off[q]), int(off[q + 1]))
+            x = qkv[r].double().cpu()
+            Q, Kk, V = (x[:, i * D:(i + 1) * D].reshape(n, H, dh).transpose(0, 1) for i in range(3))
+            s = Q @ Kk.transpose(1, 2) / dh ** 0.5
+            if flags:
+                s = s + sizes[r].double().cpu().log()
+            ref = (torch.softmax(s, -1) @ V).transpose(0, 1).reshape(n, D).numpy()
+            got = o[r].double().cpu().numpy()
+            # logits of size <= 30 in fp32: 30 * 2^-23 of the weights; a bf16 result adds its own rounding
+            assert np.abs(got - ref).max() <= (2e-5 if dtype == "f32" else 2.0 ** -8) * np.abs(ref).max(), (flags, n)
+    ctx.close()
