@@ -381,11 +381,12 @@ otas_status prepend_impl(otas_ctx* c, const void* tokens, const int32_t* tok_off
   std::memcpy(&plan[2 * B + 1], prm_cnt, B * sizeof(int32_t));
   std::memcpy(&plan[3 * B + 1], out_off, (B + 1) * sizeof(int32_t));
   if (hipSetDevice(c->device) != hipSuccess) return OTAS_EDEVICE;
-  otas_status st = upload_plan(c, plan);
-  if (st != OTAS_OK) return st;
-  const int32_t* dp = c->d_plan;
-  OTAS_LAUNCH(K_PREPEND, launch_prepend(c->desc.dtype, tokens, prompts, out, dp, dp + (B + 1), dp + (2 * B + 1),
-                                        dp + (3 * B + 1), B, max_n, c->desc.D, c->desc.n_lead, c->stream));
+  if (!plan_in_args(plan.size())) {
+    const otas_status st = upload_plan(c, plan);
+    if (st != OTAS_OK) return st;
+  }
+  OTAS_LAUNCH(K_PREPEND, launch_prepend(c->desc.dtype, tokens, prompts, out, plan.data(), plan.size(), c->d_plan, B, max_n,
+                                        c->desc.D, c->desc.n_lead, c->stream));
   return OTAS_OK;
 }
 }  // namespace
@@ -447,15 +448,14 @@ otas_status token_merge_impl(otas_ctx* c, const void* x, const void* metric, int
   std::memcpy(offsets_out, out_off, (B + 1) * sizeof(int32_t));
   const int64_t T_out = out_off[B];
   if (hipSetDevice(c->device) != hipSuccess) return OTAS_EDEVICE;
-  otas_status st = upload_plan(c, plan, 4 * (size_t)B + 2);
+  const size_t count = 4 * (size_t)B + 2;
+  otas_status st = plan_in_args(count) ? OTAS_OK : upload_plan(c, plan, count);
   if (st != OTAS_OK) return st;
-  const int32_t* dp = c->d_plan;
   const bool was_timing = c->timing;
   if (!timed) c->timing = false;
   st = [&]() -> otas_status {
-    OTAS_LAUNCH(K_PLAN, launch_merge_plan(c->desc.dtype, metric, dm, 0, 1, dm, dp, dp + (B + 1), dp + 2 * (B + 1),
-                                          dp + 2 * (B + 1) + B, B, max_n, n_lead, src_list, row_ptr, trace_src,
-                                          trace_dst, rows, c->stream));
+    OTAS_LAUNCH(K_PLAN, launch_merge_plan_host(c->desc.dtype, metric, dm, plan, count, c->d_plan, B, max_n, n_lead,
+                                               src_list, row_ptr, trace_src, trace_dst, rows, c->stream));
     OTAS_LAUNCH(K_APPLY, launch_merge_apply(c->desc.dtype, x, sizes, src_list, row_ptr, T, T_out, c->desc.D, x_out,
                                             sizes_out, c->stream));
     return OTAS_OK;
@@ -640,13 +640,17 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
     }
   }
   // Device plan.  Per lane (int32): off[l][Bg+1] for l = 0..L (relative to the lane's first row) |
-  // r_eff[l][Bg] | trace_off[l][Bg].
+  // r_eff[l][Bg] | trace_off[l][Bg].  A single lane of up to kStartQueries queries has it expanded on the device, by the
+  // pass's first LayerNorm; else it is built here and copied.
+  const bool start = G == 1 && B <= kStartQueries;
+  StartJob job;
   std::vector<int32_t> plan;
   for (LaneRun& ln : lanes) {
     const int Bg = ln.Bg;
     ln.plan_base = plan.size();
-    plan.resize(ln.plan_base + (size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg);
-    int32_t* off = &plan[ln.plan_base];
+    if ((size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg > kPlanInts - ln.plan_base) return OTAS_ENOMEM;
+    if (!start) plan.resize(ln.plan_base + (size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg);
+    int32_t* off = plan.data() + ln.plan_base;
     int32_t* pr = off + (size_t)(L + 1) * (Bg + 1);
     int32_t* pt = pr + (size_t)L * Bg;
     ln.T.assign(L + 1, 0);
@@ -655,18 +659,22 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
     ln.last_merge = -1;
     for (int l = 0; l <= L; ++l) {
       int32_t* o = off + (size_t)l * (Bg + 1);
-      o[0] = 0;
+      int at = 0;
       for (int j = 0; j < Bg; ++j) {
         const int n = len[(size_t)l * B + ln.q0 + j];
-        o[j + 1] = o[j] + n;
+        if (!start) o[j] = at;
+        at += n;
         ln.max_n[l] = std::max(ln.max_n[l], n);
       }
-      ln.T[l] = o[Bg];
+      if (!start) o[Bg] = at;
+      ln.T[l] = at;
       if (l < L)
         for (int j = 0; j < Bg; ++j) {
           const int k = reff[(size_t)l * B + ln.q0 + j];
-          pr[(size_t)l * Bg + j] = k;
-          pt[(size_t)l * Bg + j] = troff[(size_t)l * B + ln.q0 + j];
+          if (!start) {
+            pr[(size_t)l * Bg + j] = k;
+            pt[(size_t)l * Bg + j] = troff[(size_t)l * B + ln.q0 + j];
+          }
           if (k > 0) { ln.any_merge[l] = 1; ln.last_merge = l; }
         }
     }
@@ -675,8 +683,20 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
   if (hipSetDevice(c->device) != hipSuccess) return OTAS_EDEVICE;
   if (!ensure_lanes(c, G)) return OTAS_EDEVICE;
 
-  otas_status st = upload_plan(c, plan);
-  if (st != OTAS_OK) return st;
+  if (start) {
+    job.plan = c->d_plan;
+    job.kind = START_MERGE;
+    job.B = B; job.L = L; job.n_lead = n_lead; job.grow = 0;
+    for (int q = 0; q < B; ++q) {
+      job.v[q] = len[q];
+      job.v[B + q] = r[q];
+    }
+    job.ones[0] = job.ones[1] = nullptr;
+    job.n_ones[0] = job.n_ones[1] = 0;
+  } else {
+    const otas_status st = upload_plan(c, plan);
+    if (st != OTAS_OK) return st;
+  }
   // Everything below enqueues work.  If a HIP call fails after lanes or the plan stream were forked,
   // the library's own streams are drained before the error is returned, so that nothing of this call
   // is still running on them when the next call reuses the plan buffer and the workspace.
@@ -703,8 +723,13 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
     ln.sizes_now = sizes_in ? sizes_in + ln.row0 : nullptr;
     if (size_bias && !ln.sizes_now) {   // the attention bias reads sizes from the first layer on
       int32_t* sz = (int32_t*)(ws + w.sizes_a) + ln.row0;
-      OTAS_LAUNCH_ON(K_MISC, s, launch_fill_i32(sz, 1, ln.T[0], s));
+      if (start) { job.ones[0] = sz; job.n_ones[0] = ln.T[0]; }
+      else OTAS_LAUNCH_ON(K_MISC, s, launch_fill_i32(sz, 1, ln.T[0], s));
       ln.sizes_now = sz;
+    }
+    if (start && ln.last_merge < 0 && !sizes_in) {   // nothing merges: the output's sizes are all 1 (rows as at the input)
+      job.ones[1] = sizes_out;
+      job.n_ones[1] = ln.T[0];
     }
     ln.x_cur = (const char*)x0 + (size_t)ln.row0 * D * es_in;   // residual stream entering the block
     ln.x_owned = false;   // x_cur is one of the workspace buffers, so it may be updated in place
@@ -713,7 +738,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       float* xa = (float*)(ws + w.xa) + (size_t)ln.row0 * D;
       char* hbuf = ws + w.h + (size_t)ln.row0 * D * es;
       const otas_layer_weights& w0 = c->layers[layer_begin];
-      OTAS_LAUNCH_ON(K_LN, s, launch_layer_norm_widen(ln.x_cur, w0.ln1_g, w0.ln1_b, hbuf, xa, ln.T[0], D, d.ln_eps, s));
+      OTAS_LAUNCH_ON(K_LN, s, launch_layer_norm_widen(ln.x_cur, w0.ln1_g, w0.ln1_b, hbuf, xa, ln.T[0], D, d.ln_eps, s,
+                                                            start ? &job : nullptr));
       ln.x_cur = xa;
       ln.x_owned = true;
       ln.ln1_done = true;
@@ -749,7 +775,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       int32_t* row_ptr = (int32_t*)(ws + w.row_ptr) + ln.row0 + g;   // one end entry per lane
       // normalisation -> QKV -> attention -> projection + residual
       if (!ln.ln1_done)
-        OTAS_LAUNCH_ON(K_LN, s, launch_layer_norm(dt, true, ln.x_cur, wl.ln1_g, wl.ln1_b, hbuf, T, D, d.ln_eps, s));
+        OTAS_LAUNCH_ON(K_LN, s, launch_layer_norm(dt, true, ln.x_cur, wl.ln1_g, wl.ln1_b, hbuf, T, D, d.ln_eps, s,
+                                                  start && l == 0 ? &job : nullptr));
       ln.ln1_done = false;
       OTAS_LAUNCH_ON(K_QKV, s, launch_linear(dt, hbuf, wl.w_qkv, wl.b_qkv, nullptr, qkv, T, 3 * D, D, EPI_NONE, s));
       // Attention and the merge plan both read only the QKV projection.  On one stream two kernels never overlap,
@@ -844,7 +871,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
     hipStream_t s = g == 0 ? s0 : c->lane[g].main;
     if (ln.last_merge < 0) {   // nothing merged in this lane: the sizes are the input's
       if (sizes_in) OTAS_LAUNCH_ON(K_MISC, s, launch_copy_i32(sizes_in + ln.row0, sizes_out + ln.rowL, ln.T[L], s));
-      else OTAS_LAUNCH_ON(K_MISC, s, launch_fill_i32(sizes_out + ln.rowL, 1, ln.T[L], s));
+      else if (!start) OTAS_LAUNCH_ON(K_MISC, s, launch_fill_i32(sizes_out + ln.rowL, 1, ln.T[L], s));
     }
     if (g > 0) {   // join
       OTAS_HIP(hipEventRecord(c->lane[g].ev_done, s));
@@ -912,8 +939,25 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
   std::memcpy(offsets_out, off_last, (B + 1) * sizeof(int32_t));
 
   if (hipSetDevice(c->device) != hipSuccess) return OTAS_EDEVICE;
-  otas_status st = upload_plan(c, plan);
-  if (st != OTAS_OK) return st;
+  const bool start = B <= kStartQueries;   // the first LayerNorm expands the plan on the device (see run_layers)
+  StartJob job;
+  if (start) {
+    if (plan.size() > kPlanInts) return OTAS_ENOMEM;
+    job.plan = c->d_plan;
+    job.kind = START_DEEP;
+    job.B = B; job.L = L; job.n_lead = n_lead; job.grow = grow;
+    for (int q = 0; q < B; ++q) {
+      job.v[q] = offsets[q + 1] - offsets[q];
+      job.v[B + q] = prompt_offsets[q + 1] - prompt_offsets[q];
+    }
+    job.ones[0] = sizes_out;
+    job.n_ones[0] = T_max;
+    job.ones[1] = nullptr;
+    job.n_ones[1] = 0;
+  } else {
+    const otas_status st = upload_plan(c, plan);
+    if (st != OTAS_OK) return st;
+  }
   hipStream_t s = c->stream;
   char* ws = (char*)workspace;
   float* x_buf[2] = {(float*)(ws + w.xa), (float*)(ws + w.xb)};
@@ -928,7 +972,7 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
   bool ln1_done = false;
   if (dt != OTAS_F32) {                    // 16-bit tokens: widened into the workspace by the first block's LayerNorm
     OTAS_LAUNCH(K_LN, launch_layer_norm_widen(x0, c->layers[0].ln1_g, c->layers[0].ln1_b, hbuf, x_buf[0], T0, D,
-                                              d.ln_eps, s));
+                                              d.ln_eps, s, start ? &job : nullptr));
     x_cur = x_buf[0];
     cur = 0;
     ln1_done = true;
@@ -949,7 +993,8 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
                                                   n_lead, false, s));
       }
     }
-    if (!ln1_done) OTAS_LAUNCH(K_LN, launch_layer_norm(dt, true, x_cur, wl.ln1_g, wl.ln1_b, hbuf, T, D, d.ln_eps, s));
+    if (!ln1_done) OTAS_LAUNCH(K_LN, launch_layer_norm(dt, true, x_cur, wl.ln1_g, wl.ln1_b, hbuf, T, D, d.ln_eps, s,
+                                                       start && l == 0 ? &job : nullptr));
     ln1_done = false;
     OTAS_LAUNCH(K_QKV, launch_linear(dt, hbuf, wl.w_qkv, wl.b_qkv, nullptr, qkv, T, 3 * D, D, EPI_NONE, s));
     OTAS_LAUNCH(K_ATTN, launch_attention(dt, qkv, nullptr, off_l, B, max_n[l], D, H, false, hbuf, s));
@@ -971,7 +1016,7 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
       OTAS_LAUNCH(K_FC2, launch_linear(dt, hid, wl.w_fc2, wl.b_fc2, x_cur, x_next, T, D, F, EPI_RESIDUAL, s));
     }
   }
-  OTAS_LAUNCH(K_MISC, launch_fill_i32(sizes_out, 1, T_max, s));
+  if (!start) OTAS_LAUNCH(K_MISC, launch_fill_i32(sizes_out, 1, T_max, s));
   return OTAS_OK;
 }
 
@@ -1025,10 +1070,12 @@ otas_status otas_task_heads(otas_ctx* c, const float* x, const int32_t* offsets,
     std::memcpy(&plan[o_heads + 6 * (size_t)t], &r, sizeof(r));
   }
   if (hipSetDevice(c->device) != hipSuccess) return OTAS_EDEVICE;
-  otas_status st = upload_plan(c, plan);   // the plan buffer is 256-byte aligned, the records 8-byte
-  if (st != OTAS_OK) return st;
-  OTAS_LAUNCH(K_MISC, launch_task_heads(c->desc.dtype, x, c->d_plan, c->d_plan + o_task, c->d_plan + o_heads, lnf_g, lnf_b,
-                                        B, c->desc.D, c->desc.ln_eps, logits, k_max, c->stream));
+  if (!plan_in_args(plan.size())) {
+    const otas_status st = upload_plan(c, plan);
+    if (st != OTAS_OK) return st;
+  }
+  OTAS_LAUNCH(K_MISC, launch_task_heads(c->desc.dtype, x, plan.data(), plan.size(), c->d_plan, lnf_g, lnf_b, B, c->desc.D,
+                                        c->desc.ln_eps, logits, k_max, c->stream));
   return OTAS_OK;
 }
 

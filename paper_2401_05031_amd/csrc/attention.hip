@@ -412,15 +412,14 @@ __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int DH = 64, WT = kFusedThreads, G = WT / 64 / NW;
   if ((int)blockIdx.x < B * parts) {   // workgroup-uniform
+    const PlanQuery pq = plan_query(off, out_off, reff_arr, troff, (int)blockIdx.x / parts);
     if (sel_best)   // the selection only, `parts` workgroups per query: the lists are written beside the output projection
-      merge_plan_select<bf16_t, true, true, WT>(qkv, 3 * (int64_t)D, D, H, DH, off, reff_arr, n_lead, nullptr,
-                                                reinterpret_cast<float*>(smem), sel_best, sel_bcol,
-                                                (int)blockIdx.x / parts, (int)threadIdx.x, (int)blockIdx.x % parts,
-                                                parts);
+      merge_plan_select<bf16_t, true, true, WT>(qkv, 3 * (int64_t)D, D, H, DH, pq, n_lead, nullptr,
+                                                reinterpret_cast<float*>(smem), sel_best, sel_bcol, (int)threadIdx.x,
+                                                (int)blockIdx.x % parts, parts);
     else
-      merge_plan_body<bf16_t, true, WT>(qkv, 3 * (int64_t)D, D, H, DH, off, out_off, reff_arr, troff, n_lead, src_list,
-                                        row_ptr, trace_src, trace_dst, nullptr, reinterpret_cast<float*>(smem),
-                                        (int)blockIdx.x, (int)threadIdx.x);
+      merge_plan_body<bf16_t, true, WT>(qkv, 3 * (int64_t)D, D, H, DH, pq, n_lead, src_list, row_ptr, trace_src,
+                                        trace_dst, nullptr, reinterpret_cast<float*>(smem), (int)threadIdx.x);
     return;
   }
   int id = (int)blockIdx.x - B * parts;

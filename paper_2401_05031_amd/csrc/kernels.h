@@ -19,11 +19,15 @@ hipError_t launch_clock_probe(uint32_t* ticks, int32_t samples, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_copy_i32(const int32_t* src, int32_t* dst, int64_t n, hipStream_t s);
 
-// Query q takes rows d_prm_beg[q] .. + d_prm_cnt[q] - 1 of the prompt tensor.
-hipError_t launch_prepend(int dtype, const void* tokens, const void* prompts, void* out,
-                          const int32_t* d_tok_off, const int32_t* d_prm_beg, const int32_t* d_prm_cnt,
-                          const int32_t* d_out_off, int B, int max_n_out, int D, int n_lead,
-                          hipStream_t s);
+// Plans of up to kArgInts entries travel in a kernel's arguments: such a launcher reads the host array `plan` and never
+// d_plan; larger ones must have been copied to d_plan.
+constexpr int kArgInts = 960;
+inline bool plan_in_args(size_t count) { return count <= (size_t)kArgInts; }
+
+// plan: tok_off [B+1] | prm_beg [B] | prm_cnt [B] | out_off [B+1]; query q takes rows prm_beg[q] .. + prm_cnt[q] - 1 of
+// the prompt tensor.
+hipError_t launch_prepend(int dtype, const void* tokens, const void* prompts, void* out, const int32_t* plan,
+                          size_t count, const int32_t* d_plan, int B, int max_n_out, int D, int n_lead, hipStream_t s);
 
 // Prompting module in front of a layer l >= 1 on the float residual stream: overwrite the P prompt
 // rows of every query in place (grow = false, x_new == x_old) or insert P rows at n_lead while
@@ -35,22 +39,38 @@ hipError_t launch_deep_prompt(int dtype, const float* x_old, float* x_new, const
 
 // Model ends.  patchify: images [B, C, Hi, Wi] -> patch matrix [B N, C p p] (patches row by row,
 // flattened channel-major).  embed_finish: tokens [B, n_lead + N, D] = [cls | proj rows] + pos.
-// task_heads: logits[q, :K_task] = W_task LN_final(x[off[q]]) + b_task; d_heads is a device array of
-// {const void* w, const void* b, int K} records (16-byte stride + padding as laid out by the host).
+// task_heads: logits[q, :K_task] = W_task LN_final(x[off[q]]) + b_task; plan: off [B] | task [B] | pad to an even count |
+// a HeadRef per task.
 struct HeadRef { const void* w; const void* b; int32_t K; int32_t pad; };   // 24 bytes, 8-byte aligned
 hipError_t launch_patchify(int dtype, const void* img, void* out, int B, int C, int Hi, int Wi, int p, hipStream_t s);
 hipError_t launch_embed_finish(int dtype, const void* proj, const void* cls, const void* pos, void* tokens, int B,
                                int N, int D, int n_lead, hipStream_t s);
-hipError_t launch_task_heads(int dtype, const float* x, const int32_t* d_off, const int32_t* d_task,
-                             const void* d_heads, const void* g, const void* b, int B, int D, float eps,
-                             float* logits, int k_max, hipStream_t s);
+hipError_t launch_task_heads(int dtype, const float* x, const int32_t* plan, size_t count, const int32_t* d_plan,
+                             const void* g, const void* b, int B, int D, float eps, float* logits, int k_max,
+                             hipStream_t s);
+
+// What the first LayerNorm of a pass does beside its rows, in extra workgroups: it expands the pass's plan from the
+// queries' numbers (v: length [B] | r or P [B], by value: the pass needs no copy to the device) and sets up to two
+// integer arrays to 1.  The extra workgroups (one per layer) finish under the rows' own time: the LayerNorm of one ViT-B
+// query reads 3.9 us without and 4.4 with them, where the copy (3.9 us) and the fill (4.8 us) were launches of their own.
+//   kind START_MERGE: plan = off[l][B+1], l = 0 .. L | r_eff[l][B] | trace_off[l][B], l < L (lengths by the merging rule)
+//   kind START_DEEP:  plan = off[l][B+1], l < L, of lengths n + l grow P | prompt offsets [B+1]
+enum StartKind { START_MERGE = 0, START_DEEP = 1 };
+constexpr int kStartQueries = kArgInts / 2;   // a plan of more queries is built on the host and copied
+struct StartJob {
+  int32_t* plan;
+  int32_t kind, B, L, n_lead, grow;
+  int32_t* ones[2];
+  int64_t n_ones[2];
+  int32_t v[kArgInts];
+};
 
 // x_is_float: the input rows are float (the residual stream) even when dtype is bf16.
 hipError_t launch_layer_norm(int dtype, bool x_is_float, const void* x, const void* g, const void* b,
-                             void* y, int64_t T, int D, float eps, hipStream_t s);
+                             void* y, int64_t T, int D, float eps, hipStream_t s, const StartJob* job = nullptr);
 // LayerNorm of bf16 rows that also writes the rows out as floats (x_float [T, D]).
 hipError_t launch_layer_norm_widen(const void* x_bf16, const void* g, const void* b, void* y, float* x_float,
-                                   int64_t T, int D, float eps, hipStream_t s);
+                                   int64_t T, int D, float eps, hipStream_t s, const StartJob* job = nullptr);
 
 // EPI_RESIDUAL: res and y are float (the residual stream) for every dtype; otherwise y has the
 // model's dtype.
@@ -123,6 +143,11 @@ hipError_t launch_merge_plan(int dtype, const void* src, int64_t row_stride, int
                              const int32_t* d_in_off, const int32_t* d_out_off, const int32_t* d_reff,
                              const int32_t* d_troff, int B, int max_n, int n_lead, int32_t* src_list,
                              int32_t* row_ptr, int32_t* trace_src, int32_t* trace_dst, float* rows, hipStream_t s);
+// The same for a metric of its own ([T, dm], one "head"), the query's numbers from a host plan:
+// in_off [B+1] | out_off [B+1] | r_eff [B] | trace_off [B].
+hipError_t launch_merge_plan_host(int dtype, const void* metric, int dm, const int32_t* plan, size_t count,
+                                  const int32_t* d_plan, int B, int max_n, int n_lead, int32_t* src_list,
+                                  int32_t* row_ptr, int32_t* trace_src, int32_t* trace_dst, float* rows, hipStream_t s);
 size_t merge_plan_lds_bytes(int max_n, int dm);
 size_t merge_plan_rows_bytes(int64_t T, int dm);
 

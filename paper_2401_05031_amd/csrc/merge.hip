@@ -10,9 +10,12 @@
 //   merge_apply_kernel -- one 16-byte chunk of one output row per thread: gathers the listed rows,
 //       accumulates size * x in fp32 in list order, divides by the summed size.  Reads every input
 //       row once and writes every output row once, with no atomics, so results are deterministic.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "merge_plan_body.h"
+#include "plan_args.h"
 
 namespace otas {
 
@@ -26,22 +29,32 @@ size_t merge_plan_lds_bytes(int max_n, int dm) {
 }
 size_t merge_plan_rows_bytes(int64_t T, int dm) { return sizeof(float) * (size_t)T * plan_row_floats(dm); }
 
-// One workgroup of 1024 threads per query: merge_plan_body (merge_plan_body.h).
-template <typename T, bool ROWS_IN_LDS>
+// One workgroup of 1024 threads per query: merge_plan_body (merge_plan_body.h).  P: where the query's numbers come from.
+struct PlanPointers {
+  const int32_t *in_off, *out_off, *reff, *troff;   // device arrays
+  __device__ PlanQuery query(int q, int) const { return plan_query(in_off, out_off, reff, troff, q); }
+};
+template <typename I> struct PlanInts {             // in_off [B+1] | out_off [B+1] | r_eff [B] | trace_off [B]
+  I v;
+  __device__ PlanQuery query(int q, int B) const {
+    return PlanQuery{v[q], v[q + 1] - v[q], v[B + 1 + q], v[2 * B + 2 + q], v[3 * B + 2 + q]};
+  }
+};
+template <typename T, bool ROWS_IN_LDS, typename P>
 __global__ __launch_bounds__(kPlanThreads) void merge_plan_kernel(
-    const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const int32_t* __restrict__ in_off,
-    const int32_t* __restrict__ out_off, const int32_t* __restrict__ reff_arr, const int32_t* __restrict__ troff,
-    int n_lead, int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
+    const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const P plan, int B, int n_lead,
+    int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
     int32_t* __restrict__ trace_dst, float* rows) {
   extern __shared__ float lds[];
-  merge_plan_body<T, ROWS_IN_LDS>(src, row_stride, col_off, H, dm, in_off, out_off, reff_arr, troff, n_lead, src_list,
-                                  row_ptr, trace_src, trace_dst, rows, lds, (int)blockIdx.x, (int)threadIdx.x);
+  const PlanQuery pq = plan.query((int)blockIdx.x, B);
+  merge_plan_body<T, ROWS_IN_LDS>(src, row_stride, col_off, H, dm, pq, n_lead, src_list, row_ptr, trace_src, trace_dst,
+                                  rows, lds, (int)threadIdx.x);
 }
 
-hipError_t launch_merge_plan(int dtype, const void* src, int64_t row_stride, int col_off, int H, int dm,
-                             const int32_t* d_in_off, const int32_t* d_out_off, const int32_t* d_reff,
-                             const int32_t* d_troff, int B, int max_n, int n_lead, int32_t* src_list,
-                             int32_t* row_ptr, int32_t* trace_src, int32_t* trace_dst, float* rows, hipStream_t s) {
+template <typename P>
+static hipError_t merge_plan(int dtype, const void* src, int64_t row_stride, int col_off, int H, int dm, const P& plan,
+                             int B, int max_n, int n_lead, int32_t* src_list, int32_t* row_ptr, int32_t* trace_src,
+                             int32_t* trace_dst, float* rows, hipStream_t s) {
   if (B <= 0 || max_n <= 0) return hipSuccess;
   if (dm % 4 != 0 || dm > 128 || max_n > kPlanThreads) return hipErrorInvalidValue;
   const bool in_lds = merge_plan_lds_bytes(max_n, dm) <= 160 * 1024;
@@ -49,12 +62,11 @@ hipError_t launch_merge_plan(int dtype, const void* src, int64_t row_stride, int
   const size_t lds = in_lds ? merge_plan_lds_bytes(max_n, dm) : plan_small_lds_bytes(max_n);
 #define OTAS_PLAN(TYPE, IN_LDS)                                                                                  \
   do {                                                                                                           \
-    auto kern = merge_plan_kernel<TYPE, IN_LDS>;                                                                 \
+    auto kern = merge_plan_kernel<TYPE, IN_LDS, P>;                                                              \
     hipError_t e = set_max_dynamic_lds((const void*)kern, 160 * 1024);                                           \
     if (e != hipSuccess) return e;                                                                               \
-    kern<<<dim3(B), dim3(kPlanThreads), lds, s>>>((const TYPE*)src, row_stride, col_off, H, dm, d_in_off,        \
-                                                  d_out_off, d_reff, d_troff, n_lead, src_list, row_ptr,         \
-                                                  trace_src, trace_dst, rows);                                   \
+    kern<<<dim3(B), dim3(kPlanThreads), lds, s>>>((const TYPE*)src, row_stride, col_off, H, dm, plan, B, n_lead, \
+                                                  src_list, row_ptr, trace_src, trace_dst, rows);                \
   } while (0)
   if (dtype == 0) {
     if (in_lds) OTAS_PLAN(float, true); else OTAS_PLAN(float, false);
@@ -63,6 +75,23 @@ hipError_t launch_merge_plan(int dtype, const void* src, int64_t row_stride, int
   }
 #undef OTAS_PLAN
   return hipGetLastError();
+}
+
+hipError_t launch_merge_plan(int dtype, const void* src, int64_t row_stride, int col_off, int H, int dm,
+                             const int32_t* d_in_off, const int32_t* d_out_off, const int32_t* d_reff,
+                             const int32_t* d_troff, int B, int max_n, int n_lead, int32_t* src_list,
+                             int32_t* row_ptr, int32_t* trace_src, int32_t* trace_dst, float* rows, hipStream_t s) {
+  return merge_plan(dtype, src, row_stride, col_off, H, dm, PlanPointers{d_in_off, d_out_off, d_reff, d_troff}, B, max_n,
+                    n_lead, src_list, row_ptr, trace_src, trace_dst, rows, s);
+}
+
+hipError_t launch_merge_plan_host(int dtype, const void* metric, int dm, const int32_t* plan, size_t count,
+                                  const int32_t* d_plan, int B, int max_n, int n_lead, int32_t* src_list,
+                                  int32_t* row_ptr, int32_t* trace_src, int32_t* trace_dst, float* rows, hipStream_t s) {
+  return with_plan(plan, count, d_plan, [&](const auto& v) {
+    return merge_plan(dtype, metric, dm, 0, 1, dm, PlanInts<std::decay_t<decltype(v)>>{v}, B, max_n, n_lead, src_list,
+                      row_ptr, trace_src, trace_dst, rows, s);
+  });
 }
 
 // ------------------------------------------------------------------------------------ apply

@@ -14,6 +14,14 @@ namespace otas {
 
 constexpr int kPlanThreads = 1024;
 
+// What the plan needs to know of its query: first packed row and length entering the merge, first row leaving it,
+// tokens to remove, first entry of its edges in the trace.
+struct PlanQuery { int i0, n, o0, r_eff, tr0; };
+__device__ inline PlanQuery plan_query(const int32_t* in_off, const int32_t* out_off, const int32_t* reff,
+                                       const int32_t* troff, int q) {
+  return PlanQuery{in_off[q], in_off[q + 1] - in_off[q], out_off[q], reff[q], troff[q]};
+}
+
 // LDS layout of the plan kernel (4-byte words), n = query length, nA = ceil(n/2), nB = floor(n/2):
 //   mh [n][dm+4] normalised metric rows | best [nA] | bcol [nA] | merged [nA] | cnt [nB] |
 //   keep_pos [n] | ent_pos [n] | wave_tot [2][16] | part_v [512] | part_c [512]
@@ -27,7 +35,7 @@ static inline size_t plan_lists_lds_bytes(int max_n) {
 }
 constexpr size_t kPlanListsLdsMax = 4 * (3 * 512 + 512 + 2 * 1024 + 32);
 
-// One workgroup of NT threads per query (q; tid = thread index in the workgroup; lds: its dynamic LDS).
+// One workgroup of NT threads per query (pq; tid = thread index in the workgroup; lds: its dynamic LDS).
 // src: the vectors the similarity is taken on; the metric of token i is the mean over H heads of src[(i0 + i) * row_stride + col_off + h * dm + c] (H = 1 for
 // a caller-supplied metric, H heads of the attention keys inside the encoder), normalised to unit
 // length with fp32 arithmetic.
@@ -44,11 +52,11 @@ constexpr size_t kPlanListsLdsMax = 4 * (3 * 512 + 512 + 2 * 1024 + 32);
 // arithmetic in the same order whatever `parts` is.
 template <typename T, bool ROWS_IN_LDS, bool TO_GLOBAL, int NT = kPlanThreads>
 __device__ __forceinline__ void merge_plan_select(
-    const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const int32_t* __restrict__ in_off,
-    const int32_t* __restrict__ reff_arr, int n_lead, float* rows, float* lds, float* __restrict__ g_best,
-    int32_t* __restrict__ g_bcol, const int q, const int tid, const int part = 0, const int parts = 1) {
-  const int i0 = in_off[q], n = in_off[q + 1] - i0;
-  if (n <= 0 || reff_arr[q] <= 0) return;
+    const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const PlanQuery& pq, int n_lead,
+    float* rows, float* lds, float* __restrict__ g_best, int32_t* __restrict__ g_bcol, const int tid,
+    const int part = 0, const int parts = 1) {
+  const int i0 = pq.i0, n = pq.n;
+  if (n <= 0 || pq.r_eff <= 0) return;
   const int half = dm >> 1, hp = (half + 3) & ~3;   // columns per parity, and their padded count
   const int nA = (n + 1) >> 1, nB = n >> 1, ldm = 2 * hp + 4;
   const int nAb = (nA + 31) >> 5, nBb = (nB + 31) >> 5;
@@ -248,19 +256,17 @@ __device__ __forceinline__ void merge_plan_select(
   if constexpr (!TO_GLOBAL) __syncthreads();
 }
 
-// The list phases for query q by a workgroup of NT threads (a multiple of 64, at most 1024).  small: LDS for
+// The list phases for a query by a workgroup of NT threads (a multiple of 64, at most 1024).  small: LDS for
 // best [nA] | bcol [nA] | merged [nA] | cnt [nB] | keep_pos [n] | ent_pos [n] | wave_tot [32] (4-byte words).
 // FROM_GLOBAL = false: best / bcol are already there (merge_plan_select in the same workgroup);
 // true: they are read from g_best / g_bcol [i0 + a].  Integer work only, apart from comparisons of the
 // similarities: the result does not depend on NT.
 template <int NT, bool FROM_GLOBAL>
 __device__ __forceinline__ void merge_plan_lists(
-    float* small, const float* __restrict__ g_best, const int32_t* __restrict__ g_bcol,
-    const int32_t* __restrict__ in_off, const int32_t* __restrict__ out_off, const int32_t* __restrict__ reff_arr,
-    const int32_t* __restrict__ troff, int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr,
-    int32_t* __restrict__ trace_src, int32_t* __restrict__ trace_dst, const int q, const int tid) {
-  const int i0 = in_off[q], n = in_off[q + 1] - i0, o0 = out_off[q];
-  const int r_eff = reff_arr[q];
+    float* small, const float* __restrict__ g_best, const int32_t* __restrict__ g_bcol, const PlanQuery& pq,
+    int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
+    int32_t* __restrict__ trace_dst, const int tid) {
+  const int i0 = pq.i0, n = pq.n, o0 = pq.o0, r_eff = pq.r_eff;
   if (n <= 0) return;
   if (r_eff <= 0) {  // nothing merges: every output row is its own single source
     for (int i = tid; i < n; i += NT) {
@@ -303,8 +309,8 @@ __device__ __forceinline__ void merge_plan_lists(
     rank += __shfl_xor(rank, 4, kWave);
     if (part == 0 && a0 + (tid >> 3) < nA) merged[a] = rank < r_eff ? 1 : 0;
     if (part == 0 && a0 + (tid >> 3) < nA && rank < r_eff && trace_src) {
-      trace_src[troff[q] + rank] = 2 * a;
-      trace_dst[troff[q] + rank] = 2 * bcol[a] + 1;
+      trace_src[pq.tr0 + rank] = 2 * a;
+      trace_dst[pq.tr0 + rank] = 2 * bcol[a] + 1;
     }
   }
   __syncthreads();
@@ -379,19 +385,16 @@ __device__ __forceinline__ void merge_plan_lists(
   }
 }
 
-// The whole plan of query q by one workgroup of NT threads (a multiple of 64; tid = thread index; lds: its dynamic LDS).
+// The whole plan of a query by one workgroup of NT threads (a multiple of 64; tid = thread index; lds: its dynamic LDS).
 template <typename T, bool ROWS_IN_LDS, int NT = kPlanThreads>
 __device__ __forceinline__ void merge_plan_body(
-    const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const int32_t* __restrict__ in_off,
-    const int32_t* __restrict__ out_off, const int32_t* __restrict__ reff_arr, const int32_t* __restrict__ troff,
-    int n_lead, int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
-    int32_t* __restrict__ trace_dst, float* rows, float* lds, const int q, const int tid) {
-  merge_plan_select<T, ROWS_IN_LDS, false, NT>(src, row_stride, col_off, H, dm, in_off, reff_arr, n_lead, rows, lds,
-                                               nullptr, nullptr, q, tid);
-  const int n = in_off[q + 1] - in_off[q];
-  float* small = ROWS_IN_LDS ? lds + (size_t)max(n, 0) * plan_row_floats(dm) : lds;
-  merge_plan_lists<NT, false>(small, nullptr, nullptr, in_off, out_off, reff_arr, troff, src_list, row_ptr, trace_src,
-                              trace_dst, q, tid);
+    const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const PlanQuery& pq, int n_lead,
+    int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
+    int32_t* __restrict__ trace_dst, float* rows, float* lds, const int tid) {
+  merge_plan_select<T, ROWS_IN_LDS, false, NT>(src, row_stride, col_off, H, dm, pq, n_lead, rows, lds, nullptr, nullptr,
+                                               tid);
+  float* small = ROWS_IN_LDS ? lds + (size_t)max(pq.n, 0) * plan_row_floats(dm) : lds;
+  merge_plan_lists<NT, false>(small, nullptr, nullptr, pq, src_list, row_ptr, trace_src, trace_dst, tid);
 }
 
 }  // namespace otas

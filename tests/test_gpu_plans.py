@@ -1,0 +1,107 @@
+"""The small integer arrays of a call go to the GPU in the kernels' arguments up to a number of queries and through the
+device plan buffer beyond it: both sides of that line give the same rows, edges and sizes."""
+import numpy as np
+import pytest
+
+import otas_synth as synth
+from tests import harness as hz
+
+pytestmark = pytest.mark.gpu
+
+
+def _queries(cfg, B, seed):
+    rng = np.random.default_rng(seed)
+    n = rng.integers(2, 9, B)
+    base = synth.query_tokens(cfg, 0)
+    return [np.ascontiguousarray(base[(11 * q) % 180:(11 * q) % 180 + n[q]]) for q in range(B)], rng
+
+
+@pytest.mark.parametrize("B", [1, 2, 255, 480])
+def test_encoder_plan_expanded_on_the_device_equals_the_copied_one(lib, B):
+    """B queries (plan expanded by the first LayerNorm: 480 is the most) against the same B queries followed by enough
+    others to make the host build and copy the plan; fp32, where rows do not depend on the batch: bit for bit."""
+    cfg = synth.config("tiny")
+    ctx, _ = hz.make_context(cfg)
+    toks, rng = _queries(cfg, 500, 3)
+    R = rng.integers(0, 4, 500).tolist()
+    prm = [np.zeros((0, cfg.D), dtype=np.float32)] * 500
+    x0, off = hz.gpu_prepend(ctx, toks, prm)
+    many = hz.gpu_forward(ctx, x0, off, R)
+    few = hz.gpu_forward(ctx, x0[:int(off[B])].contiguous(), off[:B + 1], R[:B])
+    plain = hz.gpu_forward(ctx, x0[:int(off[B])].contiguous(), off[:B + 1], [0] * B)
+    for q in range(B):
+        assert np.array_equal(few["x"][q], many["x"][q]) and np.array_equal(few["sizes"][q], many["sizes"][q])
+        for a, b in zip(few["trace"][q], many["trace"][q]):
+            assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        assert (plain["sizes"][q] == 1).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+def test_per_layer_prompting_plan_on_both_sides(lib, mode):
+    import torch
+    cfg = synth.config("tiny")
+    ctx, _ = hz.make_context(cfg)
+    toks, rng = _queries(cfg, 500, 5)
+    P = [min(int(p), len(t) - 1) for p, t in zip(rng.integers(0, 3, 500), toks)]
+    off = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int32)
+    prm_off = np.concatenate([[0], np.cumsum(P)]).astype(np.int32)
+    x = torch.from_numpy(np.concatenate(toks)).to("cuda")
+    prompts = torch.randn((cfg.L, int(prm_off[-1]), cfg.D), generator=torch.Generator().manual_seed(1)).to("cuda")
+    got = {}
+    for B in (480, 500):
+        T, TP = int(off[B]), int(prm_off[B])
+        rows = T + (TP * (cfg.L - 1) if mode == 2 else 0)
+        out = torch.full((rows, cfg.D), float("nan"), device="cuda")
+        sizes = torch.zeros(rows, dtype=torch.int32, device="cuda")
+        ws = torch.empty(ctx.otas_workspace_bytes(B, max(T, rows)), dtype=torch.uint8, device="cuda")
+        ctx.otas_encoder_forward_deep(x[:T].contiguous(), off[:B + 1], mode, prompts[:, :TP].contiguous(), prm_off[:B + 1],
+                                      ws, out, sizes)
+        assert bool((sizes == 1).all())
+        got[B] = out
+    assert torch.equal(got[480], got[500][:got[480].shape[0]])
+    ctx.close()
+
+
+@pytest.mark.parametrize("B", [239, 240])
+def test_prepend_merge_and_heads_plans_on_both_sides(lib, B):
+    """239 queries are the most whose prepend and merge plans fit the arguments."""
+    import torch
+    cfg = synth.config("tiny")
+    ctx, _ = hz.make_context(cfg)
+    toks, rng = _queries(cfg, B, 7)
+    prm = [synth.query_tokens(cfg, 1)[q % 50:q % 50 + q % 3] for q in range(B)]
+    x0, off = hz.gpu_prepend(ctx, toks, prm)
+    ref = np.concatenate([np.concatenate([t[:1], p, t[1:]]) for t, p in zip(toks, prm)])
+    assert np.array_equal(x0.cpu().numpy(), ref)
+    T = int(off[-1])
+    metric = torch.randn((T, 12), generator=torch.Generator().manual_seed(2)).to("cuda")
+    r = rng.integers(0, 4, B).tolist()
+    n_out = [int(off[q + 1] - off[q]) - min(r[q], (int(off[q + 1] - off[q]) - 1) // 2) for q in range(B)]
+    ws = torch.empty(ctx.otas_merge_workspace_bytes(B, T), dtype=torch.uint8, device="cuda")
+    out = torch.full((sum(n_out), cfg.D), float("nan"), device="cuda")
+    sizes = torch.zeros(sum(n_out), dtype=torch.int32, device="cuda")
+    oo = ctx.otas_token_merge(x0, metric, 12, None, off, r, ws, out, sizes)
+    assert np.array_equal(np.diff(oo), n_out)
+    for q in (0, 1, B // 2, B - 1):     # alone, through the arguments
+        lo, hi = int(off[q]), int(off[q + 1])
+        o1 = torch.full((n_out[q], cfg.D), float("nan"), device="cuda")
+        s1 = torch.zeros(n_out[q], dtype=torch.int32, device="cuda")
+        ctx.otas_token_merge(x0[lo:hi].contiguous(), metric[lo:hi].contiguous(), 12, None, [0, hi - lo], [r[q]], ws, o1, s1)
+        assert torch.equal(o1, out[int(oo[q]):int(oo[q + 1])]) and torch.equal(s1, sizes[int(oo[q]):int(oo[q + 1])])
+    g = torch.Generator().manual_seed(4)
+    for classes in ([1, 7, 33], [64] * (150 if B == 240 else 3)):     # 150 tasks: the records alone pass the line
+        heads = [(torch.randn((k, cfg.D), generator=g).to("cuda"), torch.randn(k, generator=g).to("cuda")) for k in classes]
+        gam, bet = torch.ones(cfg.D, device="cuda"), torch.zeros(cfg.D, device="cuda")
+        task = [q % len(classes) for q in range(B)]
+        lg = torch.full((B, 70), float("nan"), device="cuda")
+        ctx.otas_task_heads(x0, off, task, heads, gam, bet, lg)
+        first = x0[torch.from_numpy(off[:-1].astype(np.int64)).to("cuda")].double()
+        h = torch.nn.functional.layer_norm(first, (cfg.D,), eps=1e-6)
+        for q in range(B):
+            k = classes[task[q]]
+            want = heads[task[q]][0].double() @ h[q] + heads[task[q]][1].double()
+            # D + 8 roundings of 2^-24 on sums of |w h|; |h| of a normalised row sums to less than D
+            bound = (cfg.D + 8) * 2.0 ** -24 * (heads[task[q]][0].double().abs() @ h[q].abs() + 1.0)
+            assert bool(((lg[q, :k].double() - want).abs() <= bound).all()) and bool((lg[q, k:] == 0).all())
+    ctx.close()
