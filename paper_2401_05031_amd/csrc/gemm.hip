@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -304,10 +305,39 @@ static hipError_t linear_f32(const void* x, const void* w, const void* bias, con
 // lanes per row) and applies bias / GELU / residual there, where the bias and residual loads and the
 // output stores are contiguous runs of a full row segment.  stage: this wave's region of
 // 32 * (32 TN + 4) floats, no longer used by anyone else (barrier before the call).
-template <int EPI, int TM, int TN>
-__device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage, const bf16_t* __restrict__ bias,
+// Residual rows of slab i of a wave's tile, in the layout the slab is read back in.
+template <int TN> struct ResSlab {
+  static constexpr int LPR = 8 * TN, RPI = 64 / LPR, NIT = 32 / RPI;
+  floatx4 v[NIT];
+  __device__ inline void load(const float* res, int64_t M, int N, int64_t m_slab, int n_wave, int lane) {
+    const int rrow = lane / LPR, n = n_wave + (lane % LPR) * 4;
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int64_t m = m_slab + it * RPI + rrow;
+      v[it] = *reinterpret_cast<const floatx4*>(res + (size_t)(m < M ? m : M - 1) * N + (n < N ? n : 0));
+    }
+  }
+};
+// The bias of a tile's BN columns waits in LDS for the epilogue: each of the first BN / 8 threads fetches 8 of them
+// (bias_fetch) before the operand loads and stores them (bias_stage) once the first of those have landed.  Fetched in the
+// epilogue they cost every tile a round trip to L2, or to HBM for the first tiles of a column.
+template <int BN>
+__device__ inline bf16x8 bias_fetch(const bf16_t* __restrict__ bias, int N, int n0, int tid) {
+  const int n = n0 + tid * 8;
+  const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  return tid < BN / 8 && n < N ? *reinterpret_cast<const bf16x8*>(bias + n) : zero;   // N % 8 == 0
+}
+template <int BN>
+__device__ inline void bias_stage(bf16_t* bias_s, const bf16x8& v, int tid) {
+  if (tid < BN / 8) *reinterpret_cast<bf16x8*>(bias_s + tid * 8) = v;
+}
+
+// bias_s: the bias of this wave's 32 TN columns in LDS.  first: the residual rows of slab 0, already requested
+// (HAVE_FIRST), so that the epilogue does not begin with a round trip to HBM.
+template <int EPI, int TM, int TN, bool HAVE_FIRST = false>
+__device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage, const bf16_t* bias_s,
                                      const float* res, typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N,
-                                     int64_t m_wave, int n_wave, int lane) {
+                                     int64_t m_wave, int n_wave, int lane, const ResSlab<TN>& first = ResSlab<TN>{}) {
   constexpr int WN = 32 * TN, LDR = WN + 4;
   constexpr int LPR = WN / 4;      // lanes per row when reading back
   constexpr int RPI = 64 / LPR;    // rows per read-back instruction
@@ -317,22 +347,18 @@ __device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage
   const int n = n_wave + rcol;
   const bool n_ok = n < N;         // N % 8 == 0: a 4-column group is inside or outside as a whole
   bf16x4 bb = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
-  if (EPI != EPI_PARTIAL) bb = *reinterpret_cast<const bf16x4*>(bias + (n_ok ? n : 0));
+  if (EPI != EPI_PARTIAL) bb = *reinterpret_cast<const bf16x4*>(bias_s + rcol);
   // The residual rows of slab i + 1 are requested before slab i goes through LDS, so their latency
   // is covered by a whole slab's work instead of being waited for once per slab.
-  floatx4 rr[2][NIT];
-  auto load_res = [&](int i) {
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int64_t m = m_wave + i * 32 + it * RPI + rrow;
-      rr[i & 1][it] = *reinterpret_cast<const floatx4*>(res + (size_t)(m < M ? m : M - 1) * N + (n_ok ? n : 0));
-    }
-  };
-  if (EPI == EPI_RESIDUAL) load_res(0);
+  ResSlab<TN> rr[2];
+  if (EPI == EPI_RESIDUAL) {
+    if (HAVE_FIRST) rr[0] = first;
+    else rr[0].load(res, M, N, m_wave, n_wave, lane);
+  }
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t m_slab = m_wave + i * 32;
-    if (EPI == EPI_RESIDUAL && i + 1 < TM) load_res(i + 1);
+    if (EPI == EPI_RESIDUAL && i + 1 < TM) rr[(i + 1) & 1].load(res, M, N, m_slab + 32, n_wave, lane);
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -364,7 +390,8 @@ __device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage
       if (m < M && n_ok) {
         const size_t idx = (size_t)m * N + n;
         if (EPI == EPI_RESIDUAL) {
-          floatx4 o = {v[0] + rr[i & 1][it][0], v[1] + rr[i & 1][it][1], v[2] + rr[i & 1][it][2], v[3] + rr[i & 1][it][3]};
+          const floatx4 r = rr[i & 1].v[it];
+          floatx4 o = {v[0] + r[0], v[1] + r[1], v[2] + r[2], v[3] + r[3]};
           *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(Y) + idx) = o;
         } else if (EPI == EPI_PARTIAL) {
           floatx4 o = {v[0], v[1], v[2], v[3]};
@@ -384,8 +411,8 @@ __device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage
 // float slab, and the read-back hands every lane 8 consecutive columns, so the global stores are
 // 16 bytes per lane and a row segment of 2 WN bytes goes out in one instruction.
 template <int EPI, int TM, int TN>
-__device__ inline void mfma_epilogue_bf16(const floatx16 (&acc)[TM][TN], bf16_t* stage, const bf16_t* __restrict__ bias,
-                                          bf16_t* Y, int64_t M, int N, int64_t m_wave, int n_wave, int lane) {
+__device__ inline void mfma_epilogue_bf16(const floatx16 (&acc)[TM][TN], bf16_t* stage, const bf16_t* bias_s, bf16_t* Y,
+                                          int64_t M, int N, int64_t m_wave, int n_wave, int lane) {
   constexpr int WN = 32 * TN, LDR = WN + 8;
   constexpr int LPR = WN / 8;      // lanes per row when reading back
   constexpr int RPI = 64 / LPR;    // rows per read-back instruction
@@ -398,10 +425,7 @@ __device__ inline void mfma_epilogue_bf16(const floatx16 (&acc)[TM][TN], bf16_t*
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int n = n_wave + 32 * j + 8 * g + 4 * fk;
-      bb[j][g] = *reinterpret_cast<const bf16x4*>(bias + (n < N ? n : 0));
-    }
+    for (int g = 0; g < 4; ++g) bb[j][g] = *reinterpret_cast<const bf16x4*>(bias_s + 32 * j + 8 * g + 4 * fk);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t m_slab = m_wave + i * 32;
@@ -468,6 +492,8 @@ __device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& til
 #define OTAS_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 // vmcnt(0) and lgkmcnt(0): this wave's loads have landed AND its LDS reads have returned.
 #define OTAS_WAIT_LOADS_AND_LDS() __builtin_amdgcn_s_waitcnt(7 << 4)
+// lgkmcnt(0) only (vmcnt, expcnt at their maxima).
+#define OTAS_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14))
 #define OTAS_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define OTAS_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
@@ -586,23 +612,29 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
   };
 
-  // Prologue: tiles 0 .. NS-2.  Loads complete in issue order: "at most n in flight" = all but the n
-  // youngest have landed.
+  // Prologue: the epilogue's bias and first residual rows, then tiles 0 .. NS-2.  Loads complete in issue order: "at
+  // most n in flight" = all but the n youngest have landed.
+  bf16_t* bias_s = Ws + NS * STAGE_W;
+  bf16x8 bias_v;
+  if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
+  ResSlab<TN> first;
+  if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t)
 #pragma unroll
     for (int d = 0; d < ND; ++d) dma_one(t, t, d);
 
   int st = 0, st_new = NS - 1;
-  for (int kt = 0; kt < KT; ++kt) {
-    OTAS_VMCNT(ND * (NS - 2));   // tile kt landed; tiles kt+1 .. kt+NS-2 may still be in flight
+  auto tile = [&](int kt, auto more) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int f = 0; f < NF; ++f) read_frag(st, 0, 0, f);
+    if constexpr (decltype(more)::value) {
 #pragma unroll
-    for (int d = 0; d < ND; ++d) dma_one(kt + NS - 1, st_new, d);
+      for (int d = 0; d < ND; ++d) dma_one(kt + NS - 1, st_new, d);
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < NM; ++t) {
@@ -614,17 +646,30 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     for (int t = 0; t < NM; ++t) mfma_one(1, t);
     st = st + 1 == NS ? 0 : st + 1;
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
+  };
+  static_assert(NS == 3, "the last two k-tiles below");
+  OTAS_VMCNT(ND * (NS - 2));   // tile 0 landed, and everything requested before it
+  if (EPI != EPI_PARTIAL) bias_stage<BN>(bias_s, bias_v, tid);
+  tile(0, std::bool_constant<true>());   // KT >= 2; for KT == 2 its request repeats the last tile
+  for (int kt = 1; kt < KT - 2; ++kt) {
+    OTAS_VMCNT(ND * (NS - 2));   // tile kt landed; tile kt+1 may still be in flight
+    tile(kt, std::bool_constant<true>());
   }
-  OTAS_VMCNT(0);      // every load of this wave has landed ...
+  if (KT > 2) {
+    OTAS_VMCNT(ND * (NS - 2));
+    tile(KT - 2, std::bool_constant<false>());
+  }
+  OTAS_VMCNT(0);
+  tile(KT - 1, std::bool_constant<false>());
   asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();   // ... and of every other wave: the stages become the epilogue's staging area
+  __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the stages become the epilogue's staging area
   asm volatile("" ::: "memory");
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias, Y, M, N,
+    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, TM, TN>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias, res, Y, M, N,
-                               m0 + wm * WM, n0 + wn * WN, lane);
+    mfma_epilogue<EPI, TM, TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
+                                                    bias_s + wn * WN, res, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
 template <int NS, int TM>
@@ -633,7 +678,7 @@ static hipError_t linear_mfma_k32(const void* x, const void* w, const void* bias
                                   const PlanTail* pt = nullptr) {
   constexpr int BM = 64 * TM;
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + 127) / 128;
-  const size_t lds = (size_t)NS * (BM + 128) * 32 * sizeof(bf16_t);
+  const size_t lds = ((size_t)NS * (BM + 128) * 32 + 128) * sizeof(bf16_t);   // the stages and the tile's bias
   static_assert(4 * 32 * (64 + 4) * sizeof(float) <= (size_t)NS * (BM + 128) * 32 * sizeof(bf16_t), "epilogue slab");
   static_assert(kPlanListsLdsMax <= (size_t)NS * (BM + 128) * 32 * sizeof(bf16_t), "plan lists");
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0)), (unsigned)splits), block(256);
@@ -706,11 +751,14 @@ __global__ __launch_bounds__(256, 4) void gemm_mfma64_kernel(const bf16_t* __res
   for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
   const int fr = lane & 31, fk = lane >> 5;
   const int frag_row = fr * BK, sw = (fr >> 2) & 3;
+  bf16_t* bias_s = Ws + NS * STAGE_W;
+  const bf16x8 bias_v = bias_fetch<BN>(bias, N, n0, tid);
+  ResSlab<1> first;
+  if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * 32, n0 + wn * 32, lane);
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) dma(t, t);
   int st = 0, st_new = NS - 1;
-  for (int kt = 0; kt < KT; ++kt) {
-    OTAS_VMCNT(ND * (NS - 2));
+  auto tile = [&](int kt, auto more) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -721,28 +769,48 @@ __global__ __launch_bounds__(256, 4) void gemm_mfma64_kernel(const bf16_t* __res
       af[ks] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * 32) * BK + frag_row + c);
       wf[ks] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * 32) * BK + frag_row + c);
     }
-    dma(kt + NS - 1, st_new);
+    if constexpr (decltype(more)::value) dma(kt + NS - 1, st_new);
     acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0], af[0], acc[0][0], 0, 0, 0);
     acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[1], af[1], acc[0][0], 0, 0, 0);
     st = st + 1 == NS ? 0 : st + 1;
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
+  };
+  static_assert(NS == 4, "the last three k-tiles below");
+  OTAS_VMCNT(ND * (NS - 2));   // tile 0 landed, and everything requested before it
+  bias_stage<BN>(bias_s, bias_v, tid);
+  int kt = 0;
+  if (KT < NS) {   // K = 64 or 96: the prologue requested more tiles than there are (they repeat the last one)
+    tile(kt++, std::bool_constant<false>());
+  } else {
+    tile(kt++, std::bool_constant<true>());
+    for (; kt < KT - 3; ++kt) {
+      OTAS_VMCNT(ND * (NS - 2));
+      tile(kt, std::bool_constant<true>());
+    }
+    OTAS_VMCNT(ND * (NS - 2));
+    tile(kt++, std::bool_constant<false>());
+  }
+  for (; kt < KT - 1; ++kt) {
+    OTAS_VMCNT(ND);
+    tile(kt, std::bool_constant<false>());
   }
   OTAS_VMCNT(0);
+  tile(KT - 1, std::bool_constant<false>());
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, 1, 1>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias, Y, M, N,
+    mfma_epilogue_bf16<EPI, 1, 1>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias_s + wn * 32, Y, M, N,
                                   m0 + wm * 32, n0 + wn * 32, lane);
   else
-    mfma_epilogue<EPI, 1, 1>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (32 + 4), bias, res, Y, M, N,
-                             m0 + wm * 32, n0 + wn * 32, lane);
+    mfma_epilogue<EPI, 1, 1, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (32 + 4),
+                                                  bias_s + wn * 32, res, Y, M, N, m0 + wm * 32, n0 + wn * 32, lane, first);
 }
 
 static hipError_t linear_mfma64(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
                                 int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
   const int tiles_m = (int)((M + 63) / 64), tiles_n = (N + 63) / 64;
-  const size_t lds = (size_t)4 * (64 + 64) * 32 * sizeof(bf16_t);
+  const size_t lds = ((size_t)4 * (64 + 64) * 32 + 64) * sizeof(bf16_t);   // the stages and the tile's bias
   static_assert(4 * 32 * (32 + 4) * sizeof(float) <= (size_t)4 * (64 + 64) * 32 * sizeof(bf16_t), "epilogue slab");
   static_assert(kPlanListsLdsMax <= (size_t)4 * (64 + 64) * 32 * sizeof(bf16_t), "plan lists");
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0))), block(256);
@@ -873,49 +941,60 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   // during k-step 2), then wait for this wave's loads of tile t+1, barrier -- after it nobody reads
   // stage t & 1 any more and tile t+1 is visible --, then k-step 3 while the loads of tile t+2 are
   // issued into stage t & 1 and the first fragments of tile t+1 are read.
+  // The last two tiles request nothing (LOAD), the last one reads no fragments ahead either (NEXT) and waits for no loads:
+  // the first residual rows, requested beside the last-but-one tile's k-step 3, may still be on their way.
+  bf16_t* bias_s = Ws + NS * STAGE_W;
+  const bf16x8 bias_v = bias_fetch<BN>(bias, N, n0, tid);
+  constexpr bool FIRST = EPI == EPI_RESIDUAL && TM <= 4;   // TM = 5 leaves no registers for them
+  ResSlab<TN> first;
 #pragma unroll
   for (int d = 0; d < ND; ++d) dma_one(0, 0, d);
 #pragma unroll
   for (int d = 0; d < ND; ++d) dma_one(1, 1, d);
-  OTAS_VMCNT(ND);    // tile 0 landed (this wave's part)
+  OTAS_VMCNT(ND);    // tile 0 landed (this wave's part), and the bias before it
+  bias_stage<BN>(bias_s, bias_v, tid);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int f = 0; f < NF; ++f) read_frag(0, 0, 0, f);
 
-  for (int kt = 0; kt < KT; ++kt) {
+  auto tile = [&](int kt, auto load, auto next) {
+    constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
     const int st = kt & 1;
     kstep(0, st, 1);
     kstep(1, st, 2);
     kstep(0, st, 3);
     // tile kt+1 landed, and the fragments of k-step 3 (read from stage st above, used below) are in
     // registers: after the barrier other waves start overwriting stage st
-    OTAS_WAIT_LOADS_AND_LDS();
+    if constexpr (NEXT) OTAS_WAIT_LOADS_AND_LDS();
+    else OTAS_WAIT_LDS();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if constexpr (FIRST && NEXT && !LOAD) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
     // k-step 3: fragments of (tile kt+1, k-step 0) and the ND load instructions of tile kt+2,
     // spread over the MFMAs
 #pragma unroll
     for (int t = 0; t < NM; ++t) {
       mfma_one(1, t);
-      if (t < NF) read_frag(st ^ 1, 0, 0, t);
+      if (NEXT && t < NF) read_frag(st ^ 1, 0, 0, t);
+      if constexpr (LOAD) {
 #pragma unroll
-      for (int d = t * ND / NM; d < (t + 1) * ND / NM; ++d) dma_one(kt + 2, st, d);
+        for (int d = t * ND / NM; d < (t + 1) * ND / NM; ++d) dma_one(kt + 2, st, d);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
-  }
-  OTAS_VMCNT(0);
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  };
+  for (int kt = 0; kt < KT - 2; ++kt) tile(kt, std::true_type(), std::true_type());
+  tile(KT - 2, std::false_type(), std::true_type());
+  tile(KT - 1, std::false_type(), std::false_type());   // its barrier: no wave reads a stage any more, the epilogue may write
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias, Y, M, N,
+    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, TM, TN>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias, res, Y, M, N,
-                               m0 + wm * WM, n0 + wn * WN, lane);
+    mfma_epilogue<EPI, TM, TN, FIRST>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias_s + wn * WN, res, Y,
+                                      M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
 template <int TM>
@@ -923,7 +1002,7 @@ static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bia
                                    int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
   constexpr int BM = 64 * TM;
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + 255) / 256;
-  const size_t lds = (size_t)2 * (BM + 256) * 64 * sizeof(bf16_t);
+  const size_t lds = ((size_t)2 * (BM + 256) * 64 + 256) * sizeof(bf16_t);   // the stages and the tile's bias
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0))), block(512);
 #define OTAS_MFMA(E, ...)                                                                                         \
   do {                                                                                                            \
@@ -1033,18 +1112,25 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
     }
   };
 
+  bf16_t* bias_s = Ws + 2 * STAGE;
+  bf16x8 bias_v;
+  if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
+  ResSlab<TN> first;
+  if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
 #pragma unroll
   for (int d = 0; d < 8; ++d) dma_one(0, 0, d);
 #pragma unroll
   for (int d = 0; d < 8; ++d) dma_one(1, 1, d);
   OTAS_VMCNT(8);
+  if (EPI != EPI_PARTIAL) bias_stage<BN>(bias_s, bias_v, tid);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int f = 0; f < TM + TN; ++f) read_frag(0, 0, 0, f);
 
-  for (int kt = 0; kt < KT; ++kt) {
+  auto tile = [&](int kt, auto load, auto next) {   // as in gemm_mfma256w8_kernel
+    constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
     const int st = kt & 1;
     kstep(0, st, 1);
     kstep(1, st, 2);
@@ -1058,29 +1144,30 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
 #pragma unroll
     for (int t = 0; t < 4; ++t) {   // k-step 3: first fragments of tile kt+1, loads of tile kt+2
       mfma_one(1, t);
-      read_frag(st ^ 1, 0, 0, t);
-      dma_one(kt + 2, st, 2 * t);
-      dma_one(kt + 2, st, 2 * t + 1);
+      if (NEXT) read_frag(st ^ 1, 0, 0, t);
+      if constexpr (LOAD) {
+        dma_one(kt + 2, st, 2 * t);
+        dma_one(kt + 2, st, 2 * t + 1);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
-  }
-  OTAS_VMCNT(0);
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  };
+  for (int kt = 0; kt < KT - 2; ++kt) tile(kt, std::true_type(), std::true_type());
+  tile(KT - 2, std::false_type(), std::true_type());
+  tile(KT - 1, std::false_type(), std::false_type());
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias, Y, M, N,
+    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, TM, TN>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias, res, Y, M, N,
-                               m0 + wm * WM, n0 + wn * WN, lane);
+    mfma_epilogue<EPI, TM, TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
+                                                    bias_s + wn * WN, res, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
 static hipError_t linear_mfma128k64(const void* x, const void* w, const void* bias, const float* res, void* y,
                                     int64_t M, int N, int K, int epi, hipStream_t s, int splits = 1,
                                     const PlanTail* pt = nullptr) {
   const int tiles_m = (int)((M + 127) / 128), tiles_n = (N + 127) / 128;
-  const size_t lds = (size_t)2 * 2 * 128 * 64 * sizeof(bf16_t);
+  const size_t lds = ((size_t)2 * 2 * 128 * 64 + 128) * sizeof(bf16_t);   // the stages and the tile's bias
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0)), (unsigned)splits), block(256);
   const int k_len = K / splits;
 #define OTAS_MFMA(E, ...)                                                                                         \
