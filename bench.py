@@ -290,7 +290,7 @@ def rooflines(res):
     # one row per GEMM launch of a forward pass: rows, the kernel the library picks (block tile, workgroup
     # slots on 256 CUs), tiles, rounds of those slots, microseconds, TFLOP/s
     tiles_of = {1: (64, 64, 2048), 2: (128, 128, 768), 3: (128, 128, 512), 4: (192, 256, 256), 5: (256, 256, 256),
-                6: (320, 256, 256), 7: (64, 64, 1280)}
+                6: (320, 256, 256), 7: (64, 64, 512)}
     cfg, ctx = res["cfg"], res.get("ctx")
     if ctx is not None and not cfg.deep:
         table = []
@@ -299,11 +299,11 @@ def rooflines(res):
         for kind, (rows, N, K, epi) in shapes.items():
             for l, (M, ms) in enumerate(zip(rows, res["launches"].get(kind, []))):
                 S = w["splits"][l] if kind == "gemm_fc2" else 1
-                # split products run the partial-output form of the 128 x 128 kernels: K step 64 where K / S allows it
-                kid = (3 if K % (S * 64) == 0 and K // S >= 128 else 2) if S > 1 else ctx.otas_linear_choice(M, N, K, epi)
+                # split products run the partial-output form of the 128 x 128 or the 64 x 64 kernel (not told apart here)
+                kid = 0 if S > 1 else ctx.otas_linear_choice(M, N, K, epi)
                 bm, bn, slots = tiles_of.get(kid, (0, 0, 1))
                 tiles = -(-M // bm) * -(-N // bn) * S if bm else 0
-                table.append({"kind": kind, "layer": l, "M": int(M), "N": N, "K": K, "kernel": kid, "tile": f"{bm}x{bn}",
+                table.append({"kind": kind, "layer": l, "M": int(M), "N": N, "K": K, "kernel": kid, "tile": f"{bm}x{bn}" if bm else "split",
                               "split_k": S, "tiles": int(tiles), "rounds": round(tiles / slots, 2), "us": round(ms * 1e3, 1),
                               "tflops": round(2.0 * M * N * K / (ms * 1e-3) / 1e12, 1)})
         out["gemm_per_launch"] = table

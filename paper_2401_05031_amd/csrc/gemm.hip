@@ -6,10 +6,10 @@
 //                          shapes the bf16 kernels do not take.
 //   * bf16 MFMA (v_mfma_f32_32x32x16_bf16), fp32 accumulate, operand tiles loaded straight into
 //     swizzled LDS stages, fused bias / GELU / residual epilogue (bf16 models):
-//       gemm_mfma_k32_kernel     128 x 128, K step 32, three workgroups per CU (also split-K)
-//       gemm_mfma128k64_kernel   128 x 128, K step 64, two per CU (also split-K: the form split launches run)
+//       gemm_mfma_k32_kernel     128 x 128, K step 32, three workgroups per CU
+//       gemm_mfma128k64_kernel   128 x 128, K step 64, two per CU (also split-K)
 //       gemm_mfma256w8_kernel    192 / 256 / 320 x 256, eight waves, one per CU
-//       gemm_mfma64_kernel       64 x 64, K step 32, for products of very few rows
+//       gemm_mfma64_kernel       64 x 64, K step 64 or 32, for products of very few rows (also split-K)
 //     pick_mfma_kernel chooses among them with a cost model fitted to measured launch times; splitk_factor
 //     decides with the same model whether the MLP's second linear is split over K.
 //     Each kernel has a PLAN form for the attention output projection, whose first workgroups write the lists
@@ -534,10 +534,7 @@ __device__ __forceinline__ void plan_tail_run(const PlanTail& pt, unsigned char*
 template <int EPI, int NS, int TM, bool PLAN = false>
 __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias, const float* res,
-    typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N, int K, int k_len, int tiles_m, int tiles_n,
-    PlanTail pt) {
-  // K is the row length of A and W; this workgroup contracts over k_len of it, starting at
-  // blockIdx.y * k_len (split-K launches write one float partial result [M, N] per blockIdx.y).
+    typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N, int K, int tiles_m, int tiles_n, PlanTail pt) {
   constexpr int WM = 32 * TM, BM = 2 * WM, BN = 128, BK = 32, WN = 64, TN = 2;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;   // elements per stage
   constexpr int NM = TM * TN, NF = TM + TN, ND = TM + 2;   // MFMAs / fragment reads per k-step, loads per tile
@@ -555,8 +552,8 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
   const int n0 = tile_n * BN;
 
   // DMA addressing: 16 rows of 64 B per instruction; wave w owns rows w*16*TM .. of the A tile and rows
-  // w*32 .. of the W tile.  Global addresses: uniform base (tile origin + this split's k range + k)
-  // plus a constant per-lane 32-bit byte offset.
+  // w*32 .. of the W tile.  Global addresses: uniform base (tile origin + k) plus a constant per-lane
+  // 32-bit byte offset.
   uint32_t a_off[TM], w_off[2];
 #pragma unroll
   for (int j = 0; j < TM; ++j) {
@@ -574,10 +571,9 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     const uint32_t rw = (uint32_t)(row < w_last ? row : w_last);
     w_off[j] = (rw * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
   }
-  const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K + (size_t)blockIdx.y * k_len);
-  const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K + (size_t)blockIdx.y * k_len);
-  if (EPI == EPI_PARTIAL) Y += (size_t)blockIdx.y * M * N;
-  const int KT = k_len / BK;
+  const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K);
+  const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K);
+  const int KT = K / BK;
   auto dma_one = [&](int kt, int st, int d) {   // d = 0..TM-1: A rows; TM, TM+1: W rows
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
     if (d < TM)
@@ -615,8 +611,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
   // Prologue: the epilogue's bias and first residual rows, then tiles 0 .. NS-2.  Loads complete in issue order: "at
   // most n in flight" = all but the n youngest have landed.
   bf16_t* bias_s = Ws + NS * STAGE_W;
-  bf16x8 bias_v;
-  if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
+  const bf16x8 bias_v = bias_fetch<BN>(bias, N, n0, tid);
   ResSlab<TN> first;
   if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
 #pragma unroll
@@ -649,7 +644,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
   };
   static_assert(NS == 3, "the last two k-tiles below");
   OTAS_VMCNT(ND * (NS - 2));   // tile 0 landed, and everything requested before it
-  if (EPI != EPI_PARTIAL) bias_stage<BN>(bias_s, bias_v, tid);
+  bias_stage<BN>(bias_s, bias_v, tid);
   tile(0, std::bool_constant<true>());   // KT >= 2; for KT == 2 its request repeats the last tile
   for (int kt = 1; kt < KT - 2; ++kt) {
     OTAS_VMCNT(ND * (NS - 2));   // tile kt landed; tile kt+1 may still be in flight
@@ -674,51 +669,57 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
 
 template <int NS, int TM>
 static hipError_t linear_mfma_k32(const void* x, const void* w, const void* bias, const float* res, void* y,
-                                  int64_t M, int N, int K, int epi, hipStream_t s, int splits = 1,
-                                  const PlanTail* pt = nullptr) {
+                                  int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt) {
   constexpr int BM = 64 * TM;
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + 127) / 128;
   const size_t lds = ((size_t)NS * (BM + 128) * 32 + 128) * sizeof(bf16_t);   // the stages and the tile's bias
   static_assert(4 * 32 * (64 + 4) * sizeof(float) <= (size_t)NS * (BM + 128) * 32 * sizeof(bf16_t), "epilogue slab");
   static_assert(kPlanListsLdsMax <= (size_t)NS * (BM + 128) * 32 * sizeof(bf16_t), "plan lists");
-  dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0)), (unsigned)splits), block(256);
-  const int k_len = K / splits;
+  dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0))), block(256);
 #define OTAS_MFMA(E, ...)                                                                                         \
   do {                                                                                                            \
     auto kern = gemm_mfma_k32_kernel<E, NS, TM, ##__VA_ARGS__>;                                                   \
     hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
-                                  (typename OutType<bf16_t, E>::type*)y, M, N, K, k_len, tiles_m, tiles_n,        \
+                                  (typename OutType<bf16_t, E>::type*)y, M, N, K, tiles_m, tiles_n,               \
                                   pt ? *pt : PlanTail{});                                                         \
   } while (0)
   if (pt) {
-    if (epi != EPI_RESIDUAL || splits != 1) return hipErrorInvalidValue;
+    if (epi != EPI_RESIDUAL) return hipErrorInvalidValue;
     OTAS_MFMA(EPI_RESIDUAL, true);
   } else if (epi == EPI_NONE) OTAS_MFMA(EPI_NONE);
   else if (epi == EPI_GELU) OTAS_MFMA(EPI_GELU);
-  else if (epi == EPI_PARTIAL) OTAS_MFMA(EPI_PARTIAL);
   else OTAS_MFMA(EPI_RESIDUAL);
 #undef OTAS_MFMA
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------ 64 x 64, K step 32
+// ------------------------------------------------------------------------------ 64 x 64
 // For products of so few rows that 128 x 128 tiles leave most CUs without a workgroup (small serving batches: a
 // ViT-B query is 197 rows): block tile 64 x 64, four waves of 32 x 32 in a 2 x 2 arrangement, the same
-// direct-to-LDS ring as gemm_mfma_k32_kernel with NS = 4 stages of 8 KB (up to five workgroups per CU).  Four times
-// the workgroups of the 128 x 128 tiling at twice the operand bytes per FLOP: it wins while the launch is bound by
-// the serial k-loop of a lone workgroup per CU, not by what the CUs can load.
-template <int EPI, bool PLAN = false>
-__global__ __launch_bounds__(256, 4) void gemm_mfma64_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
-                                                             const bf16_t* __restrict__ bias, const float* res,
-                                                             typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N,
-                                                             int K, int tiles_m, int tiles_n, PlanTail pt) {
-  constexpr int BM = 64, BN = 64, BK = 32, NS = 4, ND = 2;
+// direct-to-LDS ring with NS = 4 stages.  Four times the workgroups of the 128 x 128 tiling at twice the operand
+// bytes per FLOP.  Such a launch lasts as long as one workgroup's chain of k-tiles, each a barrier, an LDS round trip
+// and BK / 16 MFMAs that follow one another; K step 64 halves that chain's barriers and fetches whole cache lines (64 KB
+// of LDS, two workgroups per CU); K step 128 (128 KB, one per CU) was no faster with a CU for every tile and slower
+// beyond.  K step 32 remains for K that is no multiple of 64.
+// Stage layout: 16-byte chunk c of row r sits at chunk c ^ swz(r), which puts the 16 rows that are served per clock on all
+// 64 banks once.
+// Measured on MI355X (us, K step 32 / 64 / 128): 197 x 2304 x 768 6.3 / 5.4 / 5.6, 197 x 768 x 768 + residual 6.4 / 5.5 / 5.8,
+// 197 x 3072 x 768 + GELU 6.8 / 5.9 / 6.1, 1400 x 768 x 768 9.3 / 8.5 / 11.4, 600 x 3072 x 1024 11.7 / 9.4 / 12.2.
+template <int EPI, int BK, bool PLAN = false>
+__global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias, const float* res,
+    typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N, int K, int k_len, int tiles_m, int tiles_n, PlanTail pt) {
+  constexpr int BM = 64, BN = 64, NS = 4;
+  constexpr int CPR = BK / 8;                    // 16-byte chunks per row
+  constexpr int RPI = 64 / CPR;                  // rows per DMA instruction
+  constexpr int NI = 16 / RPI, ND = 2 * NI;      // DMA instructions per wave and operand tile, per k-tile
+  constexpr int KS = BK / 16;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][64][32]
-  bf16_t* Ws = As + NS * STAGE_A;                 // [NS][64][32]
+  bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][64][BK]
+  bf16_t* Ws = As + NS * STAGE_A;                 // [NS][64][BK]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -727,32 +728,41 @@ __global__ __launch_bounds__(256, 4) void gemm_mfma64_kernel(const bf16_t* __res
   tile_of_block(bid, tiles_m, tiles_n, tile_m, tile_n);
   const int64_t m0 = (int64_t)tile_m * BM;
   const int n0 = tile_n * BN;
-  // DMA: 16 rows of 64 B per instruction; wave w loads rows 16 w .. of the A tile and of the W tile
-  uint32_t a_off, w_off;
-  {
-    const int row = wave * 16 + (lane >> 2);
-    const int c = (lane & 3) ^ ((row >> 2) & 3);
+  auto swz = [](int r) { return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; };
+  // DMA: wave w loads rows 16 w .. of the A tile and of the W tile, RPI rows per instruction
+  uint32_t a_off[NI], w_off[NI];
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    const int row = wave * 16 + j * RPI + lane / CPR;
+    const int c = (lane % CPR) ^ swz(row);
     const int64_t a_last = M - 1 - m0;
     const int w_last = N - 1 - n0;
     const uint32_t ra = (uint32_t)(row < a_last ? row : a_last), rw = (uint32_t)(row < w_last ? row : w_last);
-    a_off = (ra * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
-    w_off = (rw * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
+    a_off[j] = (ra * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
+    w_off[j] = (rw * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
   }
-  const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K);
-  const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K);
-  const int KT = K / BK;
+  const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K + (size_t)blockIdx.y * k_len);
+  const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K + (size_t)blockIdx.y * k_len);
+  if (EPI == EPI_PARTIAL) Y += (size_t)blockIdx.y * M * N;
+  const int KT = k_len / BK;
   auto dma = [&](int kt, int st) {
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
-    __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off), OTAS_LPTR(As + st * STAGE_A + wave * 16 * BK), 16, 0, 0);
-    __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off), OTAS_LPTR(Ws + st * STAGE_W + wave * 16 * BK), 16, 0, 0);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
+                                       OTAS_LPTR(As + st * STAGE_A + (wave * 16 + j * RPI) * BK), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[j]),
+                                       OTAS_LPTR(Ws + st * STAGE_W + (wave * 16 + j * RPI) * BK), 16, 0, 0);
+    }
   };
   floatx16 acc[1][1];
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
   const int fr = lane & 31, fk = lane >> 5;
-  const int frag_row = fr * BK, sw = (fr >> 2) & 3;
+  const int frag_row = fr * BK, sw = swz(fr);   // swz of 32 w + fr is swz of fr
   bf16_t* bias_s = Ws + NS * STAGE_W;
-  const bf16x8 bias_v = bias_fetch<BN>(bias, N, n0, tid);
+  bf16x8 bias_v;
+  if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
   ResSlab<1> first;
   if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * 32, n0 + wn * 32, lane);
 #pragma unroll
@@ -762,25 +772,26 @@ __global__ __launch_bounds__(256, 4) void gemm_mfma64_kernel(const bf16_t* __res
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    bf16x8 af[2], wf[2];
+    bf16x8 af[KS], wf[KS];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int ks = 0; ks < KS; ++ks) {
       const int c = (((ks << 1) + fk) ^ sw) * 8;
       af[ks] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * 32) * BK + frag_row + c);
       wf[ks] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * 32) * BK + frag_row + c);
     }
     if constexpr (decltype(more)::value) dma(kt + NS - 1, st_new);
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[0], af[0], acc[0][0], 0, 0, 0);
-    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[1], af[1], acc[0][0], 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks], af[ks], acc[0][0], 0, 0, 0);
     st = st + 1 == NS ? 0 : st + 1;
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
   };
   static_assert(NS == 4, "the last three k-tiles below");
   OTAS_VMCNT(ND * (NS - 2));   // tile 0 landed, and everything requested before it
-  bias_stage<BN>(bias_s, bias_v, tid);
+  if (EPI != EPI_PARTIAL) bias_stage<BN>(bias_s, bias_v, tid);
   int kt = 0;
-  if (KT < NS) {   // K = 64 or 96: the prologue requested more tiles than there are (they repeat the last one)
-    tile(kt++, std::bool_constant<false>());
+  if (KT < NS) {   // up to three k-tiles: the prologue requested more than there are (they repeat the last one)
+    if (KT > 1) tile(kt++, std::bool_constant<false>());
   } else {
     tile(kt++, std::bool_constant<true>());
     for (; kt < KT - 3; ++kt) {
@@ -807,27 +818,39 @@ __global__ __launch_bounds__(256, 4) void gemm_mfma64_kernel(const bf16_t* __res
                                                   bias_s + wn * 32, res, Y, M, N, m0 + wm * 32, n0 + wn * 32, lane, first);
 }
 
-static hipError_t linear_mfma64(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
-                                int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
+template <int BK>
+static hipError_t linear_mfma64_bk(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
+                                   int N, int K, int epi, hipStream_t s, int splits, const PlanTail* pt) {
   const int tiles_m = (int)((M + 63) / 64), tiles_n = (N + 63) / 64;
-  const size_t lds = ((size_t)4 * (64 + 64) * 32 + 64) * sizeof(bf16_t);   // the stages and the tile's bias
-  static_assert(4 * 32 * (32 + 4) * sizeof(float) <= (size_t)4 * (64 + 64) * 32 * sizeof(bf16_t), "epilogue slab");
-  static_assert(kPlanListsLdsMax <= (size_t)4 * (64 + 64) * 32 * sizeof(bf16_t), "plan lists");
-  dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0))), block(256);
+  const size_t lds = ((size_t)4 * (64 + 64) * BK + 64) * sizeof(bf16_t);   // the stages and the tile's bias
+  static_assert(4 * 32 * (32 + 4) * sizeof(float) <= (size_t)4 * (64 + 64) * BK * sizeof(bf16_t), "epilogue slab");
+  static_assert(kPlanListsLdsMax <= (size_t)4 * (64 + 64) * BK * sizeof(bf16_t), "plan lists");
+  dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0)), (unsigned)splits), block(256);
+  const int k_len = K / splits;
 #define OTAS_MFMA(E, ...)                                                                                         \
   do {                                                                                                            \
-    gemm_mfma64_kernel<E, ##__VA_ARGS__><<<grid, block, lds, s>>>(                                                \
-        (const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res, (typename OutType<bf16_t, E>::type*)y, M,   \
-        N, K, tiles_m, tiles_n, pt ? *pt : PlanTail{});                                                           \
+    auto kern = gemm_mfma64_kernel<E, BK, ##__VA_ARGS__>;                                                         \
+    hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
+    if (e != hipSuccess) return e;                                                                                \
+    kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
+                                  (typename OutType<bf16_t, E>::type*)y, M, N, K, k_len, tiles_m, tiles_n,        \
+                                  pt ? *pt : PlanTail{});                                                         \
   } while (0)
   if (pt) {
-    if (epi != EPI_RESIDUAL) return hipErrorInvalidValue;
+    if (epi != EPI_RESIDUAL || splits != 1) return hipErrorInvalidValue;
     OTAS_MFMA(EPI_RESIDUAL, true);
   } else if (epi == EPI_NONE) OTAS_MFMA(EPI_NONE);
   else if (epi == EPI_GELU) OTAS_MFMA(EPI_GELU);
+  else if (epi == EPI_PARTIAL) OTAS_MFMA(EPI_PARTIAL);
   else OTAS_MFMA(EPI_RESIDUAL);
 #undef OTAS_MFMA
   return hipGetLastError();
+}
+
+static hipError_t linear_mfma64(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
+                                int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr, int splits = 1) {
+  return K % (splits * 64) == 0 ? linear_mfma64_bk<64>(x, w, bias, res, y, M, N, K, epi, s, splits, pt)
+                                : linear_mfma64_bk<32>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
 }
 
 // ------------------------------------------------------------------------------ 256x256, 8 waves
@@ -1196,7 +1219,7 @@ static hipError_t linear_mfma_kernel(int kernel, const void* x, const void* w, c
                                      const PlanTail* pt = nullptr) {
   const bool k32 = K % 32 == 0 && K >= 64, k64 = K % 64 == 0 && K >= 128;
   switch (kernel) {
-    case GK_128_K32: return k32 ? linear_mfma_k32<3, 2>(x, w, bias, res, y, M, N, K, epi, s, 1, pt) : hipErrorInvalidValue;
+    case GK_128_K32: return k32 ? linear_mfma_k32<3, 2>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     case GK_128_K64: return k64 ? linear_mfma128k64(x, w, bias, res, y, M, N, K, epi, s, 1, pt) : hipErrorInvalidValue;
     case GK_192X256: return k64 ? linear_mfma256w8<3>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     case GK_256X256: return k64 ? linear_mfma256w8<4>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
@@ -1217,13 +1240,17 @@ static double rounds_cost(double tiles, int slots, double p) {
   return full + (frac > 0 ? p + (1.0 - p) * frac : 0.0);
 }
 
+// The 64 x 64 kernel: a workgroup's chain of k-tiles, its length fixed, times what sharing a CU costs it.  Fitted to
+// launches of 21 .. 2368 rows, N = 768 .. 3072, K = 384 .. 1536 (us measured / modelled: 197 x 2304 x 768 5.4 / 5.6,
+// 600 x 2304 x 768 7.6 / 8.3, 2368 x 768 x 768 9.9 / 9.5, 1400 x 2304 x 768 13.4 / 14.2; eight-way split 197 x 768 x 3072 6.5 / 6.6).
+static double tile64_cost(int64_t M, int N, int k_len, int splits, double alpha) {
+  const double n = (double)((M + 63) / 64) * ((N + 63) / 64) * splits / 256.0;   // workgroups per CU
+  return (alpha + 0.0033 * k_len) * (n <= 1.0 ? 0.95 + 0.17 * n : 0.62 + 0.66 * n);
+}
+
 static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = nullptr) {
   if (cost_us) *cost_us = 0.0;
-  // So few outputs that even 64 x 64 tiles do not fill the chip twice: the small-tile kernel (measured on MI355X
-  // at K = 768: 197 x 2304 8.3 -> 5.9 us, 788 x 768 9.6 -> 6.4, 2368 x 768 12.1 -> 9.8; from ~470 tiles on it loses,
-  // 788 x 3072 11.1 -> 12.9, 3392 x 768 13.2 -> 14.6: it loads twice the operand bytes per FLOP)
-  if (((M + 63) / 64) * ((N + 63) / 64) <= 450 && !cost_us) return GK_64X64;
-  if (K % 64 != 0 || K < 128) return GK_128_K32;
+  if (K % 64 != 0 || K < 128) return ((M + 63) / 64) * ((N + 63) / 64) <= 450 ? GK_64X64 : GK_128_K32;
   struct Cand { int id, bm, bn, slots; double alpha[3], beta, p; };
   static const Cand cands[] = {
       {GK_128_K32, 128, 128, 768, {4.06, 7.04, 13.0}, 0.0278, 0.27},
@@ -1232,12 +1259,13 @@ static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = 
       {GK_256X256, 256, 256, 256, {5.85, 14.9, 12.7}, 0.0252, 0.72},
       {GK_320X256, 320, 256, 256, {8.34, 19.2, 14.7}, 0.0284, 0.74},
   };
-  double best = 1e30;
-  int kernel = GK_128_K32;
+  const int e = epi == EPI_RESIDUAL ? 2 : epi == EPI_GELU ? 1 : 0;
+  static const double alpha64[3] = {2.8, 3.3, 3.0};
+  double best = tile64_cost(M, N, K, 1, alpha64[e]);
+  int kernel = GK_64X64;
   for (const Cand& c : cands) {
     const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-    const double cost =
-        (c.alpha[epi == EPI_RESIDUAL ? 2 : epi == EPI_GELU ? 1 : 0] + c.beta * K) * rounds_cost(tiles, c.slots, c.p);
+    const double cost = (c.alpha[e] + c.beta * K) * rounds_cost(tiles, c.slots, c.p);
     if (cost < best) { best = cost; kernel = c.id; }
   }
   if (cost_us) *cost_us = best;
@@ -1252,8 +1280,18 @@ static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = 
 // applies the LayerNorm that follows -- so the split costs S + 1 more float passes over the
 // output than the one-kernel form followed by its LayerNorm.  S minimises the same cost model as
 // above (partial-output form of the 128 x 128 K-step-64 kernel, fitted to launches of 704 ... 7488
-// rows at N = 768, K = 3072 with S = 2 ... 12, 9 % rms) plus those passes at the rate the reduce
-// kernel reaches inside the encoder.  S never exceeds max_split.
+// rows at N = 768, K = 3072 with S = 2 ... 12, 9 % rms, or of the 64 x 64 kernel) plus those passes at the rate the
+// reduce kernel reaches inside the encoder.  S never exceeds max_split.
+// 64 x 64 tiles against 128 x 128 (us, partial products + reduce, best S of each, N = 768, K = 3072): 21 rows 8.6 / 11.1,
+// 197 10.3 / 12.9, 500 13.1 / 14.9, 1000 17.4 / 18.9, 1379 23.0 / 21.9, 2368 30.3 / 27.8.
+static double splitk_cost(int64_t M, int N, int K, int S, bool* tiles64) {
+  const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
+  const double c128 = (6.5 + 0.0153 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
+  const double c64 = tile64_cost(M, N, K / S, S, 2.8);
+  *tiles64 = c64 < c128;
+  return std::min(c64, c128);
+}
+
 int splitk_factor(int dtype, int64_t M, int N, int K, int max_split) {
   if (dtype == 0 || K < 2048 || K % 64 != 0 || N % 8 != 0 || M <= 0) return 1;
   const double pass_us = (double)M * N * 4.0 / 6.0e6;   // one float pass over the output at 6 TB/s
@@ -1261,11 +1299,11 @@ int splitk_factor(int dtype, int64_t M, int N, int K, int max_split) {
   pick_mfma_kernel(M, N, K, EPI_RESIDUAL, &unsplit);
   double best = unsplit + 1.5 * pass_us;                // + the LayerNorm pass: float in, 16-bit out
   int S = 1;
-  const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
   static const int cand[] = {2, 3, 4, 6, 8};
   for (int c : cand) {
     if (c > max_split || K % (c * 64) != 0 || K / c < 128) continue;
-    const double cost = (6.5 + 0.0153 * (K / c)) * rounds_cost(tiles * c, 512, 0.556) + (c + 2.5) * pass_us;
+    bool tiles64;
+    const double cost = splitk_cost(M, N, K, c, &tiles64) + (c + 2.5) * pass_us;
     if (cost < best) { best = cost; S = c; }
   }
   return S;
@@ -1274,9 +1312,11 @@ int splitk_factor(int dtype, int64_t M, int N, int K, int max_split) {
 hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64_t M, int N, int K, int S,
                                 hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  if (S < 1 || K % (S * 32) != 0 || K / S < 64 || N % 8 != 0) return hipErrorInvalidValue;
-  if (K % (S * 64) == 0 && K / S >= 128) return linear_mfma128k64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, S);
-  return linear_mfma_k32<3, 2>(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, S);
+  if (S < 1 || K % (S * 64) != 0 || K / S < 128 || N % 8 != 0) return hipErrorInvalidValue;
+  bool tiles64;
+  splitk_cost(M, N, K, S, &tiles64);
+  return tiles64 ? linear_mfma64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, nullptr, S)
+                 : linear_mfma128k64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, S);
 }
 
 hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,
@@ -1299,7 +1339,7 @@ bool linear_plan_tail_fits(int64_t M, int N, int K, int B) {
     case GK_192X256: bm = 192; bn = 256; slots = 256; break;
     case GK_256X256: bm = 256; bn = 256; slots = 256; break;
     case GK_320X256: bm = 320; bn = 256; slots = 256; break;
-    case GK_64X64: bm = 64; bn = 64; slots = 1024; break;
+    case GK_64X64: bm = 64; bn = 64; slots = K % 64 == 0 ? 512 : 1024; break;
     default: break;
   }
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
