@@ -23,17 +23,17 @@ __device__ inline PlanQuery plan_query(const int32_t* in_off, const int32_t* out
 }
 
 // LDS layout of the plan kernel (4-byte words), n = query length, nA = ceil(n/2), nB = floor(n/2):
-//   mh [n][dm+4] normalised metric rows | best [nA] | bcol [nA] | merged [nA] | cnt [nB] |
-//   keep_pos [n] | ent_pos [n] | wave_tot [2][16] | part_v [512] | part_c [512]
+//   mh [n][dm+4] normalised metric rows | best [nA4] | kept [nA4] | bcol [nA] | cnt [nB] |
+//   keep_pos [n] | ent_pos [n] | wave_tot [2][16] | part_v [512] | part_c [512],   nA4 = nA rounded up to 4
 // (the list phases on their own use the part from best on, without part_v / part_c).
 // Floats per metric row in LDS: the even and the odd columns each padded to a multiple of 4, plus 4.
 __host__ __device__ static inline int plan_row_floats(int dm) { return 2 * (((dm >> 1) + 3) & ~3) + 4; }
 // Bytes of LDS the list phases need for a query of up to max_n tokens, and that for the longest query there is.
 static inline size_t plan_lists_lds_bytes(int max_n) {
   const size_t nA = (max_n + 1) / 2, nB = max_n / 2;
-  return 4 * (3 * nA + nB + 2 * (size_t)max_n + 32);
+  return 4 * (3 * nA + nB + 2 * (size_t)max_n + 32 + 8);
 }
-constexpr size_t kPlanListsLdsMax = 4 * (3 * 512 + 512 + 2 * 1024 + 32);
+constexpr size_t kPlanListsLdsMax = 4 * (3 * 512 + 512 + 2 * 1024 + 32 + 8);
 
 // One workgroup of NT threads per query (pq; tid = thread index in the workgroup; lds: its dynamic LDS).
 // src: the vectors the similarity is taken on; the metric of token i is the mean over H heads of src[(i0 + i) * row_stride + col_off + h * dm + c] (H = 1 for
@@ -43,7 +43,7 @@ constexpr size_t kPlanListsLdsMax = 4 * (3 * 512 + 512 + 2 * 1024 + 32);
 // query's own rows of a [T][ldm] float buffer; written and read by this workgroup only, between its
 // barriers) instead of LDS, for queries whose rows do not fit the 160 KB; same arithmetic, same order.
 // TO_GLOBAL = false: the result (best[a] = similarity of A token a's best match, -inf for a protected leading
-// token; bcol[a] = that B token) stays in LDS behind the metric rows, valid for every thread on return.
+// token; bcol[a] = that B token) stays in LDS behind the metric rows, valid for every thread after the next barrier.
 // TO_GLOBAL = true: it goes to g_best[i0 + a], g_bcol[i0 + a] (a < nA) for merge_plan_lists in a later launch.
 // Queries with nothing to merge return at once.
 // part / parts: the A tokens are dealt to `parts` workgroups in blocks of 32 (block k goes to workgroup k % parts);
@@ -86,8 +86,8 @@ __device__ __forceinline__ void merge_plan_select(
     mh = rows + (size_t)i0 * ldm;
     best = lds;
   }
-  int* bcol = (int*)(best + nA);
-  int* wave_tot = bcol + 2 * nA + nB + 2 * n;   // behind merged, cnt, keep_pos, ent_pos of the list phases
+  int* bcol = (int*)(best + 2 * ((nA + 3) & ~3));   // behind kept of the list phases
+  int* wave_tot = bcol + nA + nB + 2 * n;           // behind cnt, keep_pos, ent_pos of the list phases
   auto row_of = [&](int i) { return mh + (size_t)((i & 1) ? nA + (i >> 1) : (i >> 1)) * ldm; };
 
   // Phase 0: head-mean metric rows, heads summed in ascending order.  A thread takes 8 columns of a token when the
@@ -253,11 +253,11 @@ __device__ __forceinline__ void merge_plan_select(
       bcol[a] = bc;
     }
   }
-  if constexpr (!TO_GLOBAL) __syncthreads();
+  // (TO_GLOBAL = false: best and bcol are visible after the barrier that merge_plan_lists begins with)
 }
 
 // The list phases for a query by a workgroup of NT threads (a multiple of 64, at most 1024).  small: LDS for
-// best [nA] | bcol [nA] | merged [nA] | cnt [nB] | keep_pos [n] | ent_pos [n] | wave_tot [32] (4-byte words).
+// best [nA4] | kept [nA4] | bcol [nA] | cnt [nB] | keep_pos [n] | ent_pos [n] | wave_tot [32] (4-byte words), 16-byte aligned.
 // FROM_GLOBAL = false: best / bcol are already there (merge_plan_select in the same workgroup);
 // true: they are read from g_best / g_bcol [i0 + a].  Integer work only, apart from comparisons of the
 // similarities: the result does not depend on NT.
@@ -275,58 +275,76 @@ __device__ __forceinline__ void merge_plan_lists(
     }
     return;
   }
-  const int nA = (n + 1) >> 1, nB = n >> 1;
+  const int nA = (n + 1) >> 1, nB = n >> 1, nA4 = (nA + 3) & ~3;
   float* best = small;
-  int* bcol = (int*)(best + nA);
-  int* merged = bcol + nA;
-  int* cnt = merged + nA;
+  int* kept = (int*)(best + nA4);   // destination of a kept edge, -1 for an A token that survives
+  int* bcol = kept + nA4;
+  int* cnt = bcol + nA;
   int* keep_pos = cnt + nB;      // [n] exclusive scan of "row survives"
   int* ent_pos = keep_pos + n;   // [n] exclusive scan of list lengths
   int* wave_tot = ent_pos + n;   // [2][16]
+  int* rank = keep_pos;          // until phase 4
+  int* slot = (int*)best;        // from the end of the ranking on
   if constexpr (FROM_GLOBAL) {
     for (int a = tid; a < nA; a += NT) {
       best[a] = g_best[i0 + a];
       bcol[a] = g_bcol[i0 + a];
     }
-    __syncthreads();
   }
+  if (tid < nA4 - nA) best[nA + tid] = -INFINITY;   // ranks behind every token it could be compared with
+  for (int a = tid; a < nA; a += NT) rank[a] = 0;
+  for (int b = tid; b < nB; b += NT) cnt[b] = 0;
+  __syncthreads();
 
   // Phase 3: keep the r_eff best edges.  rank = number of A tokens that come before this one in
-  // (similarity descending, position ascending) order; 8 consecutive lanes share an A token and
-  // split the tokens it is compared with.  slot = number of kept edges with the same destination
-  // and a lower source position (the order of a destination's source list).
-  for (int b = tid; b < nB; b += NT) cnt[b] = 0;
-  for (int a0 = 0; a0 < nA; a0 += NT / 8) {
-    const int a = min(a0 + (tid >> 3), nA - 1), part = tid & 7;
+  // (similarity descending, position ascending) order.  slot = number of kept edges with the same destination
+  // and a lower source position (the order of a destination's source list).  Both are counts over all A tokens: a
+  // thread takes one A token and one part of the tokens it is compared with (the same for its whole wave: they are
+  // read four at a time, every lane the same address), the parts are added by LDS atomics on integers.  The phases are
+  // bound by the number of LDS reads a wave waits for: with eight lanes per A token, each reading every eighth token on
+  // its own, the lists of a 577-token query took a 256-thread workgroup 20 .. 35 us, now @@L@@ (MI355X).
+  const int nAp = (nA + 63) & ~63;                 // whole waves
+  const int parts = max(1, NT / nAp), part = tid / nAp;
+  const int chunk = ((nA + parts - 1) / parts + 3) & ~3;
+  const int k_beg = part * chunk, k_end = min(nA4, k_beg + chunk);
+  auto each_a = [&](auto f) {                      // f(a) for the A tokens of this thread
+    if (part < parts)
+      for (int a = tid - part * nAp; a < nA; a += NT) f(a);   // a second round only when nAp > NT: one part then
+  };
+  each_a([&](int a) {
     const float v = best[a];
-    int rank = 0;
-    for (int k = part; k < nA; k += 8) {
-      const float u = best[k];
-      rank += (u > v || (u == v && k < a)) ? 1 : 0;
+    int c = 0;
+    for (int k = k_beg; k < k_end; k += 4) {
+      const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c += (u[j] > v || (u[j] == v && k + j < a)) ? 1 : 0;
     }
-    rank += __shfl_xor(rank, 1, kWave);
-    rank += __shfl_xor(rank, 2, kWave);
-    rank += __shfl_xor(rank, 4, kWave);
-    if (part == 0 && a0 + (tid >> 3) < nA) merged[a] = rank < r_eff ? 1 : 0;
-    if (part == 0 && a0 + (tid >> 3) < nA && rank < r_eff && trace_src) {
-      trace_src[pq.tr0 + rank] = 2 * a;
-      trace_dst[pq.tr0 + rank] = 2 * bcol[a] + 1;
-    }
-  }
+    if (parts > 1) atomicAdd(&rank[a], c);
+    else rank[a] = c;
+  });
   __syncthreads();
-  for (int a0 = 0; a0 < nA; a0 += NT / 8) {
-    const int a = min(a0 + (tid >> 3), nA - 1), part = tid & 7;
-    const int dst = bcol[a];
-    int slot = 0;
-    for (int k = part; k < a; k += 8) slot += (merged[k] && bcol[k] == dst) ? 1 : 0;
-    slot += __shfl_xor(slot, 1, kWave);
-    slot += __shfl_xor(slot, 2, kWave);
-    slot += __shfl_xor(slot, 4, kWave);
-    if (part == 0 && a0 + (tid >> 3) < nA && merged[a]) {
-      atomicAdd(&cnt[dst], 1);      // integer count: the result does not depend on the order
-      best[a] = __int_as_float(slot);   // best is dead from here on: reuse it for the slot
+  for (int a = tid; a < nA; a += NT) {
+    const bool keep = rank[a] < r_eff;
+    kept[a] = keep ? bcol[a] : -1;
+    if (keep && trace_src) {
+      trace_src[pq.tr0 + rank[a]] = 2 * a;
+      trace_dst[pq.tr0 + rank[a]] = 2 * bcol[a] + 1;
     }
+    slot[a] = 0;
   }
+  if (tid < nA4 - nA) kept[nA + tid] = -1;
+  __syncthreads();
+  each_a([&](int a) {
+    const int dst = kept[a];
+    if (dst < 0) return;
+    int c = 0;
+    for (int k = k_beg; k < min(k_end, a); k += 4) {
+      const int4 u = *reinterpret_cast<const int4*>(kept + k);
+      c += (u.x == dst && k < a) + (u.y == dst && k + 1 < a) + (u.z == dst && k + 2 < a) + (u.w == dst && k + 3 < a);
+    }
+    if (c) atomicAdd(&slot[a], c);   // integer counts: the result does not depend on the order
+    if (part == 0) atomicAdd(&cnt[dst], 1);
+  });
   __syncthreads();
 
   // Phase 4: positions.  keep(i) = 1 unless i is a merged A token; entries(i) = keep(i) * (1 +
@@ -336,7 +354,7 @@ __device__ __forceinline__ void merge_plan_lists(
   {
     const int C = (n + NT - 1) / NT;
     const int lane = tid & 63, w = tid >> 6;
-    auto keep_of = [&](int i) { return (i & 1) ? 1 : (merged[i >> 1] ? 0 : 1); };
+    auto keep_of = [&](int i) { return (i & 1) ? 1 : (kept[i >> 1] >= 0 ? 0 : 1); };
     auto ent_of = [&](int i, int k) { return k ? 1 + ((i & 1) ? cnt[i >> 1] : 0) : 0; };
     int k_sum = 0, e_sum = 0;
     for (int c = 0; c < C; ++c) {
@@ -374,9 +392,9 @@ __device__ __forceinline__ void merge_plan_lists(
   // enters its destination's list at its slot.
   for (int i = tid; i < n; i += NT) {
     const bool odd = i & 1;
-    if (!odd && merged[i >> 1]) {
-      const int a = i >> 1, d = 2 * bcol[a] + 1;
-      src_list[i0 + ent_pos[d] + 1 + __float_as_int(best[a])] = i0 + i;
+    if (!odd && kept[i >> 1] >= 0) {
+      const int a = i >> 1, d = 2 * kept[a] + 1;
+      src_list[i0 + ent_pos[d] + 1 + slot[a]] = i0 + i;
     } else {
       const int e = i0 + ent_pos[i];
       row_ptr[o0 + keep_pos[i]] = e;
