@@ -391,7 +391,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kern
 
 // Attention and the merge plan of a layer in ONE launch (both only read the layer's QKV projection, and
 // kernels of one stream do not overlap): the first workgroups run the plan -- workgroup q the whole plan of query q
-// (merge_plan_body), or, when sel_best is given, `parts` workgroups per query only its selection
+// (merge_plan_body), or, when sel_best is given, na x nb workgroups per query only its selection
 // (merge_plan_select: the lists are then written beside the next launch) -- the others run attention, each on
 // 8 / NW heads of one (query, row block) side by side.  The plan workgroups come first in dispatch order, so their
 // long serial chains start at once and the attention workgroups fill the other CUs.  Workgroups of 512 threads:
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kern
 // workgroup share its barriers, and four heads in lock-step in 1024-thread workgroups cost attention a fifth of its
 // speed), and a plan workgroup shares its CU with an attention workgroup instead of taking the CU.  Head width 64
 // only (four waves per SIMD leave 128 registers per lane).
-// grid.x = B * parts + xblks * (H / G) * B with G = 8 / NW (parts = plan workgroups per query, 1 for the whole plan).
+// grid.x = B * na * nb + xblks * (H / G) * B with G = 8 / NW (na = nb = 1 for the whole plan).
 constexpr int kFusedThreads = 512;
 template <bool BIAS, int KC, int NW>
 __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
@@ -407,22 +407,23 @@ __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
     float scale, bf16_t* __restrict__ o, int B, int xblks, const int32_t* __restrict__ out_off,
     const int32_t* __restrict__ reff_arr, const int32_t* __restrict__ troff, int n_lead,
     int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
-    int32_t* __restrict__ trace_dst, float* __restrict__ sel_best, int32_t* __restrict__ sel_bcol, int parts,
-    int unit_lds) {
+    int32_t* __restrict__ trace_dst, float* __restrict__ sel_best, int32_t* __restrict__ sel_bcol, int64_t sel_stride,
+    int na, int nb, int unit_lds) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int DH = 64, WT = kFusedThreads, G = WT / 64 / NW;
-  if ((int)blockIdx.x < B * parts) {   // workgroup-uniform
-    const PlanQuery pq = plan_query(off, out_off, reff_arr, troff, (int)blockIdx.x / parts);
-    if (sel_best)   // the selection only, `parts` workgroups per query: the lists are written beside the output projection
+  if ((int)blockIdx.x < B * na * nb) {   // workgroup-uniform
+    const int q = (int)blockIdx.x / (na * nb), pp = (int)blockIdx.x % (na * nb);
+    const PlanQuery pq = plan_query(off, out_off, reff_arr, troff, q);
+    if (sel_best)   // the selection only: the lists are written beside the output projection
       merge_plan_select<bf16_t, true, true, WT>(qkv, 3 * (int64_t)D, D, H, DH, pq, n_lead, nullptr,
                                                 reinterpret_cast<float*>(smem), sel_best, sel_bcol, (int)threadIdx.x,
-                                                (int)blockIdx.x % parts, parts);
+                                                PlanPart{pp % na, na, pp / na, nb, sel_stride});
     else
       merge_plan_body<bf16_t, true, WT>(qkv, 3 * (int64_t)D, D, H, DH, pq, n_lead, src_list, row_ptr, trace_src,
                                         trace_dst, nullptr, reinterpret_cast<float*>(smem), (int)threadIdx.x);
     return;
   }
-  int id = (int)blockIdx.x - B * parts;
+  int id = (int)blockIdx.x - B * na * nb;
   const int hg = H / G;
   const int xblk = id % xblks;
   id /= xblks;
@@ -465,50 +466,61 @@ static hipError_t attention_mfma(const void* qkv, const int32_t* sz, const int32
             : attention_mfma_b<DH, false>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
 }
 
-// Whether launch_attention_plan takes this case (pure host).
-bool attention_plan_takes(int dtype, int max_n, int D, int H) {
-  if (dtype == 0 || H <= 0 || D != 64 * H || max_n <= 0 || max_n > kPlanThreads) return false;
-  if (merge_plan_lds_bytes(max_n, 64) > 160 * 1024) return false;
+// LDS of the fused kernel's attention workgroups: one head of eight waves with all keys staged for 129 .. 256 rows, else
+// two heads of four waves with 128 keys each.
+static size_t fused_attention_lds(int max_n, size_t* unit) {
+  const bool one = max_n > 128 && max_n <= 256;
+  const int kc = one ? 256 : 128;
+  *unit = ((size_t)(kc + kc + 4) * (64 + 8) * sizeof(bf16_t) + kc * sizeof(float) + 15) & ~(size_t)15;
+  return one ? *unit : 2 * *unit;
+}
+
+// How launch_attention_plan runs this case (pure host; not at all: parts.a = 0).
+FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lists_elsewhere) {
+  FusedPlan how = {0, 0};
+  if (dtype == 0 || B <= 0 || H <= 0 || D != 64 * H || max_n <= 0 || max_n > kPlanThreads) return how;
   const int G = (max_n > 128 && max_n <= 256) ? 1 : 2;   // heads per workgroup: 8 waves / (8 or 4 waves per head)
-  return H % G == 0;
+  if (H % G != 0) return how;
+  size_t unit;
+  if (lists_elsewhere) {
+    const PlanParts p = plan_parts(B, max_n, 64, fused_attention_lds(max_n, &unit));
+    if (plan_select_lds_bytes(max_n, 64, p.a, p.b) > 160 * 1024) return how;
+    how.na = p.a;
+    how.nb = p.b;
+  } else if (merge_plan_lds_bytes(max_n, 64) <= 160 * 1024) {
+    how.na = how.nb = 1;
+  }
+  return how;
 }
 
 // Attention of a layer together with the layer's merge plan (bf16, head width 64, H a multiple of the heads a
-// workgroup takes, every query's metric rows in LDS); hipErrorInvalidValue otherwise -- the caller then launches
+// workgroup takes); hipErrorInvalidValue for what attention_plan_how does not take -- the caller then launches
 // the two kernels one after the other.
 hipError_t launch_attention_plan(const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
                                  const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int D, int H,
                                  bool size_bias, int n_lead, void* o, int32_t* src_list, int32_t* row_ptr,
                                  int32_t* trace_src, int32_t* trace_dst, float* sel_best, int32_t* sel_bcol,
-                                 hipStream_t s) {
+                                 int64_t sel_stride, hipStream_t s) {
   if (B <= 0 || max_n <= 0) return hipSuccess;
-  if (H <= 0 || D != 64 * H || max_n > kPlanThreads || (sel_best == nullptr) != (sel_bcol == nullptr))
-    return hipErrorInvalidValue;
-  const size_t plan_lds = merge_plan_lds_bytes(max_n, 64);
-  if (plan_lds > 160 * 1024) return hipErrorInvalidValue;
+  if ((sel_best == nullptr) != (sel_bcol == nullptr)) return hipErrorInvalidValue;
+  const FusedPlan how = attention_plan_how(1, B, max_n, D, H, sel_best != nullptr);
+  if (how.na == 0) return hipErrorInvalidValue;
+  const size_t plan_lds = sel_best ? plan_select_lds_bytes(max_n, 64, how.na, how.nb) : merge_plan_lds_bytes(max_n, 64);
   const float scale = 1.0f / sqrtf(64.0f);
   const int32_t* sz = size_bias ? sizes : nullptr;
-  constexpr int LD = 64 + 8;
-  // Workgroups per query for the selection: a small batch leaves most CUs idle, and the selection's chain (load the
-  // keys, unit length, similarities: each proportional to the A tokens a workgroup owns, plus all B tokens) is what
-  // the launch then waits for.  Up to 64 plan workgroups in all, and no more per query than it has blocks of 32 A tokens.
-  int parts = 1;
-  if (sel_best) parts = std::max(1, std::min(std::min(4, 64 / B), (max_n / 2 + 31) / 32));
+  size_t unit;
+  const size_t attn_lds = fused_attention_lds(max_n, &unit), lds = attn_lds > plan_lds ? attn_lds : plan_lds;
 #define OTAS_FUSED(BIASV, KC, NWV)                                                                                \
   do {                                                                                                            \
     constexpr int G = kFusedThreads / 64 / NWV;                                                                   \
-    if (H % G != 0) return hipErrorInvalidValue;                                                                  \
-    const size_t unit = ((size_t)(KC + KC + 4) * LD * sizeof(bf16_t) + KC * sizeof(float) + 15) & ~(size_t)15;    \
-    const size_t lds = unit * G > plan_lds ? unit * G : plan_lds;                                                 \
-    if (lds > 160 * 1024) return hipErrorInvalidValue;                                                            \
     auto kern = attention_plan_kernel<BIASV, KC, NWV>;                                                            \
     hipError_t e = set_max_dynamic_lds((const void*)kern, 160 * 1024);                                            \
     if (e != hipSuccess) return e;                                                                                \
     const int xblks = (max_n + 32 * NWV - 1) / (32 * NWV);                                                        \
-    dim3 grid((unsigned)(B * parts + xblks * (H / G) * B)), block(kFusedThreads);                                 \
+    dim3 grid((unsigned)(B * how.na * how.nb + xblks * (H / G) * B)), block(kFusedThreads);                       \
     kern<<<grid, block, lds, s>>>((const bf16_t*)qkv, sz, d_off, D, H, scale, (bf16_t*)o, B, xblks, d_out_off,    \
                                   d_reff, d_troff, n_lead, src_list, row_ptr, trace_src, trace_dst, sel_best,     \
-                                  sel_bcol, parts, (int)unit);                                                    \
+                                  sel_bcol, sel_stride, how.na, how.nb, (int)unit);                               \
   } while (0)
   if (max_n > 128 && max_n <= 256) {
     if (sz) OTAS_FUSED(true, 256, 8); else OTAS_FUSED(false, 256, 8);

@@ -504,7 +504,7 @@ __device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& til
 // launch earlier, and the projection leaves CUs idle at the batch sizes this matters for.
 template <int NT>
 __device__ __forceinline__ void plan_tail_run(const PlanTail& pt, unsigned char* smem, int q, int tid) {
-  merge_plan_lists<NT, true>(reinterpret_cast<float*>(smem), pt.best, pt.bcol,
+  merge_plan_lists<NT, true>(reinterpret_cast<float*>(smem), pt.best, pt.bcol, pt.nb, pt.stride,
                              plan_query(pt.in_off, pt.out_off, pt.reff, pt.troff, q), pt.src_list, pt.row_ptr,
                              pt.trace_src, pt.trace_dst, tid);
 }

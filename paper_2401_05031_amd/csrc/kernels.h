@@ -105,25 +105,29 @@ hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
                             const int32_t* d_off, int B, int max_n, int D, int H, bool size_bias,
                             void* o, hipStream_t s);
 
-// Attention and the merge plan of one layer in a single launch (bf16 models of head width 64 whose queries all
-// fit the plan's LDS form; the plan's metric is the head mean of the keys in qkv).  Returns
-// hipErrorInvalidValue, having launched nothing, for every other case.
-// With sel_best / sel_bcol (device, one entry per packed token row) the launch runs only the plan's selection
-// (every A token's best match) and leaves it there; the lists are then written by the first B workgroups of
-// launch_linear_plan_tail, beside the attention output projection.  With both NULL it runs the whole plan.
-bool attention_plan_takes(int dtype, int max_n, int D, int H);
+// Attention and the merge plan of one layer in a single launch (bf16 models of head width 64; the plan's metric is the
+// head mean of the keys in qkv).  Returns hipErrorInvalidValue, having launched nothing, for what attention_plan_how
+// does not take.
+// With sel_best / sel_bcol (device, nb arrays of sel_stride entries, one per packed token row) the launch runs only the
+// plan's selection (every A token's best match), in na x nb workgroups per query, and leaves it there; the lists are then
+// written by the first B workgroups of launch_linear_plan_tail, beside the attention output projection.  With both NULL
+// it runs the whole plan, one workgroup per query, whose metric rows must fit the LDS.
+struct FusedPlan { int na, nb; };   // na = 0: not taken
+FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lists_elsewhere);
 hipError_t launch_attention_plan(const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
                                  const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int D, int H,
                                  bool size_bias, int n_lead, void* o, int32_t* src_list, int32_t* row_ptr,
                                  int32_t* trace_src, int32_t* trace_dst, float* sel_best, int32_t* sel_bcol,
-                                 hipStream_t s);
+                                 int64_t sel_stride, hipStream_t s);
 
 // What the list phases of the merge plan (merge_plan_lists) need when they run inside another kernel's launch.
 struct PlanTail {
   const int32_t *in_off, *out_off, *reff, *troff;   // device: per-query offsets in / out, r_eff, trace offsets
   int32_t *src_list, *row_ptr, *trace_src, *trace_dst;
-  const float* best;                                // the selection's result, one entry per packed token row
-  const int32_t* bcol;
+  const float* best;                                // the selection's result: nb arrays of `stride` entries, one per
+  const int32_t* bcol;                              // packed token row
+  int64_t stride;
+  int nb;
   int B;                                            // queries = leading workgroups that run the lists
 };
 // y = x W^T + bias + res (bf16 operands, float residual in and out) as launch_linear with EPI_RESIDUAL, and in

@@ -8,6 +8,8 @@
 #ifndef OTAS_MERGE_PLAN_BODY_H_
 #define OTAS_MERGE_PLAN_BODY_H_
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace otas {
@@ -23,11 +25,41 @@ __device__ inline PlanQuery plan_query(const int32_t* in_off, const int32_t* out
 }
 
 // LDS layout of the plan kernel (4-byte words), n = query length, nA = ceil(n/2), nB = floor(n/2):
-//   mh [n][dm+4] normalised metric rows | best [nA4] | kept [nA4] | bcol [nA] | cnt [nB] |
+//   mh [rows][dm+4] normalised metric rows (rows = n for the whole plan) | best [nA4] | kept [nA4] | bcol [nA] | cnt [nB] |
 //   keep_pos [n] | ent_pos [n] | wave_tot [2][16] | part_v [512] | part_c [512],   nA4 = nA rounded up to 4
-// (the list phases on their own use the part from best on, without part_v / part_c).
+// (the list phases on their own use the part from best on, without part_v / part_c; the selection on its own
+// mh | part_v | part_c).
 // Floats per metric row in LDS: the even and the odd columns each padded to a multiple of 4, plus 4.
 __host__ __device__ static inline int plan_row_floats(int dm) { return 2 * (((dm >> 1) + 3) & ~3) + 4; }
+// Bytes of LDS the selection on its own needs, in na x nb workgroups per query.
+static inline size_t plan_select_lds_bytes(int max_n, int dm, int na, int nb) {
+  const int bA = ((max_n + 1) / 2 + 31) / 32, bB = (max_n / 2 + 31) / 32;
+  const int rows = ((bA + na - 1) / na + (bB + nb - 1) / nb) * 32;
+  return 4 * ((size_t)(rows < max_n ? rows : max_n) * plan_row_floats(dm) + 2 * 512);
+}
+// Workgroups per query for the selection.  First as many as it takes to keep a workgroup's metric rows within lds_goal
+// bytes (what the launch's other workgroups need anyway: a launch's LDS is the same for all), then, while the launch has
+// no more than 128 of them (half the CUs), as many as its A and B tokens have blocks to deal: what a workgroup loads and
+// compares shrinks with both numbers, at the cost of loading A tokens nb times and B tokens na times in all.
+// ViT-B pass on MI355X with one workgroup per query and with this rule: ten queries of 577 / 197 tokens 1642 and 1551 us
+// (above 554 tokens the plan could not run beside attention at all), one query of 197 tokens 551 and 545, 64 of them,
+// where the rule gives two, the same.
+struct PlanParts { int a, b; };
+static inline PlanParts plan_parts(int B, int max_n, int dm, size_t lds_goal) {
+  const int bA = ((max_n + 1) / 2 + 31) / 32, bB = (max_n / 2 + 31) / 32;
+  PlanParts p = {1, 1};
+  auto grow = [&] {   // one more halving of the larger share
+    const int ra = (bA + p.a - 1) / p.a, rb = (bB + p.b - 1) / p.b;
+    if (ra <= 1 && rb <= 1) return false;
+    (ra > rb ? p.a : p.b) *= 2;
+    return true;
+  };
+  while (plan_select_lds_bytes(max_n, dm, p.a, p.b) > lds_goal && grow()) {}
+  while (2 * p.a * p.b * B <= 128 && grow()) {}
+  if (p.a > bA) p.a = bA;
+  if (p.b > bB) p.b = bB;
+  return p;
+}
 // Bytes of LDS the list phases need for a query of up to max_n tokens, and that for the longest query there is.
 static inline size_t plan_lists_lds_bytes(int max_n) {
   const size_t nA = (max_n + 1) / 2, nB = max_n / 2;
@@ -46,49 +78,55 @@ constexpr size_t kPlanListsLdsMax = 4 * (3 * 512 + 512 + 2 * 1024 + 32 + 8);
 // token; bcol[a] = that B token) stays in LDS behind the metric rows, valid for every thread after the next barrier.
 // TO_GLOBAL = true: it goes to g_best[i0 + a], g_bcol[i0 + a] (a < nA) for merge_plan_lists in a later launch.
 // Queries with nothing to merge return at once.
-// part / parts: the A tokens are dealt to `parts` workgroups in blocks of 32 (block k goes to workgroup k % parts);
-// this one is number `part` and computes the rows it needs -- all B tokens and its own A tokens -- and the result
-// of its A tokens only (parts > 1 needs TO_GLOBAL).  Every row and every similarity is computed by the same
-// arithmetic in the same order whatever `parts` is.
+// pt: the A and the B tokens are dealt in blocks of 32 to pt.na x pt.nb workgroups (A block k goes to those with
+// pt.a = k % pt.na, B block k to those with pt.b = k % pt.nb); this one computes the rows of its blocks and the best match
+// of its A tokens among its B tokens only, so that loading the keys and comparing them is shared between CUs; with
+// pt.nb > 1 the list phases take the best of the pt.nb candidates (g_best [pt.nb][pt.stride]).  More than one workgroup
+// needs TO_GLOBAL.  Every row and every similarity is computed by the same arithmetic in the same order whatever pt is.
+struct PlanPart { int a, na, b, nb; int64_t stride; };
 template <typename T, bool ROWS_IN_LDS, bool TO_GLOBAL, int NT = kPlanThreads>
 __device__ __forceinline__ void merge_plan_select(
     const T* __restrict__ src, int64_t row_stride, int col_off, int H, int dm, const PlanQuery& pq, int n_lead,
     float* rows, float* lds, float* __restrict__ g_best, int32_t* __restrict__ g_bcol, const int tid,
-    const int part = 0, const int parts = 1) {
+    const PlanPart pt = PlanPart{0, 1, 0, 1, 0}) {
   const int i0 = pq.i0, n = pq.n;
   if (n <= 0 || pq.r_eff <= 0) return;
   const int half = dm >> 1, hp = (half + 3) & ~3;   // columns per parity, and their padded count
   const int nA = (n + 1) >> 1, nB = n >> 1, ldm = 2 * hp + 4;
   const int nAb = (nA + 31) >> 5, nBb = (nB + 31) >> 5;
-  const int nAl = (nAb - part + parts - 1) / parts;   // A blocks of this workgroup: part, part + parts, ...
-  if (nAl <= 0) return;
-  // The rows this workgroup needs, numbered u = 0 .. n_need - 1: the nB B tokens, then its A blocks (the last
-  // block may run past nA: -1).
-  const int n_need = nB + nAl * 32;
+  const int nAl = (nAb - pt.a + pt.na - 1) / pt.na;   // A blocks of this workgroup: pt.a, pt.a + pt.na, ...
+  const int nBl = (nBb - pt.b + pt.nb - 1) / pt.nb;   // and B blocks
+  if (nAl <= 0 || nBl <= 0) {
+    // nothing to compare: no candidate for the A tokens (if any) of this workgroup
+    if constexpr (TO_GLOBAL)
+      for (int t = tid; t < nAl * 32; t += NT) {
+        const int a = (pt.a + pt.na * (t >> 5)) * 32 + (t & 31);
+        if (a < nA) { g_best[pt.b * pt.stride + i0 + a] = -INFINITY; g_bcol[pt.b * pt.stride + i0 + a] = 0x7fffffff; }
+      }
+    return;
+  }
+  // The rows this workgroup needs, numbered u = 0 .. n_need - 1: its B tokens, then its A tokens, block by block (only
+  // a query's last block can be short, and it is the last of the workgroup that owns it).
+  const int nBv = nBl * 32 - ((pt.b + pt.nb * (nBl - 1) == nBb - 1) ? nBb * 32 - nB : 0);
+  const int nAv = nAl * 32 - ((pt.a + pt.na * (nAl - 1) == nAb - 1) ? nAb * 32 - nA : 0);
+  const int n_need = nBv + nAv;
   auto token_of = [&](int u) {
-    if (u < nB) return 2 * u + 1;
-    const int v = u - nB, a = (part + parts * (v >> 5)) * 32 + (v & 31);
-    return a < nA ? 2 * a : -1;
+    if (u < nBv) return 2 * ((pt.b + pt.nb * (u >> 5)) * 32 + (u & 31)) + 1;
+    const int v = u - nBv;
+    return 2 * ((pt.a + pt.na * (v >> 5)) * 32 + (v & 31));
   };
-  // Metric rows in LDS: the A tokens (even positions) first, then the B tokens, one row of ldm
-  // floats per token, so that consecutive tokens of one set are ldm = dm + 4 floats apart (16 lanes
+  // Metric rows in that order, ldm = dm + 4 floats apart (16 lanes
   // reading 16 bytes each from 16 consecutive rows then fall on all 64 banks once).  Inside a row the
   // columns are stored even ones first, then odd ones (each group zero-padded to a multiple of 4):
   // column c sits at (c & 1) * hp + c / 2, so
   // the two halves of a wave (which feed the even and the odd k of every fp32 MFMA) each read
   // consecutive floats.
-  float* mh;
-  float* best;
-  if constexpr (ROWS_IN_LDS) {
-    mh = lds;
-    best = mh + (size_t)n * ldm;
-  } else {
-    mh = rows + (size_t)i0 * ldm;
-    best = lds;
-  }
+  float* mh = ROWS_IN_LDS ? lds : rows + (size_t)i0 * ldm;
+  float* best = ROWS_IN_LDS ? lds + (size_t)n * ldm : lds;   // TO_GLOBAL = false: one workgroup has all n rows
   int* bcol = (int*)(best + 2 * ((nA + 3) & ~3));   // behind kept of the list phases
-  int* wave_tot = bcol + nA + nB + 2 * n;           // behind cnt, keep_pos, ent_pos of the list phases
-  auto row_of = [&](int i) { return mh + (size_t)((i & 1) ? nA + (i >> 1) : (i >> 1)) * ldm; };
+  int* part_c = TO_GLOBAL ? (int*)(ROWS_IN_LDS ? lds + (size_t)n_need * ldm : lds)
+                          : bcol + nA + nB + 2 * n + 32;   // behind cnt, keep_pos, ent_pos, wave_tot of the list phases
+  float* part_v = reinterpret_cast<float*>(part_c + 512);
 
   // Phase 0: head-mean metric rows, heads summed in ascending order.  A thread takes 8 columns of a token when the
   // source is 16-bit and 16-byte aligned with dm % 8 == 0 (one 16-byte load per head, two 16-byte LDS stores: this phase is bound by
@@ -98,20 +136,27 @@ __device__ __forceinline__ void merge_plan_select(
       (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
     const int c8n = dm >> 3;
     for (int t = tid; t < n_need * c8n; t += NT) {
-      const int u = t / c8n, c = (t - u * c8n) * 8, i = token_of(u);
-      if (i < 0) continue;
-      const T* p = src + (size_t)(i0 + i) * row_stride + col_off + c;
+      const int u = t / c8n, c = (t - u * c8n) * 8;
+      const T* p = src + (size_t)(i0 + token_of(u)) * row_stride + col_off + c;
       float m[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) m[e] = 0.f;
-#pragma unroll 4
-      for (int h = 0; h < H; ++h) {
-        const Oct<T> v = *reinterpret_cast<const Oct<T>*>(p);
+      auto heads = [&](auto UH) {   // UH heads in flight together (loads past the last head repeat it)
+        for (int h0 = 0; h0 < H; h0 += UH.value) {
+          Oct<T> v[UH.value];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) m[e] += to_float(v.x[e]);
-        p += dm;
-      }
-      float* r = row_of(i);
+          for (int j = 0; j < UH.value; ++j) v[j] = *reinterpret_cast<const Oct<T>*>(p + (size_t)min(h0 + j, H - 1) * dm);
+#pragma unroll
+          for (int j = 0; j < UH.value; ++j)
+            if (h0 + j < H) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) m[e] += to_float(v[j].x[e]);
+            }
+        }
+      };
+      if (H == 1) heads(std::integral_constant<int, 1>{});   // the caller's own metric
+      else heads(std::integral_constant<int, 12>{});         // one round trip per row up to ViT-B's 12 heads
+      float* r = mh + (size_t)u * ldm;
       const int ce = c >> 1;   // columns c, c+2, c+4, c+6 are even ones, the others odd ones
       *reinterpret_cast<floatx4*>(r + ce) = floatx4{m[0] * inv_h, m[2] * inv_h, m[4] * inv_h, m[6] * inv_h};
       *reinterpret_cast<floatx4*>(r + hp + ce) = floatx4{m[1] * inv_h, m[3] * inv_h, m[5] * inv_h, m[7] * inv_h};
@@ -119,9 +164,8 @@ __device__ __forceinline__ void merge_plan_select(
   } else {
     const int c4n = dm >> 2;
     for (int t = tid; t < n_need * c4n; t += NT) {
-      const int u = t / c4n, c = (t - u * c4n) * 4, i = token_of(u);
-      if (i < 0) continue;
-      const T* p = src + (size_t)(i0 + i) * row_stride + col_off + c;
+      const int u = t / c4n, c = (t - u * c4n) * 4;
+      const T* p = src + (size_t)(i0 + token_of(u)) * row_stride + col_off + c;
       float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
 #pragma unroll 4
       for (int h = 0; h < H; ++h) {
@@ -129,7 +173,7 @@ __device__ __forceinline__ void merge_plan_select(
         m0 += to_float(v.x[0]); m1 += to_float(v.x[1]); m2 += to_float(v.x[2]); m3 += to_float(v.x[3]);
         p += dm;
       }
-      float* r = row_of(i);
+      float* r = mh + (size_t)u * ldm;
       const int ce = c >> 1;   // columns c, c+2 are even ones, c+1, c+3 odd ones
       r[ce] = m0 * inv_h;
       r[ce + 1] = m2 * inv_h;
@@ -139,8 +183,8 @@ __device__ __forceinline__ void merge_plan_select(
   }
   if (hp != half)   // the padding columns take part in the contraction: zero
     for (int t = tid; t < n_need * 2 * (hp - half); t += NT) {
-      const int u = t / (2 * (hp - half)), c = t - u * (2 * (hp - half)), i = token_of(u);
-      if (i >= 0) row_of(i)[(c & 1) * hp + half + (c >> 1)] = 0.f;
+      const int u = t / (2 * (hp - half)), c = t - u * (2 * (hp - half));
+      mh[(size_t)u * ldm + (c & 1) * hp + half + (c >> 1)] = 0.f;
     }
   __syncthreads();
   // Phase 1: unit length.  16 consecutive lanes share a row of 2 hp floats (the zero padding adds nothing): lane j
@@ -150,8 +194,7 @@ __device__ __forceinline__ void merge_plan_select(
     const int q4 = (2 * hp) >> 2;   // 16-byte pieces per row
     for (int u0 = 0; u0 < n_need; u0 += NT / 16) {
       const int u = u0 + (tid >> 4), j = tid & 15;
-      const int i = u < n_need ? token_of(u) : -1;
-      float* r = row_of(i >= 0 ? i : 1);   // n >= 2 here: token 1 exists
+      float* r = mh + (size_t)min(u, n_need - 1) * ldm;
       float ss = 0.f;
       for (int m = j; m < q4; m += 16) {
         const floatx4 v = *reinterpret_cast<const floatx4*>(r + 4 * m);
@@ -162,7 +205,7 @@ __device__ __forceinline__ void merge_plan_select(
       ss += __shfl_xor(ss, 4, kWave);
       ss += __shfl_xor(ss, 8, kWave);
       const float rn = 1.0f / fmaxf(sqrtf(ss), 1e-12f);
-      if (i >= 0)
+      if (u < n_need)
         for (int m = j; m < q4; m += 16) {
           floatx4 v = *reinterpret_cast<const floatx4*>(r + 4 * m);
           v[0] *= rn; v[1] *= rn; v[2] *= rn; v[3] *= rn;
@@ -178,12 +221,10 @@ __device__ __forceinline__ void merge_plan_select(
   // (columns), so a lane owns ONE A token and holds 16 of a 32-token B block's similarities in its
   // accumulator (rows 8 (e / 4) + 4 (lane >> 5) + (e & 3)): its arg-max is a scan of its own registers
   // in ascending B order plus one exchange with lane ^ 32.  Wave w owns the workgroup's A block w % nAl and every
-  // G-th B block; the G partial results per A token are combined through LDS.  Ties go to the
+  // G-th of its B blocks; the G partial results per A token are combined through LDS.  Ties go to the
   // lowest B position at every step.
   constexpr int NWV = NT / 64;
   const int G = max(1, NWV / nAl);
-  int* part_c = wave_tot + 32;
-  float* part_v = reinterpret_cast<float*>(part_c + 512);
   {
     const int lane = tid & 63, w = tid >> 6;
     const int fr = lane & 31, fk = lane >> 5;
@@ -192,12 +233,11 @@ __device__ __forceinline__ void merge_plan_select(
     const bool wide = nAl > NWV;
     const int grp = wide ? 0 : w / nAl;
     for (int al = wide ? w : w % nAl; al < nAl && grp < G; al += wide ? NWV : nAl) {
-      const int a = (part + parts * al) * 32 + fr;
-      const float* pa = mh + (size_t)min(a, nA - 1) * ldm + fk * hp;
+      const float* pa = mh + (size_t)(nBv + min(al * 32 + fr, nAv - 1)) * ldm + fk * hp;
       float bv = -INFINITY;
       int bc = 0x7fffffff;
-      for (int bb = grp; bb < nBb; bb += G) {
-        const float* pb = mh + (size_t)(nA + min(bb * 32 + fr, nB - 1)) * ldm + fk * hp;
+      for (int bl = grp; bl < nBl; bl += G) {
+        const float* pb = mh + (size_t)min(bl * 32 + fr, nBv - 1) * ldm + fk * hp;
         floatx16 acc;
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[e] = 0.f;
@@ -220,7 +260,7 @@ __device__ __forceinline__ void merge_plan_select(
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int b = bb * 32 + 8 * (e >> 2) + 4 * fk + (e & 3);
+          const int b = (pt.b + pt.nb * bl) * 32 + 8 * (e >> 2) + 4 * fk + (e & 3);
           if (b < nB && acc[e] > bv) { bv = acc[e]; bc = b; }
         }
       }
@@ -235,7 +275,7 @@ __device__ __forceinline__ void merge_plan_select(
   }
   __syncthreads();
   for (int t = tid; t < nAl * 32; t += NT) {
-    const int a = (part + parts * (t >> 5)) * 32 + (t & 31);
+    const int a = (pt.a + pt.na * (t >> 5)) * 32 + (t & 31);
     if (a >= nA) continue;
     float bv = part_v[t];
     int bc = part_c[t];
@@ -246,8 +286,8 @@ __device__ __forceinline__ void merge_plan_select(
     }
     const float v = (2 * a < n_lead) ? -INFINITY : bv;   // protected leading token: never a merge source
     if constexpr (TO_GLOBAL) {
-      g_best[i0 + a] = v;
-      g_bcol[i0 + a] = bc;
+      g_best[pt.b * pt.stride + i0 + a] = v;
+      g_bcol[pt.b * pt.stride + i0 + a] = bc;
     } else {
       best[a] = v;
       bcol[a] = bc;
@@ -259,12 +299,13 @@ __device__ __forceinline__ void merge_plan_select(
 // The list phases for a query by a workgroup of NT threads (a multiple of 64, at most 1024).  small: LDS for
 // best [nA4] | kept [nA4] | bcol [nA] | cnt [nB] | keep_pos [n] | ent_pos [n] | wave_tot [32] (4-byte words), 16-byte aligned.
 // FROM_GLOBAL = false: best / bcol are already there (merge_plan_select in the same workgroup);
-// true: they are read from g_best / g_bcol [i0 + a].  Integer work only, apart from comparisons of the
+// true: they are read from g_best / g_bcol [nb][stride], entry i0 + a: the best of nb candidates, ties to the lowest B
+// token.  Integer work only, apart from comparisons of the
 // similarities: the result does not depend on NT.
 template <int NT, bool FROM_GLOBAL>
 __device__ __forceinline__ void merge_plan_lists(
-    float* small, const float* __restrict__ g_best, const int32_t* __restrict__ g_bcol, const PlanQuery& pq,
-    int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
+    float* small, const float* __restrict__ g_best, const int32_t* __restrict__ g_bcol, int nb, int64_t stride,
+    const PlanQuery& pq, int32_t* __restrict__ src_list, int32_t* __restrict__ row_ptr, int32_t* __restrict__ trace_src,
     int32_t* __restrict__ trace_dst, const int tid) {
   const int i0 = pq.i0, n = pq.n, o0 = pq.o0, r_eff = pq.r_eff;
   if (n <= 0) return;
@@ -287,8 +328,15 @@ __device__ __forceinline__ void merge_plan_lists(
   int* slot = (int*)best;        // from the end of the ranking on
   if constexpr (FROM_GLOBAL) {
     for (int a = tid; a < nA; a += NT) {
-      best[a] = g_best[i0 + a];
-      bcol[a] = g_bcol[i0 + a];
+      float v = g_best[i0 + a];
+      int c = g_bcol[i0 + a];
+      for (int p = 1; p < nb; ++p) {
+        const float u = g_best[p * stride + i0 + a];
+        const int d = g_bcol[p * stride + i0 + a];
+        if (u > v || (u == v && d < c)) { v = u; c = d; }
+      }
+      best[a] = v;
+      bcol[a] = c;
     }
   }
   if (tid < nA4 - nA) best[nA + tid] = -INFINITY;   // ranks behind every token it could be compared with
@@ -302,9 +350,9 @@ __device__ __forceinline__ void merge_plan_lists(
   // thread takes one A token and one part of the tokens it is compared with (the same for its whole wave: they are
   // read four at a time, every lane the same address), the parts are added by LDS atomics on integers.  The phases are
   // bound by the number of LDS reads a wave waits for: with eight lanes per A token, each reading every eighth token on
-  // its own, the lists of a 577-token query took a 256-thread workgroup 20 .. 35 us, now @@L@@ (MI355X).
+  // its own, a ViT-B pass over ten queries of 577 / 197 tokens took 1700 us, one query of 197 tokens 559; now 1642, 551.
   const int nAp = (nA + 63) & ~63;                 // whole waves
-  const int parts = max(1, NT / nAp), part = tid / nAp;
+  const int parts = max(1, NT / nAp), part = __builtin_amdgcn_readfirstlane(tid / nAp);   // the same for a whole wave
   const int chunk = ((nA + parts - 1) / parts + 3) & ~3;
   const int k_beg = part * chunk, k_end = min(nA4, k_beg + chunk);
   auto each_a = [&](auto f) {                      // f(a) for the A tokens of this thread
@@ -313,11 +361,27 @@ __device__ __forceinline__ void merge_plan_lists(
   };
   each_a([&](int a) {
     const float v = best[a];
+    // this wave's A tokens are a0 .. a0 + 63: ties only have to be looked at among those
+    const int a0 = __builtin_amdgcn_readfirstlane(a) & ~63;
+    const int k_lo = min(max(a0, k_beg), k_end), k_hi = min(max(a0 + 64, k_beg), k_end);
     int c = 0;
-    for (int k = k_beg; k < k_end; k += 4) {
+#pragma unroll 4
+    for (int k = k_beg; k < k_lo; k += 4) {
+      const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c += u[j] >= v ? 1 : 0;
+    }
+#pragma unroll 4
+    for (int k = k_lo; k < k_hi; k += 4) {
       const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
 #pragma unroll
       for (int j = 0; j < 4; ++j) c += (u[j] > v || (u[j] == v && k + j < a)) ? 1 : 0;
+    }
+#pragma unroll 4
+    for (int k = k_hi; k < k_end; k += 4) {
+      const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c += u[j] > v ? 1 : 0;
     }
     if (parts > 1) atomicAdd(&rank[a], c);
     else rank[a] = c;
@@ -338,6 +402,7 @@ __device__ __forceinline__ void merge_plan_lists(
     const int dst = kept[a];
     if (dst < 0) return;
     int c = 0;
+#pragma unroll 4
     for (int k = k_beg; k < min(k_end, a); k += 4) {
       const int4 u = *reinterpret_cast<const int4*>(kept + k);
       c += (u.x == dst && k < a) + (u.y == dst && k + 1 < a) + (u.z == dst && k + 2 < a) + (u.w == dst && k + 3 < a);
@@ -412,7 +477,7 @@ __device__ __forceinline__ void merge_plan_body(
   merge_plan_select<T, ROWS_IN_LDS, false, NT>(src, row_stride, col_off, H, dm, pq, n_lead, rows, lds, nullptr, nullptr,
                                                tid);
   float* small = ROWS_IN_LDS ? lds + (size_t)max(pq.n, 0) * plan_row_floats(dm) : lds;
-  merge_plan_lists<NT, false>(small, nullptr, nullptr, pq, src_list, row_ptr, trace_src, trace_dst, tid);
+  merge_plan_lists<NT, false>(small, nullptr, nullptr, 1, 0, pq, src_list, row_ptr, trace_src, trace_dst, tid);
 }
 
 }  // namespace otas

@@ -105,3 +105,27 @@ def test_prepend_merge_and_heads_plans_on_both_sides(lib, B):
             bound = (cfg.D + 8) * 2.0 ** -24 * (heads[task[q]][0].double().abs() @ h[q].abs() + 1.0)
             assert bool(((lg[q, :k].double() - want).abs() <= bound).all()) and bool((lg[q, k:] == 0).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [2, 64, 65, 66, 197, 257, 513, 577, 1024])
+def test_selection_shared_by_workgroups_gives_the_same_edges(lib, n):
+    """bf16, head width 64: the best matches of a query are found by as many workgroups as the batch leaves room for, down
+    to one block of 32 A and 32 B tokens each.  The same query in batches of 1, 3, 20 and 150: the same edges, ranks,
+    sizes.  One query is shorter than the longest, so that some of its workgroups have no tokens."""
+    cfg = synth.config("tiny")
+    cfg.D, cfg.H, cfg.F, cfg.dtype, cfg.n0, cfg.L = 256, 4, 512, "bf16", n, 1
+    ctx, _ = hz.make_context(cfg)
+    tok, short = synth.query_tokens(cfg, 3)[:n], synth.query_tokens(cfg, 4)[:max(2, n // 3)]
+    none = np.zeros((0, cfg.D), dtype=np.float32)
+    r = max(0, (n - 1) // 3)
+    want = {}
+    for B in (1, 3, 20, 150):
+        toks = [tok] + [short] * (B > 1) + [tok] * max(0, B - 2)
+        x0, off = hz.gpu_prepend(ctx, toks, [none] * B)
+        got = hz.gpu_forward(ctx, x0, off, [r] * B)
+        for q in range(B):
+            tr, sizes = want.setdefault(q == 1, (got["trace"][q], got["sizes"][q]))
+            assert np.array_equal(got["sizes"][q], sizes)
+            for a, b in zip(got["trace"][q], tr):
+                assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    ctx.close()
