@@ -310,11 +310,16 @@ template <int TN> struct ResSlab {
   static constexpr int LPR = 8 * TN, RPI = 64 / LPR, NIT = 32 / RPI;
   floatx4 v[NIT];
   __device__ inline void load(const float* res, int64_t M, int N, int64_t m_slab, int n_wave, int lane) {
-    const int rrow = lane / LPR, n = n_wave + (lane % LPR) * 4;
+    // a uniform base and 32-bit offsets: addresses of 64 bits per lane would not fit the registers of the large tiles
+    const int64_t m_base = m_slab < M ? m_slab : M - 1;
+    const uint32_t last = (uint32_t)(M - 1 - m_base < 31 ? M - 1 - m_base : 31);
+    const char* base = reinterpret_cast<const char*>(res + (size_t)m_base * N);
+    const int n = n_wave + (lane % LPR) * 4;
+    const uint32_t row = lane / LPR, col = n < N ? n : 0;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-      const int64_t m = m_slab + it * RPI + rrow;
-      v[it] = *reinterpret_cast<const floatx4*>(res + (size_t)(m < M ? m : M - 1) * N + (n < N ? n : 0));
+      const uint32_t r = row + it * RPI;
+      v[it] = *reinterpret_cast<const floatx4*>(base + ((r < last ? r : last) * (uint32_t)N + col) * 4u);
     }
   }
 };
@@ -332,40 +337,58 @@ __device__ inline void bias_stage(bf16_t* bias_s, const bf16x8& v, int tid) {
   if (tid < BN / 8) *reinterpret_cast<bf16x8*>(bias_s + tid * 8) = v;
 }
 
+// A wave's accumulators, 32 TM rows x 32 TN columns in 16 x 16 blocks (a lane holds, of block row lane & 15, four
+// consecutive columns), as the epilogues see them: slab i (32 rows) is 4 TN quads per lane; quad k sits at row(k), col(k) of
+// the slab and takes bias quad k % NB.
+template <int TM, int TN> struct Acc {
+  static constexpr int NB = 2 * TN;
+  floatx4 v[2 * TM][2 * TN];
+  __device__ inline void clear() {
+#pragma unroll
+    for (int i = 0; i < 2 * TM; ++i)
+#pragma unroll
+      for (int j = 0; j < 2 * TN; ++j) v[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ inline void mfma(int i, int j, const bf16x8& w, const bf16x8& a) {
+    v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, v[i][j], 0, 0, 0);
+  }
+  __device__ inline const floatx4& quad(int i, int k) const { return v[2 * i + k / NB][k % NB]; }
+  static __device__ inline int row(int k, int lane) { return 16 * (k / NB) + (lane & 15); }
+  static __device__ inline int col(int k, int lane) { return 16 * (k % NB) + 4 * (lane >> 4); }
+};
+
 // bias_s: the bias of this wave's 32 TN columns in LDS.  first: the residual rows of slab 0, already requested
 // (HAVE_FIRST), so that the epilogue does not begin with a round trip to HBM.
 template <int EPI, int TM, int TN, bool HAVE_FIRST = false>
-__device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage, const bf16_t* bias_s,
+__device__ inline void mfma_epilogue(const Acc<TM, TN>& acc, float* stage, const bf16_t* bias_s,
                                      const float* res, typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N,
                                      int64_t m_wave, int n_wave, int lane, const ResSlab<TN>& first = ResSlab<TN>{}) {
+  typedef Acc<TM, TN> A;
   constexpr int WN = 32 * TN, LDR = WN + 4;
   constexpr int LPR = WN / 4;      // lanes per row when reading back
   constexpr int RPI = 64 / LPR;    // rows per read-back instruction
   constexpr int NIT = 32 / RPI;
-  const int fr = lane & 31, fk = lane >> 5;
   const int rrow = lane / LPR, rcol = (lane % LPR) * 4;
   const int n = n_wave + rcol;
   const bool n_ok = n < N;         // N % 8 == 0: a 4-column group is inside or outside as a whole
   bf16x4 bb = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
   if (EPI != EPI_PARTIAL) bb = *reinterpret_cast<const bf16x4*>(bias_s + rcol);
   // The residual rows of slab i + 1 are requested before slab i goes through LDS, so their latency
-  // is covered by a whole slab's work instead of being waited for once per slab.
+  // is covered by a whole slab's work instead of being waited for once per slab.  Without the first slab's rows (320-row
+  // tiles: no registers for two slabs of them) a slab's rows are requested as it leaves its accumulators.
   ResSlab<TN> rr[2];
-  if (EPI == EPI_RESIDUAL) {
-    if (HAVE_FIRST) rr[0] = first;
-    else rr[0].load(res, M, N, m_wave, n_wave, lane);
-  }
+  if (EPI == EPI_RESIDUAL && HAVE_FIRST) rr[0] = first;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t m_slab = m_wave + i * 32;
-    if (EPI == EPI_RESIDUAL && i + 1 < TM) rr[(i + 1) & 1].load(res, M, N, m_slab + 32, n_wave, lane);
+    if (EPI == EPI_RESIDUAL && HAVE_FIRST && i + 1 < TM) rr[(i + 1) & 1].load(res, M, N, m_slab + 32, n_wave, lane);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const floatx4 v = {acc[i][j][g * 4 + 0], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]};
-        *reinterpret_cast<floatx4*>(stage + fr * LDR + j * 32 + g * 8 + fk * 4) = v;
-      }
+    for (int k = 0; k < 4 * TN; ++k)
+      *reinterpret_cast<floatx4*>(stage + A::row(k, lane) * LDR + A::col(k, lane)) = acc.quad(i, k);
+    if (EPI == EPI_RESIDUAL && !HAVE_FIRST) {
+      __builtin_amdgcn_sched_barrier(0);
+      rr[i & 1].load(res, M, N, m_slab, n_wave, lane);
+    }
     // the slab is read back four rows per lane at a time before anything is stored: one LDS wait per group
     // instead of one per store
     constexpr int GRP = NIT < 4 ? NIT : 4;
@@ -382,24 +405,17 @@ __device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = EPI == EPI_PARTIAL ? a[e] : a[e] + (float)bb[e];
-      if (EPI == EPI_GELU) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = gelu_bf16(v[e]);
-      }
-      const int64_t m = m_slab + row;
-      if (m < M && n_ok) {
-        const size_t idx = (size_t)m * N + n;
+      if (m_slab + row < M && n_ok) {
+        typedef typename OutType<bf16_t, EPI>::type OT;
+        OT* yp = reinterpret_cast<OT*>(reinterpret_cast<char*>(Y + (size_t)m_slab * N) +
+                                       ((uint32_t)row * (uint32_t)N + (uint32_t)n) * (uint32_t)sizeof(OT));
+        static_assert(EPI == EPI_RESIDUAL || EPI == EPI_PARTIAL, "float outputs");
+        floatx4 o = {v[0], v[1], v[2], v[3]};
         if (EPI == EPI_RESIDUAL) {
           const floatx4 r = rr[i & 1].v[it];
-          floatx4 o = {v[0] + r[0], v[1] + r[1], v[2] + r[2], v[3] + r[3]};
-          *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(Y) + idx) = o;
-        } else if (EPI == EPI_PARTIAL) {
-          floatx4 o = {v[0], v[1], v[2], v[3]};
-          *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(Y) + idx) = o;
-        } else {
-          bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
-          *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(Y) + idx) = o;
+          o = floatx4{v[0] + r[0], v[1] + r[1], v[2] + r[2], v[3] + r[3]};
         }
+        *reinterpret_cast<floatx4*>(yp) = o;
       }
     }
   }
@@ -411,37 +427,33 @@ __device__ inline void mfma_epilogue(const floatx16 (&acc)[TM][TN], float* stage
 // float slab, and the read-back hands every lane 8 consecutive columns, so the global stores are
 // 16 bytes per lane and a row segment of 2 WN bytes goes out in one instruction.
 template <int EPI, int TM, int TN>
-__device__ inline void mfma_epilogue_bf16(const floatx16 (&acc)[TM][TN], bf16_t* stage, const bf16_t* bias_s, bf16_t* Y,
+__device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage, const bf16_t* bias_s, bf16_t* Y,
                                           int64_t M, int N, int64_t m_wave, int n_wave, int lane) {
+  typedef Acc<TM, TN> A;
   constexpr int WN = 32 * TN, LDR = WN + 8;
   constexpr int LPR = WN / 8;      // lanes per row when reading back
   constexpr int RPI = 64 / LPR;    // rows per read-back instruction
   constexpr int NIT = 32 / RPI;
-  const int fr = lane & 31, fk = lane >> 5;
   const int rrow = lane / LPR, rcol = (lane % LPR) * 8;
   const int n_out = n_wave + rcol;
   const bool n_ok = n_out < N;     // N % 8 == 0: an 8-column group is inside or outside as a whole
-  bf16x4 bb[TN][4];
+  bf16x4 bb[A::NB];
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) bb[j][g] = *reinterpret_cast<const bf16x4*>(bias_s + 32 * j + 8 * g + 4 * fk);
+  for (int k = 0; k < A::NB; ++k) bb[k] = *reinterpret_cast<const bf16x4*>(bias_s + A::col(k, lane));
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int64_t m_slab = m_wave + i * 32;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int k = 0; k < 4 * TN; ++k) {
+      float v[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[e] = acc[i][j][g * 4 + e] + (float)bb[j][g][e];
-          if (EPI == EPI_GELU) v[e] = gelu_bf16(v[e]);
-        }
-        const bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
-        *reinterpret_cast<bf16x4*>(stage + fr * LDR + j * 32 + g * 8 + fk * 4) = o;
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc.quad(i, k)[e] + (float)bb[k % A::NB][e];
+        if (EPI == EPI_GELU) v[e] = gelu_bf16(v[e]);
       }
+      const bf16x4 o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
+      *reinterpret_cast<bf16x4*>(stage + A::row(k, lane) * LDR + A::col(k, lane)) = o;
+    }
     // all of the slab's rows are read back before the first is stored: one LDS wait per slab instead of one per
     // store, and one address computation (the rows of a lane are RPI * N elements apart)
     bf16x8 a[NIT];
@@ -529,15 +541,14 @@ __device__ __forceinline__ void plan_tail_run(const PlanTail& pt, unsigned char*
 // while one waits at its barrier or for its fragments, or runs its epilogue (bias, GELU, the residual
 // traffic), the others keep the matrix pipe busy.
 //   iteration t: wait for this wave's loads of tile t, barrier, start the loads of tile t+NS-1 into
-//                the stage tile t-1 used, then the two k-steps of tile t (fragment reads of the
-//                second step are issued between the MFMAs of the first).
+//                the stage tile t-1 used, then the MFMAs of tile t.
 template <int EPI, int NS, int TM, bool PLAN = false>
 __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias, const float* res,
     typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N, int K, int tiles_m, int tiles_n, PlanTail pt) {
   constexpr int WM = 32 * TM, BM = 2 * WM, BN = 128, BK = 32, WN = 64, TN = 2;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;   // elements per stage
-  constexpr int NM = TM * TN, NF = TM + TN, ND = TM + 2;   // MFMAs / fragment reads per k-step, loads per tile
+  constexpr int RB = 2 * TM, CB = 2 * TN, ND = TM + 2;   // 16-row and 16-column blocks of a wave, loads per tile
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][BM][32]
   bf16_t* Ws = As + NS * STAGE_A;                 // [NS][128][32]
@@ -576,6 +587,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
   const int KT = K / BK;
   auto dma_one = [&](int kt, int st, int d) {   // d = 0..TM-1: A rows; TM, TM+1: W rows
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
+    asm volatile("" : "+v"(d < TM ? a_off[d] : w_off[d - TM]));   // as in gemm_mfma256w8_kernel
     if (d < TM)
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[d]),
                                        OTAS_LPTR(As + st * STAGE_A + (wave * (16 * TM) + d * 16) * BK), 16, 0, 0);
@@ -584,29 +596,11 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
                                        OTAS_LPTR(Ws + st * STAGE_W + (wave * 32 + (d - TM) * 16) * BK), 16, 0, 0);
   };
 
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  Acc<TM, TN> acc;
+  acc.clear();
 
-  const int fr = lane & 31, fk = lane >> 5;
-  const int frag_row = fr * BK, sw = (fr >> 2) & 3;
-  bf16x8 af[2][TM], wf[2][TN];
-  auto read_frag = [&](int st, int ks, int slot, int f) {   // f = 0..TM-1: A tiles; then the W tiles
-    const int c = (((ks << 1) + fk) ^ sw) * 8;
-    if (f < TM)
-      af[slot][f] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * WM + f * 32) * BK + frag_row + c);
-    else
-      wf[slot][f - TM] =
-          *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * WN + (f - TM) * 32) * BK + frag_row + c);
-  };
-  auto mfma_one = [&](int slot, int t) {
-    const int i = t / TN, j = t % TN;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
-  };
+  const int fr = lane & 15, fk = lane >> 4;
+  const int frag = fr * BK + (fk ^ ((fr >> 2) & 3)) * 8;   // a k-tile is one MFMA deep
 
   // Prologue: the epilogue's bias and first residual rows, then tiles 0 .. NS-2.  Loads complete in issue order: "at
   // most n in flight" = all but the n youngest have landed.
@@ -624,21 +618,24 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    bf16x8 af[RB], wf[CB];
+    wf[0] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + wn * WN * BK + frag);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) read_frag(st, 0, 0, f);
+    for (int i = 0; i < RB; ++i) af[i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * WM + i * 16) * BK + frag);
     if constexpr (decltype(more)::value) {
 #pragma unroll
       for (int d = 0; d < ND; ++d) dma_one(kt + NS - 1, st_new, d);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < NM; ++t) {
-      mfma_one(0, t);
-      if (t < NF) read_frag(st, 1, 1, t);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int j = 0; j < CB; ++j)
 #pragma unroll
-    for (int t = 0; t < NM; ++t) mfma_one(1, t);
+      for (int i = 0; i < RB; ++i) {
+        acc.mfma(i, j, wf[j], af[i]);
+        if (j == 0 && i < CB - 1)
+          wf[i + 1] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * WN + (i + 1) * 16) * BK + frag);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     st = st + 1 == NS ? 0 : st + 1;
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
   };
@@ -715,7 +712,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   constexpr int CPR = BK / 8;                    // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;                  // rows per DMA instruction
   constexpr int NI = 16 / RPI, ND = 2 * NI;      // DMA instructions per wave and operand tile, per k-tile
-  constexpr int KS = BK / 16;
+  constexpr int KS = BK / 32;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][64][BK]
@@ -749,17 +746,17 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
+      asm volatile("" : "+v"(a_off[j]), "+v"(w_off[j]));   // as in gemm_mfma256w8_kernel
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
                                        OTAS_LPTR(As + st * STAGE_A + (wave * 16 + j * RPI) * BK), 16, 0, 0);
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[j]),
                                        OTAS_LPTR(Ws + st * STAGE_W + (wave * 16 + j * RPI) * BK), 16, 0, 0);
     }
   };
-  floatx16 acc[1][1];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
-  const int fr = lane & 31, fk = lane >> 5;
-  const int frag_row = fr * BK, sw = swz(fr);   // swz of 32 w + fr is swz of fr
+  Acc<1, 1> acc;
+  acc.clear();
+  const int fr = lane & 15, fk = lane >> 4;
+  const int frag_row = fr * BK, sw = swz(fr);   // swz of 16 w + fr is swz of fr
   bf16_t* bias_s = Ws + NS * STAGE_W;
   bf16x8 bias_v;
   if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
@@ -772,17 +769,21 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    bf16x8 af[KS], wf[KS];
+    bf16x8 af[KS][2], wf[KS][2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int c = (((ks << 1) + fk) ^ sw) * 8;
-      af[ks] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * 32) * BK + frag_row + c);
-      wf[ks] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * 32) * BK + frag_row + c);
+      const int c = (((ks << 2) + fk) ^ sw) * 8;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        af[ks][i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * 32 + 16 * i) * BK + frag_row + c);
+        wf[ks][i] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * 32 + 16 * i) * BK + frag_row + c);
+      }
     }
     if constexpr (decltype(more)::value) dma(kt + NS - 1, st_new);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks], af[ks], acc[0][0], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc.mfma(i >> 1, i & 1, wf[ks][i & 1], af[ks][i >> 1]);
     st = st + 1 == NS ? 0 : st + 1;
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
   };
@@ -877,7 +878,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   constexpr int WM = 32 * TM, BM = 2 * WM, BN = 256, BK = 64, WN = 64, TN = 2, NS = 2;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   constexpr int NA = BM / 64;   // DMA instructions per wave for the A tile (8 rows each), 4 for W
-  constexpr int NM = TM * TN, NF = TM + TN, ND = NA + 4;
+  constexpr int ND = NA + 4;
+  constexpr int RB = 2 * TM, CB = 2 * TN, HB = 2;   // 16-row and 16-column blocks of a wave
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][BM][64]
   bf16_t* Ws = As + NS * STAGE_A;                 // [NS][256][64]
@@ -919,6 +921,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   const int KT = K / BK;
   auto dma_one = [&](int kt, int st, int d) {   // d = 0..NA-1: A rows; NA..NA+3: W rows
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
+    // opaque, or the compiler keeps the sums base + offset instead, 64 bits each: 18 registers that the tile needs
+    asm volatile("" : "+v"(d < NA ? a_off[d] : w_off[d - NA]));
     if (d < NA)
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[d]),
                                        OTAS_LPTR(As + st * STAGE_A + (wave * (8 * NA) + d * 8) * BK), 16, 0, 0);
@@ -927,45 +931,50 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
                                        OTAS_LPTR(Ws + st * STAGE_W + (wave * 32 + (d - NA) * 8) * BK), 16, 0, 0);
   };
 
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  Acc<TM, TN> acc;
+  acc.clear();
 
-  const int fr = lane & 31, fk = lane >> 5;
+  // Fragments of a k-step (32 columns of K): lane (row = lane & 15, lane >> 4) holds 8 columns of a row.  W's blocks have
+  // two registers each, for this k-step and the next; A's are read for the next k-step as soon as their row of MFMAs has
+  // been issued.
+  const int fr = lane & 15, fk = lane >> 4;
   const int frag_row = fr * BK, sw = (fr >> 1) & 7;
-  bf16x8 af[2][TM], wf[2][TN];
-  auto read_frag = [&](int st, int ks, int slot, int f) {   // f = 0..TM-1: A tiles; then the W tiles
-    const int c = (((ks << 1) + fk) ^ sw) * 8;
-    if (f < TM)
-      af[slot][f] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * WM + f * 32) * BK + frag_row + c);
-    else
-      wf[slot][f - TM] =
-          *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * WN + (f - TM) * 32) * BK + frag_row + c);
+  bf16x8 af[RB], wf[2][CB];
+  auto read_a = [&](int st, int ks, int i) {
+    const int c = (((ks << 2) + fk) ^ sw) * 8;
+    af[i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * WM + i * 16) * BK + frag_row + c);
   };
-  auto mfma_one = [&](int slot, int t) {
-    const int i = t / TN, j = t % TN;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
+  auto read_w = [&](int st, int ks, int j) {
+    const int c = (((ks << 2) + fk) ^ sw) * 8;
+    wf[ks][j] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * WN + j * 16) * BK + frag_row + c);
   };
-  // one k-step: NM MFMAs, each of the first NF followed by one fragment read of the next k-step
-  auto kstep = [&](int slot, int st_next, int ks_next) {
+  // Row blocks i0 .. i1 - 1 of k-step ks.  next: the fragments of k-step ks ^ 1 are read from stage st, in the order of
+  // their use: W's behind the MFMAs of row i0, A's finished blocks behind the later ones.  load(t): what else to issue
+  // behind MFMA t.
+  auto rows = [&](int ks, int i0, int i1, int st, auto next, auto load) {
 #pragma unroll
-    for (int t = 0; t < NM; ++t) {
-      mfma_one(slot, t);
-      if (t < NF) read_frag(st_next, ks_next, slot ^ 1, t);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int i = i0; i < i1; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        acc.mfma(i, j, wf[ks][j], af[i]);
+        if constexpr (decltype(next)::value) {
+          if (i == i0) read_w(st, ks ^ 1, j);
+          else if (i == i0 + 1 && j <= i0) read_a(st, ks ^ 1, j);
+          else if (i > i0 + 1 && j == 0) read_a(st, ks ^ 1, i - 1);
+          if (i == i1 - 1 && j == CB - 1) read_a(st, ks ^ 1, i);
+        }
+        load((i - i0) * CB + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
   };
+  auto no_load = [](int) {};
 
-  // Two stages.  Per tile t (stage t & 1): k-steps 0..2 (the fragments of k-step 3 are read
-  // during k-step 2), then wait for this wave's loads of tile t+1, barrier -- after it nobody reads
-  // stage t & 1 any more and tile t+1 is visible --, then k-step 3 while the loads of tile t+2 are
-  // issued into stage t & 1 and the first fragments of tile t+1 are read.
+  // Two stages.  Per tile t (stage t & 1): k-step 0, during which the fragments of k-step 1 are read; the first HB row
+  // blocks of k-step 1, which cover the last of those reads; then wait for this wave's loads of tile t+1, barrier -- after
+  // it nobody reads stage t & 1 any more and tile t+1 is visible --, then the rest of k-step 1 while the loads of tile t+2
+  // are issued into stage t & 1 and the first fragments of tile t+1 are read.
   // The last two tiles request nothing (LOAD), the last one reads no fragments ahead either (NEXT) and waits for no loads:
-  // the first residual rows, requested beside the last-but-one tile's k-step 3, may still be on their way.
+  // the first residual rows, requested beside the last-but-one tile's k-step 1, may still be on their way.
   bf16_t* bias_s = Ws + NS * STAGE_W;
   const bf16x8 bias_v = bias_fetch<BN>(bias, N, n0, tid);
   constexpr bool FIRST = EPI == EPI_RESIDUAL && TM <= 4;   // TM = 5 leaves no registers for them
@@ -980,15 +989,16 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
-  for (int f = 0; f < NF; ++f) read_frag(0, 0, 0, f);
+  for (int j = 0; j < CB; ++j) read_w(0, 0, j);
+#pragma unroll
+  for (int i = 0; i < RB; ++i) read_a(0, 0, i);
 
   auto tile = [&](int kt, auto load, auto next) {
     constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
     const int st = kt & 1;
-    kstep(0, st, 1);
-    kstep(1, st, 2);
-    kstep(0, st, 3);
-    // tile kt+1 landed, and the fragments of k-step 3 (read from stage st above, used below) are in
+    rows(0, 0, RB, st, std::true_type(), no_load);
+    rows(1, 0, HB, st, std::false_type(), no_load);
+    // tile kt+1 landed, and the fragments of k-step 1 (read from stage st above, used below) are in
     // registers: after the barrier other waves start overwriting stage st
     if constexpr (NEXT) OTAS_WAIT_LOADS_AND_LDS();
     else OTAS_WAIT_LDS();
@@ -996,18 +1006,11 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if constexpr (FIRST && NEXT && !LOAD) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
-    // k-step 3: fragments of (tile kt+1, k-step 0) and the ND load instructions of tile kt+2,
-    // spread over the MFMAs
-#pragma unroll
-    for (int t = 0; t < NM; ++t) {
-      mfma_one(1, t);
-      if (NEXT && t < NF) read_frag(st ^ 1, 0, 0, t);
+    rows(1, HB, RB, st ^ 1, next, [&](int t) {
       if constexpr (LOAD) {
-#pragma unroll
-        for (int d = t * ND / NM; d < (t + 1) * ND / NM; ++d) dma_one(kt + 2, st, d);
+        if (t % 2 == 1 && t / 2 < ND) dma_one(kt + 2, st, t / 2);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   };
   for (int kt = 0; kt < KT - 2; ++kt) tile(kt, std::true_type(), std::true_type());
   tile(KT - 2, std::false_type(), std::true_type());
@@ -1059,6 +1062,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
                                                                  int N, int K, int k_len, int tiles_m, int tiles_n,
                                                                  PlanTail pt) {
   constexpr int BM = 128, BN = 128, BK = 64, WM = 64, WN = 64, TM = 2, TN = 2;
+  constexpr int RB = 2 * TM, CB = 2 * TN, HB = 2;   // as in gemm_mfma256w8_kernel
   constexpr int STAGE = BM * BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [2][128][64]
@@ -1095,6 +1099,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   auto dma_one = [&](int kt, int st, int d) {   // d = 0..7
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
     const int j = d >> 1;
+    asm volatile("" : "+v"((d & 1) == 0 ? a_off[j] : w_off[j]));   // as in gemm_mfma256w8_kernel
     if ((d & 1) == 0)
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
                                        OTAS_LPTR(As + st * STAGE + (wave * 32 + j * 8) * BK), 16, 0, 0);
@@ -1103,37 +1108,37 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
                                        OTAS_LPTR(Ws + st * STAGE + (wave * 32 + j * 8) * BK), 16, 0, 0);
   };
 
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  Acc<TM, TN> acc;
+  acc.clear();
 
-  const int fr = lane & 31, fk = lane >> 5;
+  const int fr = lane & 15, fk = lane >> 4;
   const int frag_row = fr * BK, sw = (fr >> 1) & 7;
-  bf16x8 af[2][TM], wf[2][TN];
-  auto read_frag = [&](int st, int ks, int slot, int f) {   // f = 0,1: A tiles; 2,3: W tiles
-    const int c = (((ks << 1) + fk) ^ sw) * 8;
-    if (f < TM)
-      af[slot][f] = *reinterpret_cast<const bf16x8*>(As + st * STAGE + (wm * WM + f * 32) * BK + frag_row + c);
-    else
-      wf[slot][f - TM] =
-          *reinterpret_cast<const bf16x8*>(Ws + st * STAGE + (wn * WN + (f - TM) * 32) * BK + frag_row + c);
+  bf16x8 af[RB], wf[2][CB];
+  auto read_a = [&](int st, int ks, int i) {
+    const int c = (((ks << 2) + fk) ^ sw) * 8;
+    af[i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE + (wm * WM + i * 16) * BK + frag_row + c);
   };
-  auto mfma_one = [&](int slot, int t) {
-    const int i = t / TN, j = t % TN;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
+  auto read_w = [&](int st, int ks, int j) {
+    const int c = (((ks << 2) + fk) ^ sw) * 8;
+    wf[ks][j] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE + (wn * WN + j * 16) * BK + frag_row + c);
   };
-  auto kstep = [&](int slot, int st_next, int ks_next) {   // 4 MFMAs, the next k-step's 4 fragments in between
+  auto rows = [&](int ks, int i0, int i1, int st, auto next, auto load) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      mfma_one(slot, t);
-      read_frag(st_next, ks_next, slot ^ 1, t);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int i = i0; i < i1; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        acc.mfma(i, j, wf[ks][j], af[i]);
+        if constexpr (decltype(next)::value) {
+          if (i == i0) read_w(st, ks ^ 1, j);
+          else if (i == i0 + 1 && j <= i0) read_a(st, ks ^ 1, j);
+          else if (i > i0 + 1 && j == 0) read_a(st, ks ^ 1, i - 1);
+          if (i == i1 - 1 && j == CB - 1) read_a(st, ks ^ 1, i);
+        }
+        load((i - i0) * CB + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
   };
+  auto no_load = [](int) {};
 
   bf16_t* bias_s = Ws + 2 * STAGE;
   bf16x8 bias_v;
@@ -1150,31 +1155,24 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
-  for (int f = 0; f < TM + TN; ++f) read_frag(0, 0, 0, f);
+  for (int j = 0; j < CB; ++j) read_w(0, 0, j);
+#pragma unroll
+  for (int i = 0; i < RB; ++i) read_a(0, 0, i);
 
   auto tile = [&](int kt, auto load, auto next) {   // as in gemm_mfma256w8_kernel
     constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
     const int st = kt & 1;
-    kstep(0, st, 1);
-    kstep(1, st, 2);
-    kstep(0, st, 3);
-    // tile kt+1 landed, and the fragments of k-step 3 (read from stage st above, used below) are in
-    // registers: after the barrier other waves start overwriting stage st
+    rows(0, 0, RB, st, std::true_type(), no_load);
+    rows(1, 0, HB, st, std::false_type(), no_load);
     OTAS_WAIT_LOADS_AND_LDS();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {   // k-step 3: first fragments of tile kt+1, loads of tile kt+2
-      mfma_one(1, t);
-      if (NEXT) read_frag(st ^ 1, 0, 0, t);
-      if constexpr (LOAD) {
-        dma_one(kt + 2, st, 2 * t);
-        dma_one(kt + 2, st, 2 * t + 1);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    rows(1, HB, RB, st ^ 1, next, [&](int t) {
+      if constexpr (LOAD) dma_one(kt + 2, st, t);
+    });
   };
+  static_assert((RB - HB) * CB == 8, "a load behind each MFMA");
   for (int kt = 0; kt < KT - 2; ++kt) tile(kt, std::true_type(), std::true_type());
   tile(KT - 2, std::false_type(), std::true_type());
   tile(KT - 1, std::false_type(), std::false_type());
@@ -1229,23 +1227,25 @@ static hipError_t linear_mfma_kernel(int kernel, const void* x, const void* w, c
   }
 }
 
-// Kernel choice by a cost model fitted to per-launch times measured on MI355X inside the encoder
-// (ViT-B shapes, all three epilogues, every kernel forced in turn).  A kernel with tile bm x bn and S
+// Kernel choice by a cost model fitted to launches of every kernel on MI355X (197 .. 67000 rows, D = 768 / 1024 / 1280, the
+// four products of a block; 6 % rms, picks 0.4 % above the best kernel of each shape).  A kernel with tile bm x bn and S
 // workgroup slots on the chip (256 CUs x workgroups per CU) takes
 //     (alpha[epilogue] + beta K) * G(tiles),   G = full rounds + p + (1 - p) * (last round's fill),
 // i.e. whole rounds of S tiles, a partly filled last round costing p of a round plus its share.
-// The choice depends on the shape only, so a shape always runs the same kernel.
+// The choice depends on the shape only, so a shape always runs the same kernel.  The K-step-32 kernel is nowhere the
+// fastest where K is a multiple of 64, and not among the candidates.
 static double rounds_cost(double tiles, int slots, double p) {
   const double full = std::floor(tiles / slots), frac = tiles / slots - full;
   return full + (frac > 0 ? p + (1.0 - p) * frac : 0.0);
 }
 
-// The 64 x 64 kernel: a workgroup's chain of k-tiles, its length fixed, times what sharing a CU costs it.  Fitted to
-// launches of 21 .. 2368 rows, N = 768 .. 3072, K = 384 .. 1536 (us measured / modelled: 197 x 2304 x 768 5.4 / 5.6,
-// 600 x 2304 x 768 7.6 / 8.3, 2368 x 768 x 768 9.9 / 9.5, 1400 x 2304 x 768 13.4 / 14.2; eight-way split 197 x 768 x 3072 6.5 / 6.6).
-static double tile64_cost(int64_t M, int N, int k_len, int splits, double alpha) {
-  const double n = (double)((M + 63) / 64) * ((N + 63) / 64) * splits / 256.0;   // workgroups per CU
-  return (alpha + 0.0033 * k_len) * (n <= 1.0 ? 0.95 + 0.17 * n : 0.62 + 0.66 * n);
+// The 64 x 64 kernel: the chains of k-tiles of a CU's workgroups, which share its path to L2 and so take as long as one
+// after the other, the fullest CU's being the launch's.  Fitted to the same launches (us measured / modelled at 1, 2, 3, 4
+// workgroups per CU: K = 768 4.8 / 4.8, 6.4 / 7.2, 9.6 / 9.5, 11.5 / 11.9; K = 3072 + residual 11.1 / 12.0, 20.9 / 22.4,
+// 31.0 / 32.9, 40.8 / 43.3).
+static double tile64_cost(int64_t M, int N, int k_len, int splits, bool float_out, double alpha) {
+  const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * splits;
+  return alpha + (0.0031 * k_len + (float_out ? 0.9 : 0.0)) * (double)((tiles + 255) / 256);
 }
 
 static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = nullptr) {
@@ -1253,15 +1253,14 @@ static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = 
   if (K % 64 != 0 || K < 128) return ((M + 63) / 64) * ((N + 63) / 64) <= 450 ? GK_64X64 : GK_128_K32;
   struct Cand { int id, bm, bn, slots; double alpha[3], beta, p; };
   static const Cand cands[] = {
-      {GK_128_K32, 128, 128, 768, {4.06, 7.04, 13.0}, 0.0278, 0.27},
-      {GK_128_K64, 128, 128, 512, {3.17, 6.37, 8.75}, 0.0161, 0.58},
-      {GK_192X256, 192, 256, 256, {4.36, 10.8, 11.9}, 0.0215, 0.72},
-      {GK_256X256, 256, 256, 256, {5.85, 14.9, 12.7}, 0.0252, 0.72},
-      {GK_320X256, 320, 256, 256, {8.34, 19.2, 14.7}, 0.0284, 0.74},
+      {GK_128_K64, 128, 128, 512, {3.36, 4.99, 9.81}, 0.0131, 0.514},
+      {GK_192X256, 192, 256, 256, {5.69, 8.07, 13.2}, 0.0183, 0.546},
+      {GK_256X256, 256, 256, 256, {5.53, 9.37, 16.0}, 0.0236, 0.566},
+      {GK_320X256, 320, 256, 256, {6.98, 11.3, 23.0}, 0.0278, 0.582},
   };
   const int e = epi == EPI_RESIDUAL ? 2 : epi == EPI_GELU ? 1 : 0;
-  static const double alpha64[3] = {2.8, 3.3, 3.0};
-  double best = tile64_cost(M, N, K, 1, alpha64[e]);
+  static const double alpha64[3] = {2.4, 3.1, 1.6};
+  double best = tile64_cost(M, N, K, 1, e == 2, alpha64[e]);
   int kernel = GK_64X64;
   for (const Cand& c : cands) {
     const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
@@ -1286,8 +1285,8 @@ static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = 
 // 197 10.3 / 12.9, 500 13.1 / 14.9, 1000 17.4 / 18.9, 1379 23.0 / 21.9, 2368 30.3 / 27.8.
 static double splitk_cost(int64_t M, int N, int K, int S, bool* tiles64) {
   const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
-  const double c128 = (6.5 + 0.0153 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
-  const double c64 = tile64_cost(M, N, K / S, S, 2.8);
+  const double c128 = (6.5 + 0.0130 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
+  const double c64 = tile64_cost(M, N, K / S, S, true, 2.4);
   *tiles64 = c64 < c128;
   return std::min(c64, c128);
 }
