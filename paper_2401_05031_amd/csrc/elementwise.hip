@@ -1,6 +1,7 @@
 // HBM-bound row kernels: integer fill/copy, the prompting module's ragged concatenation
 // (Sec. II-B / III-B), LayerNorm (Sec. II-A "normalization"), and the merging module's data
 // movement fused with the LayerNorm behind it (Sec. II-C).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -684,8 +685,9 @@ hipError_t launch_embed_finish(int dtype, const void* proj, const void* cls, con
 
 // Back end (Sec. III-B: every task has its own head): the first row of a query's output is normalised (final LayerNorm,
 // two-pass fp32 statistics, stored in the model's dtype like every GEMM operand) and multiplied with its task's head
-// [K, D].  grid (ceil(k_max / 32), B), eight classes per wave: every wave holds the whole row in registers and normalises
-// it for itself, its lanes share a class's row in the same pieces of 8 columns, fp32 accumulate, one butterfly per class.
+// [K, D].  grid (B, ceil((k_max - c0) / 32)): queries in the first dimension, whose limit no batch reaches (the second one
+// ends at 65535).  Eight classes per wave: every wave holds the whole row in registers and normalises it for itself, its
+// lanes share a class's row in the same pieces of 8 columns, fp32 accumulate, one butterfly per class.
 // Bound by latency: the row, gamma, beta and the first pieces of the weights are requested together and no wave waits
 // for another.  Measured on MI355X against one workgroup per query with one class per thread, each walking its row
 // alone (us): one query with 10 classes 15.7 -> 5.7, seven queries with up to 100 19.6 -> 6.8.
@@ -693,16 +695,16 @@ constexpr int kHeadClasses = 32;
 template <typename T, int NCH, typename P>
 __global__ __launch_bounds__(256) void task_head_kernel(const float* __restrict__ x, const P plan, int B,
                                                         const T* __restrict__ g, const T* __restrict__ bta, int D,
-                                                        float eps, float* __restrict__ logits, int k_max) {
+                                                        float eps, float* __restrict__ logits, int k_max, int c0) {
   constexpr int V = 8, NC = kHeadClasses / 4;
-  const int q = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int q = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float* xr = x + (size_t)plan[q] * D;
   // plan: first rows [B] | task [B] | pad to an even count | per task {w, b, K, pad} (6 ints)
   const int rec = ((2 * B + 1) & ~1) + 6 * plan[B + q];
   const T* w = reinterpret_cast<const T*>((uint64_t)(uint32_t)plan[rec] | (uint64_t)(uint32_t)plan[rec + 1] << 32);
   const T* b = reinterpret_cast<const T*>((uint64_t)(uint32_t)plan[rec + 2] | (uint64_t)(uint32_t)plan[rec + 3] << 32);
   const int K = plan[rec + 4];
-  const int k0 = blockIdx.x * kHeadClasses + wave * NC;
+  const int k0 = c0 + blockIdx.y * kHeadClasses + wave * NC;
   if (k0 >= K) {   // classes beyond the task's count read 0
     if (lane < NC && k0 + lane < k_max) logits[(size_t)q * k_max + k0 + lane] = 0.f;
     return;
@@ -779,19 +781,23 @@ hipError_t launch_task_heads(int dtype, const float* x, const int32_t* plan, siz
                              hipStream_t s) {
   if (B <= 0 || k_max <= 0) return hipSuccess;
   const int nch = (D / 8 + 63) / 64;
-  dim3 grid((unsigned)((k_max + kHeadClasses - 1) / kHeadClasses), (unsigned)B), block(256);
+  const int blocks = (k_max - 1) / kHeadClasses + 1;
   return with_plan(plan, count, d_plan, [&](const auto& pl) {
     typedef std::decay_t<decltype(pl)> P;
-#define OTAS_HEAD(TYPE, N) \
-  task_head_kernel<TYPE, N, P><<<grid, block, 0, s>>>(x, pl, B, (const TYPE*)g, (const TYPE*)b, D, eps, logits, k_max)
+    for (int done = 0; done < blocks; done += 65535) {
+      const dim3 grid((unsigned)B, (unsigned)std::min(blocks - done, 65535)), block(256);
+#define OTAS_HEAD(TYPE, N)                                                                                              \
+  task_head_kernel<TYPE, N, P><<<grid, block, 0, s>>>(x, pl, B, (const TYPE*)g, (const TYPE*)b, D, eps, logits, k_max, \
+                                                      done * kHeadClasses)
 #define OTAS_HEADS(N) do { if (dtype == 0) OTAS_HEAD(float, N); else OTAS_HEAD(bf16_t, N); } while (0)
-    if (nch <= 1) OTAS_HEADS(1);
-    else if (nch <= 2) OTAS_HEADS(2);
-    else if (nch <= 4) OTAS_HEADS(4);
-    else if (nch <= 8) OTAS_HEADS(8);
-    else return hipErrorInvalidValue;
+      if (nch <= 1) OTAS_HEADS(1);
+      else if (nch <= 2) OTAS_HEADS(2);
+      else if (nch <= 4) OTAS_HEADS(4);
+      else if (nch <= 8) OTAS_HEADS(8);
+      else return hipErrorInvalidValue;
 #undef OTAS_HEADS
 #undef OTAS_HEAD
+    }
     return hipGetLastError();
   });
 }

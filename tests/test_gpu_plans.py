@@ -107,6 +107,25 @@ def test_prepend_merge_and_heads_plans_on_both_sides(lib, B):
     ctx.close()
 
 
+def test_heads_of_more_queries_than_a_second_grid_dimension_holds(lib):
+    import torch
+    cfg = synth.config("tiny")
+    ctx, _ = hz.make_context(cfg)
+    B, g = 70000, torch.Generator().manual_seed(6)
+    x = torch.randn((B, cfg.D), generator=g).to("cuda")
+    heads = [(torch.randn((k, cfg.D), generator=g).to("cuda"), torch.randn(k, generator=g).to("cuda")) for k in (3, 2)]
+    gam, bet = torch.ones(cfg.D, device="cuda"), torch.zeros(cfg.D, device="cuda")
+    lg = torch.full((B, 3), float("nan"), device="cuda")
+    ctx.otas_task_heads(x, np.arange(B + 1, dtype=np.int32), np.arange(B, dtype=np.int32) % 2, heads, gam, bet, lg)
+    h = torch.nn.functional.layer_norm(x.double(), (cfg.D,), eps=1e-6)
+    for t, (w, b) in enumerate(heads):
+        k, got = w.shape[0], lg[t::2]
+        bound = (cfg.D + 8) * 2.0 ** -24 * (h[t::2].abs() @ w.double().abs().T + 1.0)      # as in the test above
+        assert bool(((got[:, :k].double() - (h[t::2] @ w.double().T + b.double())).abs() <= bound).all())
+        assert bool((got[:, k:] == 0).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("n", [2, 64, 65, 66, 197, 257, 513, 577, 1024])
 def test_selection_shared_by_workgroups_gives_the_same_edges(lib, n):
     """bf16, head width 64: the best matches of a query are found by as many workgroups as the batch leaves room for, down
