@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
       s[e] = key < n ? v : -INFINITY;
       mx = fmaxf(mx, s[e]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+    mx = xor32_max(mx);
     const float m_new = fmaxf(m_run, mx);
     const float alpha = expf(m_run - m_new);   // 0 on the first block
     m_run = m_new;
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
 #pragma unroll
       for (int t = 0; t < DT; ++t) oacc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t][e], s[e], oacc[t], 0, 0, 0);
   }
-  const float l_run = l_part + __shfl_xor(l_part, 32, kWave);
+  const float l_run = xor32_sum(l_part);
   if (fk == 0) {
     ml[wave * 64 + fr] = m_run;
     ml[wave * 64 + 32 + fr] = l_run;
@@ -301,7 +301,7 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[e]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+      mx = xor32_max(mx);
       if (!BIAS) mx *= scale2;
       if (__any(mx > m_run)) {   // some row's maximum moved: rescale what has been accumulated
         const float m_new = fmaxf(m_run, mx);
@@ -361,7 +361,7 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
     }
   }
   if (!wave_active) return;
-  const float l_tot = l_part + __shfl_xor(l_part, 32, kWave);
+  const float l_tot = xor32_sum(l_part);
   if (my_row < n) {
     const float inv = 1.0f / l_tot;
     bf16_t* orow = o + (size_t)(base + my_row) * D + h * DH;

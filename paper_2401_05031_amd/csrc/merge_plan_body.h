@@ -200,10 +200,9 @@ __device__ __forceinline__ void merge_plan_select(
         const floatx4 v = *reinterpret_cast<const floatx4*>(r + 4 * m);
         ss = fmaf(v[0], v[0], ss); ss = fmaf(v[1], v[1], ss); ss = fmaf(v[2], v[2], ss); ss = fmaf(v[3], v[3], ss);
       }
-      ss += __shfl_xor(ss, 1, kWave);
-      ss += __shfl_xor(ss, 2, kWave);
-      ss += __shfl_xor(ss, 4, kWave);
-      ss += __shfl_xor(ss, 8, kWave);
+      ss = dpp_sum<kDppXor2>(dpp_sum<kDppXor1>(ss));
+      ss = dpp_sum<kDppHalfMirror>(ss);   // the lanes of a quad agree by now: the mirrored lane holds the other quad's sum
+      ss = dpp_sum<dpp_ror(8)>(ss);
       const float rn = 1.0f / fmaxf(sqrtf(ss), 1e-12f);
       if (u < n_need)
         for (int m = j; m < q4; m += 16) {
@@ -264,8 +263,8 @@ __device__ __forceinline__ void merge_plan_select(
           if (b < nB && acc[e] > bv) { bv = acc[e]; bc = b; }
         }
       }
-      const float ov = __shfl_xor(bv, 32, kWave);
-      const int oc = __shfl_xor(bc, 32, kWave);
+      const float ov = wave_halves(bv).hi;   // the lower half's lanes (fk == 0) decide
+      const int oc = __float_as_int(wave_halves(__int_as_float(bc)).hi);
       if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
       if (fk == 0) {
         part_v[grp * (nAl * 32) + al * 32 + fr] = bv;
