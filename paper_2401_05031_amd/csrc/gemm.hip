@@ -1247,8 +1247,7 @@ static double tile64_cost(int64_t M, int N, int k_len, int splits, bool float_ou
   return alpha + (0.0031 * k_len + (float_out ? 0.9 : 0.0)) * (double)((tiles + 255) / 256);
 }
 
-static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = nullptr) {
-  if (cost_us) *cost_us = 0.0;
+static int pick_mfma_kernel(int64_t M, int N, int K, int epi) {
   if (K % 64 != 0 || K < 128) return ((M + 63) / 64) * ((N + 63) / 64) <= 450 ? GK_64X64 : GK_128_K32;
   struct Cand { int id, bm, bn, slots; double alpha[3], beta, p; };
   static const Cand cands[] = {
@@ -1266,7 +1265,6 @@ static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = 
     const double cost = (c.alpha[e] + c.beta * K) * rounds_cost(tiles, c.slots, c.p);
     if (cost < best) { best = cost; kernel = c.id; }
   }
-  if (cost_us) *cost_us = best;
   return kernel;
 }
 
@@ -1276,45 +1274,55 @@ static int pick_mfma_kernel(int64_t M, int N, int K, int epi, double* cost_us = 
 // each contract over K / S and write a float partial result; a second kernel adds the partial
 // results in split order (a fixed order: results are reproducible), the bias and the residual, and
 // applies the LayerNorm that follows -- so the split costs S + 1 more float passes over the
-// output than the one-kernel form followed by its LayerNorm.  S minimises the same cost model as
-// above (partial-output form of the 128 x 128 K-step-64 kernel, fitted to launches of 704 ... 7488
-// rows at N = 768, K = 3072 with S = 2 ... 12, 9 % rms, or of the 64 x 64 kernel) plus those passes at the rate the
-// reduce kernel reaches inside the encoder.  S never exceeds max_split.
-// 64 x 64 tiles against 128 x 128 (us, partial products + reduce, best S of each, N = 768, K = 3072): 21 rows 8.6 / 11.1,
-// 197 10.3 / 12.9, 500 13.1 / 14.9, 1000 17.4 / 18.9, 1379 23.0 / 21.9, 2368 30.3 / 27.8.
-static double splitk_cost(int64_t M, int N, int K, int S, bool* tiles64) {
-  const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
-  const double c128 = (6.5 + 0.0130 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
-  const double c64 = tile64_cost(M, N, K / S, S, true, 2.4);
-  *tiles64 = c64 < c128;
-  return std::min(c64, c128);
+// output than the one-kernel form followed by its LayerNorm.  S never exceeds max_split.
+//
+// S sets the order in which a row's sums are added, hence the last bits of a pass and, where two merge candidates tie
+// within them, its merge decisions.  It is therefore a rule of its own that does not follow the kernels: the constants
+// below stay when a kernel or pick_mfma_kernel's model changes.  They were fitted to launches inside the encoder, whose
+// operands come from HBM (residual form: one row per tile shape; partial products: launches of 704 ... 7488 rows at
+// N = 768, K = 3072 with S = 2 ... 12, 9 % rms), the passes are priced at the rate the reduce kernel reaches there.  S taken
+// from pick_mfma_kernel's stand-alone model instead (1 or 2 where this gives 6 from 400 to 1400 rows of N = 768) measured
+// the same within 0.3 % on passes of 7 ... 128 queries and 1 % faster on one query with r = 16 (522.5 against 527.9 us).
+static double residual_in_pass_us(int64_t M, int N, int K) {
+  struct Shape { int bm, bn, slots; double alpha, beta, p; };   // as in pick_mfma_kernel
+  static const Shape shapes[] = {{128, 128, 768, 13.0, 0.0278, 0.27}, {128, 128, 512, 8.75, 0.0161, 0.58},
+                                 {192, 256, 256, 11.9, 0.0215, 0.72}, {256, 256, 256, 12.7, 0.0252, 0.72},
+                                 {320, 256, 256, 14.7, 0.0284, 0.74}};
+  double best = 1e30;
+  for (const Shape& c : shapes) {
+    const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+    best = std::min(best, (c.alpha + c.beta * K) * rounds_cost(tiles, c.slots, c.p));
+  }
+  return best;
 }
 
 int splitk_factor(int dtype, int64_t M, int N, int K, int max_split) {
   if (dtype == 0 || K < 2048 || K % 64 != 0 || N % 8 != 0 || M <= 0) return 1;
   const double pass_us = (double)M * N * 4.0 / 6.0e6;   // one float pass over the output at 6 TB/s
-  double unsplit;
-  pick_mfma_kernel(M, N, K, EPI_RESIDUAL, &unsplit);
-  double best = unsplit + 1.5 * pass_us;                // + the LayerNorm pass: float in, 16-bit out
+  double best = residual_in_pass_us(M, N, K) + 1.5 * pass_us;   // + the LayerNorm pass: float in, 16-bit out
   int S = 1;
+  const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
   static const int cand[] = {2, 3, 4, 6, 8};
   for (int c : cand) {
     if (c > max_split || K % (c * 64) != 0 || K / c < 128) continue;
-    bool tiles64;
-    const double cost = splitk_cost(M, N, K, c, &tiles64) + (c + 2.5) * pass_us;
+    const double cost = (6.5 + 0.0153 * (K / c)) * rounds_cost(tiles * c, 512, 0.556) + (c + 2.5) * pass_us;
     if (cost < best) { best = cost; S = c; }
   }
   return S;
+}
+
+// Which tiles the partial products of a split run in: the same bits either way.
+static bool splitk_tiles64(int64_t M, int N, int K, int S) {
+  const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
+  return tile64_cost(M, N, K / S, S, true, 2.4) < (6.5 + 0.0130 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
 }
 
 hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64_t M, int N, int K, int S,
                                 hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (S < 1 || K % (S * 64) != 0 || K / S < 128 || N % 8 != 0) return hipErrorInvalidValue;
-  bool tiles64;
-  splitk_cost(M, N, K, S, &tiles64);
-  return tiles64 ? linear_mfma64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, nullptr, S)
-                 : linear_mfma128k64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, S);
+  return splitk_tiles64(M, N, K, S) ? linear_mfma64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, nullptr, S)
+                                    : linear_mfma128k64(x, w, nullptr, nullptr, part, M, N, K, EPI_PARTIAL, s, S);
 }
 
 hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,

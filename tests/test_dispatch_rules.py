@@ -1,0 +1,30 @@
+"""Pure-host rules of the dispatch, through the built library (no GPU)."""
+import ctypes
+import os
+
+import paper_2401_05031_amd as otas
+
+
+def _library():
+    if not os.path.exists(otas.lib_path()):
+        from paper_2401_05031_amd import build
+        build.build(verbose=False)
+    return ctypes.CDLL(otas.lib_path())
+
+
+def test_split_counts_of_the_second_linear_are_fixed():
+    """How many partial products the MLP's second linear is summed from sets the order of additions, hence the bits of a
+    pass: the counts are pinned on the rows a ViT-B pass with r = 16 has in its layers (batches of 1, 7, 24 and 64) and
+    on some of ViT-L and ViT-H."""
+    split = _library()._ZN4otas13splitk_factorEiliii
+    split.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    split.restype = ctypes.c_int
+    want = {(768, 3072, 1): [8] * 11,
+            (768, 3072, 7): [6, 6, 6, 6, 6, 6, 8, 8, 8, 8, 8],
+            (768, 3072, 24): [2, 2, 3, 3, 3, 4, 4, 4, 6, 6, 8],
+            (768, 3072, 64): [1, 1, 1, 1, 1, 1, 1, 2, 3, 4, 6]}
+    for (N, K, B), counts in want.items():
+        assert [split(1, B * (197 - 16 * (l + 1)), N, K, 8) for l in range(11)] == counts, B
+    assert [split(1, M, 1024, 4096, 8) for M in (128, 1000, 2000, 4000, 25216)] == [8, 8, 4, 2, 1]
+    assert [split(1, M, 1280, 5120, 8) for M in (128, 1000, 2000, 4000, 67072)] == [8, 4, 2, 1, 1]
+    assert split(1, 1344, 768, 3072, 4) == 4 and split(0, 1344, 768, 3072, 8) == 1 and split(1, 1344, 768, 1536, 8) == 1
