@@ -92,7 +92,8 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
     }
     mx = xor32_max(mx);
     const float m_new = fmaxf(m_run, mx);
-    const float alpha = expf(m_run - m_new);   // 0 on the first block
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;   // no key of weight so far (sizes 0, logits below the range): all 0
+    const float alpha = expf(m_run - m_ref);                // 0 on the first block
     m_run = m_new;
     l_part *= alpha;
 #pragma unroll
@@ -101,8 +102,14 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
       for (int e = 0; e < 16; ++e) oacc[t][e] *= alpha;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      s[e] = expf(s[e] - m_new);
+      s[e] = expf(s[e] - m_ref);
       l_part += s[e];
+    }
+    if (kb + 32 > n) {   // values past the end: zero, or an infinite last one would turn the row to NaN (0 x inf)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int t = 0; t < DT; ++t) vf[t][e] = kb + 8 * (e >> 2) + 4 * fk + (e & 3) < n ? vf[t][e] : 0.f;
     }
 #pragma unroll
     for (int e = 0; e < 16; ++e)

@@ -74,3 +74,46 @@ def test_fp32_attention_tile_edges(lib, dtype, D, H):
             # logits of size <= 30 in fp32: 30 * 2^-23 of the weights; a bf16 result adds its own rounding
             assert np.abs(got - ref).max() <= (2e-5 if dtype == "f32" else 2.0 ** -8) * np.abs(ref).max(), (flags, n)
     ctx.close()
+
+
+@pytest.mark.parametrize("H", [1, 4])
+def test_fp32_attention_keys_without_weight_and_infinite_values(lib, H):
+    """A row's whole key block may have no weight: sizes 0 under the size bias, or logits that overflow to -inf.  Such keys
+    get weight 0, wherever they lie among the blocks and the waves.  An infinite value reaches the rows that weigh it
+    and its own column only, also as the last key of a sequence that ends inside a block."""
+    import torch
+    D, n = 128, 170
+    dh = D // H
+    ctx, _ = _context(lib, D, H, "f32")
+    g = torch.Generator(device="cuda").manual_seed(H)
+    qkv = torch.randn((n, 3 * D), generator=g, device="cuda")
+    one = torch.ones(n, dtype=torch.int32, device="cuda")
+
+    def check(x, sizes, flags):
+        o = torch.full((n, D), float("nan"), device="cuda")
+        ctx.otas_attention(x, sizes, np.array([0, n], dtype=np.int32), flags, o)
+        x = x.cpu()
+        Q, Kk, V = (x[:, i * D:(i + 1) * D].reshape(n, H, dh).transpose(0, 1) for i in range(3))
+        s = (Q @ Kk.transpose(1, 2)).double() / dh ** 0.5      # products in 32 bits: the overflow is the point
+        if flags:
+            s = s + sizes.cpu().double().log()
+        ref = (torch.softmax(s, -1) @ V.double()).transpose(0, 1).reshape(n, D)
+        got = o.cpu().double()
+        assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not bool(torch.isnan(got).any())
+        fin = ~torch.isinf(ref)
+        assert float((got - ref)[fin].abs().max()) <= 2e-5 * float(ref[fin].abs().max())     # as in the test above
+
+    for lo, hi in [(0, 32), (32, 64), (0, 160), (128, 170), (5, 170)]:
+        sizes = one.clone()
+        sizes[lo:hi] = 0
+        check(qkv, sizes, lib.OTAS_FLAG_SIZE_BIAS)
+        x = qkv.clone()
+        x[:, :D:dh] = 1e25                       # first column of every head's queries ...
+        x[lo:hi, D:2 * D:dh] = -1e25             # ... times the keys': -1e50
+        x[:lo, D:2 * D:dh] = 0
+        x[hi:, D:2 * D:dh] = 0
+        check(x, one, 0)
+    x = qkv.clone()
+    x[n - 1, 2 * D + 3] = float("inf")
+    check(x, one, 0)
+    ctx.close()
