@@ -786,13 +786,14 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       // selection (the long part: keys, similarities, best matches) and the lists, which need nothing else, are
       // written by extra workgroups of the projection's launch: the plan's serial chain beside attention gets
       // shorter by a quarter, and the selection can be shared by several workgroups per query.  Its result waits in the
-      // split-K partial buffer (at least two float rows of D per token row), idle between two MLPs.
+      // split-K partial buffer, idle between two MLPs: two float rows of D >= 64 per token row at least, and it takes
+      // 2 nb <= 32 entries per token row.
       FusedPlan how = {0, 0};
       bool tail = false;
       if (ln.any_merge[l] && plan_inline) {
         tail = linear_plan_tail_fits(T, D, D, Bg);
         how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, tail);
-        tail = tail && how.na > 0 && 2 * how.nb <= 2 * D;
+        tail = tail && how.na > 0;
         if (!tail) how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, false);
       }
       const bool fuse = how.na > 0;

@@ -482,10 +482,10 @@ static size_t fused_attention_lds(int max_n, size_t* unit) {
   return one ? *unit : 2 * *unit;
 }
 
-// How launch_attention_plan runs this case (pure host; not at all: parts.a = 0).
+// How launch_attention_plan runs this case (pure host; not at all: na = 0).  Below two tokens there is nothing to select.
 FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lists_elsewhere) {
   FusedPlan how = {0, 0};
-  if (dtype == 0 || B <= 0 || H <= 0 || D != 64 * H || max_n <= 0 || max_n > kPlanThreads) return how;
+  if (dtype == 0 || B <= 0 || H <= 0 || D != 64 * H || max_n < 2 || max_n > kPlanThreads) return how;
   const int G = (max_n > 128 && max_n <= 256) ? 1 : 2;   // heads per workgroup: 8 waves / (8 or 4 waves per head)
   if (H % G != 0) return how;
   size_t unit;

@@ -28,3 +28,22 @@ def test_split_counts_of_the_second_linear_are_fixed():
     assert [split(1, M, 1024, 4096, 8) for M in (128, 1000, 2000, 4000, 25216)] == [8, 8, 4, 2, 1]
     assert [split(1, M, 1280, 5120, 8) for M in (128, 1000, 2000, 4000, 67072)] == [8, 4, 2, 1, 1]
     assert split(1, 1344, 768, 3072, 4) == 4 and split(0, 1344, 768, 3072, 8) == 1 and split(1, 1344, 768, 1536, 8) == 1
+
+
+class FusedPlan(ctypes.Structure):
+    _fields_ = [("na", ctypes.c_int), ("nb", ctypes.c_int)]
+
+
+def test_workgroups_of_the_selection():
+    """Queries of 0 and 1 tokens have no pair to compare: not taken, whatever asks.  From 2 tokens on the selection has at
+    least one workgroup and no more of either kind than there are blocks of 32 tokens."""
+    how = _library()._ZN4otas18attention_plan_howEiiiiib
+    how.argtypes = [ctypes.c_int] * 5 + [ctypes.c_bool]
+    how.restype = FusedPlan
+    for B in (1, 7, 200):
+        for elsewhere in (False, True):
+            for max_n in (-1, 0, 1, 1025):
+                assert how(1, B, max_n, 256, 4, elsewhere).na == 0
+        for max_n in (2, 3, 64, 65, 66, 197, 1024):
+            p = how(1, B, max_n, 256, 4, True)
+            assert 1 <= p.na <= ((max_n + 1) // 2 + 31) // 32 and 1 <= p.nb <= (max_n // 2 + 31) // 32
