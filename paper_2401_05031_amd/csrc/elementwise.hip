@@ -63,17 +63,18 @@ hipError_t launch_copy_i32(const int32_t* a, int32_t* b, int64_t n, hipStream_t 
 // One 16-byte chunk per thread.  blockIdx.y = query; blockIdx.x strides over the query's
 // (row, chunk) pairs.  Output row i of a query comes from: i < n_lead -> token i;
 // i < n_lead + P -> prompt i - n_lead; else token i - P.
-// plan: tok_off [B+1] | prm_beg [B] | prm_cnt [B] | out_off [B+1].
+// plan: tok_off [B+1] | prm_beg [B] | prm_cnt [B] | out_off [B+1].  gx = gridDim.x, 256 threads: asked for as gridDim and
+// blockDim they would add 256 bytes of implicit arguments to the plan's.
 template <typename T, typename P>
-__global__ void prepend_kernel(const T* __restrict__ tokens, const T* __restrict__ prompts, T* __restrict__ out,
-                               const P plan, int B, int D, int n_lead) {
+__global__ __launch_bounds__(256) void prepend_kernel(const T* __restrict__ tokens, const T* __restrict__ prompts, T* __restrict__ out,
+                               const P plan, int B, int D, int n_lead, int gx) {
   constexpr int V = Vec<T>::N;
   const int q = blockIdx.y;
   const int o0 = plan[3 * B + 1 + q], n_out = plan[3 * B + 2 + q] - o0;
   const int t0 = plan[q], p0 = plan[B + 1 + q], Pq = plan[2 * B + 1 + q];   // the query's rows of the prompt tensor
   const int chunks = D / V;
   const int total = n_out * chunks;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < total; t += gridDim.x * blockDim.x) {
+  for (int t = blockIdx.x * 256 + threadIdx.x; t < total; t += gx * 256) {
     const int i = t / chunks, c = (t - i * chunks) * V;
     const T* src;
     if (i < n_lead) src = tokens + (size_t)(t0 + i) * D;
@@ -95,10 +96,10 @@ hipError_t launch_prepend(int dtype, const void* tokens, const void* prompts, vo
     typedef std::decay_t<decltype(pl)> P;
     if (dtype == 0)
       prepend_kernel<float, P><<<grid, block, 0, s>>>((const float*)tokens, (const float*)prompts, (float*)out, pl, B, D,
-                                                      n_lead);
+                                                      n_lead, (int)gx);
     else
       prepend_kernel<bf16_t, P><<<grid, block, 0, s>>>((const bf16_t*)tokens, (const bf16_t*)prompts, (bf16_t*)out, pl, B,
-                                                       D, n_lead);
+                                                       D, n_lead, (int)gx);
     return hipGetLastError();
   });
 }

@@ -20,8 +20,11 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_copy_i32(const int32_t* src, int32_t* dst, int64_t n, hipStream_t s);
 
 // Plans of up to kArgInts entries travel in a kernel's arguments: such a launcher reads the host array `plan` and never
-// d_plan; larger ones must have been copied to d_plan.
+// d_plan; larger ones must have been copied to d_plan.  HIP promises a kernel 4 KB of arguments; the implicit ones that
+// the compiler adds to kernels that ask for gridDim or blockDim (256 bytes) count as well, so kernels that take a plan ask
+// for neither.  A test reads what every built kernel takes.
 constexpr int kArgInts = 960;
+constexpr size_t kKernelArgBytes = 4096;
 inline bool plan_in_args(size_t count) { return count <= (size_t)kArgInts; }
 
 // plan: tok_off [B+1] | prm_beg [B] | prm_cnt [B] | out_off [B+1]; query q takes rows prm_beg[q] .. + prm_cnt[q] - 1 of
@@ -64,6 +67,7 @@ struct StartJob {
   int64_t n_ones[2];
   int32_t v[kArgInts];
 };
+static_assert(sizeof(StartJob) + 64 <= kKernelArgBytes, "the job and the LayerNorm's own arguments");
 
 // x_is_float: the input rows are float (the residual stream) even when dtype is bf16.
 hipError_t launch_layer_norm(int dtype, bool x_is_float, const void* x, const void* g, const void* b,

@@ -9,7 +9,7 @@
 
 namespace otas {
 
-// In a kernel's arguments (4 KB at most on this runtime's dispatch path).  A copy to the device buffer costs a launch of
+// In a kernel's arguments.  A copy to the device buffer costs a launch of
 // its own (4 - 6 us on the GPU and, with the event that guards the staging slot, about 10 us on the host), which for the
 // calls that launch one or two kernels is a third of the call: otas_token_merge of 64 queries of 197 tokens, back to
 // back, 32.6 us with the copy, 25.3 without (MI355X).

@@ -1,0 +1,60 @@
+"""What the built library's GPU code says of its kernels (the AMDGPU metadata note of its code objects; no GPU)."""
+import os
+import struct
+
+import msgpack
+import pytest
+
+import paper_2401_05031_amd as otas
+
+BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
+NT_AMDGPU_METADATA = 32
+
+
+def _kernels_of_elf(elf):
+    phoff, = struct.unpack_from("<Q", elf, 32)
+    size, count = struct.unpack_from("<HH", elf, 54)
+    for i in range(count):
+        kind, _, at, _, _, length = struct.unpack_from("<IIQQQQ", elf, phoff + i * size)
+        end = at + length
+        while kind == 4 and at < end:                              # PT_NOTE
+            name, desc, note = struct.unpack_from("<III", elf, at)
+            body = at + 12 + (name + 3) // 4 * 4
+            if note == NT_AMDGPU_METADATA:
+                return msgpack.unpackb(elf[body:body + desc])["amdhsa.kernels"]
+            at = body + (desc + 3) // 4 * 4
+    return []
+
+
+def built_kernels():
+    """Metadata of every gfx950 kernel in the library."""
+    if not os.path.exists(otas.lib_path()):
+        from paper_2401_05031_amd import build
+        build.build(verbose=False)
+    with open(otas.lib_path(), "rb") as f:
+        data = f.read()
+    out, at = [], data.find(BUNDLE)
+    while at >= 0:
+        entries, = struct.unpack_from("<Q", data, at + len(BUNDLE))
+        p = at + len(BUNDLE) + 8
+        for _ in range(entries):
+            first, size, name = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + name]:
+                out += _kernels_of_elf(data[at + first:at + first + size])
+            p += 24 + name
+        at = data.find(BUNDLE, at + 1)
+    return out
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    found = built_kernels()
+    assert len(found) > 100
+    return found
+
+
+def test_kernel_arguments_stay_within_what_hip_promises(kernels):
+    """4 KB, the implicit arguments among them: kernels that carry a plan in their arguments come close."""
+    sizes = {k[".name"]: k[".kernarg_segment_size"] for k in kernels}
+    assert max(sizes.values()) > 3840                              # the plan's 960 entries are among them
+    assert {n: s for n, s in sizes.items() if s > 4096} == {}
