@@ -58,3 +58,22 @@ def test_kernel_arguments_stay_within_what_hip_promises(kernels):
     sizes = {k[".name"]: k[".kernarg_segment_size"] for k in kernels}
     assert max(sizes.values()) > 3840                              # the plan's 960 entries are among them
     assert {n: s for n, s in sizes.items() if s > 4096} == {}
+
+
+def test_every_kernel_has_its_place_in_the_traffic_figures(kernels, tmp_path):
+    """The per-family HBM figures are counted by kernel name: no kernel of the library is outside the families and the
+    named rest, every product (bf16 and fp32) counts as one, and an unknown kernel stops the tool."""
+    from paper_2401_05031_amd import traffic
+    names = [k[".name"] for k in kernels]
+    assert {n for n in names if traffic.family(n) is None} == set()
+    assert {n for n in names if "gemm" in n and traffic.family(n) != "gemm"} == set()
+    assert {traffic.family(n) for n in names} == set(traffic.FAMILIES) | {""}
+    csv = tmp_path / "fetch.csv"
+    rows = ["Kernel_Name,Counter_Name,Counter_Value", "__amd_rocclr_copyBuffer,FETCH_SIZE,262144",
+            "void otas::gemm_f32_kernel<float>,FETCH_SIZE,8", "void otas::gemm_mfma64_kernel<0>,FETCH_SIZE,4"]
+    csv.write_text("\n".join(rows))
+    per, cal = traffic._load(str(csv), "FETCH_SIZE")
+    assert per["gemm"] == [2, 12.0] and cal == 262144
+    csv.write_text("\n".join(rows + ["void otas::renamed_kernel,FETCH_SIZE,4"]))
+    with pytest.raises(ValueError, match="renamed_kernel"):
+        traffic._load(str(csv), "FETCH_SIZE")
