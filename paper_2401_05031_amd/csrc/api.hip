@@ -649,34 +649,31 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
     const int Bg = ln.Bg;
     ln.plan_base = plan.size();
     if ((size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg > kPlanInts - ln.plan_base) return OTAS_ENOMEM;
-    if (!start) plan.resize(ln.plan_base + (size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg);
-    int32_t* off = plan.data() + ln.plan_base;
-    int32_t* pr = off + (size_t)(L + 1) * (Bg + 1);
-    int32_t* pt = pr + (size_t)L * Bg;
     ln.T.assign(L + 1, 0);
     ln.max_n.assign(L + 1, 0);
     ln.any_merge.assign(L, 0);
     ln.last_merge = -1;
+    for (int l = 0; l <= L; ++l)
+      for (int q = ln.q0; q < ln.q1; ++q) {
+        const int n = len[(size_t)l * B + q];
+        ln.T[l] += n;
+        ln.max_n[l] = std::max(ln.max_n[l], n);
+        if (l < L && reff[(size_t)l * B + q] > 0) { ln.any_merge[l] = 1; ln.last_merge = l; }
+      }
+    if (start) continue;
+    plan.resize(ln.plan_base + (size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg);
+    int32_t* off = plan.data() + ln.plan_base;
+    int32_t* pr = off + (size_t)(L + 1) * (Bg + 1);
+    int32_t* pt = pr + (size_t)L * Bg;
     for (int l = 0; l <= L; ++l) {
       int32_t* o = off + (size_t)l * (Bg + 1);
-      int at = 0;
+      o[0] = 0;
       for (int j = 0; j < Bg; ++j) {
-        const int n = len[(size_t)l * B + ln.q0 + j];
-        if (!start) o[j] = at;
-        at += n;
-        ln.max_n[l] = std::max(ln.max_n[l], n);
+        o[j + 1] = o[j] + len[(size_t)l * B + ln.q0 + j];
+        if (l == L) continue;
+        pr[(size_t)l * Bg + j] = reff[(size_t)l * B + ln.q0 + j];
+        pt[(size_t)l * Bg + j] = troff[(size_t)l * B + ln.q0 + j];
       }
-      if (!start) o[Bg] = at;
-      ln.T[l] = at;
-      if (l < L)
-        for (int j = 0; j < Bg; ++j) {
-          const int k = reff[(size_t)l * B + ln.q0 + j];
-          if (!start) {
-            pr[(size_t)l * Bg + j] = k;
-            pt[(size_t)l * Bg + j] = troff[(size_t)l * B + ln.q0 + j];
-          }
-          if (k > 0) { ln.any_merge[l] = 1; ln.last_merge = l; }
-        }
     }
   }
 
