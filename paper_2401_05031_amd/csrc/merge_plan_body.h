@@ -8,6 +8,7 @@
 #ifndef OTAS_MERGE_PLAN_BODY_H_
 #define OTAS_MERGE_PLAN_BODY_H_
 
+#include <cfloat>
 #include <type_traits>
 
 #include "common.h"
@@ -233,8 +234,10 @@ __device__ __forceinline__ void merge_plan_select(
     const int grp = wide ? 0 : w / nAl;
     for (int al = wide ? w : w % nAl; al < nAl && grp < G; al += wide ? NWV : nAl) {
       const float* pa = mh + (size_t)(nBv + min(al * 32 + fr, nAv - 1)) * ldm + fk * hp;
-      float bv = -INFINITY;
-      int bc = 0x7fffffff;
+      // An A token that compares with no B token (NaN in its metric, or in all of theirs) goes to B token 0, behind every
+      // other and before a protected one: the list phases index with its choice.
+      float bv = -FLT_MAX;
+      int bc = 0;
       for (int bl = grp; bl < nBl; bl += G) {
         const float* pb = mh + (size_t)min(bl * 32 + fr, nBv - 1) * ldm + fk * hp;
         floatx16 acc;

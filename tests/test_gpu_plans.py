@@ -148,3 +148,52 @@ def test_selection_shared_by_workgroups_gives_the_same_edges(lib, n):
             for a, b in zip(got["trace"][q], tr):
                 assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     ctx.close()
+
+
+def _check_edges(n, r, src, dst, sizes):
+    """r distinct unprotected A tokens, each merged into an existing B token, and no token lost."""
+    assert len(src) == r and len(np.unique(src)) == r
+    assert (src % 2 == 0).all() and (src >= 2).all() and (src < n).all()
+    assert (dst % 2 == 1).all() and (dst >= 1).all() and (dst < n).all()
+    assert int(sizes.sum()) == n and (sizes >= 1).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [3, 65, 197, 600])
+def test_merge_of_tokens_that_compare_with_none(lib, dtype, n):
+    """NaN similarities (a broken or overflowing token) still give a merge: every index a later kernel reads with stays
+    inside the query, the tokens that can be compared rank first, the leading token is never merged.  As an
+    operator, and in the encoder (one workgroup per query, and as many as a lone query gets)."""
+    import torch
+    cfg = synth.config("tiny")
+    cfg.D, cfg.H, cfg.F, cfg.dtype, cfg.n0, cfg.L = 256, 4, 512, dtype, n, 1
+    ctx, _ = hz.make_context(cfg)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(n)
+    r = (n - 1) // 2                                               # all that the length allows
+    a_bad, all_b = [2] if n < 5 else [2, n // 2 // 2 * 2, (n - 1) // 2 * 2], list(range(1, n, 2))
+    for bad in ([], a_bad, all_b, a_bad + all_b, list(range(n))):
+        x = torch.randn((n, cfg.D), generator=g, device="cuda").to(dt)
+        metric = torch.randn((n, 64), generator=g, device="cuda").to(dt)
+        metric[bad] = float("nan")
+        ws = torch.empty(ctx.otas_merge_workspace_bytes(1, n), dtype=torch.uint8, device="cuda")
+        out = torch.full((n - r, cfg.D), float("nan"), device="cuda", dtype=dt)
+        sizes = torch.zeros(n - r, dtype=torch.int32, device="cuda")
+        src, dst = (torch.full((r,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        ctx.otas_token_merge(x, metric, 64, None, [0, n], [r], ws, out, sizes, src, dst)
+        src, dst = src.cpu().numpy(), dst.cpu().numpy()
+        _check_edges(n, r, src, dst, sizes.cpu().numpy())
+        assert bool(torch.isfinite(out).all())
+        if bad == a_bad:                                           # the A tokens that compare with none come last
+            assert sorted(src[r - len(a_bad):]) == sorted(a_bad) and (dst[r - len(a_bad):] == 1).all()
+        tok = x.float().cpu().numpy()
+        tok[bad] = float("nan")
+        for B in (1, 100):
+            toks = [x.float().cpu().numpy()] * B
+            toks[B // 2] = tok
+            x0, off = hz.gpu_prepend(ctx, toks, [np.zeros((0, cfg.D), dtype=np.float32)] * B)
+            got = hz.gpu_forward(ctx, x0, off, [r] * B)
+            for q in range(B):
+                _check_edges(n, r, *got["trace"][q][0], got["sizes"][q])
+                assert q == B // 2 or np.isfinite(got["x"][q]).all()
+    ctx.close()
