@@ -716,6 +716,34 @@ def test_linear_every_named_kernel_whole_output(torch_cuda, lib, kernel):
     ctx.close()
 
 
+@pytest.mark.parametrize("K", [64, 96, 128, 160, 192, 224, 256, 320])
+@pytest.mark.parametrize("kernel", [2, 7])
+def test_linear_short_k_loops(torch_cuda, lib, kernel, K):
+    """Contractions of one to ten k-tiles: the 128 x 128 K-step-32 kernel and the 64 x 64 kernel (K step 64, and 32 where K
+    is no multiple of 64) finish their last k-tiles outside the main loop, with wait counts of their own for 1, 2 and
+    3 tiles.  Ragged rows and columns, all three epilogues, the whole output.  Bound: K + 8 roundings of 2^-24 on the
+    terms' absolute sum (GELU's slope is at most 1.13), and the bf16 rounding of a 16-bit output."""
+    torch = torch_cuda
+    cfg = synth.config("vitb_plain")
+    cfg.L = 1
+    ctx, _ = hz.make_context(cfg)
+    g = torch.Generator(device="cuda").manual_seed(K + kernel)
+    for M, N in [(1, 8), (61, 72), (333, 200), (129, 392)]:
+        x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+        res = torch.randn((M, N), generator=g, device="cuda")
+        xd, wd, bd = x.double().cpu(), w.double().cpu(), b.double().cpu()
+        lin, mag = xd @ wd.T + bd, xd.abs() @ wd.abs().T + bd.abs()
+        for epi in (0, 1, 2):
+            out = torch.full((M, N), float("nan"), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+            ctx.otas_linear_kernel(kernel, x, w, b, res if epi == 2 else None, M, N, K, epi, out)
+            want = torch.nn.functional.gelu(lin) if epi == 1 else lin + res.double().cpu() if epi == 2 else lin
+            bound = (K + 8) * 2.0 ** -24 * 1.13 * (mag + (res.double().cpu().abs() if epi == 2 else 0))
+            if epi != 2:
+                bound = bound + 2.0 ** -8 * want.abs() + 1e-7
+            assert bool(((out.double().cpu() - want).abs() <= bound).all()), (M, N, epi)
+    ctx.close()
+
+
 def test_longest_sequences_f32(torch_cuda, lib):
     """Long merging queries next to a short one, fp32, r larger than half the tokens: 554 tokens (the longest
     whose unit metric vectors fit the plan kernel's LDS at d_h = 64), 577 (a 384-pixel image at patch 16: the
