@@ -780,7 +780,7 @@ def test_longest_sequences_f32(torch_cuda, lib):
 def test_long_ragged_sequences_bf16_plan_split_over_two_launches(torch_cuda, lib):
     """bf16, head width 64, H = 4: the encoder runs the merge plan's selection beside attention and writes its lists
     beside the output projection (256 threads there: a 554-token query gives every thread three positions of the
-    scans; 554 is the longest query this path takes).  Ragged lengths 554 / 300 / 130 / 9, r up to 100, one query that
+    scans).  Ragged lengths 554 / 300 / 130 / 9, r up to 100, one query that
     merges nothing.  Lock-step against the oracle: sizes identical, every differing edge a near-tie."""
     torch = torch_cuda
     cfg = synth.config("tiny")
@@ -798,6 +798,21 @@ def test_long_ragged_sequences_bf16_plan_split_over_two_launches(torch_cuda, lib
     print(rep)
     assert rep["sizes_equal"] and rep["max_err"] <= BF16_TOL and rep["max_deficit"] <= NEAR_TIE
     assert np.diff(gpu["offsets"]).tolist() == [254, 189, 82, 3, 77]   # 9 -> 6 -> 4 -> 3: r clamps to half the unprotected tokens
+    ctx.close()
+
+
+@pytest.mark.parametrize("H", [1, 3, 4, 7, 8, 11, 13, 16, 17, 25, 33])
+def test_merge_decisions_for_every_grouping_of_heads(torch_cuda, lib, H):
+    """bf16, head width 64: the metric averages the keys of H heads, loaded in even groups of at most 16.  Lock-step
+    against the oracle: sizes identical, every differing edge a near-tie."""
+    cfg = synth.config("tiny")
+    cfg.D, cfg.H, cfg.F, cfg.dtype, cfg.n0, cfg.L, cfg.B = 64 * H, H, 128, "bf16", 130, 2, 2
+    cfg.strategies = [(0, 30), (2, 7)]
+    ctx, layers = hz.make_context(cfg)
+    toks, prm, P, R = synth.batch(cfg)
+    x0, off = hz.gpu_prepend(ctx, toks, prm)
+    rep = hz.compare_lockstep(cfg, layers, toks, prm, R, hz.gpu_forward(ctx, x0, off, R))
+    assert rep["sizes_equal"] and rep["max_err"] <= BF16_TOL and rep["max_deficit"] <= NEAR_TIE, rep
     ctx.close()
 
 
