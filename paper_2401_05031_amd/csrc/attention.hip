@@ -22,8 +22,9 @@ namespace otas {
 // Both products are computed transposed, as in the bf16 kernel below: a lane owns one query row, and the
 // accumulator element e of lane half h of the first product is key 8 (e / 4) + 4 h + (e & 3), which the second
 // product takes as k-slot h of its MFMA e straight from registers.  K, V and Q go from global memory to registers
-// (no wave shares a key block with another): what bounds it is the matrix pipe, 2 x 32 MFMAs of 64 clocks per key
-// block at head width 64, and, at few waves per SIMD, the chain load -> logits -> softmax -> product.
+// (no wave shares a key block with another): per key block 2 x 32 MFMAs of 64 clocks at head width 64;
+// what bounds it, at few waves per SIMD, is the chain load -> logits -> softmax -> product (the matrix pipe is busy 19 %
+// of the time at 6 x 201 tokens, 12 heads).
 // Measured on MI355X against one wave per query row on the vector ALU (us): 6 x 201 tokens, 12 heads of 64
 // 119 -> 21.6; 2 x 201 tokens, 3 heads 31 -> 12.
 template <typename T, int DT>

@@ -173,12 +173,6 @@ template <typename T, int NCH> struct RowChunks {   // chunk lane + 64 i of 8 co
   __device__ inline float get(int i, int k) const { return v[i][k / Vec<T>::N].get(k % Vec<T>::N); }
 };
 
-// One wave per row, the row held in registers (NCH 16-byte chunks per lane), two-pass statistics
-// in fp32 (mean, then the biased variance of the centred values).
-// XT = type of the input row (the residual stream is float), T = type of gamma, beta and the output.
-// Each lane owns chunks of 8 consecutive columns (two 16-byte loads of a float row).
-// xw != nullptr: the row is also written out as floats (16-bit tokens entering the float residual
-// stream: the widening copy rides on the first block's LayerNorm).
 // Row l of the plan (StartJob in kernels.h) by one workgroup of 256 threads, two queries a thread.
 __device__ inline void start_plan_row(const StartJob& job, int l) {
   __shared__ int wave_tot[2][4];
@@ -243,6 +237,13 @@ __device__ inline void start_job(const StartJob& job, int64_t blk) {
 }
 struct NoJob {};
 
+// One wave per row, the row held in registers (NCH chunks per lane), two-pass statistics
+// in fp32 (mean, then the biased variance of the centred values).
+// XT = type of the input row (the residual stream is float), T = type of gamma, beta and the output.
+// Each lane owns chunks of 8 consecutive columns (two 16-byte loads of a float row).
+// J: StartJob for a pass's first LayerNorm, whose leading job_blocks workgroups set the pass up, else NoJob.
+// xw != nullptr: the row is also written out as floats (16-bit tokens entering the float residual
+// stream: the widening copy rides on the first block's LayerNorm).
 template <typename XT, typename T, int NCH, typename J>
 __global__ __launch_bounds__(256) void layer_norm_kernel(const XT* __restrict__ x, const T* __restrict__ g,
                                                          const T* __restrict__ b, T* __restrict__ y,

@@ -13,7 +13,7 @@
 //       gemm_mfma256w8_kernel    192 / 256 / 320 x 256, eight waves, one per CU
 //       gemm_mfma64_kernel       64 x 64, K step 64 or 32, for products of very few rows (also split-K)
 //     pick_mfma_kernel chooses among them with a cost model fitted to measured launch times; splitk_factor
-//     decides with the same model whether the MLP's second linear is split over K.
+//     decides by a rule of its own whether the MLP's second linear is split over K.
 //     Each kernel has a PLAN form for the attention output projection, whose first workgroups write the lists
 //     of the layer's merge plan (merge_plan_lists) instead of computing a tile.
 #include <algorithm>
@@ -51,7 +51,9 @@ __device__ inline float epilogue_value(float acc, float bias, const float* res, 
 // ascending order, and the quarters are added as ((q0 + q1) + q2) + q3.
 //   gemm_f32_kernel        64 x 64 tile, eight waves of 32 x 32: four for each half of K, so that a CU with a single
 //                          workgroup has two waves per SIMD to cover LDS and barrier waits; operands through two LDS
-//                          stages of K step 32 per half.  Bound by the matrix pipe from about 256 tiles on.
+//                          stages of K step 32 per half.  The matrix pipe is busy 43 % of the time over a ViT-B pass of
+//                          1206 rows (75 TFLOP/s): a k-tile's fragments are waited for after its barrier, and 228 to
+//                          912 tiles do not fill whole rounds of 512.
 //   gemm_f32_small_kernel  32 x 32 tile, four waves, one quarter of K each, operands straight into registers, the four
 //                          sums added through LDS.  With few tiles a launch lasts as long as one wave's chain of
 //                          MFMAs (32 clocks per column of K); a quarter of K per wave makes that four times
@@ -1231,6 +1233,9 @@ static hipError_t linear_mfma_kernel(int kernel, const void* x, const void* w, c
 // workgroup slots on the chip (256 CUs x workgroups per CU) takes
 //     (alpha[epilogue] + beta K) * G(tiles),   G = full rounds + p + (1 - p) * (last round's fill),
 // i.e. whole rounds of S tiles, a partly filled last round costing p of a round plus its share.
+// Those are launches repeated on their own, operands in the caches.  Inside a pass (ViT-B, 64 queries, r = 16) the kernels
+// it picks take longer than it gives: QKV and FC1 2 - 19 % at 20 us and more, the projection 13 - 32 %, the MLP's second
+// linear 17 - 30 %, launches under 20 us 18 - 50 % (of which about 1 us is the timing events').
 // The choice depends on the shape only, so a shape always runs the same kernel.  The K-step-32 kernel is nowhere the
 // fastest where K is a multiple of 64, and not among the candidates.
 static double rounds_cost(double tiles, int slots, double p) {
