@@ -152,9 +152,19 @@ otas_status upload_plan(otas_ctx* c, const std::vector<int32_t>& host) {
 }
 
 struct WorkspaceLayout {
-  size_t xa, xb, h, qkv, hid, part, sizes_a, sizes_b, src_list, row_ptr, total;
+  size_t xa, xb, h, qkv, hid, part, metric, sizes_a, sizes_b, src_list, row_ptr, total;
+  // columns per token row; where the two share a buffer, the same, and `metric` is room beside it for the merge plan's
+  // metric rows of queries too long for its LDS (else those use the hidden rows; the projection is still read beside them)
+  size_t qkv_cols, hid_cols;
   int part_factor;   // float rows of the split-K buffer per token row
 };
+
+// The QKV projection is dead once the output projection has run, the MLP's hidden rows live only after it.  Batches for
+// which the two do not fit the L2s (32 MB) side by side keep them in one buffer: a block's working set is smaller by 3 D
+// columns a row, and more of what a kernel reads is still in the 256 MB last-level cache.  ViT-B, 64 queries (252 MB apart,
+// 174 shared; us per pass on MI355X): no merging 3014 -> 3003, r = 16 1954 -> 1944, prompts growing through the layers 3357
+// -> 3297; ViT-L, 128 queries 9569 -> 9497.  One query is quicker with two buffers (528, shared 531).
+constexpr size_t kSharedActBytes = (size_t)32 << 20;
 
 WorkspaceLayout forward_layout(const otas_model_desc& d, int64_t T0) {
   const size_t es = elem_size(d.dtype);
@@ -165,8 +175,17 @@ WorkspaceLayout forward_layout(const otas_model_desc& d, int64_t T0) {
   w.xa = take(rows * d.D * sizeof(float));   // the residual stream is float for every dtype
   w.xb = take(rows * d.D * sizeof(float));
   w.h = take(rows * d.D * es);
-  w.qkv = take(rows * 3 * d.D * es);
-  w.hid = take(rows * d.F * es);
+  const bool share = rows * (3 * (size_t)d.D + d.F) * es > kSharedActBytes;
+  w.qkv_cols = 3 * (size_t)d.D;
+  w.hid_cols = (size_t)d.F;
+  w.qkv = take(rows * w.qkv_cols * es);
+  w.hid = take(rows * w.hid_cols * es);
+  w.metric = 0;
+  if (share) {   // the size stays that of two buffers: what a workspace serves must not shrink as T0 falls below the limit
+    w.qkv_cols = w.hid_cols = (size_t)std::max(3 * d.D, d.F);
+    w.hid = w.qkv;
+    w.metric = w.qkv + rows * w.qkv_cols * es;   // min(3 D, F) columns a row are left
+  }
   w.part_factor = part_rows_factor(rows);
   w.part = take(d.dtype == OTAS_BF16 ? w.part_factor * rows * d.D * sizeof(float) : 0);   // split-K partial products
   w.sizes_a = take(rows * sizeof(int32_t));
@@ -609,8 +628,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       mx = std::max(mx, n);
       len[(size_t)(l + 1) * B + q] = n - k;
     }
-    // a query too long for the plan kernel's LDS keeps its metric rows in the (then unused) MLP hidden buffer,
-    // F elements per token: that has to hold a metric row
+    // a query too long for the plan kernel's LDS keeps its metric rows in the (then unused) MLP hidden buffer, or in the
+    // part of it that the projection does not share: F elements per token (3 D always do) have to hold a metric row
     if (any && merge_plan_lds_bytes(mx, dh) > 160 * 1024 &&
         (size_t)d.F * elem_size(d.dtype) * 64 < merge_plan_rows_bytes(64, dh))
       return OTAS_EUNSUPPORTED;
@@ -765,8 +784,9 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       // the lane's rows of every buffer
       float* x_free[2] = {(float*)(ws + w.xa) + (size_t)ln.row0 * D, (float*)(ws + w.xb) + (size_t)ln.row0 * D};
       char* hbuf = ws + w.h + (size_t)ln.row0 * D * es;
-      char* qkv = ws + w.qkv + (size_t)ln.row0 * 3 * D * es;
-      char* hid = ws + w.hid + (size_t)ln.row0 * F * es;
+      char* qkv = ws + w.qkv + (size_t)ln.row0 * w.qkv_cols * es;   // [T][3 D] until the projection has run
+      char* hid = ws + w.hid + (size_t)ln.row0 * w.hid_cols * es;   // [T][F] after it, possibly the same rows
+      float* metric_rows = (float*)(w.metric ? ws + w.metric + merge_plan_rows_bytes(ln.row0, dh) : hid);
       int32_t* sizes_buf[2] = {(int32_t*)(ws + w.sizes_a) + ln.row0, (int32_t*)(ws + w.sizes_b) + ln.row0};
       int32_t* src_list = (int32_t*)(ws + w.src_list) + ln.row0;
       int32_t* row_ptr = (int32_t*)(ws + w.row_ptr) + ln.row0 + g;   // one end entry per lane
@@ -814,7 +834,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
           OTAS_LAUNCH_ON(K_PLAN, ps,
                          launch_merge_plan(dt, qkv, 3 * (int64_t)D, D, H, dh, off_l, off_n, d_reff, d_tr, Bg,
                                            ln.max_n[l], n_lead, src_list, row_ptr, trace ? trace_src : nullptr,
-                                           trace ? trace_dst : nullptr, (float*)hid, ps));
+                                           trace ? trace_dst : nullptr, metric_rows, ps));
           if (!plan_inline) OTAS_HIP(hipEventRecord(hw.ev_join, hw.side));
         }
         OTAS_LAUNCH_ON(K_ATTN, s,
@@ -969,7 +989,7 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
   float* x_buf[2] = {(float*)(ws + w.xa), (float*)(ws + w.xb)};
   void* hbuf = ws + w.h;
   void* qkv = ws + w.qkv;
-  void* hid = ws + w.hid;
+  void* hid = ws + w.hid;   // possibly the same rows: written once the projection has run
   const int32_t* d_prm_off = c->d_plan + (size_t)L * (B + 1);
   const size_t es = elem_size(dt);
 
