@@ -27,7 +27,7 @@ __device__ inline PlanQuery plan_query(const int32_t* in_off, const int32_t* out
 
 // LDS layout of the plan kernel (4-byte words), n = query length, nA = ceil(n/2), nB = floor(n/2):
 //   mh [rows][dm+4] normalised metric rows (rows = n for the whole plan) | best [nA4] | kept [nA4] | bcol [nA] | cnt [nB] |
-//   keep_pos [n] | ent_pos [n] | wave_tot [2][16] | part_v [512] | part_c [512],   nA4 = nA rounded up to 4
+//   keep_pos [n] | ent_pos [n] | wave_tot [32] | part_v [512] | part_c [512],   nA4 = nA rounded up to 4
 // (the list phases on their own use the part from best on, without part_v / part_c; the selection on its own
 // mh | part_v | part_c).
 // Floats per metric row in LDS: the even and the odd columns each padded to a multiple of 4, plus 4.
@@ -323,22 +323,33 @@ __device__ __forceinline__ void merge_plan_lists(
   }
   const int nA = (n + 1) >> 1, nB = n >> 1, nA4 = (nA + 3) & ~3;
   float* best = small;
-  int* kept = (int*)(best + nA4);   // destination of a kept edge, -1 for an A token that survives
+  int* kept = (int*)(best + nA4);   // destination of a kept edge (from its slot's count on: + slot << 16), -1: survives
   int* bcol = kept + nA4;
   int* cnt = bcol + nA;
   int* keep_pos = cnt + nB;      // [n] exclusive scan of "row survives"
   int* ent_pos = keep_pos + n;   // [n] exclusive scan of list lengths
-  int* wave_tot = ent_pos + n;   // [2][16]
+  int* wave_tot = ent_pos + n;   // [16]
   int* rank = keep_pos;          // until phase 4
-  int* slot = (int*)best;        // from the end of the ranking on
+  int* edge = (int*)best;        // from the end of the ranking on: the kept edges by rank, destination << 16 | source
   if constexpr (FROM_GLOBAL) {
+    // All candidates of an A token are requested before the first is compared: written on other CUs a launch earlier, each
+    // is a round trip beyond the XCD's L2, and one after the other they were the longest part of the lists.
+    constexpr int NC = 4;
     for (int a = tid; a < nA; a += NT) {
-      float v = g_best[i0 + a];
-      int c = g_bcol[i0 + a];
-      for (int p = 1; p < nb; ++p) {
-        const float u = g_best[p * stride + i0 + a];
-        const int d = g_bcol[p * stride + i0 + a];
-        if (u > v || (u == v && d < c)) { v = u; c = d; }
+      float v = -INFINITY;
+      int c = 0x7fffffff;
+      for (int p0 = 0; p0 < nb; p0 += NC) {
+        float u[NC];
+        int d[NC];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {   // past the last candidate: that one again
+          const int64_t at = min(p0 + j, nb - 1) * stride + i0 + a;
+          u[j] = g_best[at];
+          d[j] = g_bcol[at];
+        }
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+          if (u[j] > v || (u[j] == v && d[j] < c)) { v = u[j]; c = d[j]; }
       }
       best[a] = v;
       bcol[a] = c;
@@ -350,109 +361,106 @@ __device__ __forceinline__ void merge_plan_lists(
   __syncthreads();
 
   // Phase 3: keep the r_eff best edges.  rank = number of A tokens that come before this one in
-  // (similarity descending, position ascending) order.  slot = number of kept edges with the same destination
-  // and a lower source position (the order of a destination's source list).  Both are counts over all A tokens: a
+  // (similarity descending, position ascending) order: a count over all A tokens.  A
   // thread takes one A token and one part of the tokens it is compared with (the same for its whole wave: they are
-  // read four at a time, every lane the same address), the parts are added by LDS atomics on integers.  The phases are
+  // read four at a time, every lane the same address), the parts are added by LDS atomics on integers.  The phase is
   // bound by the number of LDS reads a wave waits for: with eight lanes per A token, each reading every eighth token on
   // its own, a ViT-B pass over ten queries of 577 / 197 tokens took 1700 us, one query of 197 tokens 559; now 1642, 551.
   const int nAp = (nA + 63) & ~63;                 // whole waves
   const int parts = max(1, NT / nAp), part = __builtin_amdgcn_readfirstlane(tid / nAp);   // the same for a whole wave
   const int chunk = ((nA + parts - 1) / parts + 3) & ~3;
   const int k_beg = part * chunk, k_end = min(nA4, k_beg + chunk);
-  auto each_a = [&](auto f) {                      // f(a) for the A tokens of this thread
-    if (part < parts)
-      for (int a = tid - part * nAp; a < nA; a += NT) f(a);   // a second round only when nAp > NT: one part then
-  };
-  each_a([&](int a) {
-    const float v = best[a];
-    // this wave's A tokens are a0 .. a0 + 63: ties only have to be looked at among those
-    const int a0 = __builtin_amdgcn_readfirstlane(a) & ~63;
-    const int k_lo = min(max(a0, k_beg), k_end), k_hi = min(max(a0 + 64, k_beg), k_end);
-    int c = 0;
+  if (part < parts)
+    for (int a = tid - part * nAp; a < nA; a += NT) {   // a second round only when nAp > NT: one part then
+      const float v = best[a];
+      // this wave's A tokens are a0 .. a0 + 63: ties only have to be looked at among those
+      const int a0 = __builtin_amdgcn_readfirstlane(a) & ~63;
+      const int k_lo = min(max(a0, k_beg), k_end), k_hi = min(max(a0 + 64, k_beg), k_end);
+      int c = 0;
 #pragma unroll 4
-    for (int k = k_beg; k < k_lo; k += 4) {
-      const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
+      for (int k = k_beg; k < k_lo; k += 4) {
+        const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) c += u[j] >= v ? 1 : 0;
-    }
+        for (int j = 0; j < 4; ++j) c += u[j] >= v ? 1 : 0;
+      }
 #pragma unroll 4
-    for (int k = k_lo; k < k_hi; k += 4) {
-      const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
+      for (int k = k_lo; k < k_hi; k += 4) {
+        const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) c += (u[j] > v || (u[j] == v && k + j < a)) ? 1 : 0;
-    }
+        for (int j = 0; j < 4; ++j) c += (u[j] > v || (u[j] == v && k + j < a)) ? 1 : 0;
+      }
 #pragma unroll 4
-    for (int k = k_hi; k < k_end; k += 4) {
-      const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
+      for (int k = k_hi; k < k_end; k += 4) {
+        const floatx4 u = *reinterpret_cast<const floatx4*>(best + k);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) c += u[j] > v ? 1 : 0;
+        for (int j = 0; j < 4; ++j) c += u[j] > v ? 1 : 0;
+      }
+      if (parts > 1) atomicAdd(&rank[a], c);
+      else rank[a] = c;
     }
-    if (parts > 1) atomicAdd(&rank[a], c);
-    else rank[a] = c;
-  });
   __syncthreads();
   for (int a = tid; a < nA; a += NT) {
-    const bool keep = rank[a] < r_eff;
-    kept[a] = keep ? bcol[a] : -1;
-    if (keep && trace_src) {
-      trace_src[pq.tr0 + rank[a]] = 2 * a;
-      trace_dst[pq.tr0 + rank[a]] = 2 * bcol[a] + 1;
+    const int k = rank[a], dst = bcol[a];
+    const bool keep = k < r_eff;
+    if (!keep) kept[a] = -1;
+    else {
+      edge[k] = dst << 16 | a;
+      if (trace_src) {
+        trace_src[pq.tr0 + k] = 2 * a;
+        trace_dst[pq.tr0 + k] = 2 * dst + 1;
+      }
     }
-    slot[a] = 0;
   }
-  if (tid < nA4 - nA) kept[nA + tid] = -1;
+  if (tid < (-r_eff & 3)) edge[r_eff + tid] = 0x7fffffff;   // counts as nobody's neighbour below; r_eff <= nA
   __syncthreads();
-  each_a([&](int a) {
-    const int dst = kept[a];
-    if (dst < 0) return;
+  // slot = number of kept edges with the same destination and a lower source position (the order of a destination's
+  // source list): counted among the r_eff kept edges, a few dozen of the hundreds of A tokens.
+  for (int i = tid; i < r_eff; i += NT) {
+    const int me = edge[i], a = me & 0xffff, dst = me >> 16, lo = dst << 16;
     int c = 0;
 #pragma unroll 4
-    for (int k = k_beg; k < min(k_end, a); k += 4) {
-      const int4 u = *reinterpret_cast<const int4*>(kept + k);
-      c += (u.x == dst && k < a) + (u.y == dst && k + 1 < a) + (u.z == dst && k + 2 < a) + (u.w == dst && k + 3 < a);
+    for (int k = 0; k < r_eff; k += 4) {
+      const int4 u = *reinterpret_cast<const int4*>(edge + k);
+      c += ((unsigned)(u.x - lo) < (unsigned)a) + ((unsigned)(u.y - lo) < (unsigned)a) +
+           ((unsigned)(u.z - lo) < (unsigned)a) + ((unsigned)(u.w - lo) < (unsigned)a);
     }
-    if (c) atomicAdd(&slot[a], c);   // integer counts: the result does not depend on the order
-    if (part == 0) atomicAdd(&cnt[dst], 1);
-  });
+    kept[a] = dst | c << 16;
+    atomicAdd(&cnt[dst], 1);   // an integer count: the result does not depend on the order
+  }
   __syncthreads();
 
   // Phase 4: positions.  keep(i) = 1 unless i is a merged A token; entries(i) = keep(i) * (1 +
-  // number of sources merged into i).  Exclusive scans of both over i = 0..n-1: every thread takes
-  // ceil(n / NT) consecutive positions (one when n <= NT), wave scan of the thread sums by shuffles,
-  // then the wave totals.
+  // number of sources merged into i).  Exclusive scans of both over i = 0..n-1, in the two halves of a word (both totals
+  // are at most n <= 1024): every thread takes ceil(n / NT) consecutive positions (one when n <= NT), wave scan of the
+  // thread sums by shuffles, then the wave totals.
   {
     const int C = (n + NT - 1) / NT;
     const int lane = tid & 63, w = tid >> 6;
-    auto keep_of = [&](int i) { return (i & 1) ? 1 : (kept[i >> 1] >= 0 ? 0 : 1); };
-    auto ent_of = [&](int i, int k) { return k ? 1 + ((i & 1) ? cnt[i >> 1] : 0) : 0; };
-    int k_sum = 0, e_sum = 0;
+    auto counts_of = [&](int i) {   // entries << 16 | keep
+      if (i & 1) return (1 + cnt[i >> 1]) << 16 | 1;
+      return kept[i >> 1] >= 0 ? 0 : 1 << 16 | 1;
+    };
+    int sum = 0;
     for (int c = 0; c < C; ++c) {
       const int i = tid * C + c;
-      if (i < n) {
-        const int k = keep_of(i);
-        k_sum += k;
-        e_sum += ent_of(i, k);
-      }
+      if (i < n) sum += counts_of(i);
     }
-    int sk = k_sum, se = e_sum;
+    int scan = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const int tk = __shfl_up(sk, o, kWave), te = __shfl_up(se, o, kWave);
-      if (lane >= o) { sk += tk; se += te; }
+      const int t = __shfl_up(scan, o, kWave);
+      if (lane >= o) scan += t;
     }
-    if (lane == 63) { wave_tot[w] = sk; wave_tot[16 + w] = se; }
+    if (lane == 63) wave_tot[w] = scan;
     __syncthreads();
-    int pk = sk - k_sum, pe = se - e_sum;
-    for (int j = 0; j < w; ++j) { pk += wave_tot[j]; pe += wave_tot[16 + j]; }
+    int pos = scan - sum;
+    for (int j = 0; j < w; ++j) pos += wave_tot[j];
     for (int c = 0; c < C; ++c) {
       const int i = tid * C + c;
       if (i < n) {
-        const int k = keep_of(i), e = ent_of(i, k);
-        keep_pos[i] = pk;
-        ent_pos[i] = pe;
-        pk += k;
-        pe += e;
+        keep_pos[i] = pos & 0xffff;
+        ent_pos[i] = pos >> 16;
+        pos += counts_of(i);
       }
     }
   }
@@ -463,8 +471,8 @@ __device__ __forceinline__ void merge_plan_lists(
   for (int i = tid; i < n; i += NT) {
     const bool odd = i & 1;
     if (!odd && kept[i >> 1] >= 0) {
-      const int a = i >> 1, d = 2 * kept[a] + 1;
-      src_list[i0 + ent_pos[d] + 1 + slot[a]] = i0 + i;
+      const int k = kept[i >> 1], d = 2 * (k & 0xffff) + 1;
+      src_list[i0 + ent_pos[d] + 1 + (k >> 16)] = i0 + i;
     } else {
       const int e = i0 + ent_pos[i];
       row_ptr[o0 + keep_pos[i]] = e;
