@@ -27,6 +27,15 @@
 
 namespace otas {
 
+// At most n of this wave's loads still in flight.
+#define OTAS_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+// vmcnt(0) and lgkmcnt(0): this wave's loads have landed AND its LDS reads have returned.
+#define OTAS_WAIT_LOADS_AND_LDS() __builtin_amdgcn_s_waitcnt(7 << 4)
+// lgkmcnt(0) only (vmcnt, expcnt at their maxima).
+#define OTAS_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14))
+#define OTAS_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
+#define OTAS_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
+
 // Output element type: the residual epilogue writes the float residual stream, the others the
 // model's storage type.
 template <typename T, int EPI> struct OutType { typedef T type; };
@@ -41,6 +50,24 @@ __device__ inline float epilogue_value(float acc, float bias, const float* res, 
   return v;
 }
 
+// Tile order.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2, and inside
+// an XCD the ~32 resident workgroups are consecutive in that XCD's sequence.  Give XCD x the
+// sequence positions s = id / 8 of one contiguous band of tiles, and inside the band walk groups of
+// GM tile rows column by column, so that the tiles in flight on one XCD form a compact block that
+// shares activation and weight panels through that L2.
+__device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
+  constexpr int GM = 8;
+  const int nblk = tiles_m * tiles_n;
+  const int per = nblk >> 3;
+  int t = bid;
+  if (bid < per * 8) t = (bid & 7) * per + (bid >> 3);   // full bands; the remainder keeps its id
+  const int group = GM * tiles_n;
+  const int g = t / group, idx = t - g * group;
+  const int rows = min(GM, tiles_m - g * GM);            // the last group may be shorter
+  tile_n = idx / rows;
+  tile_m = g * GM + (idx - tile_n * rows);
+}
+
 // ------------------------------------------------------------------------------ true fp32 on the matrix cores
 // f32 models, and the fallback for bf16 shapes the bf16 MFMA kernels do not take (operands widened on the way in):
 // v_mfma_f32_16x16x4_f32, whose products and sums are fp32 (256 FLOP per clock and CU, 157 TFLOP/s on the chip; the
@@ -49,18 +76,23 @@ __device__ inline float epilogue_value(float acc, float bias, const float* res, 
 // Two kernels with the same arithmetic in the same order, so that a row's result does not depend on which one the
 // batch's row count picks: K is cut into four quarters (multiples of 32), each quarter is summed from zero in
 // ascending order, and the quarters are added as ((q0 + q1) + q2) + q3.
-//   gemm_f32_kernel        64 x 64 tile, eight waves of 32 x 32: four for each half of K, so that a CU with a single
-//                          workgroup has two waves per SIMD to cover LDS and barrier waits; operands through two LDS
-//                          stages of K step 32 per half.  The matrix pipe is busy 43 % of the time over a ViT-B pass of
-//                          1206 rows (75 TFLOP/s): a k-tile's fragments are waited for after its barrier, and 228 to
-//                          912 tiles do not fill whole rounds of 512.
+//   gemm_f32_dma_kernel    f32, K a multiple of 128.  64 x 64 tile, eight waves of 32 x 32: four for each half of K, so that
+//                          a CU with a single workgroup has two waves per SIMD.  Operands straight into LDS, the next
+//                          k-tile's fragments read behind this one's MFMAs.  With several tiles per CU the matrix pipe is
+//                          busy 93 % of the time (4616 x 768 x 3072: 123 TFLOP/s on 876 tiles, 3.4 a CU); what a pass of
+//                          1206 rows loses beyond that are the last tiles of 228 to 912 on 256 CUs.  A third stage (one
+//                          workgroup per CU) is slower (4616 x 2304 x 768 133 -> 157 us), bands of tiles per XCD change
+//                          nothing.
+//   gemm_f32_kernel        the same tile for any other K % 8 == 0 and for bf16 operands: staged through registers (columns past K
+//                          are zeroed there), the fragments of a k-tile waited for after its barrier.
 //   gemm_f32_small_kernel  32 x 32 tile, four waves, one quarter of K each, operands straight into registers, the four
 //                          sums added through LDS.  With few tiles a launch lasts as long as one wave's chain of
 //                          MFMAs (32 clocks per column of K); a quarter of K per wave makes that four times
 //                          shorter, at twice the operand bytes per FLOP.
-// Measured on MI355X against tiles of 4 x 4 FMAs per thread on the vector ALU, which these replace (us): 1206 x 768 x
-// 3072 205 -> 68, 1206 x 3072 x 768 90 -> 73, 402 x 192 x 768 51 -> 9, 402 x 576 x 192 16 -> 5.
-constexpr int kF32SmallTiles = 150;
+// Measured on MI355X (us; tiles of 4 x 4 FMAs per thread on the vector ALU, gemm_f32_kernel, gemm_f32_dma_kernel): 1206 x 768
+// x 3072 + residual 205, 68, 48; 1206 x 3072 x 768 + GELU 90, 73, 53; 1206 x 2304 x 768 -, 54, 40; 1206 x 768 x 768 + residual
+// -, 20.7, 16.2.  gemm_f32_small_kernel: 402 x 192 x 768 51 -> 9, 402 x 576 x 192 16 -> 5.
+constexpr int kF32SmallTiles = 512;
 __host__ __device__ static inline int f32_quarter(int K) { return ((K + 3) / 4 + 31) & ~31; }
 
 // Four consecutive outputs of row m from column n (N % 8 == 0: inside or outside as a whole).
@@ -188,6 +220,170 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(const T* __restrict__ A, 
   }
 }
 
+// The same tile and the same arithmetic for f32 operands whose K is a multiple of 128 (quarters of whole k-tiles: nothing to
+// zero).  Operand tiles go straight into LDS (see "direct-to-LDS kernels" below; rows of 32 floats are 128 bytes, so chunk
+// c of row r sits at c ^ ((r >> 1) & 7) as in the bf16 kernels), and a wave reads the fragments of k-tile t + 1 into a
+// second set of registers behind the MFMAs of k-tile t: after a barrier the MFMAs start at once, and nothing of a stage is
+// needed any more when its next tile is requested.  Both halves of K share the barrier.
+template <int EPI>
+__global__ __launch_bounds__(512, 4) void gemm_f32_dma_kernel(const float* __restrict__ A, const float* __restrict__ W,
+                                                              const float* __restrict__ bias, const float* res, float* Y,
+                                                              int64_t M, int N, int K) {
+  constexpr int BK = 32, TILE = 64 * BK, NS = 2;   // floats of an operand tile
+  extern __shared__ __attribute__((aligned(16))) float f32_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = wave >> 2, w4 = wave & 3, wm = w4 >> 1, wn = w4 & 1;
+  float* st_base = f32_lds + half * (NS * 2 * TILE);   // [NS][A 64 x 32 | W 64 x 32]
+  const int64_t m0 = (int64_t)blockIdx.y * 64;
+  const int n0 = blockIdx.x * 64;
+  const int qt = K / 128, KT = 2 * qt;   // k-tiles of a quarter and of a half
+  // wave w4 loads rows 16 w4 .. of both operand tiles, 8 rows of 128 bytes per instruction
+  uint32_t a_off[2], w_off[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = w4 * 16 + j * 8 + (lane >> 3);
+    const int c = (lane & 7) ^ ((row >> 1) & 7);
+    const int64_t a_last = M - 1 - m0;   // rows past the end repeat the last row
+    const int w_last = N - 1 - n0;
+    const uint32_t ra = (uint32_t)(row < a_last ? row : a_last), rw = (uint32_t)(row < w_last ? row : w_last);
+    a_off[j] = (ra * (uint32_t)K + (uint32_t)c * 4u) * (uint32_t)sizeof(float);
+    w_off[j] = (rw * (uint32_t)K + (uint32_t)c * 4u) * (uint32_t)sizeof(float);
+  }
+  const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K + (size_t)half * KT * BK);
+  const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K + (size_t)half * KT * BK);
+  auto dma_one = [&](int kt, int st, int d) {   // d = 0, 1: A rows; 2, 3: W rows
+    const size_t kb = (size_t)kt * BK * sizeof(float);
+    const int j = d & 1;
+    asm volatile("" : "+v"(d < 2 ? a_off[j] : w_off[j]));   // as in gemm_mfma256w8_kernel
+    if (d < 2)
+      __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
+                                       OTAS_LPTR(st_base + st * 2 * TILE + (w4 * 16 + j * 8) * BK), 16, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[j]),
+                                       OTAS_LPTR(st_base + st * 2 * TILE + TILE + (w4 * 16 + j * 8) * BK), 16, 0, 0);
+  };
+  floatx4 acc[2][2], first[2][2];   // [row block][column block] of 16 x 16: the quarter being summed, the half's first one
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = first[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  floatx4 fa[2][2][2], fw[2][2][2];   // [k-tile & 1][block][16-column half of the k-tile]
+  const int sw = (fr >> 1) & 7;
+  auto read_frag = [&](int buf, int st, int x) {   // x = 0 .. 7: in the order the MFMAs need them
+    const int g = x >> 2, i = x & 1;
+    const float* p = st_base + st * 2 * TILE + (((g << 2) + fk) ^ sw) * 4 + fr * BK;
+    if (x & 2) fa[buf][i][g] = *reinterpret_cast<const floatx4*>(p + (wm * 32 + 16 * i) * BK);
+    else fw[buf][i][g] = *reinterpret_cast<const floatx4*>(p + TILE + (wn * 32 + 16 * i) * BK);
+  };
+  // What this wave finishes: rows wm * 32 + 16 half .. of the tile, two blocks of columns.
+  const int orow = wm * 32 + 16 * half + fr, ocol = wn * 32 + 4 * fk;
+  const int64_t m_out = m0 + orow;
+  floatx4 res_v[2];
+  auto step = [&](int buf, int kt, auto load, auto next) {   // buf = kt & 1, which is k-tile kt's stage too
+    constexpr bool LOAD = decltype(load)::value, NEXT = decltype(next)::value;
+    if constexpr (!NEXT && EPI == EPI_RESIDUAL) {   // the residual rows travel under the last k-tile
+      const float* p = res + (size_t)(m_out < M ? m_out : M - 1) * N;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) res_v[j] = *reinterpret_cast<const floatx4*>(p + (n0 + ocol + 16 * j < N ? n0 + ocol + 16 * j : 0));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[i >> 1][i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[buf][i & 1][g][u], fa[buf][i >> 1][g][u],
+                                                                    acc[i >> 1][i & 1], 0, 0, 0);
+          const int t = g * 16 + u * 4 + i;
+          if constexpr (LOAD) { if (t % 2 == 0 && t < 8) dma_one(kt + 2, buf, t / 2); }
+          if constexpr (NEXT) { if (t >= 8 && t < 16) read_frag(buf ^ 1, buf ^ 1, t - 8); }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    if (kt + 1 == qt) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        first[i >> 1][i & 1] = acc[i >> 1][i & 1];
+        acc[i >> 1][i & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  };
+  // Before k-tile t's barrier a wave has its fragments of t in registers (so its stage may be written again) and its loads
+  // of k-tile t + 1 have landed.
+  auto sync = [&] {
+    OTAS_WAIT_LOADS_AND_LDS();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+#pragma unroll
+  for (int d = 0; d < 4; ++d) dma_one(0, 0, d);
+#pragma unroll
+  for (int d = 0; d < 4; ++d) dma_one(1, 1, d);   // KT >= 2
+  OTAS_VMCNT(4);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int x = 0; x < 8; ++x) read_frag(0, 0, x);
+  int kt = 0;
+  for (; kt < KT - 2; kt += 2) {
+    sync();
+    step(0, kt, std::true_type(), std::true_type());
+    sync();
+    step(1, kt + 1, std::true_type(), std::true_type());
+  }
+  sync();
+  step(0, KT - 2, std::false_type(), std::true_type());
+  sync();
+  step(1, KT - 1, std::false_type(), std::false_type());
+  // Each half finishes one row block of 16 of every wave's two: the first half's waves send the sum of their two quarters
+  // of the second block, the second half's both of theirs of the first (the order of additions is ((q0 + q1) + q2) + q3).
+  constexpr int LDX = 64 + 4;
+  float* x01 = f32_lds;                    // [wm][16][LDX]
+  float* x2 = f32_lds + 32 * LDX;
+  float* x3 = f32_lds + 64 * LDX;
+  const int xr = (wm * 16 + fr) * LDX + ocol;
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();            // every wave has its last fragments: the stages may be overwritten
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (half) {
+      *reinterpret_cast<floatx4*>(x2 + xr + 16 * j) = first[0][j];
+      *reinterpret_cast<floatx4*>(x3 + xr + 16 * j) = acc[0][j];
+    } else {
+      *reinterpret_cast<floatx4*>(x01 + xr + 16 * j) = first[1][j] + acc[1][j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    floatx4 v;
+    if (half) {
+      v = *reinterpret_cast<const floatx4*>(x01 + xr + 16 * j);
+      v += first[1][j];
+      v += acc[1][j];
+    } else {
+      v = first[0][j] + acc[0][j];
+      v += *reinterpret_cast<const floatx4*>(x2 + xr + 16 * j);
+      v += *reinterpret_cast<const floatx4*>(x3 + xr + 16 * j);
+    }
+    const int n = n0 + ocol + 16 * j;
+    if (m_out < M && n < N) {   // N % 8 == 0: four columns are inside or outside as a whole
+      const floatx4 b = *reinterpret_cast<const floatx4*>(bias + n);
+      floatx4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        o[e] = v[e] + b[e];
+        if (EPI == EPI_GELU) o[e] = gelu_exact(o[e]);
+        if (EPI == EPI_RESIDUAL) o[e] += res_v[j][e];
+      }
+      *reinterpret_cast<floatx4*>(Y + (size_t)m_out * N + n) = o;
+    }
+  }
+}
+constexpr size_t kF32DmaLds = sizeof(float) * 2 * 2 * 2 * 64 * 32;   // [K half][stage][operand][64][32]
+
 template <typename T, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const T* __restrict__ A, const T* __restrict__ W,
                                                              const T* __restrict__ bias, const float* res,
@@ -277,13 +473,28 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const T* __restrict
 template <typename T>
 static hipError_t linear_f32(const void* x, const void* w, const void* bias, const float* res, void* y,
                              int64_t M, int N, int K, int epi, hipStream_t s) {
-  // Fewer than 256 tiles of 64 x 64 leave SIMDs without a wave; the small tiles then finish first as long as their
-  // own number (four times as many, a quarter of the MFMAs per wave) does not pile up.  Measured (us, small against
-  // large): 84 tiles of K = 3072 49 / 66, 156 tiles 73 / 68; 156 tiles of K = 768 21.7 / 20.9.
-  const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-  const bool small = tiles < kF32SmallTiles;
+  // Up to two workgroups per CU the small tiles finish first, a third round of them is slower than the large tiles' one.
+  // Measured (us, small against gemm_f32_dma_kernel): K = 768 240 small tiles 8.9 / 15.9, 312 15.6 / 16.2, 504 15.4 / 16.1,
+  // 528 21.3 / 16.1; K = 3072 240 small tiles 25.5 / 51.8, 312 49.0 / 52.2, 528 71.5 / 52.6.
+  const bool small = ((M + 31) / 32) * ((N + 31) / 32) <= kF32SmallTiles;
   const int b = small ? 32 : 64;
   dim3 grid((N + b - 1) / b, (unsigned)((M + b - 1) / b)), block(small ? 256 : 512);
+  if constexpr (std::is_same<T, float>::value) {
+    if (!small && K % 128 == 0) {
+#define OTAS_GEMM(E)                                                                                        \
+  do {                                                                                                      \
+    auto kern = gemm_f32_dma_kernel<E>;                                                                     \
+    hipError_t e = set_max_dynamic_lds((const void*)kern, (int)kF32DmaLds);                                 \
+    if (e != hipSuccess) return e;                                                                          \
+    kern<<<grid, block, kF32DmaLds, s>>>((const float*)x, (const float*)w, (const float*)bias, res, (float*)y, M, N, K); \
+  } while (0)
+      if (epi == EPI_NONE) OTAS_GEMM(EPI_NONE);
+      else if (epi == EPI_GELU) OTAS_GEMM(EPI_GELU);
+      else OTAS_GEMM(EPI_RESIDUAL);
+#undef OTAS_GEMM
+      return hipGetLastError();
+    }
+  }
 #define OTAS_GEMM(E)                                                                                        \
   do {                                                                                                      \
     auto kern = small ? gemm_f32_small_kernel<T, E> : gemm_f32_kernel<T, E>;                               \
@@ -474,24 +685,6 @@ __device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage,
 // lane then holds, for one output row m, runs of 4 consecutive output columns n, which makes the
 // epilogue's loads and stores 8- or 16-byte vectors along the row.
 
-// Tile order.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2, and inside
-// an XCD the ~32 resident workgroups are consecutive in that XCD's sequence.  Give XCD x the
-// sequence positions s = id / 8 of one contiguous band of tiles, and inside the band walk groups of
-// GM tile rows column by column, so that the tiles in flight on one XCD form a compact block that
-// shares activation and weight panels through that L2.
-__device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
-  constexpr int GM = 8;
-  const int nblk = tiles_m * tiles_n;
-  const int per = nblk >> 3;
-  int t = bid;
-  if (bid < per * 8) t = (bid & 7) * per + (bid >> 3);   // full bands; the remainder keeps its id
-  const int group = GM * tiles_n;
-  const int g = t / group, idx = t - g * group;
-  const int rows = min(GM, tiles_m - g * GM);            // the last group may be shorter
-  tile_n = idx / rows;
-  tile_m = g * GM + (idx - tile_n * rows);
-}
-
 // ------------------------------------------------------------------------------ direct-to-LDS kernels
 // Operand tiles go from global memory straight into LDS (global_load_lds_dwordx4: 16 bytes per lane,
 // each wave instruction fills 1 KB of consecutive LDS; no staging registers, no ds_write) through a
@@ -504,13 +697,6 @@ __device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& til
 // rows of one chunk column fall on 16 different (row mod 4, chunk position) pairs, i.e. on all 64
 // banks once.  Lane i of a DMA instruction writes LDS row base + i/4, chunk position i%4, so it must
 // fetch logical chunk (i%4) ^ ((row >> 2) & 3) of that row.
-#define OTAS_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
-// vmcnt(0) and lgkmcnt(0): this wave's loads have landed AND its LDS reads have returned.
-#define OTAS_WAIT_LOADS_AND_LDS() __builtin_amdgcn_s_waitcnt(7 << 4)
-// lgkmcnt(0) only (vmcnt, expcnt at their maxima).
-#define OTAS_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14))
-#define OTAS_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
-#define OTAS_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 
 // The list phases of the merge plan inside a GEMM launch (PLAN variants of the kernels below): the launch's first

@@ -117,3 +117,29 @@ def test_fp32_attention_keys_without_weight_and_infinite_values(lib, H):
     x[n - 1, 2 * D + 3] = float("inf")
     check(x, one, 0)
     ctx.close()
+
+
+@pytest.mark.parametrize("N,K", [(8, 8), (8, 128), (72, 128), (136, 256), (200, 384), (768, 640), (64, 3072)])
+def test_fp32_gemm_large_tiles_every_epilogue(lib, N, K):
+    """M just past what the small tiles take (more than 512 tiles of 32 x 32): one to 24 k-tiles a quarter, a ragged last
+    tile in both directions, no epilogue / GELU / residual, against float64 and, bit for bit, the small tiles' rows."""
+    import torch
+    ctx, dt = _context(lib, 64, 1, "f32")
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    M = 32 * (512 // ((N + 31) // 32) + 1) + 7
+    x, w = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
+    b, res = torch.randn(N, generator=g, device="cuda"), torch.randn((M, N), generator=g, device="cuda")
+    xd, wd = x.double(), w.double()
+    lin = xd @ wd.T + b.double()
+    # at most K roundings of 2^-24 on terms of total size sum |x w|; GELU's slope is below 1.13 and its own error a few units
+    size = xd.abs() @ wd.abs().T + b.double().abs()
+    for epi, ref, bound in ((0, lin, (K + 8) * 2.0 ** -24 * size),
+                            (1, torch.nn.functional.gelu(lin), 1.13 * (K + 16) * 2.0 ** -24 * size),
+                            (2, lin + res.double(), (K + 8) * 2.0 ** -24 * (size + res.double().abs()))):
+        out = {}
+        for m in (33, M):
+            out[m] = torch.full((m, N), float("nan"), device="cuda")
+            ctx.otas_linear_kernel(1, x[:m].contiguous(), w, b, res[:m].contiguous() if epi == 2 else None, m, N, K, epi, out[m])
+        assert bool(((out[M].double() - ref).abs() <= bound).all()), epi
+        assert torch.equal(out[33], out[M][:33]), epi
+    ctx.close()
