@@ -152,10 +152,11 @@ otas_status upload_plan(otas_ctx* c, const std::vector<int32_t>& host) {
 }
 
 struct WorkspaceLayout {
-  size_t xa, xb, h, qkv, hid, part, metric, sizes_a, sizes_b, src_list, row_ptr, total;
-  // columns per token row; where the two share a buffer, the same, and `metric` is room beside it for the merge plan's
-  // metric rows of queries too long for its LDS (else those use the hidden rows; the projection is still read beside them)
-  size_t qkv_cols, hid_cols;
+  size_t xa, xb, h, qkv, hid, spare, part, sizes_a, sizes_b, src_list, row_ptr, total;
+  // columns per token row, the same where the two share a buffer.  spare: room that is free while the projection is still
+  // needed (the hidden rows, or what is left beside a shared buffer): the metric rows of queries too long for the merge
+  // plan's LDS, an f32 model's selection
+  size_t qkv_cols, hid_cols, spare_cols;
   int part_factor;   // float rows of the split-K buffer per token row
 };
 
@@ -180,11 +181,13 @@ WorkspaceLayout forward_layout(const otas_model_desc& d, int64_t T0) {
   w.hid_cols = (size_t)d.F;
   w.qkv = take(rows * w.qkv_cols * es);
   w.hid = take(rows * w.hid_cols * es);
-  w.metric = 0;
+  w.spare = w.hid;
+  w.spare_cols = w.hid_cols;
   if (share) {   // the size stays that of two buffers: what a workspace serves must not shrink as T0 falls below the limit
     w.qkv_cols = w.hid_cols = (size_t)std::max(3 * d.D, d.F);
     w.hid = w.qkv;
-    w.metric = w.qkv + rows * w.qkv_cols * es;   // min(3 D, F) columns a row are left
+    w.spare = w.qkv + rows * w.qkv_cols * es;
+    w.spare_cols = (size_t)std::min(3 * d.D, d.F);
   }
   w.part_factor = part_rows_factor(rows);
   w.part = take(d.dtype == OTAS_BF16 ? w.part_factor * rows * d.D * sizeof(float) : 0);   // split-K partial products
@@ -786,7 +789,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       char* hbuf = ws + w.h + (size_t)ln.row0 * D * es;
       char* qkv = ws + w.qkv + (size_t)ln.row0 * w.qkv_cols * es;   // [T][3 D] until the projection has run
       char* hid = ws + w.hid + (size_t)ln.row0 * w.hid_cols * es;   // [T][F] after it, possibly the same rows
-      float* metric_rows = (float*)(w.metric ? ws + w.metric + merge_plan_rows_bytes(ln.row0, dh) : hid);
+      char* spare = ws + w.spare + (size_t)ln.row0 * w.spare_cols * es;   // free until FC1, also where the two share rows
       int32_t* sizes_buf[2] = {(int32_t*)(ws + w.sizes_a) + ln.row0, (int32_t*)(ws + w.sizes_b) + ln.row0};
       int32_t* src_list = (int32_t*)(ws + w.src_list) + ln.row0;
       int32_t* row_ptr = (int32_t*)(ws + w.row_ptr) + ln.row0 + g;   // one end entry per lane
@@ -802,23 +805,24 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       // Where the projection's launch below has workgroup slots to spare, the fused launch runs only the plan's
       // selection (the long part: keys, similarities, best matches) and the lists, which need nothing else, are
       // written by extra workgroups of the projection's launch: the plan's serial chain beside attention gets
-      // shorter by a quarter, and the selection can be shared by several workgroups per query.  Its result waits in the
-      // split-K partial buffer, idle between two MLPs: two float rows of D >= 64 per token row at least, and it takes
-      // 2 nb <= 32 entries per token row.
+      // shorter by a quarter, and the selection can be shared by several workgroups per query.  Its result, 2 nb <= 32 entries
+      // per token row, waits in the split-K partial buffer, idle between two MLPs: two float rows of D >= 64 per token row
+      // at least; an f32 model, which has none, keeps it where the hidden rows will be.
       FusedPlan how = {0, 0};
       bool tail = false;
-      if (ln.any_merge[l] && plan_inline) {
-        tail = linear_plan_tail_fits(T, D, D, Bg);
+      // (an f32 model under per-launch timing keeps the plan's launch and its record: same arithmetic, same bits)
+      if (ln.any_merge[l] && plan_inline && !(dt == OTAS_F32 && c->timing)) {
+        tail = linear_plan_tail_fits(dt, T, D, D, Bg);
         how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, tail);
-        tail = tail && how.na > 0;
+        tail = tail && how.na > 0 && (dt != OTAS_F32 || 8 * how.nb <= (int)(w.spare_cols * es));
         if (!tail) how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, false);
       }
       const bool fuse = how.na > 0;
-      float* sel_best = (float*)(ws + w.part) + (size_t)w.part_factor * ln.row0 * D;
+      float* sel_best = dt == OTAS_F32 ? (float*)spare : (float*)(ws + w.part) + (size_t)w.part_factor * ln.row0 * D;
       int32_t* sel_bcol = (int32_t*)(sel_best + (size_t)how.nb * T);
       if (fuse) {
         OTAS_LAUNCH_ON(K_ATTN, s,
-                       launch_attention_plan(qkv, ln.sizes_now, off_l, off_n, d_reff, d_tr, Bg, ln.max_n[l], D, H,
+                       launch_attention_plan(dt, qkv, ln.sizes_now, off_l, off_n, d_reff, d_tr, Bg, ln.max_n[l], D, H,
                                              size_bias, n_lead, hbuf, src_list, row_ptr,
                                              trace ? trace_src : nullptr, trace ? trace_dst : nullptr,
                                              tail ? sel_best : nullptr, tail ? sel_bcol : nullptr, T, s));
@@ -834,7 +838,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
           OTAS_LAUNCH_ON(K_PLAN, ps,
                          launch_merge_plan(dt, qkv, 3 * (int64_t)D, D, H, dh, off_l, off_n, d_reff, d_tr, Bg,
                                            ln.max_n[l], n_lead, src_list, row_ptr, trace ? trace_src : nullptr,
-                                           trace ? trace_dst : nullptr, metric_rows, ps));
+                                           trace ? trace_dst : nullptr, (float*)spare, ps));
           if (!plan_inline) OTAS_HIP(hipEventRecord(hw.ev_join, hw.side));
         }
         OTAS_LAUNCH_ON(K_ATTN, s,
@@ -846,7 +850,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       if (tail) {
         const PlanTail pt{off_l, off_n, d_reff, d_tr, src_list, row_ptr, trace ? trace_src : nullptr,
                           trace ? trace_dst : nullptr, sel_best, sel_bcol, T, how.nb, Bg};
-        OTAS_LAUNCH_ON(K_PROJ, s, launch_linear_plan_tail(hbuf, wl.w_proj, wl.b_proj, (const float*)ln.x_cur, x_attn, T,
+        OTAS_LAUNCH_ON(K_PROJ, s, launch_linear_plan_tail(dt, hbuf, wl.w_proj, wl.b_proj, (const float*)ln.x_cur, x_attn, T,
                                                           D, D, pt, ln.max_n[l], s));
       } else {
         OTAS_LAUNCH_ON(K_PROJ, s, launch_linear(dt, hbuf, wl.w_proj, wl.b_proj, (const float*)ln.x_cur, x_attn, T, D,

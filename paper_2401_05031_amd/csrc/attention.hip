@@ -28,20 +28,17 @@ namespace otas {
 // Measured on MI355X against one wave per query row on the vector ALU (us): 6 x 201 tokens, 12 heads of 64
 // 119 -> 21.6; 2 x 201 tokens, 3 heads 31 -> 12.
 template <typename T, int DT>
-__global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict__ qkv,
-                                                            const int32_t* __restrict__ sizes,
-                                                            const int32_t* __restrict__ off, int D, int H,
-                                                            float scale, T* __restrict__ o) {
+__device__ __forceinline__ void attention_f32_body(const T* __restrict__ qkv, const int32_t* __restrict__ sizes,
+                                                   const int32_t* __restrict__ off, int D, int H, float scale,
+                                                   T* __restrict__ o, const int q, const int h, const int xblk, float* lds) {
   constexpr int NG = 4 * DT;             // groups of 8 columns of a head, zero-filled past its width
   constexpr int LDO = 32 * DT + 4;
-  extern __shared__ __attribute__((aligned(16))) float lds[];
   float* ml = lds;                       // [4][2][32] row maximum and sum of every wave
   float* osh = lds + 256;                // [4][32][LDO]
   const int dh = D / H;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, fr = lane & 31, fk = lane >> 5;
-  const int q = blockIdx.z, h = blockIdx.y;
   const int base = off[q], n = off[q + 1] - base;
-  const int row0 = blockIdx.x * 32;
+  const int row0 = xblk * 32;
   if (row0 >= n) return;                 // the whole workgroup
   const size_t ld = (size_t)3 * D;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -154,12 +151,46 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict_
   }
 }
 
+template <typename T, int DT>
+__global__ __launch_bounds__(256) void attention_f32_kernel(const T* __restrict__ qkv, const int32_t* __restrict__ sizes,
+                                                               const int32_t* __restrict__ off, int D, int H, float scale,
+                                                               T* __restrict__ o) {
+  extern __shared__ __attribute__((aligned(16))) float f32_smem[];
+  attention_f32_body<T, DT>(qkv, sizes, off, D, H, scale, o, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x, f32_smem);
+}
+
+// Together with the selection of the layer's merge plan, as attention_plan_kernel below does for bf16 models: the first
+// B na nb workgroups select, the others are attention's, H heads and xblks row blocks a query.  The lists are written by
+// the projection's launch.  Two queries of 201 tokens, 3 heads of 64 (MI355X): plan 17.1 and attention 11.9 us one after
+// the other, 13.5 in one launch and 2 us more for the projection; the two-layer pass 126 -> 100 us.
+template <int DT>
+__global__ __launch_bounds__(256) void attention_select_f32_kernel(
+    const float* __restrict__ qkv, const int32_t* __restrict__ sizes, const int32_t* __restrict__ off, int D, int H,
+    float scale, float* __restrict__ o, int B, int xblks, const int32_t* __restrict__ out_off,
+    const int32_t* __restrict__ reff_arr, const int32_t* __restrict__ troff, int n_lead, float* __restrict__ sel_best,
+    int32_t* __restrict__ sel_bcol, int64_t sel_stride, int na, int nb) {
+  extern __shared__ __attribute__((aligned(16))) float f32_smem[];
+  int id = (int)blockIdx.x;
+  if (id < B * na * nb) {   // workgroup-uniform
+    const int q = id / (na * nb), pp = id % (na * nb);
+    merge_plan_select<float, true, true, 256>(qkv, 3 * (int64_t)D, D, H, D / H, plan_query(off, out_off, reff_arr, troff, q),
+                                              n_lead, nullptr, f32_smem, sel_best, sel_bcol, (int)threadIdx.x,
+                                              PlanPart{pp % na, na, pp / na, nb, sel_stride});
+    return;
+  }
+  id -= B * na * nb;
+  const int xblk = id % xblks;
+  id /= xblks;
+  attention_f32_body<float, DT>(qkv, sizes, off, D, H, scale, o, id / H, id % H, xblk, f32_smem);
+}
+static size_t attention_f32_lds(int dh) { return sizeof(float) * (256 + 4 * 32 * (32 * (size_t)((dh + 31) / 32) + 4)); }
+
 template <typename T>
 static hipError_t attention_f32(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int D,
                                 int H, float scale, void* o, hipStream_t s) {
   const int dt = (D / H + 31) / 32;
   dim3 grid((max_n + 31) / 32, H, B), block(256);
-  const size_t lds = sizeof(float) * (256 + 4 * 32 * (32 * (size_t)dt + 4));
+  const size_t lds = attention_f32_lds(D / H);
 #define OTAS_ATTN(N)                                                                                              \
   do {                                                                                                            \
     auto kern = attention_f32_kernel<T, N>;                                                                       \
@@ -486,7 +517,15 @@ static size_t fused_attention_lds(int max_n, size_t* unit) {
 // How launch_attention_plan runs this case (pure host; not at all: na = 0).  Below two tokens there is nothing to select.
 FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lists_elsewhere) {
   FusedPlan how = {0, 0};
-  if (dtype == 0 || B <= 0 || H <= 0 || D != 64 * H || max_n < 2 || max_n > kPlanThreads) return how;
+  if (B <= 0 || H <= 0 || D <= 0 || max_n < 2 || max_n > kPlanThreads) return how;
+  if (dtype == 0) {   // f32 models: the selection only
+    const int dh = D / H;
+    if (!lists_elsewhere || D % H != 0 || dh % 4 != 0 || dh > 128) return how;
+    const PlanParts p = plan_parts(B, max_n, dh, attention_f32_lds(dh));
+    if (plan_select_lds_bytes(max_n, dh, p.a, p.b) > 160 * 1024) return how;
+    return FusedPlan{p.a, p.b};
+  }
+  if (D != 64 * H) return how;
   const int G = (max_n > 128 && max_n <= 256) ? 1 : 2;   // heads per workgroup: 8 waves / (8 or 4 waves per head)
   if (H % G != 0) return how;
   size_t unit;
@@ -504,15 +543,35 @@ FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lis
 // Attention of a layer together with the layer's merge plan (bf16, head width 64, H a multiple of the heads a
 // workgroup takes); hipErrorInvalidValue for what attention_plan_how does not take -- the caller then launches
 // the two kernels one after the other.
-hipError_t launch_attention_plan(const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
+hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
                                  const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int D, int H,
                                  bool size_bias, int n_lead, void* o, int32_t* src_list, int32_t* row_ptr,
                                  int32_t* trace_src, int32_t* trace_dst, float* sel_best, int32_t* sel_bcol,
                                  int64_t sel_stride, hipStream_t s) {
   if (B <= 0 || max_n <= 0) return hipSuccess;
   if ((sel_best == nullptr) != (sel_bcol == nullptr)) return hipErrorInvalidValue;
-  const FusedPlan how = attention_plan_how(1, B, max_n, D, H, sel_best != nullptr);
+  const FusedPlan how = attention_plan_how(dtype, B, max_n, D, H, sel_best != nullptr);
   if (how.na == 0) return hipErrorInvalidValue;
+  if (dtype == 0) {
+    const int dh = D / H, xblks = (max_n + 31) / 32;
+    const size_t sel_lds = plan_select_lds_bytes(max_n, dh, how.na, how.nb), attn_lds = attention_f32_lds(dh);
+    const dim3 grid((unsigned)(B * how.na * how.nb + xblks * H * B));
+#define OTAS_FUSED(N)                                                                                             \
+  do {                                                                                                            \
+    auto kern = attention_select_f32_kernel<N>;                                                                   \
+    hipError_t e = set_max_dynamic_lds((const void*)kern, 160 * 1024);                                            \
+    if (e != hipSuccess) return e;                                                                                \
+    kern<<<grid, dim3(256), attn_lds > sel_lds ? attn_lds : sel_lds, s>>>(                                        \
+        (const float*)qkv, size_bias ? sizes : nullptr, d_off, D, H, 1.0f / sqrtf((float)dh), (float*)o, B, xblks, \
+        d_out_off, d_reff, d_troff, n_lead, sel_best, sel_bcol, sel_stride, how.na, how.nb);                      \
+  } while (0)
+    if (dh <= 32) OTAS_FUSED(1);
+    else if (dh <= 64) OTAS_FUSED(2);
+    else if (dh <= 96) OTAS_FUSED(3);
+    else OTAS_FUSED(4);
+#undef OTAS_FUSED
+    return hipGetLastError();
+  }
   const size_t plan_lds = sel_best ? plan_select_lds_bytes(max_n, 64, how.na, how.nb) : merge_plan_lds_bytes(max_n, 64);
   const float scale = 1.0f / sqrtf(64.0f);
   const int32_t* sz = size_bias ? sizes : nullptr;

@@ -68,6 +68,33 @@ __device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& til
   tile_m = g * GM + (idx - tile_n * rows);
 }
 
+// The list phases of the merge plan inside a GEMM launch (PLAN variants of the kernels below): the launch's first
+// pt.B workgroups each write the lists of one query and leave; the others compute tiles as if those did not exist.
+// The attention output projection runs this way: the lists depend on the selection made beside attention one
+// launch earlier, and the projection leaves CUs idle at the batch sizes this matters for.
+template <int NT>
+__device__ __forceinline__ void plan_tail_run(const PlanTail& pt, unsigned char* smem, int q, int tid) {
+  merge_plan_lists<NT, true>(reinterpret_cast<float*>(smem), pt.best, pt.bcol, pt.nb, pt.stride,
+                             plan_query(pt.in_off, pt.out_off, pt.reff, pt.troff, q), pt.src_list, pt.row_ptr,
+                             pt.trace_src, pt.trace_dst, tid);
+}
+// The same for a grid of tile columns x tile rows: the workgroups of the first rows of the grid, as many as B takes, are the
+// plan's (those past B have nothing to do).  True: this workgroup is done; else tile_row is its row of tiles.
+template <int NT, bool PLAN>
+__device__ __forceinline__ bool plan_tail_or_tile_row(const PlanTail& pt, unsigned char* smem, int& tile_row) {
+  tile_row = (int)blockIdx.y;
+  if constexpr (PLAN) {
+    const int rows = (pt.B + (int)gridDim.x - 1) / (int)gridDim.x;
+    if (tile_row < rows) {
+      const int q = tile_row * (int)gridDim.x + (int)blockIdx.x;
+      if (q < pt.B) plan_tail_run<NT>(pt, smem, q, (int)threadIdx.x);
+      return true;
+    }
+    tile_row -= rows;
+  }
+  return false;
+}
+
 // ------------------------------------------------------------------------------ true fp32 on the matrix cores
 // f32 models, and the fallback for bf16 shapes the bf16 MFMA kernels do not take (operands widened on the way in):
 // v_mfma_f32_16x16x4_f32, whose products and sums are fp32 (256 FLOP per clock and CU, 157 TFLOP/s on the chip; the
@@ -225,17 +252,20 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(const T* __restrict__ A, 
 // c of row r sits at c ^ ((r >> 1) & 7) as in the bf16 kernels), and a wave reads the fragments of k-tile t + 1 into a
 // second set of registers behind the MFMAs of k-tile t: after a barrier the MFMAs start at once, and nothing of a stage is
 // needed any more when its next tile is requested.  Both halves of K share the barrier.
-template <int EPI>
-__global__ __launch_bounds__(512, 4) void gemm_f32_dma_kernel(const float* __restrict__ A, const float* __restrict__ W,
-                                                              const float* __restrict__ bias, const float* res, float* Y,
-                                                              int64_t M, int N, int K) {
+template <typename T, int EPI, bool PLAN = false>
+__global__ __launch_bounds__(512, 4) void gemm_f32_dma_kernel(const T* __restrict__ A, const T* __restrict__ W,
+                                                              const T* __restrict__ bias, const float* res, float* Y,
+                                                              int64_t M, int N, int K, PlanTail pt) {
+  static_assert(std::is_same<T, float>::value, "the operands go to LDS as they are");
   constexpr int BK = 32, TILE = 64 * BK, NS = 2;   // floats of an operand tile
   extern __shared__ __attribute__((aligned(16))) float f32_lds[];
   const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = wave >> 2, w4 = wave & 3, wm = w4 >> 1, wn = w4 & 1;
   float* st_base = f32_lds + half * (NS * 2 * TILE);   // [NS][A 64 x 32 | W 64 x 32]
-  const int64_t m0 = (int64_t)blockIdx.y * 64;
+  int tile_row;
+  if (plan_tail_or_tile_row<512, PLAN>(pt, reinterpret_cast<unsigned char*>(f32_lds), tile_row)) return;
+  const int64_t m0 = (int64_t)tile_row * 64;
   const int n0 = blockIdx.x * 64;
   const int qt = K / 128, KT = 2 * qt;   // k-tiles of a quarter and of a half
   // wave w4 loads rows 16 w4 .. of both operand tiles, 8 rows of 128 bytes per instruction
@@ -384,16 +414,19 @@ __global__ __launch_bounds__(512, 4) void gemm_f32_dma_kernel(const float* __res
 }
 constexpr size_t kF32DmaLds = sizeof(float) * 2 * 2 * 2 * 64 * 32;   // [K half][stage][operand][64][32]
 
-template <typename T, int EPI>
+template <typename T, int EPI, bool PLAN = false>
 __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const T* __restrict__ A, const T* __restrict__ W,
                                                              const T* __restrict__ bias, const float* res,
                                                              typename OutType<T, EPI>::type* Y, int64_t M, int N,
-                                                             int K) {
+                                                             int K, PlanTail pt) {
   constexpr int LD = 36, NS = 4;   // batches of 32 columns, NS - 1 of them requested ahead
   __shared__ __attribute__((aligned(16))) float part[4][32][LD];
+  static_assert(sizeof(part) >= kPlanListsLdsMax, "plan lists");
   const int tid = threadIdx.x, lane = tid & 63, fr = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: the loop below has scalar branches only
-  const int64_t m0 = (int64_t)blockIdx.y * 32;
+  int tile_row;
+  if (plan_tail_or_tile_row<256, PLAN>(pt, reinterpret_cast<unsigned char*>(part), tile_row)) return;
+  const int64_t m0 = (int64_t)tile_row * 32;
   const int n0 = blockIdx.x * 32;
   const int KQ = f32_quarter(K), k_beg = wave * KQ, k_end = min(K, k_beg + KQ);
   // rows past the end repeat the last one: their outputs are not stored
@@ -470,44 +503,45 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const T* __restrict
   f32_epilogue4<T, EPI>(v, bias, res, Y, m0 + r, n0 + c, M, N);
 }
 
-template <typename T>
-static hipError_t linear_f32(const void* x, const void* w, const void* bias, const float* res, void* y,
-                             int64_t M, int N, int K, int epi, hipStream_t s) {
+static bool f32_small_tiles(int64_t M, int N) {
   // Up to two workgroups per CU the small tiles finish first, a third round of them is slower than the large tiles' one.
   // Measured (us, small against gemm_f32_dma_kernel): K = 768 240 small tiles 8.9 / 15.9, 312 15.6 / 16.2, 504 15.4 / 16.1,
   // 528 21.3 / 16.1; K = 3072 240 small tiles 25.5 / 51.8, 312 49.0 / 52.2, 528 71.5 / 52.6.
-  const bool small = ((M + 31) / 32) * ((N + 31) / 32) <= kF32SmallTiles;
-  const int b = small ? 32 : 64;
-  dim3 grid((N + b - 1) / b, (unsigned)((M + b - 1) / b)), block(small ? 256 : 512);
-  if constexpr (std::is_same<T, float>::value) {
-    if (!small && K % 128 == 0) {
-#define OTAS_GEMM(E)                                                                                        \
+  return ((M + 31) / 32) * ((N + 31) / 32) <= kF32SmallTiles;
+}
+
+// pt: the launch's first workgroups also write the lists of pt->B queries (f32 operands and EPI_RESIDUAL only).
+template <typename T>
+static hipError_t linear_f32(const void* x, const void* w, const void* bias, const float* res, void* y,
+                             int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
+  constexpr bool F32 = std::is_same<T, float>::value;
+  const bool small = f32_small_tiles(M, N), dma = F32 && !small && K % 128 == 0;
+  if (pt && (!F32 || epi != EPI_RESIDUAL || !(small || dma))) return hipErrorInvalidValue;
+  const int b = small ? 32 : 64, cols = (N + b - 1) / b;
+  const dim3 grid(cols, (unsigned)((M + b - 1) / b + (pt ? (pt->B + cols - 1) / cols : 0)), 1), block(small ? 256 : 512);
+  const PlanTail tail = pt ? *pt : PlanTail{};
+#define OTAS_GEMM(LDS, KERN, E, ...)                                                                        \
   do {                                                                                                      \
-    auto kern = gemm_f32_dma_kernel<E>;                                                                     \
-    hipError_t e = set_max_dynamic_lds((const void*)kern, (int)kF32DmaLds);                                 \
+    auto kern = KERN;                                                                                       \
+    hipError_t e = LDS ? set_max_dynamic_lds((const void*)kern, (int)(LDS)) : hipSuccess;                   \
     if (e != hipSuccess) return e;                                                                          \
-    kern<<<grid, block, kF32DmaLds, s>>>((const float*)x, (const float*)w, (const float*)bias, res, (float*)y, M, N, K); \
+    kern<<<grid, block, LDS, s>>>((const T*)x, (const T*)w, (const T*)bias, res,                            \
+                                  (typename OutType<T, E>::type*)y, M, N, K, ##__VA_ARGS__);                \
   } while (0)
-      if (epi == EPI_NONE) OTAS_GEMM(EPI_NONE);
-      else if (epi == EPI_GELU) OTAS_GEMM(EPI_GELU);
-      else OTAS_GEMM(EPI_RESIDUAL);
-#undef OTAS_GEMM
-      return hipGetLastError();
-    }
+#define OTAS_GEMM_EPI(LDS, KERN, E, ...)                                              \
+  do {                                                                               \
+    if (E == EPI_NONE) OTAS_GEMM(LDS, (KERN<T, EPI_NONE>), EPI_NONE, ##__VA_ARGS__);  \
+    else if (E == EPI_GELU) OTAS_GEMM(LDS, (KERN<T, EPI_GELU>), EPI_GELU, ##__VA_ARGS__); \
+    else OTAS_GEMM(LDS, (KERN<T, EPI_RESIDUAL>), EPI_RESIDUAL, ##__VA_ARGS__);        \
+  } while (0)
+  if constexpr (F32) {
+    if (pt && small) { OTAS_GEMM(0, (gemm_f32_small_kernel<float, EPI_RESIDUAL, true>), EPI_RESIDUAL, tail); return hipGetLastError(); }
+    if (pt) { OTAS_GEMM(kF32DmaLds, (gemm_f32_dma_kernel<float, EPI_RESIDUAL, true>), EPI_RESIDUAL, tail); return hipGetLastError(); }
+    if (dma) { OTAS_GEMM_EPI(kF32DmaLds, gemm_f32_dma_kernel, epi, tail); return hipGetLastError(); }
   }
-#define OTAS_GEMM(E)                                                                                        \
-  do {                                                                                                      \
-    auto kern = small ? gemm_f32_small_kernel<T, E> : gemm_f32_kernel<T, E>;                               \
-    if (!small) {                                                                                          \
-      hipError_t e = set_max_dynamic_lds((const void*)kern, (int)kF32Lds);                                 \
-      if (e != hipSuccess) return e;                                                                        \
-    }                                                                                                       \
-    kern<<<grid, block, small ? 0 : kF32Lds, s>>>((const T*)x, (const T*)w, (const T*)bias, res,                             \
-                                (typename OutType<T, E>::type*)y, M, N, K);                                 \
-  } while (0)
-  if (epi == EPI_NONE) OTAS_GEMM(EPI_NONE);
-  else if (epi == EPI_GELU) OTAS_GEMM(EPI_GELU);
-  else OTAS_GEMM(EPI_RESIDUAL);
+  if (small) OTAS_GEMM_EPI(0, gemm_f32_small_kernel, epi, tail);
+  else OTAS_GEMM_EPI(kF32Lds, gemm_f32_kernel, epi);
+#undef OTAS_GEMM_EPI
 #undef OTAS_GEMM
   return hipGetLastError();
 }
@@ -699,16 +733,6 @@ __device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage,
 // fetch logical chunk (i%4) ^ ((row >> 2) & 3) of that row.
 
 
-// The list phases of the merge plan inside a GEMM launch (PLAN variants of the kernels below): the launch's first
-// pt.B workgroups each write the lists of one query and leave; the others compute tiles as if those did not exist.
-// The attention output projection runs this way: the lists depend on the selection made beside attention one
-// launch earlier, and the projection leaves CUs idle at the batch sizes this matters for.
-template <int NT>
-__device__ __forceinline__ void plan_tail_run(const PlanTail& pt, unsigned char* smem, int q, int tid) {
-  merge_plan_lists<NT, true>(reinterpret_cast<float*>(smem), pt.best, pt.bcol, pt.nb, pt.stride,
-                             plan_query(pt.in_off, pt.out_off, pt.reff, pt.troff, q), pt.src_list, pt.row_ptr,
-                             pt.trace_src, pt.trace_dst, tid);
-}
 #define OTAS_PLAN_TAIL_OR_TILE(NT)                          \
   int bid = (int)blockIdx.x;                                \
   if constexpr (PLAN) {                                     \
@@ -1528,7 +1552,12 @@ hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bi
 // Whether the projection's launch has workgroup slots to spare for B list workgroups: they take a slot each (a
 // launch's dynamic LDS is the same for all its workgroups), so beside a launch that fills its last round they would
 // cost a round of their own (measured: + 5 us on such launches, what the selection-only plan saves beside attention).
-bool linear_plan_tail_fits(int64_t M, int N, int K, int B) {
+bool linear_plan_tail_fits(int dtype, int64_t M, int N, int K, int B) {
+  if (dtype == 0 && M > 0 && B > 0) {
+    if (f32_small_tiles(M, N)) return true;   // at most two tiles per CU, room for eight
+    const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
+    return K % 128 == 0 && tiles % 512 != 0 && tiles % 512 + B <= 512;
+  }
   if (M <= 0 || B <= 0 || !(K % 32 == 0 && K >= 64 && N % 8 == 0)) return false;
   int bm = 128, bn = 128, slots = 768;
   switch (pick_mfma_kernel(M, N, K, EPI_RESIDUAL)) {
@@ -1543,11 +1572,12 @@ bool linear_plan_tail_fits(int64_t M, int N, int K, int B) {
   return tiles % slots + B <= slots && tiles % slots != 0;
 }
 
-hipError_t launch_linear_plan_tail(const void* x, const void* w, const void* bias, const float* res, void* y,
+hipError_t launch_linear_plan_tail(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,
                                    int64_t M, int N, int K, const PlanTail& tail, int max_n, hipStream_t s) {
-  if (M <= 0 || tail.B <= 0 || max_n > kPlanThreads || plan_lists_lds_bytes(max_n) > kPlanListsLdsMax ||
-      !(K % 32 == 0 && K >= 64 && N % 8 == 0))
+  if (M <= 0 || tail.B <= 0 || max_n > kPlanThreads || plan_lists_lds_bytes(max_n) > kPlanListsLdsMax)
     return hipErrorInvalidValue;
+  if (dtype == 0) return linear_f32<float>(x, w, bias, res, y, M, N, K, EPI_RESIDUAL, s, &tail);
+  if (!(K % 32 == 0 && K >= 64 && N % 8 == 0)) return hipErrorInvalidValue;
   return linear_mfma_kernel(pick_mfma_kernel(M, N, K, EPI_RESIDUAL), x, w, bias, res, y, M, N, K, EPI_RESIDUAL, s, &tail);
 }
 

@@ -109,8 +109,8 @@ hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
                             const int32_t* d_off, int B, int max_n, int D, int H, bool size_bias,
                             void* o, hipStream_t s);
 
-// Attention and the merge plan of one layer in a single launch (bf16 models of head width 64; the plan's metric is the
-// head mean of the keys in qkv).  Returns hipErrorInvalidValue, having launched nothing, for what attention_plan_how
+// Attention and the merge plan of one layer in a single launch (bf16 models of head width 64, and f32 models, whose launch
+// takes the selection only; the plan's metric is the head mean of the keys in qkv).  Returns hipErrorInvalidValue, having launched nothing, for what attention_plan_how
 // does not take.
 // With sel_best / sel_bcol (device, nb arrays of sel_stride entries, one per packed token row) the launch runs only the
 // plan's selection (every A token's best match), in na x nb workgroups per query, and leaves it there; the lists are then
@@ -118,7 +118,7 @@ hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
 // it runs the whole plan, one workgroup per query, whose metric rows must fit the LDS.
 struct FusedPlan { int na, nb; };   // na = 0: not taken
 FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lists_elsewhere);
-hipError_t launch_attention_plan(const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
+hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
                                  const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int D, int H,
                                  bool size_bias, int n_lead, void* o, int32_t* src_list, int32_t* row_ptr,
                                  int32_t* trace_src, int32_t* trace_dst, float* sel_best, int32_t* sel_bcol,
@@ -134,12 +134,12 @@ struct PlanTail {
   int nb;
   int B;                                            // queries = leading workgroups that run the lists
 };
-// y = x W^T + bias + res (bf16 operands, float residual in and out) as launch_linear with EPI_RESIDUAL, and in
+// y = x W^T + bias + res (operands of the model's type, float residual in and out) as launch_linear with EPI_RESIDUAL, and in
 // the same launch the list phases of the merge plan for tail.B queries of at most max_n tokens.
-// hipErrorInvalidValue, having launched nothing, when no MFMA kernel takes the shape.  linear_plan_tail_fits: whether
+// hipErrorInvalidValue, having launched nothing, when no kernel with such a form takes the shape.  linear_plan_tail_fits: whether
 // the launch's last round has B workgroup slots to spare (pure host); if not, the lists are better written elsewhere.
-bool linear_plan_tail_fits(int64_t M, int N, int K, int B);
-hipError_t launch_linear_plan_tail(const void* x, const void* w, const void* bias, const float* res, void* y,
+bool linear_plan_tail_fits(int dtype, int64_t M, int N, int K, int B);
+hipError_t launch_linear_plan_tail(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,
                                    int64_t M, int N, int K, const PlanTail& tail, int max_n, hipStream_t s);
 
 // The metric of token i is the mean over H heads of src[i * row_stride + col_off + h * dm + c]

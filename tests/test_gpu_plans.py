@@ -197,3 +197,24 @@ def test_merge_of_tokens_that_compare_with_none(lib, dtype, n):
                 _check_edges(n, r, *got["trace"][q][0], got["sizes"][q])
                 assert q == B // 2 or np.isfinite(got["x"][q]).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("D,H", [(192, 3), (200, 2)])
+def test_fp32_selection_beside_attention_equals_the_plan_kernel(lib, D, H):
+    """f32 models: a query alone runs its selection beside attention, in as many workgroups as its tokens have blocks, and
+    its lists beside the projection; in this batch, whose projection is too large for the small tiles and no multiple of
+    128 wide, the plan is a kernel of its own.  Rows, sizes and edges bit for bit."""
+    import torch
+    cfg = synth.Config("fused", L=2, D=D, H=H, F=256, dtype="f32", B=1, n0=2, seed=17)
+    ctx, _ = hz.make_context(cfg)
+    ns = [2, 3, 33, 64, 65, 66, 129, 577, 1024, 300, 300, 300, 300]
+    off = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
+    x0 = torch.randn((int(off[-1]), D), generator=torch.Generator().manual_seed(3)).to("cuda")
+    R = [1, 1, 4, 8, 32, 5, 64, 23, 400, 16, 0, 149, 7]
+    many = hz.gpu_forward(ctx, x0, off, R)
+    for q, n in enumerate(ns):
+        one = hz.gpu_forward(ctx, x0[int(off[q]):int(off[q + 1])].contiguous(), [0, n], [R[q]])
+        assert np.array_equal(one["x"][0], many["x"][q]) and np.array_equal(one["sizes"][0], many["sizes"][q]), n
+        for a, b in zip(one["trace"][0], many["trace"][q]):
+            assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), n
+    ctx.close()
