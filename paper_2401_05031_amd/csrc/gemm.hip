@@ -55,8 +55,8 @@ __device__ inline float epilogue_value(float acc, float bias, const float* res, 
 // sequence positions s = id / 8 of one contiguous band of tiles, and inside the band walk groups of
 // GM tile rows column by column, so that the tiles in flight on one XCD form a compact block that
 // shares activation and weight panels through that L2.
+template <int GM = 8>
 __device__ inline void tile_of_block(int bid, int tiles_m, int tiles_n, int& tile_m, int& tile_n) {
-  constexpr int GM = 8;
   const int nblk = tiles_m * tiles_n;
   const int per = nblk >> 3;
   int t = bid;
@@ -1102,7 +1102,11 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   const int wm = wave >> 2, wn = wave & 3;
   int tile_m, tile_n;
   OTAS_PLAN_TAIL_OR_TILE(512)
-  tile_of_block(bid, tiles_m, tiles_n, tile_m, tile_n);
+  // The float outputs have few tile columns and a long K: two rows at a time, an activation panel is still in the L2 for its
+  // last column.  us with groups of 8 / 2 / 1 rows: 40000 x 1280 x 5120 518 / 484 / 478, 67072 x 1280 x 5120 865 / 836 / 840,
+  // 25216 x 1024 x 4096 233 / 226 / 225, 25216 x 1024 x 1024 84 / 82 / 80, 67072 x 1280 x 1280 295 / 295 / 303.  The other
+  // products are no faster that way (12608 x 3072 x 768 + GELU 61.4 / 64.4 / 65.7).
+  tile_of_block<EPI == EPI_RESIDUAL ? 2 : 8>(bid, tiles_m, tiles_n, tile_m, tile_n);
   const int64_t m0 = (int64_t)tile_m * BM;
   const int n0 = tile_n * BN;
 
