@@ -674,7 +674,8 @@ __device__ inline void mfma_epilogue(const Acc<TM, TN>& acc, float* stage, const
 // and only then transposed through the wave's LDS slab, [32][WN + 8] bf16: half the LDS traffic of the
 // float slab, and the read-back hands every lane 8 consecutive columns, so the global stores are
 // 16 bytes per lane and a row segment of 2 WN bytes goes out in one instruction.
-template <int EPI, int TM, int TN>
+// NT: the output goes past the L2's replacement (see streams_output).
+template <int EPI, int TM, int TN, bool NT = false>
 __device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage, const bf16_t* bias_s, bf16_t* Y,
                                           int64_t M, int N, int64_t m_wave, int n_wave, int lane) {
   typedef Acc<TM, TN> A;
@@ -710,7 +711,11 @@ __device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage,
     bf16_t* yp = Y + (size_t)(m_slab + rrow) * N + n_out;
 #pragma unroll
     for (int it = 0; it < NIT; ++it)
-      if (m_slab + it * RPI + rrow < M && n_ok) *reinterpret_cast<bf16x8*>(yp + (size_t)it * RPI * N) = a[it];
+      if (m_slab + it * RPI + rrow < M && n_ok) {
+        bf16x8* p = reinterpret_cast<bf16x8*>(yp + (size_t)it * RPI * N);
+        if (NT) __builtin_nontemporal_store(a[it], p);
+        else *p = a[it];
+      }
   }
 }
 
@@ -1087,7 +1092,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
                                                                 const bf16_t* __restrict__ W,
                                                                 const bf16_t* __restrict__ bias, const float* res,
                                                                 typename OutType<bf16_t, EPI>::type* Y, int64_t M,
-                                                                int N, int K, int tiles_m, int tiles_n, PlanTail pt) {
+                                                                int N, int K, int tiles_m, int tiles_n, bool stream,
+                                                                PlanTail pt) {
   constexpr int WM = 32 * TM, BM = 2 * WM, BN = 256, BK = 64, WN = 64, TN = 2, NS = 2;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   constexpr int NA = BM / 64;   // DMA instructions per wave for the A tile (8 rows each), 4 for W
@@ -1232,12 +1238,25 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   for (int kt = 0; kt < KT - 2; ++kt) tile(kt, std::true_type(), std::true_type());
   tile(KT - 2, std::false_type(), std::true_type());
   tile(KT - 1, std::false_type(), std::false_type());   // its barrier: no wave reads a stage any more, the epilogue may write
-  if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
-                                    m0 + wm * WM, n0 + wn * WN, lane);
-  else
+  if constexpr (EPI == EPI_NONE || EPI == EPI_GELU) {
+    bf16_t* slab = reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8);
+    if (stream) mfma_epilogue_bf16<EPI, TM, TN, true>(acc, slab, bias_s + wn * WN, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane);
+    else mfma_epilogue_bf16<EPI, TM, TN>(acc, slab, bias_s + wn * WN, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane);
+  } else
     mfma_epilogue<EPI, TM, TN, FIRST>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias_s + wn * WN, res, Y,
                                       M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
+}
+
+// Whether a bf16 output is written past the L2's replacement (non-temporal stores): the launch itself is about 2 us shorter
+// from 20 MB up (its panels stay in the L2, and less of the output is left to write back when it ends), but what reads the
+// output next finds less of it there.  In a ViT-B pass of 64 queries with r = 16 (MI355X, us, with / without; the next kernel):
+// FC1 of 8512 rows (52 MB) 49.9 / 52.1 (second linear 54.2 / 53.7), 5440 (33 MB) 30.6 / 32.6 (48.9 / 49.8), 11584 (71 MB) 65.2 /
+// 65.2 (77.4 / 74.5); QKV of 4416 rows (20 MB) 20.8 / 21.6 (attention 12.2 / 12.2), 6464 (30 MB) 24.4 / 25.1 (15.6 / 15.3), 12608
+// (58 MB) 47.4 / 46.3 (31.8 / 28.6).  An output that the 256 MB last-level cache cannot hold is not found there anyway: ViT-H,
+// 256 queries 62479 -> 61694 us a pass.
+static bool streams_output(int64_t M, int N, int epi) {
+  const int64_t bytes = 2 * M * N;
+  return bytes <= ((int64_t)(epi == EPI_GELU ? 56 : 32) << 20) || bytes > (int64_t)256 << 20;
 }
 
 template <int TM>
@@ -1254,7 +1273,7 @@ static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bia
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
                                   (typename OutType<bf16_t, E>::type*)y, M, N, K, tiles_m, tiles_n,               \
-                                  pt ? *pt : PlanTail{});                                                         \
+                                  streams_output(M, N, epi), pt ? *pt : PlanTail{});                                                         \
   } while (0)
   if (pt) {
     if (epi != EPI_RESIDUAL) return hipErrorInvalidValue;
