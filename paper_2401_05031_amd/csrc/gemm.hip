@@ -10,7 +10,7 @@
 //     of nothing but MFMAs on random operands: 1.91 against 1.82 PFLOP/s; 67072 x 3840 x 1280 544 against 573 us).
 //       gemm_mfma_k32_kernel     128 x 128, K step 32, three workgroups per CU (K that is no multiple of 64)
 //       gemm_mfma128k64_kernel   128 x 128, K step 64, two per CU (also split-K)
-//       gemm_mfma256w8_kernel    192 / 256 / 320 x 256, eight waves, one per CU
+//       gemm_mfma256w8_kernel    160, 192, 224, 256, 288 or 320 x 256, eight waves, one per CU
 //       gemm_mfma64_kernel       64 x 64, K step 64 or 32, for products of very few rows (also split-K)
 //     pick_mfma_kernel chooses among them with a cost model fitted to measured launch times; splitk_factor
 //     decides by a rule of its own whether the MLP's second linear is split over K.
@@ -557,7 +557,7 @@ static hipError_t linear_f32(const void* x, const void* w, const void* bias, con
 template <int TN> struct ResSlab {
   static constexpr int LPR = 8 * TN, RPI = 64 / LPR, NIT = 32 / RPI;
   floatx4 v[NIT];
-  __device__ inline void load(const float* res, int64_t M, int N, int64_t m_slab, int n_wave, int lane) {
+  __device__ inline void load(const float* res, int64_t M, int N, int64_t m_slab, int n_wave, int lane, int rows = 32) {
     // a uniform base and 32-bit offsets: addresses of 64 bits per lane would not fit the registers of the large tiles
     const int64_t m_base = m_slab < M ? m_slab : M - 1;
     const uint32_t last = (uint32_t)(M - 1 - m_base < 31 ? M - 1 - m_base : 31);
@@ -566,6 +566,7 @@ template <int TN> struct ResSlab {
     const uint32_t row = lane / LPR, col = n < N ? n : 0;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
+      if (it * RPI >= rows) break;   // a half slab
       const uint32_t r = row + it * RPI;
       v[it] = *reinterpret_cast<const floatx4*>(base + ((r < last ? r : last) * (uint32_t)N + col) * 4u);
     }
@@ -585,33 +586,36 @@ __device__ inline void bias_stage(bf16_t* bias_s, const bf16x8& v, int tid) {
   if (tid < BN / 8) *reinterpret_cast<bf16x8*>(bias_s + tid * 8) = v;
 }
 
-// A wave's accumulators, 32 TM rows x 32 TN columns in 16 x 16 blocks (a lane holds, of block row lane & 15, four
-// consecutive columns), as the epilogues see them: slab i (32 rows) is 4 TN quads per lane; quad k sits at row(k), col(k) of
-// the slab and takes bias quad k % NB.
-template <int TM, int TN> struct Acc {
-  static constexpr int NB = 2 * TN;
-  floatx4 v[2 * TM][2 * TN];
+// A wave's accumulators, RB x CB blocks of 16 x 16 (a lane holds, of block row lane & 15, four
+// consecutive columns), as the epilogues see them: slab i (32 rows; the last has 16 where RB is odd) is 2 CB quads per lane;
+// quad k sits at row(k), col(k) of the slab and takes bias quad k % CB.
+template <int RB, int CB> struct Acc {
+  static constexpr int NB = CB, SLABS = (RB + 1) / 2;
+  floatx4 v[RB][CB];
   __device__ inline void clear() {
 #pragma unroll
-    for (int i = 0; i < 2 * TM; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
-      for (int j = 0; j < 2 * TN; ++j) v[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < CB; ++j) v[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
   __device__ inline void mfma(int i, int j, const bf16x8& w, const bf16x8& a) {
     v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, v[i][j], 0, 0, 0);
   }
-  __device__ inline const floatx4& quad(int i, int k) const { return v[2 * i + k / NB][k % NB]; }
-  static __device__ inline int row(int k, int lane) { return 16 * (k / NB) + (lane & 15); }
-  static __device__ inline int col(int k, int lane) { return 16 * (k % NB) + 4 * (lane >> 4); }
+  __device__ inline const floatx4& quad(int i, int k) const { return v[2 * i + k / CB][k % CB]; }
+  static constexpr __device__ inline int rows(int i) { return 2 * i + 2 <= RB ? 32 : 16; }   // of slab i
+  static __device__ inline int row(int k, int lane) { return 16 * (k / CB) + (lane & 15); }
+  static __device__ inline int col(int k, int lane) { return 16 * (k % CB) + 4 * (lane >> 4); }
 };
 
 // bias_s: the bias of this wave's 32 TN columns in LDS.  first: the residual rows of slab 0, already requested
 // (HAVE_FIRST), so that the epilogue does not begin with a round trip to HBM.
-template <int EPI, int TM, int TN, bool HAVE_FIRST = false>
-__device__ inline void mfma_epilogue(const Acc<TM, TN>& acc, float* stage, const bf16_t* bias_s,
+template <int EPI, int RB, int CB, bool HAVE_FIRST = false>
+__device__ inline void mfma_epilogue(const Acc<RB, CB>& acc, float* stage, const bf16_t* bias_s,
                                      const float* res, typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N,
-                                     int64_t m_wave, int n_wave, int lane, const ResSlab<TN>& first = ResSlab<TN>{}) {
-  typedef Acc<TM, TN> A;
+                                     int64_t m_wave, int n_wave, int lane,
+                                     const ResSlab<CB / 2>& first = ResSlab<CB / 2>{}) {
+  typedef Acc<RB, CB> A;
+  constexpr int TN = CB / 2;
   constexpr int WN = 32 * TN, LDR = WN + 4;
   constexpr int LPR = WN / 4;      // lanes per row when reading back
   constexpr int RPI = 64 / LPR;    // rows per read-back instruction
@@ -627,15 +631,16 @@ __device__ inline void mfma_epilogue(const Acc<TM, TN>& acc, float* stage, const
   ResSlab<TN> rr[2];
   if (EPI == EPI_RESIDUAL && HAVE_FIRST) rr[0] = first;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+  for (int i = 0; i < A::SLABS; ++i) {
     const int64_t m_slab = m_wave + i * 32;
-    if (EPI == EPI_RESIDUAL && HAVE_FIRST && i + 1 < TM) rr[(i + 1) & 1].load(res, M, N, m_slab + 32, n_wave, lane);
+    if (EPI == EPI_RESIDUAL && HAVE_FIRST && i + 1 < A::SLABS)
+      rr[(i + 1) & 1].load(res, M, N, m_slab + 32, n_wave, lane, A::rows(i + 1));
 #pragma unroll
-    for (int k = 0; k < 4 * TN; ++k)
+    for (int k = 0; k < CB * A::rows(i) / 16; ++k)
       *reinterpret_cast<floatx4*>(stage + A::row(k, lane) * LDR + A::col(k, lane)) = acc.quad(i, k);
     if (EPI == EPI_RESIDUAL && !HAVE_FIRST) {
       __builtin_amdgcn_sched_barrier(0);
-      rr[i & 1].load(res, M, N, m_slab, n_wave, lane);
+      rr[i & 1].load(res, M, N, m_slab, n_wave, lane, A::rows(i));
     }
     // the slab is read back four rows per lane at a time before anything is stored: one LDS wait per group
     // instead of one per store
@@ -643,6 +648,7 @@ __device__ inline void mfma_epilogue(const Acc<TM, TN>& acc, float* stage, const
     floatx4 ag[GRP];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
+      if (it * RPI >= A::rows(i)) break;
       const int row = it * RPI + rrow;
       if (it % GRP == 0) {
 #pragma unroll
@@ -675,10 +681,11 @@ __device__ inline void mfma_epilogue(const Acc<TM, TN>& acc, float* stage, const
 // float slab, and the read-back hands every lane 8 consecutive columns, so the global stores are
 // 16 bytes per lane and a row segment of 2 WN bytes goes out in one instruction.
 // NT: the output goes past the L2's replacement (see streams_output).
-template <int EPI, int TM, int TN, bool NT = false>
-__device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage, const bf16_t* bias_s, bf16_t* Y,
+template <int EPI, int RB, int CB, bool NT = false>
+__device__ inline void mfma_epilogue_bf16(const Acc<RB, CB>& acc, bf16_t* stage, const bf16_t* bias_s, bf16_t* Y,
                                           int64_t M, int N, int64_t m_wave, int n_wave, int lane) {
-  typedef Acc<TM, TN> A;
+  typedef Acc<RB, CB> A;
+  constexpr int TN = CB / 2;
   constexpr int WN = 32 * TN, LDR = WN + 8;
   constexpr int LPR = WN / 8;      // lanes per row when reading back
   constexpr int RPI = 64 / LPR;    // rows per read-back instruction
@@ -690,10 +697,10 @@ __device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage,
 #pragma unroll
   for (int k = 0; k < A::NB; ++k) bb[k] = *reinterpret_cast<const bf16x4*>(bias_s + A::col(k, lane));
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+  for (int i = 0; i < A::SLABS; ++i) {
     const int64_t m_slab = m_wave + i * 32;
 #pragma unroll
-    for (int k = 0; k < 4 * TN; ++k) {
+    for (int k = 0; k < CB * A::rows(i) / 16; ++k) {
       float v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -707,11 +714,12 @@ __device__ inline void mfma_epilogue_bf16(const Acc<TM, TN>& acc, bf16_t* stage,
     // store, and one address computation (the rows of a lane are RPI * N elements apart)
     bf16x8 a[NIT];
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) a[it] = *reinterpret_cast<const bf16x8*>(stage + (it * RPI + rrow) * LDR + rcol);
+    for (int it = 0; it < NIT; ++it)
+      if (it * RPI < A::rows(i)) a[it] = *reinterpret_cast<const bf16x8*>(stage + (it * RPI + rrow) * LDR + rcol);
     bf16_t* yp = Y + (size_t)(m_slab + rrow) * N + n_out;
 #pragma unroll
     for (int it = 0; it < NIT; ++it)
-      if (m_slab + it * RPI + rrow < M && n_ok) {
+      if (it * RPI < A::rows(i) && m_slab + it * RPI + rrow < M && n_ok) {
         bf16x8* p = reinterpret_cast<bf16x8*>(yp + (size_t)it * RPI * N);
         if (NT) __builtin_nontemporal_store(a[it], p);
         else *p = a[it];
@@ -814,7 +822,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
                                        OTAS_LPTR(Ws + st * STAGE_W + (wave * 32 + (d - TM) * 16) * BK), 16, 0, 0);
   };
 
-  Acc<TM, TN> acc;
+  Acc<2 * TM, 2 * TN> acc;
   acc.clear();
 
   const int fr = lane & 15, fk = lane >> 4;
@@ -875,10 +883,10 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
   __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the stages become the epilogue's staging area
   asm volatile("" ::: "memory");
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
+    mfma_epilogue_bf16<EPI, 2 * TM, 2 * TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, TM, TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
+    mfma_epilogue<EPI, 2 * TM, 2 * TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
                                                     bias_s + wn * WN, res, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
@@ -971,7 +979,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
                                        OTAS_LPTR(Ws + st * STAGE_W + (wave * 16 + j * RPI) * BK), 16, 0, 0);
     }
   };
-  Acc<1, 1> acc;
+  Acc<2, 2> acc;
   acc.clear();
   const int fr = lane & 15, fk = lane >> 4;
   const int frag_row = fr * BK, sw = swz(fr);   // swz of 16 w + fr is swz of fr
@@ -1030,10 +1038,10 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, 1, 1>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias_s + wn * 32, Y, M, N,
+    mfma_epilogue_bf16<EPI, 2, 2>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias_s + wn * 32, Y, M, N,
                                   m0 + wm * 32, n0 + wn * 32, lane);
   else
-    mfma_epilogue<EPI, 1, 1, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (32 + 4),
+    mfma_epilogue<EPI, 2, 2, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (32 + 4),
                                                   bias_s + wn * 32, res, Y, M, N, m0 + wm * 32, n0 + wn * 32, lane, first);
 }
 
@@ -1084,21 +1092,23 @@ static hipError_t linear_mfma64(const void* x, const void* w, const void* bias, 
 // in the matrix pipe.  A load is in flight for one whole 64-wide tile before it is needed.
 // Stage layout: 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7) (conflict-free for the
 // linear DMA writes and for the 16-lanes-per-clock fragment reads).
-// The tile height is a template parameter: BM = 64 TM rows (TM = 3, 4, 5: 192, 256, 320) by 256
-// columns.  Whole rounds of one workgroup per CU are what this kernel costs, so the launcher picks
+// The tile height is a template parameter: BM = 32 RB rows (RB = 5 .. 10: 160, 192, .. 320; a wave has RB blocks of 16) by
+// 256 columns.  Whole rounds of one workgroup per CU are what this kernel costs, so the launcher picks
 // the height whose tile count wastes the least of the last round.
-template <int EPI, int TM, bool PLAN = false>
+template <int EPI, int RB, bool PLAN = false>
 __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __restrict__ A,
                                                                 const bf16_t* __restrict__ W,
                                                                 const bf16_t* __restrict__ bias, const float* res,
                                                                 typename OutType<bf16_t, EPI>::type* Y, int64_t M,
                                                                 int N, int K, int tiles_m, int tiles_n, bool stream,
                                                                 PlanTail pt) {
-  constexpr int WM = 32 * TM, BM = 2 * WM, BN = 256, BK = 64, WN = 64, TN = 2, NS = 2;
+  constexpr int WM = 16 * RB, BM = 2 * WM, BN = 256, BK = 64, WN = 64, TN = 2, NS = 2;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
-  constexpr int NA = BM / 64;   // DMA instructions per wave for the A tile (8 rows each), 4 for W
-  constexpr int ND = NA + 4;
-  constexpr int RB = 2 * TM, CB = 2 * TN, HB = 2;   // 16-row and 16-column blocks of a wave
+  // DMA instructions per wave (8 rows each): NA for the A tile, 4 for W, and where RB is odd one more for A's last 32 rows,
+  // which only the first four waves have
+  constexpr bool ODD = RB % 2;
+  constexpr int NA = BM / 64, ND = NA + 4 + ODD;
+  constexpr int CB = 2 * TN, HB = 2;   // 16-column blocks of a wave; row blocks before the barrier
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][BM][64]
   bf16_t* Ws = As + NS * STAGE_A;                 // [NS][256][64]
@@ -1122,10 +1132,10 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   // (i%8) ^ ((row >> 1) & 7) of that row.
   // Global addresses are a uniform base (tile origin + k, scalar registers) plus a per-lane 32-bit
   // byte offset that never changes, so issuing a load costs no vector arithmetic.
-  uint32_t a_off[NA], w_off[4];
+  uint32_t a_off[NA + ODD], w_off[4];
 #pragma unroll
-  for (int j = 0; j < NA; ++j) {
-    const int row = wave * (8 * NA) + j * 8 + (lane >> 3);
+  for (int j = 0; j < NA + ODD; ++j) {
+    const int row = (j < NA ? wave * (8 * NA) + j * 8 : NA * 64 + wave * 8) + (lane >> 3);
     const int c = (lane & 7) ^ ((row >> 1) & 7);
     const int64_t last = M - 1 - m0;                  // rows past the end repeat the last row
     const uint32_t r = (uint32_t)(row < last ? row : last);
@@ -1142,19 +1152,23 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K);
   const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K);
   const int KT = K / BK;
-  auto dma_one = [&](int kt, int st, int d) {   // d = 0..NA-1: A rows; NA..NA+3: W rows
+  auto dma_one = [&](int kt, int st, int d) {   // d = 0..NA-1: A rows; NA..NA+3: W rows; NA+4: A's last rows
+    if (ODD && d == ND - 1 && wave >= 4) return;
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
+    const bool is_w = d >= NA && d < NA + 4;
+    const int ja = d < NA ? d : NA;
     // opaque, or the compiler keeps the sums base + offset instead, 64 bits each: 18 registers that the tile needs
-    asm volatile("" : "+v"(d < NA ? a_off[d] : w_off[d - NA]));
-    if (d < NA)
-      __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[d]),
-                                       OTAS_LPTR(As + st * STAGE_A + (wave * (8 * NA) + d * 8) * BK), 16, 0, 0);
-    else
+    asm volatile("" : "+v"(is_w ? w_off[d - NA] : a_off[ja]));
+    if (is_w)
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[d - NA]),
                                        OTAS_LPTR(Ws + st * STAGE_W + (wave * 32 + (d - NA) * 8) * BK), 16, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds(
+          OTAS_GPTR(a_base + kb + a_off[ja]),
+          OTAS_LPTR(As + st * STAGE_A + (d < NA ? wave * (8 * NA) + d * 8 : NA * 64 + wave * 8) * BK), 16, 0, 0);
   };
 
-  Acc<TM, TN> acc;
+  Acc<RB, CB> acc;
   acc.clear();
 
   // Fragments of a k-step (32 columns of K): lane (row = lane & 15, lane >> 4) holds 8 columns of a row.  W's blocks have
@@ -1200,13 +1214,15 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   // the first residual rows, requested beside the last-but-one tile's k-step 1, may still be on their way.
   bf16_t* bias_s = Ws + NS * STAGE_W;
   const bf16x8 bias_v = bias_fetch<BN>(bias, N, n0, tid);
-  constexpr bool FIRST = EPI == EPI_RESIDUAL && TM <= 4;   // TM = 5 leaves no registers for them
+  constexpr bool FIRST = EPI == EPI_RESIDUAL && RB <= 8;   // larger tiles leave no registers for them
   ResSlab<TN> first;
 #pragma unroll
   for (int d = 0; d < ND; ++d) dma_one(0, 0, d);
 #pragma unroll
   for (int d = 0; d < ND; ++d) dma_one(1, 1, d);
-  OTAS_VMCNT(ND);    // tile 0 landed (this wave's part), and the bias before it
+  // tile 0 landed (this wave's part), and the bias before it
+  if (ODD && wave >= 4) OTAS_VMCNT(ND - 1);
+  else OTAS_VMCNT(ND);
   bias_stage<BN>(bias_s, bias_v, tid);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
@@ -1231,7 +1247,8 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
     if constexpr (FIRST && NEXT && !LOAD) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
     rows(1, HB, RB, st ^ 1, next, [&](int t) {
       if constexpr (LOAD) {
-        if (t % 2 == 1 && t / 2 < ND) dma_one(kt + 2, st, t / 2);
+        constexpr int EVERY = (RB - HB) * CB >= 2 * ND ? 2 : 1;
+        if (t % EVERY == EVERY - 1 && t / EVERY < ND) dma_one(kt + 2, st, t / EVERY);
       }
     });
   };
@@ -1240,10 +1257,10 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
   tile(KT - 1, std::false_type(), std::false_type());   // its barrier: no wave reads a stage any more, the epilogue may write
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU) {
     bf16_t* slab = reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8);
-    if (stream) mfma_epilogue_bf16<EPI, TM, TN, true>(acc, slab, bias_s + wn * WN, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane);
-    else mfma_epilogue_bf16<EPI, TM, TN>(acc, slab, bias_s + wn * WN, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane);
+    if (stream) mfma_epilogue_bf16<EPI, RB, CB, true>(acc, slab, bias_s + wn * WN, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane);
+    else mfma_epilogue_bf16<EPI, RB, CB>(acc, slab, bias_s + wn * WN, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane);
   } else
-    mfma_epilogue<EPI, TM, TN, FIRST>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias_s + wn * WN, res, Y,
+    mfma_epilogue<EPI, RB, CB, FIRST>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4), bias_s + wn * WN, res, Y,
                                       M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
@@ -1259,16 +1276,16 @@ static bool streams_output(int64_t M, int N, int epi) {
   return bytes <= ((int64_t)(epi == EPI_GELU ? 56 : 32) << 20) || bytes > (int64_t)256 << 20;
 }
 
-template <int TM>
+template <int RB>
 static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bias, const float* res, void* y,
                                    int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
-  constexpr int BM = 64 * TM;
+  constexpr int BM = 32 * RB;
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + 255) / 256;
   const size_t lds = ((size_t)2 * (BM + 256) * 64 + 256) * sizeof(bf16_t);   // the stages and the tile's bias
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0))), block(512);
 #define OTAS_MFMA(E, ...)                                                                                         \
   do {                                                                                                            \
-    auto kern = gemm_mfma256w8_kernel<E, TM, ##__VA_ARGS__>;                                                      \
+    auto kern = gemm_mfma256w8_kernel<E, RB, ##__VA_ARGS__>;                                                      \
     hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
@@ -1342,7 +1359,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
                                        OTAS_LPTR(Ws + st * STAGE + (wave * 32 + j * 8) * BK), 16, 0, 0);
   };
 
-  Acc<TM, TN> acc;
+  Acc<2 * TM, 2 * TN> acc;
   acc.clear();
 
   const int fr = lane & 15, fk = lane >> 4;
@@ -1411,10 +1428,10 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   tile(KT - 2, std::false_type(), std::true_type());
   tile(KT - 1, std::false_type(), std::false_type());
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, TM, TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
+    mfma_epilogue_bf16<EPI, 2 * TM, 2 * TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, TM, TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
+    mfma_epilogue<EPI, 2 * TM, 2 * TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
                                                     bias_s + wn * WN, res, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
@@ -1453,22 +1470,32 @@ static hipError_t linear_mfma_kernel(int kernel, const void* x, const void* w, c
   switch (kernel) {
     case GK_128_K32: return k32 ? linear_mfma_k32<3, 2>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     case GK_128_K64: return k64 ? linear_mfma128k64(x, w, bias, res, y, M, N, K, epi, s, 1, pt) : hipErrorInvalidValue;
-    case GK_192X256: return k64 ? linear_mfma256w8<3>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_256X256: return k64 ? linear_mfma256w8<4>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_320X256: return k64 ? linear_mfma256w8<5>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_160X256: return k64 ? linear_mfma256w8<5>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_192X256: return k64 ? linear_mfma256w8<6>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_224X256: return k64 ? linear_mfma256w8<7>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_256X256: return k64 ? linear_mfma256w8<8>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_288X256: return k64 ? linear_mfma256w8<9>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_320X256: return k64 ? linear_mfma256w8<10>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     case GK_64X64: return k32 ? linear_mfma64(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }
 
-// Kernel choice by a cost model fitted to launches of every kernel on MI355X (197 .. 67000 rows, D = 768 / 1024 / 1280, the
-// four products of a block; 6 % rms, picks 0.4 % above the best kernel of each shape).  A kernel with tile bm x bn and S
+// Kernel choice by a cost model fitted to launches of every kernel on MI355X (a quarter of a round to two rounds of tiles, K =
+// 768 ... 5120, three buffers of each operand in turn; 7 - 9 % rms).  On the four products of a block at 5440 ... 67072 rows of
+// D = 768 / 1024 / 1280 its picks take 0.1 % longer than the best kernel of each shape, and 1.6 % less than the best of
+// 128 x 128, 192, 256 and 320 x 256 (heights in steps of 64 rows: 67072 x 1280 x 5120 810 -> 765 us, 25216 x 1024 x 4096 215
+// -> 208, 12608 x 768 x 3072 74.6 -> 73.0, 8512 x 3072 x 768 48.8 -> 45.2); on 70 smaller ones whose pick they changed 4 %
+// less.  A kernel with tile bm x bn and S
 // workgroup slots on the chip (256 CUs x workgroups per CU) takes
 //     (alpha[epilogue] + beta K) * G(tiles),   G = full rounds + p + (1 - p) * (last round's fill),
 // i.e. whole rounds of S tiles, a partly filled last round costing p of a round plus its share.
 // Those are launches repeated on their own, operands in the caches.  Inside a pass (ViT-B, 64 queries, r = 16) the kernels
 // it picks take longer than it gives: QKV and FC1 2 - 19 % at 20 us and more, the projection 13 - 32 %, the MLP's second
 // linear 17 - 30 %, launches under 20 us 18 - 50 % (of which about 1 us is the timing events').
+// Two constants are not the fit's but what the pass shows: 160 rows with the residual (fitted 10.4: 12608 x 768 x 3072 alone
+// 73.0 against 74.6 us with 192 rows, in a pass of 64 queries 71.5 against 69.5) and 224 with GELU (7.0: 14144 x 3072 x 768 alone
+// 76.8 against 78.9 with 256 rows, in the pass 81.3 against 78.2).
 // The choice depends on the shape only, so a shape always runs the same kernel.  The K-step-32 kernel is nowhere the
 // fastest where K is a multiple of 64, and not among the candidates.
 static double rounds_cost(double tiles, int slots, double p) {
@@ -1480,23 +1507,26 @@ static double rounds_cost(double tiles, int slots, double p) {
 // after the other, the fullest CU's being the launch's.  Fitted to the same launches (us measured / modelled at 1, 2, 3, 4
 // workgroups per CU: K = 768 4.8 / 4.8, 6.4 / 7.2, 9.6 / 9.5, 11.5 / 11.9; K = 3072 + residual 11.1 / 12.0, 20.9 / 22.4,
 // 31.0 / 32.9, 40.8 / 43.3).
-static double tile64_cost(int64_t M, int N, int k_len, int splits, bool float_out, double alpha) {
+static double tile64_cost(int64_t M, int N, int k_len, int splits, double per_tile, double alpha) {
   const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64) * splits;
-  return alpha + (0.0031 * k_len + (float_out ? 0.9 : 0.0)) * (double)((tiles + 255) / 256);
+  return alpha + (0.0031 * k_len + per_tile) * (double)((tiles + 255) / 256);
 }
 
 static int pick_mfma_kernel(int64_t M, int N, int K, int epi) {
   if (K % 64 != 0 || K < 128) return ((M + 63) / 64) * ((N + 63) / 64) <= 450 ? GK_64X64 : GK_128_K32;
   struct Cand { int id, bm, bn, slots; double alpha[3], beta, p; };
   static const Cand cands[] = {
-      {GK_128_K64, 128, 128, 512, {3.36, 4.99, 9.81}, 0.0131, 0.514},
-      {GK_192X256, 192, 256, 256, {5.69, 8.07, 13.2}, 0.0183, 0.546},
-      {GK_256X256, 256, 256, 256, {5.53, 9.37, 16.0}, 0.0236, 0.566},
-      {GK_320X256, 320, 256, 256, {6.98, 11.3, 23.0}, 0.0278, 0.582},
+      {GK_128_K64, 128, 128, 512, {4.06, 5.74, 9.65}, 0.0148, 0.527},
+      {GK_160X256, 160, 256, 256, {3.63, 5.29, 15.2}, 0.0187, 0.655},
+      {GK_192X256, 192, 256, 256, {4.23, 6.17, 12.7}, 0.0211, 0.595},
+      {GK_224X256, 224, 256, 256, {4.94, 10.0, 15.8}, 0.0237, 0.580},
+      {GK_256X256, 256, 256, 256, {5.61, 8.97, 17.4}, 0.0261, 0.570},
+      {GK_288X256, 288, 256, 256, {7.71, 10.8, 23.7}, 0.0278, 0.572},
+      {GK_320X256, 320, 256, 256, {7.77, 12.1, 25.7}, 0.0302, 0.571},
   };
   const int e = epi == EPI_RESIDUAL ? 2 : epi == EPI_GELU ? 1 : 0;
   static const double alpha64[3] = {2.4, 3.1, 1.6};
-  double best = tile64_cost(M, N, K, 1, e == 2, alpha64[e]);
+  double best = tile64_cost(M, N, K, 1, e == 2 ? 1.15 : 0.0, alpha64[e]);
   int kernel = GK_64X64;
   for (const Cand& c : cands) {
     const double tiles = (double)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
@@ -1552,7 +1582,7 @@ int splitk_factor(int dtype, int64_t M, int N, int K, int max_split) {
 // Which tiles the partial products of a split run in: the same bits either way.
 static bool splitk_tiles64(int64_t M, int N, int K, int S) {
   const double tiles = (double)((M + 127) / 128) * ((N + 127) / 128);
-  return tile64_cost(M, N, K / S, S, true, 2.4) < (6.5 + 0.0130 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
+  return tile64_cost(M, N, K / S, S, 0.9, 2.4) < (6.5 + 0.0130 * (K / S)) * rounds_cost(tiles * S, 512, 0.556);
 }
 
 hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64_t M, int N, int K, int S,
@@ -1585,7 +1615,10 @@ bool linear_plan_tail_fits(int dtype, int64_t M, int N, int K, int B) {
   int bm = 128, bn = 128, slots = 768;
   switch (pick_mfma_kernel(M, N, K, EPI_RESIDUAL)) {
     case GK_128_K64: slots = 512; break;
+    case GK_160X256: bm = 160; bn = 256; slots = 256; break;
     case GK_192X256: bm = 192; bn = 256; slots = 256; break;
+    case GK_224X256: bm = 224; bn = 256; slots = 256; break;
+    case GK_288X256: bm = 288; bn = 256; slots = 256; break;
     case GK_256X256: bm = 256; bn = 256; slots = 256; break;
     case GK_320X256: bm = 320; bn = 256; slots = 256; break;
     case GK_64X64: bm = 64; bn = 64; slots = K % 64 == 0 ? 512 : 1024; break;

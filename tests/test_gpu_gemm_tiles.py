@@ -1,0 +1,59 @@
+"""The 256-column GEMM kernels at every tile height, at the edges of their tiles, loops and output rules."""
+import pytest
+
+import otas_synth as synth
+from tests import harness as hz
+
+pytestmark = pytest.mark.gpu
+ROWS = {4: 192, 5: 256, 6: 320, 8: 160, 9: 224, 10: 288}
+
+
+def _context():
+    cfg = synth.config("vitb_plain")
+    cfg.L = 1
+    return hz.make_context(cfg)[0]
+
+
+@pytest.mark.parametrize("K", [128, 192, 256, 448])
+@pytest.mark.parametrize("kernel", sorted(ROWS))
+def test_tile_heights_at_their_edges(lib, kernel, K):
+    """Two to seven k-tiles; one row short of, at and past one and two tiles, one of them inside a wave's last 16 rows; ragged
+    columns; all epilogues.  Against float64 (K + 8 roundings of 2^-24 on the terms' absolute sum, GELU's slope below 1.13,
+    the rounding of a bf16 output), and bit for bit against the 128 x 128 kernel: K is walked in the same order."""
+    import torch
+    ctx, bm = _context(), ROWS[kernel]
+    g = torch.Generator(device="cuda").manual_seed(K + kernel)
+    for M, N in [(1, 8), (bm - 1, 264), (bm, 256), (bm + 1, 200), (2 * bm + bm // 2 + 5, 520)]:
+        x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+        res = torch.randn((M, N), generator=g, device="cuda")
+        xd, wd, bd = x.double(), w.double(), b.double()
+        lin, mag = xd @ wd.T + bd, xd.abs() @ wd.abs().T + bd.abs()
+        for epi in (0, 1, 2):
+            out = {}
+            for k in (kernel, 3):
+                out[k] = torch.full((M, N), float("nan"), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+                ctx.otas_linear_kernel(k, x, w, b, res if epi == 2 else None, M, N, K, epi, out[k])
+            want = torch.nn.functional.gelu(lin) if epi == 1 else lin + res.double() if epi == 2 else lin
+            bound = (K + 8) * 2.0 ** -24 * 1.13 * (mag + (res.double().abs() if epi == 2 else 0))
+            if epi != 2:
+                bound = bound + 2.0 ** -8 * want.abs() + 1e-7
+            assert bool(((out[kernel].double() - want).abs() <= bound).all()), (M, N, epi)
+            assert torch.equal(out[kernel], out[3]), (M, N, epi)
+    ctx.close()
+
+
+@pytest.mark.parametrize("epi,M,N", [(0, 16391, 1016), (0, 16400, 1024), (1, 14341, 2040), (1, 14400, 2048)])
+@pytest.mark.parametrize("kernel", sorted(ROWS))
+def test_outputs_on_both_sides_of_the_streaming_rule(lib, kernel, epi, M, N):
+    """Outputs just under and just over 32 MB (56 MB with GELU): stored past the L2's replacement or not, the same rows as
+    the 128 x 128 kernel's."""
+    import torch
+    ctx, K = _context(), 128
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+    out = {}
+    for k in (kernel, 3):
+        out[k] = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ctx.otas_linear_kernel(k, x, w, b, None, M, N, K, epi, out[k])
+    assert torch.equal(out[kernel], out[3])
+    ctx.close()
