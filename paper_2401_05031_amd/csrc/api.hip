@@ -152,20 +152,33 @@ otas_status upload_plan(otas_ctx* c, const std::vector<int32_t>& host) {
 }
 
 struct WorkspaceLayout {
-  size_t xa, xb, h, qkv, hid, spare, part, sizes_a, sizes_b, src_list, row_ptr, total;
-  // columns per token row, the same where the two share a buffer.  spare: room that is free while the projection is still
-  // needed (the hidden rows, or what is left beside a shared buffer): the metric rows of queries too long for the merge
-  // plan's LDS, an f32 model's selection
-  size_t qkv_cols, hid_cols, spare_cols;
+  size_t xa, xb, h, qkv, hid, part, sizes_a, sizes_b, src_list, row_ptr, total;
+  size_t spare;      // what is left of the two buffers behind max(3 D, F) columns a row from qkv on
   int part_factor;   // float rows of the split-K buffer per token row
 };
 
-// The QKV projection is dead once the output projection has run, the MLP's hidden rows live only after it.  Batches for
-// which the two do not fit the L2s (32 MB) side by side keep them in one buffer: a block's working set is smaller by 3 D
-// columns a row, and more of what a kernel reads is still in the 256 MB last-level cache.  ViT-B, 64 queries (252 MB apart,
-// 174 shared; us per pass on MI355X): no merging 3014 -> 3003, r = 16 1954 -> 1944, prompts growing through the layers 3357
-// -> 3297; ViT-L, 128 queries 9569 -> 9497.  One query is quicker with two buffers (528, shared 531).
+// Where a block keeps its QKV projection, which is dead once the output projection has run, and its hidden rows, which live
+// only after it.  Blocks for which the two do not fit the L2s (32 MB) side by side keep them in the same rows: the working
+// set is smaller by 3 D columns a row, and more of what a kernel reads is still in the 256 MB last-level cache.  ViT-B, 64
+// queries (252 MB apart, 174 shared; us per pass on MI355X): no merging 3014 -> 3003, r = 16 1954 -> 1944, prompts growing
+// through the layers 3357 -> 3297; ViT-L, 128 queries 9569 -> 9497.  Small blocks are quicker with two buffers (one query 528,
+// shared 531), late ones of a merging batch too (204 queries of 37 tokens, r = 22, 843 us; shared throughout 853).
+// spare: room that is free while the projection is still needed (the hidden rows, or what is left beside shared rows): the
+// metric rows of queries too long for the merge plan's LDS, an f32 model's selection.
 constexpr size_t kSharedActBytes = (size_t)32 << 20;
+struct ActBuffers { char *qkv, *hid, *spare; size_t spare_cols; };
+// row0: the lane's first row; rows: what decides (the block's, or with several lanes, which are in different blocks at a
+// time and must agree, the whole batch's)
+ActBuffers act_buffers(const otas_model_desc& d, const WorkspaceLayout& w, char* ws, int64_t row0, int64_t rows) {
+  const size_t es = elem_size(d.dtype), qkv_cols = 3 * (size_t)d.D, hid_cols = (size_t)d.F;
+  if ((size_t)rows * (qkv_cols + hid_cols) * es <= kSharedActBytes) {
+    char* hid = ws + w.hid + (size_t)row0 * hid_cols * es;
+    return ActBuffers{ws + w.qkv + (size_t)row0 * qkv_cols * es, hid, hid, hid_cols};
+  }
+  char* act = ws + w.qkv + (size_t)row0 * std::max(qkv_cols, hid_cols) * es;
+  const size_t left = std::min(qkv_cols, hid_cols);
+  return ActBuffers{act, act, ws + w.spare + (size_t)row0 * left * es, left};
+}
 
 WorkspaceLayout forward_layout(const otas_model_desc& d, int64_t T0) {
   const size_t es = elem_size(d.dtype);
@@ -176,19 +189,9 @@ WorkspaceLayout forward_layout(const otas_model_desc& d, int64_t T0) {
   w.xa = take(rows * d.D * sizeof(float));   // the residual stream is float for every dtype
   w.xb = take(rows * d.D * sizeof(float));
   w.h = take(rows * d.D * es);
-  const bool share = rows * (3 * (size_t)d.D + d.F) * es > kSharedActBytes;
-  w.qkv_cols = 3 * (size_t)d.D;
-  w.hid_cols = (size_t)d.F;
-  w.qkv = take(rows * w.qkv_cols * es);
-  w.hid = take(rows * w.hid_cols * es);
-  w.spare = w.hid;
-  w.spare_cols = w.hid_cols;
-  if (share) {   // the size stays that of two buffers: what a workspace serves must not shrink as T0 falls below the limit
-    w.qkv_cols = w.hid_cols = (size_t)std::max(3 * d.D, d.F);
-    w.hid = w.qkv;
-    w.spare = w.qkv + rows * w.qkv_cols * es;
-    w.spare_cols = (size_t)std::min(3 * d.D, d.F);
-  }
+  w.qkv = take(rows * 3 * d.D * es);
+  w.hid = take(rows * d.F * es);
+  w.spare = w.qkv + rows * (size_t)std::max(3 * d.D, d.F) * es;
   w.part_factor = part_rows_factor(rows);
   w.part = take(d.dtype == OTAS_BF16 ? w.part_factor * rows * d.D * sizeof(float) : 0);   // split-K partial products
   w.sizes_a = take(rows * sizeof(int32_t));
@@ -787,9 +790,9 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       // the lane's rows of every buffer
       float* x_free[2] = {(float*)(ws + w.xa) + (size_t)ln.row0 * D, (float*)(ws + w.xb) + (size_t)ln.row0 * D};
       char* hbuf = ws + w.h + (size_t)ln.row0 * D * es;
-      char* qkv = ws + w.qkv + (size_t)ln.row0 * w.qkv_cols * es;   // [T][3 D] until the projection has run
-      char* hid = ws + w.hid + (size_t)ln.row0 * w.hid_cols * es;   // [T][F] after it, possibly the same rows
-      char* spare = ws + w.spare + (size_t)ln.row0 * w.spare_cols * es;   // free until FC1, also where the two share rows
+      const ActBuffers act = act_buffers(d, w, ws, ln.row0, G > 1 ? T0 : T);
+      char* qkv = act.qkv;   // [T][3 D] until the projection has run
+      char* hid = act.hid;   // [Tn][F] after it
       int32_t* sizes_buf[2] = {(int32_t*)(ws + w.sizes_a) + ln.row0, (int32_t*)(ws + w.sizes_b) + ln.row0};
       int32_t* src_list = (int32_t*)(ws + w.src_list) + ln.row0;
       int32_t* row_ptr = (int32_t*)(ws + w.row_ptr) + ln.row0 + g;   // one end entry per lane
@@ -814,11 +817,11 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       if (ln.any_merge[l] && plan_inline && !(dt == OTAS_F32 && c->timing)) {
         tail = linear_plan_tail_fits(dt, T, D, D, Bg);
         how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, tail);
-        tail = tail && how.na > 0 && (dt != OTAS_F32 || 8 * how.nb <= (int)(w.spare_cols * es));
+        tail = tail && how.na > 0 && (dt != OTAS_F32 || 8 * how.nb <= (int)(act.spare_cols * es));
         if (!tail) how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, false);
       }
       const bool fuse = how.na > 0;
-      float* sel_best = dt == OTAS_F32 ? (float*)spare : (float*)(ws + w.part) + (size_t)w.part_factor * ln.row0 * D;
+      float* sel_best = dt == OTAS_F32 ? (float*)act.spare : (float*)(ws + w.part) + (size_t)w.part_factor * ln.row0 * D;
       int32_t* sel_bcol = (int32_t*)(sel_best + (size_t)how.nb * T);
       if (fuse) {
         OTAS_LAUNCH_ON(K_ATTN, s,
@@ -838,7 +841,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
           OTAS_LAUNCH_ON(K_PLAN, ps,
                          launch_merge_plan(dt, qkv, 3 * (int64_t)D, D, H, dh, off_l, off_n, d_reff, d_tr, Bg,
                                            ln.max_n[l], n_lead, src_list, row_ptr, trace ? trace_src : nullptr,
-                                           trace ? trace_dst : nullptr, (float*)spare, ps));
+                                           trace ? trace_dst : nullptr, (float*)act.spare, ps));
           if (!plan_inline) OTAS_HIP(hipEventRecord(hw.ev_join, hw.side));
         }
         OTAS_LAUNCH_ON(K_ATTN, s,
@@ -992,8 +995,6 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
   char* ws = (char*)workspace;
   float* x_buf[2] = {(float*)(ws + w.xa), (float*)(ws + w.xb)};
   void* hbuf = ws + w.h;
-  void* qkv = ws + w.qkv;
-  void* hid = ws + w.hid;   // possibly the same rows: written once the projection has run
   const int32_t* d_prm_off = c->d_plan + (size_t)L * (B + 1);
   const size_t es = elem_size(dt);
 
@@ -1011,6 +1012,8 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
     const otas_layer_weights& wl = c->layers[l];
     const int32_t* off_l = c->d_plan + (size_t)l * (B + 1);
     const int64_t T = plan[(size_t)l * (B + 1) + B];
+    const ActBuffers act = act_buffers(d, w, ws, 0, T);
+    void *qkv = act.qkv, *hid = act.hid;
     if (l >= 1 && P_total > 0) {   // prompting module (cur >= 0 here: layer 0 wrote into the workspace)
       const char* pl = (const char*)prompts + (size_t)l * P_total * D * es;
       if (grow) {

@@ -17,13 +17,13 @@ pytestmark = pytest.mark.gpu
 def test_shared_activation_buffer_changes_nothing(lib, dtype, D, H, F, n, B):
     """Rows do not depend on the batch in these shapes (no split over K), so bit for bit; lanes own rows of every buffer."""
     import torch
-    cfg = synth.Config("shared", L=2, D=D, H=H, F=F, dtype=dtype, B=1, n0=n, strategies=[(0, 12)], seed=31)
+    cfg = synth.Config("shared", L=3, D=D, H=H, F=F, dtype=dtype, B=1, n0=n, strategies=[(0, 12)], seed=31)
     ctx, _ = hz.make_context(cfg)
     assert B * n * (3 * D + F) * (4 if dtype == "f32" else 2) > 32 << 20
     g = torch.Generator().manual_seed(5)
     x0 = torch.randn((B * n, D), generator=g).to("cuda").to(ctx.torch_dtype)
     off = np.arange(B + 1, dtype=np.int32) * n
-    R = [12 + q % 3 for q in range(B)]
+    R = [n // 3 + q % 3 for q in range(B)]     # the later blocks are below the line
     alone = {q: hz.gpu_forward(ctx, x0[q * n:(q + 1) * n].contiguous(), [0, n], [R[q]]) for q in (0, 1, B // 2, B - 1)}
     for lanes in (1, 3):
         ctx.otas_set_lanes(lanes)
