@@ -815,7 +815,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       bool tail = false;
       // (an f32 model under per-launch timing keeps the plan's launch and its record: same arithmetic, same bits)
       if (ln.any_merge[l] && plan_inline && !(dt == OTAS_F32 && c->timing)) {
-        tail = linear_plan_tail_fits(dt, T, D, D, Bg);
+        tail = linear_plan_tail_fits(dt, hbuf, wl.w_proj, T, D, D, Bg);
         how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, tail);
         tail = tail && how.na > 0 && (dt != OTAS_F32 || 8 * how.nb <= (int)(act.spare_cols * es));
         if (!tail) how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, false);

@@ -510,12 +510,17 @@ static bool f32_small_tiles(int64_t M, int N) {
   return ((M + 31) / 32) * ((N + 31) / 32) <= kF32SmallTiles;
 }
 
+// The direct-to-LDS kernel takes whole k-tiles and rows that begin on 16 bytes.
+static bool f32_dma_takes(const void* x, const void* w, int K) {
+  return K % 128 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w)) & 15) == 0;
+}
+
 // pt: the launch's first workgroups also write the lists of pt->B queries (f32 operands and EPI_RESIDUAL only).
 template <typename T>
 static hipError_t linear_f32(const void* x, const void* w, const void* bias, const float* res, void* y,
                              int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
   constexpr bool F32 = std::is_same<T, float>::value;
-  const bool small = f32_small_tiles(M, N), dma = F32 && !small && K % 128 == 0;
+  const bool small = f32_small_tiles(M, N), dma = F32 && !small && f32_dma_takes(x, w, K);
   if (pt && (!F32 || epi != EPI_RESIDUAL || !(small || dma))) return hipErrorInvalidValue;
   const int b = small ? 32 : 64, cols = (N + b - 1) / b;
   const dim3 grid(cols, (unsigned)((M + b - 1) / b + (pt ? (pt->B + cols - 1) / cols : 0)), 1), block(small ? 256 : 512);
@@ -1605,11 +1610,11 @@ hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bi
 // Whether the projection's launch has workgroup slots to spare for B list workgroups: they take a slot each (a
 // launch's dynamic LDS is the same for all its workgroups), so beside a launch that fills its last round they would
 // cost a round of their own (measured: + 5 us on such launches, what the selection-only plan saves beside attention).
-bool linear_plan_tail_fits(int dtype, int64_t M, int N, int K, int B) {
+bool linear_plan_tail_fits(int dtype, const void* x, const void* w, int64_t M, int N, int K, int B) {
   if (dtype == 0 && M > 0 && B > 0) {
     if (f32_small_tiles(M, N)) return true;   // at most two tiles per CU, room for eight
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    return K % 128 == 0 && tiles % 512 != 0 && tiles % 512 + B <= 512;
+    return f32_dma_takes(x, w, K) && tiles % 512 != 0 && tiles % 512 + B <= 512;
   }
   if (M <= 0 || B <= 0 || !(K % 32 == 0 && K >= 64 && N % 8 == 0)) return false;
   int bm = 128, bn = 128, slots = 768;

@@ -138,7 +138,7 @@ struct PlanTail {
 // the same launch the list phases of the merge plan for tail.B queries of at most max_n tokens.
 // hipErrorInvalidValue, having launched nothing, when no kernel with such a form takes the shape.  linear_plan_tail_fits: whether
 // the launch's last round has B workgroup slots to spare (pure host); if not, the lists are better written elsewhere.
-bool linear_plan_tail_fits(int dtype, int64_t M, int N, int K, int B);
+bool linear_plan_tail_fits(int dtype, const void* x, const void* w, int64_t M, int N, int K, int B);
 hipError_t launch_linear_plan_tail(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,
                                    int64_t M, int N, int K, const PlanTail& tail, int max_n, hipStream_t s);
 

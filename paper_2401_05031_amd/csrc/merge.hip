@@ -98,9 +98,9 @@ hipError_t launch_merge_plan_host(int dtype, const void* metric, int dm, const i
 constexpr int64_t kApplyThreads = 256 * 2048;   // what the chip holds at a time
 // A thread takes U chunks of an output row, `per` apart (per = chunks of a row / U, rounded up): the chain list bounds ->
 // sources -> rows costs the launch a round trip each per round of workgroups the chip holds, so a large call has fewer
-// threads with more loads each.  I: an integer that counts the threads (a division of 64 bits is 40 instructions).  11584 x
+// threads with more loads each.  11584 x
 // 768 rows out of 12608 (MI355X): 8.5 us with one chunk a thread and 64-bit indices, 8.2 so; a call 23.7 -> 23.35.
-template <typename T, int U, typename I>
+template <typename T, int U>
 __global__ __launch_bounds__(256) void merge_apply_kernel(const T* __restrict__ x, const int32_t* __restrict__ sizes,
                                                           const int32_t* __restrict__ src_list,
                                                           const int32_t* __restrict__ row_ptr, int64_t T_in,
@@ -108,10 +108,10 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(const T* __restrict__ 
                                                           int32_t* __restrict__ sizes_out) {
   constexpr int V = Vec<T>::N;
   const int chunks = D / V, per = (chunks + U - 1) / U;
-  const I t = (I)blockIdx.x * 256 + threadIdx.x;
-  const int64_t j = (int64_t)(t / (I)per);
+  const uint32_t t = blockIdx.x * 256 + threadIdx.x;   // a launch holds fewer than 2^32 threads
+  const int64_t j = t / (uint32_t)per;
   if (j >= T_out) return;
-  const int c0 = (int)(t - (I)j * (I)per);
+  const int c0 = (int)(t - (uint32_t)j * (uint32_t)per);
   const int beg = row_ptr[j];
   const int end = (j + 1 < T_out) ? row_ptr[j + 1] : (int)T_in;
   const int first = src_list[beg];
@@ -165,12 +165,12 @@ static hipError_t merge_apply(const void* x, const int32_t* sizes, const int32_t
   const int U = all > kApplyThreads ? 2 : 1;
   const int64_t tasks = T_out * ((chunks + U - 1) / U);
   const dim3 grid((unsigned)((tasks + 255) / 256)), block(256);
-#define OTAS_APPLY(UU, I)                                                                                        \
-  merge_apply_kernel<T, UU, I><<<grid, block, 0, s>>>((const T*)x, sizes, src_list, row_ptr, T_in, T_out, D,     \
-                                                      (T*)x_out, sizes_out)
-  if (U == 1) OTAS_APPLY(1, uint32_t);
-  else if (tasks < ((int64_t)1 << 32) - 256) OTAS_APPLY(2, uint32_t);
-  else OTAS_APPLY(2, uint64_t);
+  if (tasks > ((int64_t)1 << 32) - 256) return hipErrorInvalidValue;   // more threads than a launch holds
+#define OTAS_APPLY(UU)                                                                                          \
+  merge_apply_kernel<T, UU><<<grid, block, 0, s>>>((const T*)x, sizes, src_list, row_ptr, T_in, T_out, D,       \
+                                                   (T*)x_out, sizes_out)
+  if (U == 1) OTAS_APPLY(1);
+  else OTAS_APPLY(2);
 #undef OTAS_APPLY
   return hipGetLastError();
 }

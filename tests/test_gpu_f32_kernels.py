@@ -143,3 +143,22 @@ def test_fp32_gemm_large_tiles_every_epilogue(lib, N, K):
         assert bool(((out[M].double() - ref).abs() <= bound).all()), epi
         assert torch.equal(out[33], out[M][:33]), epi
     ctx.close()
+
+
+@pytest.mark.parametrize("which", ["x", "w"])
+def test_fp32_gemm_operands_that_do_not_begin_on_16_bytes(lib, which):
+    """A view four bytes into a buffer takes the kernel that stages through registers: the same rows bit for bit."""
+    import torch
+    ctx, dt = _context(lib, 64, 1, "f32")
+    M, N, K = 2100, 256, 256
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x, w = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
+    b = torch.randn(N, generator=g, device="cuda")
+    shift = lambda t: torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
+    want, got = torch.empty((M, N), device="cuda"), torch.full((M, N), float("nan"), device="cuda")
+    ctx.otas_linear_kernel(1, x, w, b, None, M, N, K, 0, want)
+    xs, ws = (shift(x), w) if which == "x" else (x, shift(w))
+    assert (xs.data_ptr() | ws.data_ptr()) & 15 == 4
+    ctx.otas_linear_kernel(1, xs, ws, b, None, M, N, K, 0, got)
+    assert torch.equal(want, got)
+    ctx.close()
