@@ -586,6 +586,17 @@ struct LaneRun {
   bool ln1_done;   // the previous block's split-K reduce already wrote this block's LN1 output
 };
 
+// What the row kernel in front of a linear of w [N, K] may read ahead.  A small batch's linears are one round of tiles whose first
+// k-tiles wait for a weight that lies in the last-level cache or in HBM, while the kernel before them leaves most CUs idle.
+// Up to 2048 rows that pays: one ViT-B query with r = 16 522 -> 506 us a pass (MI355X); with the shorter list phases of the
+// merge plan together, four queries 633 -> 603 (up to 512 rows only: 610), seven 745 -> 706 (720), one ViT-L query 1148 -> 1098,
+// one ViT-H query 2405 -> 2306 (32 workgroups: 2490, too few for 13 MB; 128: 2299).
+WarmWeight warm_weight(int dtype, const void* w, int64_t rows, int N, int K) {
+  if (dtype == OTAS_F32 || rows > 2048) return WarmWeight{};
+  const int64_t bytes = (int64_t)N * K * 2;
+  return WarmWeight{w, bytes, bytes > ((int64_t)8 << 20) ? 128 : 64};
+}
+
 otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, const void* x0, bool x0_is_float,
                        const int32_t* sizes_in, const int32_t* offsets, const int32_t* r, int32_t B, uint32_t flags,
                        void* workspace, size_t workspace_bytes, void* x_out, int32_t* sizes_out,
@@ -869,7 +880,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
         // merge-apply and the block's second LayerNorm in one pass over the rows
         OTAS_LAUNCH_ON(K_APPLY, s,
                        launch_merge_apply_ln(dt, (const float*)x_attn, ln.sizes_now, src_list, row_ptr, T, Tn, D,
-                                             (float*)x_other, sizes_next, wl.ln2_g, wl.ln2_b, hbuf, d.ln_eps, s));
+                                             (float*)x_other, sizes_next, wl.ln2_g, wl.ln2_b, hbuf, d.ln_eps, s,
+                                             warm_weight(dt, wl.w_fc1, Tn, F, D)));
         ln.sizes_now = sizes_next;
         x_mlp = x_other;
       } else {
@@ -889,7 +901,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
         OTAS_LAUNCH_ON(K_REDUCE, s,
                        launch_splitk_reduce_ln(part, S, wl.b_fc2, (const float*)x_mlp, (float*)x_next, Tn, D,
                                                more ? wn->ln1_g : nullptr, more ? wn->ln1_b : nullptr,
-                                               more ? (void*)hbuf : nullptr, d.ln_eps, s));
+                                               more ? (void*)hbuf : nullptr, d.ln_eps, s,
+                                               more ? warm_weight(dt, wn->w_qkv, Tn, 3 * D, D) : WarmWeight{}));
         ln.ln1_done = more;
       } else {
         OTAS_LAUNCH_ON(K_FC2, s, launch_linear(dt, hid, wl.w_fc2, wl.b_fc2, (const float*)x_mlp, x_next, Tn, D, F,

@@ -358,20 +358,25 @@ hipError_t launch_layer_norm_widen(const void* x_bf16, const void* g, const void
   return layer_norm_dispatch<bf16_t, bf16_t>(x_bf16, g, b, y, T, D, eps, s, job, x_float);
 }
 
-// ---------------------------------------------------------------------------------- merge-apply + LayerNorm
-// The merging module's data movement (Sec. II-C: size-weighted average of every surviving token
-// with the tokens merged into it, survivors in their original order) fused with the LayerNorm that
-// follows it in the block.  One wave per OUTPUT row: it gathers the rows listed for it
-// (row_ptr / src_list, the surviving row first, then its sources in ascending position), forms
-// sum(size * x) / sum(size) in fp32 in list order, writes the merged residual row and its size,
-// and normalises the row it still holds in registers.  Same arithmetic, in the same order, as
-// merge_apply_kernel followed by layer_norm_kernel.
+// Workgroups past the launch's rows read the weight of the next linear into the L2 of the XCD they run on (workgroup ids go
+// round the XCDs): of the eighth of its rows whose tiles that XCD will compute, one word of every cache line.
+__device__ inline void warm_weight(const WarmWeight& w, int first) {
+  const int e = (int)blockIdx.x - first, xcd = (int)blockIdx.x & 7, per = w.wgs >> 3;
+  const int64_t lines = w.bytes >> 7, beg = lines * xcd / 8, end = lines * (xcd + 1) / 8;
+  for (int64_t l = beg + (int64_t)(e >> 3) * 256 + threadIdx.x; l < end; l += (int64_t)per * 256) {
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(static_cast<const char*>(w.w) + (l << 7));
+    asm volatile("" ::"v"(v));
+  }
+}
+
 template <typename T, int NCH>
 __global__ __launch_bounds__(256) void merge_apply_ln_kernel(
     const float* __restrict__ x, const int32_t* __restrict__ sizes, const int32_t* __restrict__ src_list,
     const int32_t* __restrict__ row_ptr, int64_t T_in, int64_t T_out, int D, float* __restrict__ x_out,
-    int32_t* __restrict__ sizes_out, const T* __restrict__ g, const T* __restrict__ b, T* __restrict__ y, float eps) {
+    int32_t* __restrict__ sizes_out, const T* __restrict__ g, const T* __restrict__ b, T* __restrict__ y, float eps,
+    WarmWeight warm) {
   constexpr int V = 8;
+  if ((int)blockIdx.x >= (int)gridDim.x - warm.wgs) return warm_weight(warm, (int)gridDim.x - warm.wgs);
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + wave_index();
   if (row >= T_out) return;
@@ -479,12 +484,12 @@ template <typename T>
 static hipError_t merge_apply_ln_dispatch(const float* x, const int32_t* sizes, const int32_t* src_list,
                                           const int32_t* row_ptr, int64_t T_in, int64_t T_out, int D, float* x_out,
                                           int32_t* sizes_out, const void* g, const void* b, void* y, float eps,
-                                          hipStream_t s) {
+                                          hipStream_t s, const WarmWeight& warm) {
   const int nch = (D / 8 + 63) / 64;
-  dim3 grid((unsigned)((T_out + 3) / 4)), block(256);
+  dim3 grid((unsigned)((T_out + 3) / 4 + warm.wgs)), block(256);
 #define OTAS_MLN(N)                                                                                               \
   merge_apply_ln_kernel<T, N><<<grid, block, 0, s>>>(x, sizes, src_list, row_ptr, T_in, T_out, D, x_out, sizes_out, \
-                                                     (const T*)g, (const T*)b, (T*)y, eps)
+                                                     (const T*)g, (const T*)b, (T*)y, eps, warm)
   if (nch <= 1) OTAS_MLN(1);
   else if (nch <= 2) OTAS_MLN(2);
   else if (nch <= 3) OTAS_MLN(3);
@@ -497,12 +502,13 @@ static hipError_t merge_apply_ln_dispatch(const float* x, const int32_t* sizes, 
 
 hipError_t launch_merge_apply_ln(int dtype, const float* x, const int32_t* sizes, const int32_t* src_list,
                                  const int32_t* row_ptr, int64_t T_in, int64_t T_out, int D, float* x_out,
-                                 int32_t* sizes_out, const void* g, const void* b, void* y, float eps, hipStream_t s) {
+                                 int32_t* sizes_out, const void* g, const void* b, void* y, float eps, hipStream_t s,
+                                 const WarmWeight& warm) {
   if (T_out <= 0) return hipSuccess;
   return dtype == 0 ? merge_apply_ln_dispatch<float>(x, sizes, src_list, row_ptr, T_in, T_out, D, x_out, sizes_out, g,
-                                                     b, y, eps, s)
+                                                     b, y, eps, s, warm)
                     : merge_apply_ln_dispatch<bf16_t>(x, sizes, src_list, row_ptr, T_in, T_out, D, x_out, sizes_out,
-                                                      g, b, y, eps, s);
+                                                      g, b, y, eps, s, warm);
 }
 
 // ---------------------------------------------------------------------------------- split-K reduce + LayerNorm
@@ -515,8 +521,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(const float* __re
                                                                float* x_out, int64_t M, int D,
                                                                const bf16_t* __restrict__ g,
                                                                const bf16_t* __restrict__ b, bf16_t* __restrict__ y,
-                                                               float eps) {
+                                                               float eps, WarmWeight warm) {
   constexpr int V = 8;
+  if ((int)blockIdx.x >= (int)gridDim.x - warm.wgs) return warm_weight(warm, (int)gridDim.x - warm.wgs);
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + wave_index();
   if (row >= M) return;
@@ -599,19 +606,19 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(const float* __re
 
 hipError_t launch_splitk_reduce_ln(const float* part, int S, const void* bias, const float* res, float* x_out,
                                    int64_t M, int D, const void* g, const void* b, void* y, float eps,
-                                   hipStream_t s) {
+                                   hipStream_t s, const WarmWeight& warm) {
   if (M <= 0) return hipSuccess;
   if (S < 1 || D % 8 != 0) return hipErrorInvalidValue;
   const int nch = (D / 8 + 63) / 64;
-  dim3 grid((unsigned)((M + 3) / 4)), block(256);
+  dim3 grid((unsigned)((M + 3) / 4 + warm.wgs)), block(256);
 #define OTAS_RED(N)                                                                                              \
   do {                                                                                                           \
     if (y)                                                                                                       \
       splitk_reduce_ln_kernel<N, true><<<grid, block, 0, s>>>(part, S, (const bf16_t*)bias, res, x_out, M, D,    \
-                                                              (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)y, eps); \
+                                                              (const bf16_t*)g, (const bf16_t*)b, (bf16_t*)y, eps, warm); \
     else                                                                                                         \
       splitk_reduce_ln_kernel<N, false><<<grid, block, 0, s>>>(part, S, (const bf16_t*)bias, res, x_out, M, D,   \
-                                                               nullptr, nullptr, nullptr, eps);                  \
+                                                               nullptr, nullptr, nullptr, eps, warm);            \
   } while (0)
   if (nch <= 1) OTAS_RED(1);
   else if (nch <= 2) OTAS_RED(2);

@@ -101,9 +101,11 @@ hipError_t launch_linear_kernel(int kernel, int dtype, const void* x, const void
 int splitk_factor(int dtype, int64_t M, int N, int K, int max_split = 8);
 hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64_t M, int N, int K, int S,
                                 hipStream_t s);
+// A weight that workgroups beside a launch's own read into the L2s for the next linear (wgs = 0: none).
+struct WarmWeight { const void* w = nullptr; int64_t bytes = 0; int wgs = 0; };
 hipError_t launch_splitk_reduce_ln(const float* part, int S, const void* bias, const float* res, float* x_out,
                                    int64_t M, int D, const void* g, const void* b, void* y, float eps,
-                                   hipStream_t s);
+                                   hipStream_t s, const WarmWeight& warm = WarmWeight{});
 
 hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
                             const int32_t* d_off, int B, int max_n, int D, int H, bool size_bias,
@@ -170,6 +172,6 @@ hipError_t launch_merge_apply(int dtype, const void* x, const int32_t* sizes,
 hipError_t launch_merge_apply_ln(int dtype, const float* x, const int32_t* sizes, const int32_t* src_list,
                                  const int32_t* row_ptr, int64_t T_in, int64_t T_out, int D, float* x_out,
                                  int32_t* sizes_out, const void* g, const void* b, void* y, float eps,
-                                 hipStream_t s);
+                                 hipStream_t s, const WarmWeight& warm = WarmWeight{});
 
 }  // namespace otas

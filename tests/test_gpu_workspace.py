@@ -43,3 +43,19 @@ def test_workspace_bytes_never_shrink_as_a_batch_grows(lib):
     sizes = [ctx.otas_workspace_bytes(4, T) for T in range(line - 2048, line + 2048, 64)]
     assert sizes == sorted(sizes)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,F", [(72, 136), (64, 8)])
+def test_weights_read_ahead_change_nothing(lib, D, F):
+    """Up to 2048 rows merge-apply's launch also reads FC1's weight (here of 153 and 8 cache lines, dealt to eight parts):
+    the rows are those of a batch above the line."""
+    import torch
+    n, B = 30, 80
+    cfg = synth.Config("warm", L=2, D=D, H=1, F=F, dtype="bf16", B=1, n0=n, seed=5)
+    ctx, _ = hz.make_context(cfg)
+    x0 = torch.randn((B * n, D), generator=torch.Generator().manual_seed(2)).to("cuda").to(ctx.torch_dtype)
+    many = hz.gpu_forward(ctx, x0, np.arange(B + 1, dtype=np.int32) * n, [5] * B)
+    for q in (0, B - 1):
+        one = hz.gpu_forward(ctx, x0[q * n:(q + 1) * n].contiguous(), [0, n], [5])
+        assert np.array_equal(one["x"][0], many["x"][q]) and np.array_equal(one["sizes"][0], many["sizes"][q])
+    ctx.close()
