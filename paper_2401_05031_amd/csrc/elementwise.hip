@@ -369,6 +369,14 @@ __device__ inline void warm_weight(const WarmWeight& w, int first) {
   }
 }
 
+// ---------------------------------------------------------------------------------- merge-apply + LayerNorm
+// The merging module's data movement (Sec. II-C: size-weighted average of every surviving token
+// with the tokens merged into it, survivors in their original order) fused with the LayerNorm that
+// follows it in the block.  One wave per OUTPUT row: it gathers the rows listed for it
+// (row_ptr / src_list, the surviving row first, then its sources in ascending position), forms
+// sum(size * x) / sum(size) in fp32 in list order, writes the merged residual row and its size,
+// and normalises the row it still holds in registers.  Same arithmetic, in the same order, as
+// merge_apply_kernel followed by layer_norm_kernel.
 template <typename T, int NCH>
 __global__ __launch_bounds__(256) void merge_apply_ln_kernel(
     const float* __restrict__ x, const int32_t* __restrict__ sizes, const int32_t* __restrict__ src_list,
