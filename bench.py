@@ -31,6 +31,9 @@ RATED_MHZ = 2400.0             # the clock the data-sheet peaks are quoted at
 BASELINE_METRIC = "images/sec per (prompts, r) strategy, ViT-B/16 batch 64 bf16; merge-kernel HBM GB/s"
 
 
+READ_AHEAD_ROWS = 4096     # kWarmRows of the library
+
+
 def algorithmic_work(cfg, lengths0, r, otas, ctx):
     """Per-kind algorithmic FLOPs / bytes of ONE forward, from the host-known length schedule and the
     library's own split-K decision (which decides whether a block's first LayerNorm is a launch of its
@@ -53,6 +56,8 @@ def algorithmic_work(cfg, lengths0, r, otas, ctx):
          # method itself needs: token rows in and out, the metric rows, sizes in and out)
          "merge_apply_method_bytes": 0.0, "merge_apply_method_bytes_per_layer": [],
          "layer_norm_method_bytes": 0.0, "splitk_reduce_method_bytes": 0.0}
+    # bf16 launches of up to READ_AHEAD_ROWS rows also read the next linear's weight
+    ahead = lambda rows, n_out: n_out * D * e if e == 2 and rows <= READ_AHEAD_ROWS else 0
     ln1_fused = False
     for l in range(L):
         w["gemm_qkv"] += 2.0 * T[l] * D * 3 * D
@@ -65,7 +70,7 @@ def algorithmic_work(cfg, lengths0, r, otas, ctx):
             w["layer_norm_method_bytes"] += T[l] * D * 2.0 * e
         if Tm[l] != T[l]:
             # merge-apply fused with LN2: float rows in and out, a size and a list entry per row, operand row out
-            b = (T[l] + Tm[l]) * (D * 4.0 + 8.0) + Tm[l] * D * e
+            b = (T[l] + Tm[l]) * (D * 4.0 + 8.0) + Tm[l] * D * e + ahead(Tm[l], F)
             w["merge_apply_bytes"] += b
             w["merge_apply_bytes_per_layer"].append(b)
             bm = (T[l] + Tm[l]) * D * e + T[l] * (D // H) * e + 4.0 * (T[l] + Tm[l])
@@ -79,6 +84,7 @@ def algorithmic_work(cfg, lengths0, r, otas, ctx):
         ln1_fused = S > 1 and l + 1 < L
         if S > 1:   # S float partial rows + residual row in, residual row out, next block's operand row out
             w["splitk_reduce_bytes"] += Tm[l] * D * (4.0 * (S + 2) + (e if l + 1 < L else 0))
+            w["splitk_reduce_bytes"] += ahead(Tm[l], 3 * D) if l + 1 < L else 0
             w["splitk_reduce_method_bytes"] += Tm[l] * D * (e * 2 + (e if l + 1 < L else 0))   # residual in/out, operand out
     w["T"] = T.tolist()
     w["Tm"] = [int(v) for v in Tm]
@@ -311,7 +317,8 @@ def rooflines(res):
         if k[n][1] > 0:
             out[n] = {"avg_launch_us": round(k[n][0] * 1e3 / k[n][1], 2), "launches_per_step": k[n][1]}
     out["note_hbm_kernels"] = ("achieved / frac count the bytes these kernels move with the float residual stream "
-                               "(4 B per element of a token row); frac_on_method_bytes prices the same launches at "
+                               "(4 B per element of a token row) and, in launches of up to 4096 rows, of the next "
+                               "linear's weight, which they read ahead; frac_on_method_bytes prices the same launches at "
                                "what the method needs with rows in the model's dtype (2 B): the gap is the cost of "
                                "keeping the residual in float")
     out["kernel_ms_per_step"] = {n: round(v[0], 4) for n, v in k.items()}

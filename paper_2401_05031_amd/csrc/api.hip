@@ -587,12 +587,18 @@ struct LaneRun {
 };
 
 // What the row kernel in front of a linear of w [N, K] may read ahead.  A small batch's linears are one round of tiles whose first
-// k-tiles wait for a weight that lies in the last-level cache or in HBM, while the kernel before them leaves most CUs idle.
-// Up to 2048 rows that pays: one ViT-B query with r = 16 522 -> 506 us a pass (MI355X); with the shorter list phases of the
-// merge plan together, four queries 633 -> 603 (up to 512 rows only: 610), seven 745 -> 706 (720), one ViT-L query 1148 -> 1098,
-// one ViT-H query 2405 -> 2306 (32 workgroups: 2490, too few for 13 MB; 128: 2299).
+// k-tiles wait for a weight that lies in HBM, while the kernel before them leaves HBM idle.  A weight that is in the
+// 256 MB last-level cache from the pass before gains nothing and loses nothing (one ViT-B model over and over, up to eight
+// queries: 472 / 472, 602 / 602, 758 / 760 us a pass without / with).  MI355X, us a pass without reading ahead, then up to 512, 1024,
+// 2048, 4096 rows: eight ViT-B models in turn, r = 12, one query 532, 513, 513, 513, 513, four 655, 644, 634, 634, 634, eight 831,
+// 830, 819, 803, 802, 24 1299, 1299, 1298, 1293, 1276; ViT-L, r = 7, three 1382, 1329, 1321, 1321, 1321, twenty 2897, 2895, 2889,
+// 2873, 2860; ViT-H, r = 7, four 3447, 3387, 3257, 3258, 3257, ten 4739, 4732, 4677, 4603, 4571.  Past that the linears have the
+// rounds to cover it themselves: up to 4096, 6144, 8192 rows, any, ViT-B 28 queries 1381, 1373, 1374, 1374, 64 of which half merge
+// 2939, 2936, 2938, 2962, ViT-L 45 4747, 4756, 4759, 4763, 80 7212, 7217, 7220, 7259, ViT-H 60 13775, 13771, 13784, 13812.
+// 64 workgroups, 128 for weights of more than 8 MB (one ViT-H query 2299 with 128, 2306 with 64, 2490 with 32).
+constexpr int64_t kWarmRows = 4096;
 WarmWeight warm_weight(int dtype, const void* w, int64_t rows, int N, int K) {
-  if (dtype == OTAS_F32 || rows > 2048) return WarmWeight{};
+  if (dtype == OTAS_F32 || rows > kWarmRows) return WarmWeight{};
   const int64_t bytes = (int64_t)N * K * 2;
   return WarmWeight{w, bytes, bytes > ((int64_t)8 << 20) ? 128 : 64};
 }

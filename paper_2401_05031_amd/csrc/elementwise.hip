@@ -358,12 +358,13 @@ hipError_t launch_layer_norm_widen(const void* x_bf16, const void* g, const void
   return layer_norm_dispatch<bf16_t, bf16_t>(x_bf16, g, b, y, T, D, eps, s, job, x_float);
 }
 
-// Workgroups past the launch's rows read the weight of the next linear into the L2 of the XCD they run on (workgroup ids go
-// round the XCDs): of the eighth of its rows whose tiles that XCD will compute, one word of every cache line.
+// Workgroups past the launch's rows read the weight of the next linear, one word of every cache line once.  What that gains is
+// the way from HBM to the last-level cache under a kernel that leaves HBM idle: the lines end up in one XCD's L2, and
+// which one does not matter (each XCD the columns of its own tiles: 0 - 4 % slower from 800 rows on, as those
+// overlap and the weight is read two to four times).
 __device__ inline void warm_weight(const WarmWeight& w, int first) {
-  const int e = (int)blockIdx.x - first, xcd = (int)blockIdx.x & 7, per = w.wgs >> 3;
-  const int64_t lines = w.bytes >> 7, beg = lines * xcd / 8, end = lines * (xcd + 1) / 8;
-  for (int64_t l = beg + (int64_t)(e >> 3) * 256 + threadIdx.x; l < end; l += (int64_t)per * 256) {
+  const int64_t lines = w.bytes >> 7;
+  for (int64_t l = (int64_t)((int)blockIdx.x - first) * 256 + threadIdx.x; l < lines; l += (int64_t)w.wgs * 256) {
     const uint32_t v = *reinterpret_cast<const uint32_t*>(static_cast<const char*>(w.w) + (l << 7));
     asm volatile("" ::"v"(v));
   }

@@ -101,7 +101,7 @@ hipError_t launch_linear_kernel(int kernel, int dtype, const void* x, const void
 int splitk_factor(int dtype, int64_t M, int N, int K, int max_split = 8);
 hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64_t M, int N, int K, int S,
                                 hipStream_t s);
-// A weight that workgroups beside a launch's own read into the L2s for the next linear (wgs = 0: none).
+// A weight that wgs workgroups beside a launch's own read into the last-level cache for the next linear (wgs = 0: none).
 struct WarmWeight { const void* w = nullptr; int64_t bytes = 0; int wgs = 0; };
 hipError_t launch_splitk_reduce_ln(const float* part, int S, const void* bias, const float* res, float* x_out,
                                    int64_t M, int D, const void* g, const void* b, void* y, float eps,

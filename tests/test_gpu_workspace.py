@@ -1,5 +1,7 @@
 """Batches whose QKV projection and hidden rows share one workspace buffer: a query's rows are those of the query alone,
 for which the two lie apart."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -47,15 +49,55 @@ def test_workspace_bytes_never_shrink_as_a_batch_grows(lib):
 
 @pytest.mark.parametrize("D,F", [(72, 136), (64, 8)])
 def test_weights_read_ahead_change_nothing(lib, D, F):
-    """Up to 2048 rows merge-apply's launch also reads FC1's weight (here of 153 and 8 cache lines, dealt to eight parts):
-    the rows are those of a batch above the line."""
+    """Up to 4096 rows merge-apply's launch also reads FC1's weight (here of 153 and 8 cache lines): the rows are those of a
+    batch that is above the line after every merge."""
     import torch
-    n, B = 30, 80
-    cfg = synth.Config("warm", L=2, D=D, H=1, F=F, dtype="bf16", B=1, n0=n, seed=5)
+    n, r, B, L = 30, 5, 220, 2
+    assert B * (n - L * r) > 4096 > n
+    cfg = synth.Config("warm", L=L, D=D, H=1, F=F, dtype="bf16", B=1, n0=n, seed=5)
     ctx, _ = hz.make_context(cfg)
     x0 = torch.randn((B * n, D), generator=torch.Generator().manual_seed(2)).to("cuda").to(ctx.torch_dtype)
-    many = hz.gpu_forward(ctx, x0, np.arange(B + 1, dtype=np.int32) * n, [5] * B)
+    many = hz.gpu_forward(ctx, x0, np.arange(B + 1, dtype=np.int32) * n, [r] * B)
     for q in (0, B - 1):
-        one = hz.gpu_forward(ctx, x0[q * n:(q + 1) * n].contiguous(), [0, n], [5])
+        one = hz.gpu_forward(ctx, x0[q * n:(q + 1) * n].contiguous(), [0, n], [r])
         assert np.array_equal(one["x"][0], many["x"][q]) and np.array_equal(one["sizes"][0], many["sizes"][q])
     ctx.close()
+
+
+class WarmWeight(ctypes.Structure):
+    _fields_ = [("w", ctypes.c_void_p), ("bytes", ctypes.c_int64), ("wgs", ctypes.c_int)]
+
+
+@pytest.mark.parametrize("wgs,lines", [(64, 8), (64, 153), (64, 64 * 256 + 1), (128, 100 * 1024)])
+@pytest.mark.parametrize("M,D", [(1, 64), (30, 72), (197, 768), (5, 1280)])
+def test_launches_with_and_without_read_ahead(lib, M, D, wgs, lines):
+    """Merge-apply and both forms of the split-K reduce, each with and without the workgroups that read a weight: fewer lines
+    than workgroups, a line past whole rounds of them, a weight of more than 8 MB; the same bits, the weight as it was."""
+    import paper_2401_05031_amd as otas
+    import torch
+    so = ctypes.CDLL(otas.lib_path())
+    g = torch.Generator(device="cuda").manual_seed(M + D + lines)
+    rand = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    w = torch.randint(-99, 99, (lines * 32,), generator=g, device="cuda", dtype=torch.int32)
+    x, part, S = rand(2 * M, D), rand(3, M, D), 3
+    gamma, beta, bias = (rand(D).to(torch.bfloat16) for _ in range(3))
+    src = torch.arange(2 * M, device="cuda", dtype=torch.int32)       # row j: the average of rows 2 j and 2 j + 1
+    ptr = torch.arange(M, device="cuda", dtype=torch.int32) * 2
+    p = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else None)
+    stream, kept = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), w.clone()
+
+    def launches(warm):
+        xo, y = torch.full((3, M, D), float("nan"), device="cuda"), torch.zeros((2, M, D), device="cuda", dtype=torch.bfloat16)
+        sizes = torch.zeros(M, device="cuda", dtype=torch.int32)
+        assert so._ZN4otas21launch_merge_apply_lnEiPKfPKiS3_S3_lliPfPiPKvS7_PvfP12ihipStream_tRKNS_10WarmWeightE(
+            1, p(x), p(None), p(src), p(ptr), ctypes.c_int64(2 * M), ctypes.c_int64(M), D, p(xo[0]), p(sizes), p(gamma),
+            p(beta), p(y[0]), ctypes.c_float(1e-6), stream, ctypes.byref(warm)) == 0
+        for i, (ga, be, out) in enumerate([(gamma, beta, y[1]), (None, None, None)]):
+            assert so._ZN4otas23launch_splitk_reduce_lnEPKfiPKvS1_PfliS3_S3_PvfP12ihipStream_tRKNS_10WarmWeightE(
+                p(part), S, p(bias), p(x), p(xo[1 + i]), ctypes.c_int64(M), D, p(ga), p(be), p(out), ctypes.c_float(1e-6),
+                stream, ctypes.byref(warm)) == 0
+        return xo, y, sizes
+
+    plain, warm = launches(WarmWeight(None, 0, 0)), launches(WarmWeight(w.data_ptr(), lines * 128, wgs))
+    assert all(torch.equal(a, b) for a, b in zip(plain, warm)) and torch.equal(w, kept)
+    assert torch.equal(plain[0][1], plain[0][2]) and bool((plain[2] == 2).all())
