@@ -820,8 +820,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       ln.ln1_done = false;
       OTAS_LAUNCH_ON(K_QKV, s, launch_linear(dt, hbuf, wl.w_qkv, wl.b_qkv, nullptr, qkv, T, 3 * D, D, EPI_NONE, s));
       // Attention and the merge plan both read only the QKV projection.  On one stream two kernels never overlap,
-      // so where the plan stays on this stream and one kernel can hold both (bf16, head width 64), they go out
-      // as ONE launch whose first workgroups are the plan's; it is recorded as an attention launch.
+      // so where the plan stays on this stream and one kernel can hold both (bf16 models of head width 64, f32 models), they
+      // go out as ONE launch whose first workgroups are the plan's; it is recorded as an attention launch.
       // Where the projection's launch below has workgroup slots to spare, the fused launch runs only the plan's
       // selection (the long part: keys, similarities, best matches) and the lists, which need nothing else, are
       // written by extra workgroups of the projection's launch: the plan's serial chain beside attention gets
@@ -830,8 +830,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       // at least; an f32 model, which has none, keeps it where the hidden rows will be.
       FusedPlan how = {0, 0};
       bool tail = false;
-      // (an f32 model under per-launch timing keeps the plan's launch and its record: same arithmetic, same bits)
-      if (ln.any_merge[l] && plan_inline && !(dt == OTAS_F32 && c->timing)) {
+      if (ln.any_merge[l] && plan_inline) {
         tail = linear_plan_tail_fits(dt, hbuf, wl.w_proj, T, D, D, Bg);
         how = attention_plan_how(dt, Bg, ln.max_n[l], D, H, tail);
         tail = tail && how.na > 0 && (dt != OTAS_F32 || 8 * how.nb <= (int)(act.spare_cols * es));
