@@ -1269,16 +1269,20 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
                                       M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
-// Whether a bf16 output is written past the L2's replacement (non-temporal stores): the launch itself is about 2 us shorter
-// from 20 MB up (its panels stay in the L2, and less of the output is left to write back when it ends), but what reads the
-// output next finds less of it there.  In a ViT-B pass of 64 queries with r = 16 (MI355X, us, with / without; the next kernel):
-// FC1 of 8512 rows (52 MB) 49.9 / 52.1 (second linear 54.2 / 53.7), 5440 (33 MB) 30.6 / 32.6 (48.9 / 49.8), 11584 (71 MB) 65.2 /
-// 65.2 (77.4 / 74.5); QKV of 4416 rows (20 MB) 20.8 / 21.6 (attention 12.2 / 12.2), 6464 (30 MB) 24.4 / 25.1 (15.6 / 15.3), 12608
-// (58 MB) 47.4 / 46.3 (31.8 / 28.6).  An output that the 256 MB last-level cache cannot hold is not found there anyway: ViT-H,
-// 256 queries 62479 -> 61694 us a pass.
+// Whether a bf16 output is written past the L2's replacement (non-temporal stores): the launch's panels stay in the L2s and less
+// of the output is left to write back when it ends, but what reads the output next finds less of it there.  Measured
+// inside ViT passes of 1500 ... 68000 rows at D = 768, 1024 and 1280 (MI355X; us per block, streamed less not streamed,
+// ranges over the sizes and widths):
+//   QKV   16 - 26 MB -0.9 ... +0.6, 26 - 32 +0.1 ... +1.8, 32 - 128 -0.5 ... +7.7 (mean +3), 135 - 165 -2.6 ... +1.8, 168 - 256 -12 ... +3.2
+//         (mean -5), above -10 ... +0.4
+//   GELU  16 - 32 MB at D = 768 -1.6 ... +4.7 (mean +0.9 without merging, -0.3 with), at 1024 and 1280 -2.6 ... +1.3 (mean -1.1);
+//         32 - 64 -4.2 ... +1.5 (mean -1.8), 65 - 157 -4.5 ... +9.2 (mean +2.6), 163 - 170 -8.9 ... +3.4, above -29 ... -6
+// So: outputs that the 256 MB last-level cache cannot hold beside the rest, and those behind GELU that are more than half of
+// the L2s (32 MB) and up to a quarter of the last-level cache.  The 256-wide kernels are picked from about 16 MB on.
 static bool streams_output(int64_t M, int N, int epi) {
+  constexpr int64_t MB = 1 << 20;
   const int64_t bytes = 2 * M * N;
-  return bytes <= ((int64_t)(epi == EPI_GELU ? 56 : 32) << 20) || bytes > (int64_t)256 << 20;
+  return bytes > 160 * MB || (epi == EPI_GELU && bytes > 16 * MB && bytes <= 64 * MB);
 }
 
 template <int RB>
@@ -1295,7 +1299,7 @@ static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bia
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
                                   (typename OutType<bf16_t, E>::type*)y, M, N, K, tiles_m, tiles_n,               \
-                                  streams_output(M, N, epi), pt ? *pt : PlanTail{});                                                         \
+                                  streams_output(M, N, epi), pt ? *pt : PlanTail{});                                            \
   } while (0)
   if (pt) {
     if (epi != EPI_RESIDUAL) return hipErrorInvalidValue;

@@ -42,18 +42,22 @@ def test_tile_heights_at_their_edges(lib, kernel, K):
     ctx.close()
 
 
-@pytest.mark.parametrize("epi,M,N", [(0, 16391, 1016), (0, 16400, 1024), (1, 14341, 2040), (1, 14400, 2048)])
+MB = 1 << 20
+
+
+@pytest.mark.parametrize("epi,N,line", [(0, 1024, 160 * MB), (1, 1024, 16 * MB), (1, 2048, 64 * MB), (1, 2048, 160 * MB)])
 @pytest.mark.parametrize("kernel", sorted(ROWS))
-def test_outputs_on_both_sides_of_the_streaming_rule(lib, kernel, epi, M, N):
-    """Outputs just under and just over 32 MB (56 MB with GELU): stored past the L2's replacement or not, the same rows as
-    the 128 x 128 kernel's."""
+def test_outputs_on_both_sides_of_the_streaming_rule(lib, kernel, epi, N, line):
+    """Outputs of just the bytes at which the rule changes, one row fewer and one more: stored past the L2's replacement or
+    not, the same rows as the 128 x 128 kernel's."""
     import torch
-    ctx, K = _context(), 128
-    g = torch.Generator(device="cuda").manual_seed(M)
-    x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
-    out = {}
-    for k in (kernel, 3):
-        out[k] = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-        ctx.otas_linear_kernel(k, x, w, b, None, M, N, K, epi, out[k])
-    assert torch.equal(out[kernel], out[3])
+    ctx, K, most = _context(), 128, line // (2 * N) + 1
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((most, K), (N, K), (N,)))
+    want = torch.empty((most, N), dtype=torch.bfloat16, device="cuda")
+    ctx.otas_linear_kernel(3, x, w, b, None, most, N, K, epi, want)
+    for M in (most - 2, most - 1, most):
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ctx.otas_linear_kernel(kernel, x, w, b, None, M, N, K, epi, out)
+        assert torch.equal(out, want[:M]), M
     ctx.close()
