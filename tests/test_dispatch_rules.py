@@ -47,3 +47,45 @@ def test_workgroups_of_the_selection():
         for max_n in (2, 3, 64, 65, 66, 197, 1024):
             p = how(1, B, max_n, 256, 4, True)
             assert 1 <= p.na <= ((max_n + 1) // 2 + 31) // 32 and 1 <= p.nb <= (max_n // 2 + 31) // 32
+
+
+def _choice():
+    choice = _library()._ZN4otas20linear_kernel_choiceEiliii
+    choice.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
+    return choice
+
+
+# the ids of otas_linear_kernel
+K128, H160, H192, H224, H256, H288, H320, T64 = 3, 8, 4, 9, 5, 10, 6, 7
+
+
+def test_kernels_of_the_products_of_a_block_are_fixed():
+    """What the cost model picks for QKV, FC1, the projection and the second linear at a range of rows: a change of its
+    constants shows here."""
+    rows = (200, 700, 1500, 2600, 4000, 6000, 9000, 12000, 15000, 20000, 30000, 50000)
+    want = {768: [[T64, T64, K128, K128, H160, H224, H192, H224, H288, H256, H288, H256],
+                  [T64, T64, K128, K128, H192, H288, H224, H288, H256, H320, H288, H320],
+                  [T64, T64, T64, T64, T64, K128, K128, H160, H192, H256, H192, H320],
+                  [T64, T64, T64, T64, T64, K128, K128, H160, H192, H256, H192, H320]],
+            1024: [[T64, T64, K128, K128, H192, H288, H224, H288, H256, H320, H288, H320],
+                   [T64, T64, K128, H192, H256, H192, H288, H256, H320, H320, H320, H320],
+                   [T64, T64, T64, T64, T64, K128, H160, H192, H256, H320, H256, H288],
+                   [T64, T64, T64, T64, K128, K128, H160, H192, H256, H320, H256, H288]],
+            1280: [[T64, T64, K128, H160, H256, H192, H288, H256, H320, H320, H320, H320],
+                   [T64, K128, K128, H224, H160, H256, H256, H320, H320, H320, H320, H320],
+                   [T64, T64, T64, K128, K128, K128, H192, H256, H320, H224, H320, H256],
+                   [T64, T64, T64, K128, K128, K128, H192, H256, H320, H224, H320, H256]]}
+    choice = _choice()
+    for D, lists in want.items():
+        products = [(3 * D, D, 0), (4 * D, D, 1), (D, D, 2), (D, 4 * D, 2)]
+        assert [[choice(1, M, N, K, epi) for M in rows] for N, K, epi in products] == lists, D
+
+
+def test_small_tiles_stay_within_four_workgroups_per_cu():
+    """The 64 x 64 kernel's cost is known for up to 1024 tiles; past them it is not picked, whatever the width."""
+    choice = _choice()
+    for D in (128, 192, 256, 512, 768, 1280):
+        for N, K, epi in ((3 * D, D, 0), (4 * D, D, 1), (D, D, 2), (D, 4 * D, 2)):
+            most = 1024 // ((N + 63) // 64) * 64        # rows
+            assert choice(1, most + 1, N, K, epi) != T64 and choice(1, 64, N, K, epi) == T64
+            assert all(choice(1, M, N, K, epi) != T64 for M in (2 * most + 5, 10 * most, 100 * most))
