@@ -119,7 +119,7 @@ __device__ __forceinline__ bool plan_tail_or_tile_row(const PlanTail& pt, unsign
 // Measured on MI355X (us; tiles of 4 x 4 FMAs per thread on the vector ALU, gemm_f32_kernel, gemm_f32_dma_kernel): 1206 x 768
 // x 3072 + residual 205, 68, 48; 1206 x 3072 x 768 + GELU 90, 73, 53; 1206 x 2304 x 768 -, 54, 40; 1206 x 768 x 768 + residual
 // -, 20.7, 16.2.  gemm_f32_small_kernel: 402 x 192 x 768 51 -> 9, 402 x 576 x 192 16 -> 5.
-constexpr int kF32SmallTiles = 512;
+constexpr int kF32SmallTiles = 512, kF32SmallTilesStaged = 600;
 __host__ __device__ static inline int f32_quarter(int K) { return ((K + 3) / 4 + 31) & ~31; }
 
 // Four consecutive outputs of row m from column n (N % 8 == 0: inside or outside as a whole).
@@ -503,11 +503,16 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const T* __restrict
   f32_epilogue4<T, EPI>(v, bias, res, Y, m0 + r, n0 + c, M, N);
 }
 
-static bool f32_small_tiles(int64_t M, int N) {
-  // Up to two workgroups per CU the small tiles finish first, a third round of them is slower than the large tiles' one.
+// dma: whether the large tiles would be gemm_f32_dma_kernel's.
+static bool f32_small_tiles(int64_t M, int N, bool dma) {
+  // Up to two workgroups per CU the small tiles finish first, a third round of them is slower than the large tiles' one if
+  // those go straight into LDS, about as fast as that of the staged kernel.
   // Measured (us, small against gemm_f32_dma_kernel): K = 768 240 small tiles 8.9 / 15.9, 312 15.6 / 16.2, 504 15.4 / 16.1,
-  // 528 21.3 / 16.1; K = 3072 240 small tiles 25.5 / 51.8, 312 49.0 / 52.2, 528 71.5 / 52.6.
-  return ((M + 31) / 32) * ((N + 31) / 32) <= kF32SmallTiles;
+  // 528 21.3 / 16.1; K = 3072 240 small tiles 25.5 / 51.8, 312 49.0 / 52.2, 528 71.5 / 52.6.  Against gemm_f32_kernel, 504, 552, 624,
+  // 768 small tiles: f32, K = 192 6.2 / 9.1, 8.4 / 9.3, 8.5 / 9.4, 10.8 / 9.7; 776 14.7 / 22.5, 19.4 / 22.6, 19.5 / 22.7, 20.7 / 22.9; 1056 20.6 /
+  // 27.4, 29.4 / 27.5, 29.7 / 27.6, 29.8 / 27.9; 3080 43.0 / 68.9, 60.5 / 68.6, 61.3 / 69.0, 61.7 / 69.1; bf16, K = 776 15.1 / 22.6, 20.3 / 22.7, 20.7 /
+  // 22.7, 25.9 / 22.9; 3080 46.4 / 69.9, 67.8 / 69.8, 68.5 / 69.8, 69.1 / 70.1.
+  return ((M + 31) / 32) * ((N + 31) / 32) <= (dma ? kF32SmallTiles : kF32SmallTilesStaged);
 }
 
 // The direct-to-LDS kernel takes whole k-tiles and rows that begin on 16 bytes.
@@ -520,7 +525,7 @@ template <typename T>
 static hipError_t linear_f32(const void* x, const void* w, const void* bias, const float* res, void* y,
                              int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
   constexpr bool F32 = std::is_same<T, float>::value;
-  const bool small = f32_small_tiles(M, N), dma = F32 && !small && f32_dma_takes(x, w, K);
+  const bool can_dma = F32 && f32_dma_takes(x, w, K), small = f32_small_tiles(M, N, can_dma), dma = can_dma && !small;
   if (pt && (!F32 || epi != EPI_RESIDUAL || !(small || dma))) return hipErrorInvalidValue;
   const int b = small ? 32 : 64, cols = (N + b - 1) / b;
   const dim3 grid(cols, (unsigned)((M + b - 1) / b + (pt ? (pt->B + cols - 1) / cols : 0)), 1), block(small ? 256 : 512);
@@ -1615,9 +1620,10 @@ hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bi
 // cost a round of their own (measured: + 5 us on such launches, what the selection-only plan saves beside attention).
 bool linear_plan_tail_fits(int dtype, const void* x, const void* w, int64_t M, int N, int K, int B) {
   if (dtype == 0 && M > 0 && B > 0) {
-    if (f32_small_tiles(M, N)) return true;   // at most two tiles per CU, room for eight (B = 4000 beside them still gains: 506 -> 403 us)
+    const bool dma = f32_dma_takes(x, w, K);
+    if (f32_small_tiles(M, N, dma)) return true;   // at most three tiles per CU, room for eight (B = 4000 beside them still gains: 506 -> 403 us)
     const int64_t tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    return f32_dma_takes(x, w, K) && tiles % 512 != 0 && tiles % 512 + B <= 512;
+    return dma && tiles % 512 != 0 && tiles % 512 + B <= 512;
   }
   if (M <= 0 || B <= 0 || !(K % 32 == 0 && K >= 64 && N % 8 == 0)) return false;
   int bm = 128, bn = 128, slots = 768;

@@ -121,12 +121,12 @@ def test_fp32_attention_keys_without_weight_and_infinite_values(lib, H):
 
 @pytest.mark.parametrize("N,K", [(8, 8), (8, 128), (72, 128), (136, 256), (200, 384), (768, 640), (64, 3072)])
 def test_fp32_gemm_large_tiles_every_epilogue(lib, N, K):
-    """M just past what the small tiles take (more than 512 tiles of 32 x 32): one to 24 k-tiles a quarter, a ragged last
+    """M just past what the small tiles take (512 tiles of 32 x 32, 600 where K is no multiple of 128): one to 24 k-tiles a quarter, a ragged last
     tile in both directions, no epilogue / GELU / residual, against float64 and, bit for bit, the small tiles' rows."""
     import torch
     ctx, dt = _context(lib, 64, 1, "f32")
     g = torch.Generator(device="cuda").manual_seed(N + K)
-    M = 32 * (512 // ((N + 31) // 32) + 1) + 7
+    M = 32 * ((600 if K % 128 else 512) // ((N + 31) // 32) + 1) + 7
     x, w = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
     b, res = torch.randn(N, generator=g, device="cuda"), torch.randn((M, N), generator=g, device="cuda")
     xd, wd = x.double(), w.double()
@@ -150,7 +150,7 @@ def test_fp32_gemm_operands_that_do_not_begin_on_16_bytes(lib, which):
     """A view four bytes into a buffer takes the kernel that stages through registers: the same rows bit for bit."""
     import torch
     ctx, dt = _context(lib, 64, 1, "f32")
-    M, N, K = 2100, 256, 256
+    M, N, K = 2500, 256, 256                     # 632 tiles of 32 x 32: past the small ones with either kernel
     g = torch.Generator(device="cuda").manual_seed(9)
     x, w = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
     b = torch.randn(N, generator=g, device="cuda")

@@ -1,5 +1,7 @@
 """The small integer arrays of a call go to the GPU in the kernels' arguments up to a number of queries and through the
 device plan buffer beyond it: both sides of that line give the same rows, edges and sizes."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -207,14 +209,61 @@ def test_fp32_selection_beside_attention_equals_the_plan_kernel(lib, D, H):
     import torch
     cfg = synth.Config("fused", L=2, D=D, H=H, F=256, dtype="f32", B=1, n0=2, seed=17)
     ctx, _ = hz.make_context(cfg)
-    ns = [2, 3, 33, 64, 65, 66, 129, 577, 1024, 300, 300, 300, 300]
+    ns = [2, 3, 33, 64, 65, 66, 129, 577, 1024, 300, 300, 300, 300, 300]
     off = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
     x0 = torch.randn((int(off[-1]), D), generator=torch.Generator().manual_seed(3)).to("cuda")
-    R = [1, 1, 4, 8, 32, 5, 64, 23, 400, 16, 0, 149, 7]
+    R = [1, 1, 4, 8, 32, 5, 64, 23, 400, 16, 0, 149, 7, 9]
     many = hz.gpu_forward(ctx, x0, off, R)
     for q, n in enumerate(ns):
         one = hz.gpu_forward(ctx, x0[int(off[q]):int(off[q + 1])].contiguous(), [0, n], [R[q]])
         assert np.array_equal(one["x"][0], many["x"][q]) and np.array_equal(one["sizes"][0], many["sizes"][q]), n
         for a, b in zip(one["trace"][0], many["trace"][q]):
             assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), n
+    ctx.close()
+
+
+class PlanTail(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("in_off", "out_off", "reff", "troff", "src_list", "row_ptr", "trace_src",
+                                               "trace_dst", "best", "bcol")] + [
+        ("stride", ctypes.c_int64), ("nb", ctypes.c_int), ("B", ctypes.c_int)]
+
+
+@pytest.mark.parametrize("shift", ["", "x", "w"])
+@pytest.mark.parametrize("M,D,B", [(600, 192, 3), (3200, 192, 40), (3201, 192, 40), (3300, 192, 40), (2048, 256, 8), (2080, 256, 8),
+                                   (2400, 256, 8), (8200, 256, 100), (8200, 256, 510), (1206, 768, 6), (200, 72, 200)])
+def test_fp32_lists_beside_the_projection_where_they_are_said_to_fit(lib, M, D, B, shift):
+    """Row counts on both sides of the small tiles (512 tiles, 600 where the large ones are staged), few and many queries,
+    operands four bytes into a buffer: where linear_plan_tail_fits says so the launch takes the shape, whose rows are then the
+    plain launch's and whose lists (nothing merges) name every row once; where the large tiles are staged it refuses."""
+    import torch
+    so = ctypes.CDLL(lib.lib_path())
+    fits = so._ZN4otas21linear_plan_tail_fitsEiPKvS1_liii
+    fits.restype, vp = ctypes.c_bool, ctypes.c_void_p
+    cfg = synth.config("tiny")
+    ctx, _ = hz.make_context(cfg)
+    g = torch.Generator(device="cuda").manual_seed(M + B)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda")
+    off4 = lambda t: torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
+    x, w, b, res = rand(M, D), rand(D, D), rand(D), rand(M, D)
+    x, w = off4(x) if shift == "x" else x, off4(w) if shift == "w" else w
+    want, got = torch.empty((M, D), device="cuda"), torch.full((M, D), float("nan"), device="cuda")
+    ctx.otas_linear_kernel(0, x, w, b, res, M, D, D, 2, want)
+    ints = lambda a: torch.as_tensor(a, dtype=torch.int32).to("cuda")
+    off, zero = ints(np.linspace(0, M, B + 1).astype(np.int64)), ints([0] * B)
+    lists, ptr = ints([-1] * M), ints([-1] * (M + 1))
+    best, col = rand(M), ints([0] * M)
+    p = lambda t: vp(t.data_ptr())
+    pt = PlanTail(*(t.data_ptr() for t in (off, off, zero, zero, lists, ptr)), None, None, best.data_ptr(), col.data_ptr(), M, 1, B)
+    ok = fits(0, p(x), p(w), ctypes.c_int64(M), D, D, B)
+    small, dma = -(-M // 32) * -(-D // 32), D % 128 == 0 and not shift
+    assert ok or small > (512 if dma else 600)
+    status = so._ZN4otas23launch_linear_plan_tailEiPKvS1_S1_PKfPvliiRKNS_8PlanTailEiP12ihipStream_t(
+        0, p(x), p(w), p(b), p(res), p(got), ctypes.c_int64(M), D, D, ctypes.byref(pt), -(-M // B),
+        vp(torch.cuda.current_stream().cuda_stream))
+    assert status == 0 if ok or dma else status == 1           # hipErrorInvalidValue
+    if status == 0:
+        assert torch.equal(got, want)
+        assert lists.tolist() == list(range(M)) and ptr[:M].tolist() == list(range(M))
+    else:
+        assert bool(torch.isnan(got).all()) and bool((lists == -1).all())
     ctx.close()
