@@ -157,6 +157,11 @@ struct WorkspaceLayout {
   int part_factor;   // float rows of the split-K buffer per token row
 };
 
+// The matrices of all blocks.
+int64_t model_bytes(const otas_model_desc& d) {
+  return (int64_t)d.L * (4 * (int64_t)d.D * d.D + 2 * (int64_t)d.D * d.F) * (int64_t)elem_size(d.dtype);
+}
+
 // Where a block keeps its QKV projection, which is dead once the output projection has run, and its hidden rows, which live
 // only after it.  Blocks for which the two do not fit the L2s (32 MB) side by side keep them in the same rows: the working
 // set is smaller by 3 D columns a row, and more of what a kernel reads is still in the 256 MB last-level cache.  ViT-B, 64
@@ -893,7 +898,8 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
         OTAS_LAUNCH_ON(K_LN, s, launch_layer_norm(dt, true, x_mlp, wl.ln2_g, wl.ln2_b, hbuf, Tn, D, d.ln_eps, s));
       }
       // MLP + residual
-      OTAS_LAUNCH_ON(K_FC1, s, launch_linear(dt, hbuf, wl.w_fc1, wl.b_fc1, nullptr, hid, Tn, F, D, EPI_GELU, s));
+      OTAS_LAUNCH_ON(K_FC1, s, launch_linear(dt, hbuf, wl.w_fc1, wl.b_fc1, nullptr, hid, Tn, F, D, EPI_GELU, s,
+                                             model_bytes(d)));
       void* x_next = (l == L - 1) ? (void*)((float*)x_out + (size_t)ln.rowL * D) : x_mlp;
       const int S = splitk_factor(dt, Tn, D, F, (int)std::min<int64_t>(8, w.part_factor * ln.T[0] / std::max<int64_t>(Tn, 1)));
       if (S > 1) {
@@ -1053,7 +1059,7 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
     OTAS_LAUNCH(K_PROJ, launch_linear(dt, hbuf, wl.w_proj, wl.b_proj, x_cur, x_buf[cur], T, D, D, EPI_RESIDUAL, s));
     x_cur = x_buf[cur];
     OTAS_LAUNCH(K_LN, launch_layer_norm(dt, true, x_cur, wl.ln2_g, wl.ln2_b, hbuf, T, D, d.ln_eps, s));
-    OTAS_LAUNCH(K_FC1, launch_linear(dt, hbuf, wl.w_fc1, wl.b_fc1, nullptr, hid, T, F, D, EPI_GELU, s));
+    OTAS_LAUNCH(K_FC1, launch_linear(dt, hbuf, wl.w_fc1, wl.b_fc1, nullptr, hid, T, F, D, EPI_GELU, s, model_bytes(d)));
     void* x_next = (l == L - 1) ? x_out : (void*)x_buf[cur];
     // few rows, long K: split over K as in run_layers; the next block's LayerNorm is not folded into the reduce,
     // because that block first replaces or inserts prompt rows

@@ -1276,23 +1276,27 @@ __global__ __launch_bounds__(512, 1) void gemm_mfma256w8_kernel(const bf16_t* __
 
 // Whether a bf16 output is written past the L2's replacement (non-temporal stores): the launch's panels stay in the L2s and less
 // of the output is left to write back when it ends, but what reads the output next finds less of it there.  Measured
-// inside ViT passes of 1500 ... 68000 rows at D = 768, 1024 and 1280 (MI355X; us per block, streamed less not streamed,
-// ranges over the sizes and widths):
-//   QKV   16 - 26 MB -0.9 ... +0.6, 26 - 32 +0.1 ... +1.8, 32 - 128 -0.5 ... +7.7 (mean +3), 135 - 165 -2.6 ... +1.8, 168 - 256 -12 ... +3.2
-//         (mean -5), above -10 ... +0.4
-//   GELU  16 - 32 MB at D = 768 -1.6 ... +4.7 (mean +0.9 without merging, -0.3 with), at 1024 and 1280 -2.6 ... +1.3 (mean -1.1);
-//         32 - 64 -4.2 ... +1.5 (mean -1.8), 65 - 157 -4.5 ... +9.2 (mean +2.6), 163 - 170 -8.9 ... +3.4, above -29 ... -6
-// So: outputs that the 256 MB last-level cache cannot hold beside the rest, and those behind GELU that are more than half of
-// the L2s (32 MB) and up to a quarter of the last-level cache.  The 256-wide kernels are picked from about 16 MB on.
-static bool streams_output(int64_t M, int N, int epi) {
+// inside passes of 1500 ... 68000 rows (MI355X; us per block, streamed less not streamed, ranges over the sizes):
+//   QKV   D = 768, 1024, 1280: 16 - 26 MB -0.9 ... +0.6, 26 - 32 +0.1 ... +1.8, 32 - 128 -0.5 ... +7.7 (mean +3), 135 - 165
+//         -2.6 ... +1.8, 168 - 256 -12 ... +3.2 (mean -5), above -10 ... +0.4
+//   GELU  models of 170 MB of weights and more (12 layers at D = 768, 24 at 1024, 32 at 1280): 16 - 32 MB -2.6 ... +4.7 (mean -0.2;
+//         at 768 +0.9 without merging, -0.3 with), 32 - 64 -4.2 ... +1.5 (mean -1.8), 65 - 157 -4.5 ... +9.2 (mean +2.6),
+//         163 - 170 -8.9 ... +3.4, above -29 ... -6
+//         models that stay in the last-level cache from pass to pass (113 MB: 8 layers at 768; 75 and 42 MB: 12 at 512 and 384; 57: 4
+//         at 768): 16 - 64 MB -1.5 ... +8.7 (mean +3.7), 71 - 157 -13 ... +8, above 160 -24 ... -3
+// So: outputs that the 256 MB last-level cache cannot hold beside the rest, and for models of more weights than half of it
+// those behind GELU that are more than half of the L2s (32 MB) and up to a quarter of the last-level cache.  The 256-wide
+// kernels are picked from about 16 MB on.
+bool streams_output(int64_t M, int N, int epi, int64_t model_bytes) {
   constexpr int64_t MB = 1 << 20;
   const int64_t bytes = 2 * M * N;
-  return bytes > 160 * MB || (epi == EPI_GELU && bytes > 16 * MB && bytes <= 64 * MB);
+  return bytes > 160 * MB ||
+         (epi == EPI_GELU && model_bytes > 128 * MB && bytes > 16 * MB && bytes <= 64 * MB);
 }
 
 template <int RB>
-static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bias, const float* res, void* y,
-                                   int64_t M, int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr) {
+static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
+                                   int N, int K, int epi, hipStream_t s, const PlanTail* pt, int64_t model_bytes) {
   constexpr int BM = 32 * RB;
   const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + 255) / 256;
   const size_t lds = ((size_t)2 * (BM + 256) * 64 + 256) * sizeof(bf16_t);   // the stages and the tile's bias
@@ -1304,7 +1308,7 @@ static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bia
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
                                   (typename OutType<bf16_t, E>::type*)y, M, N, K, tiles_m, tiles_n,               \
-                                  streams_output(M, N, epi), pt ? *pt : PlanTail{});                                            \
+                                  streams_output(M, N, epi, model_bytes), pt ? *pt : PlanTail{});                               \
   } while (0)
   if (pt) {
     if (epi != EPI_RESIDUAL) return hipErrorInvalidValue;
@@ -1479,17 +1483,17 @@ static hipError_t linear_mfma128k64(const void* x, const void* w, const void* bi
 // Runs one named kernel (gemm_kernel_id in kernels.h); hipErrorInvalidValue if it does not take the shape.
 static hipError_t linear_mfma_kernel(int kernel, const void* x, const void* w, const void* bias, const float* res,
                                      void* y, int64_t M, int N, int K, int epi, hipStream_t s,
-                                     const PlanTail* pt = nullptr) {
+                                     const PlanTail* pt = nullptr, int64_t model_bytes = 0) {
   const bool k32 = K % 32 == 0 && K >= 64, k64 = K % 64 == 0 && K >= 128;
   switch (kernel) {
     case GK_128_K32: return k32 ? linear_mfma_k32<3, 2>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     case GK_128_K64: return k64 ? linear_mfma128k64(x, w, bias, res, y, M, N, K, epi, s, 1, pt) : hipErrorInvalidValue;
-    case GK_160X256: return k64 ? linear_mfma256w8<5>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_192X256: return k64 ? linear_mfma256w8<6>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_224X256: return k64 ? linear_mfma256w8<7>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_256X256: return k64 ? linear_mfma256w8<8>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_288X256: return k64 ? linear_mfma256w8<9>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
-    case GK_320X256: return k64 ? linear_mfma256w8<10>(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
+    case GK_160X256: return k64 ? linear_mfma256w8<5>(x, w, bias, res, y, M, N, K, epi, s, pt, model_bytes) : hipErrorInvalidValue;
+    case GK_192X256: return k64 ? linear_mfma256w8<6>(x, w, bias, res, y, M, N, K, epi, s, pt, model_bytes) : hipErrorInvalidValue;
+    case GK_224X256: return k64 ? linear_mfma256w8<7>(x, w, bias, res, y, M, N, K, epi, s, pt, model_bytes) : hipErrorInvalidValue;
+    case GK_256X256: return k64 ? linear_mfma256w8<8>(x, w, bias, res, y, M, N, K, epi, s, pt, model_bytes) : hipErrorInvalidValue;
+    case GK_288X256: return k64 ? linear_mfma256w8<9>(x, w, bias, res, y, M, N, K, epi, s, pt, model_bytes) : hipErrorInvalidValue;
+    case GK_320X256: return k64 ? linear_mfma256w8<10>(x, w, bias, res, y, M, N, K, epi, s, pt, model_bytes) : hipErrorInvalidValue;
     case GK_64X64: return k32 ? linear_mfma64(x, w, bias, res, y, M, N, K, epi, s, pt) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
@@ -1607,11 +1611,11 @@ hipError_t launch_linear_splitk(const void* x, const void* w, float* part, int64
 }
 
 hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,
-                         int64_t M, int N, int K, int epi, hipStream_t s) {
+                         int64_t M, int N, int K, int epi, hipStream_t s, int64_t model_bytes) {
   if (M <= 0) return hipSuccess;
   if (dtype == 0) return linear_f32<float>(x, w, bias, res, y, M, N, K, epi, s);
   if (K % 32 == 0 && K >= 64 && N % 8 == 0)
-    return linear_mfma_kernel(pick_mfma_kernel(M, N, K, epi), x, w, bias, res, y, M, N, K, epi, s);
+    return linear_mfma_kernel(pick_mfma_kernel(M, N, K, epi), x, w, bias, res, y, M, N, K, epi, s, nullptr, model_bytes);
   return linear_f32<bf16_t>(x, w, bias, res, y, M, N, K, epi, s);
 }
 

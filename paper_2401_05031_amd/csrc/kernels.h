@@ -77,10 +77,12 @@ hipError_t launch_layer_norm_widen(const void* x_bf16, const void* g, const void
                                    int64_t T, int D, float eps, hipStream_t s, const StartJob* job = nullptr);
 
 // EPI_RESIDUAL: res and y are float (the residual stream) for every dtype; otherwise y has the
-// model's dtype.
+// model's dtype.  model_bytes: the weights of the model whose pass this is part of (0: none; decides with the output's
+// size whether it is stored past the caches, no result depends on it).
 hipError_t launch_linear(int dtype, const void* x, const void* w, const void* bias,
                          const float* res, void* y, int64_t M, int N, int K, int epi,
-                         hipStream_t s);
+                         hipStream_t s, int64_t model_bytes = 0);
+bool streams_output(int64_t M, int N, int epi, int64_t model_bytes);
 
 // The same with the kernel named by the caller (tests and profiling exercise every kernel at every
 // shape this way): GK_AUTO = launch_linear's own choice, GK_FMA = fp32 arithmetic (any dtype),

@@ -89,3 +89,18 @@ def test_small_tiles_stay_within_four_workgroups_per_cu():
             most = 1024 // ((N + 63) // 64) * 64        # rows
             assert choice(1, most + 1, N, K, epi) != T64 and choice(1, 64, N, K, epi) == T64
             assert all(choice(1, M, N, K, epi) != T64 for M in (2 * most + 5, 10 * most, 100 * most))
+
+
+def test_which_outputs_go_past_the_caches():
+    """More than 160 MB always; behind GELU 16 to 64 MB if the model has more than 128 MB of weights."""
+    streams = _library()._ZN4otas14streams_outputEliil
+    streams.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64]
+    streams.restype = ctypes.c_bool
+    MB, N = 1 << 20, 1024                            # 2 KB a row
+    for epi in (0, 1):
+        for model in (0, 128 * MB, 128 * MB + 1):
+            large = epi == 1 and model > 128 * MB
+            for mb, want in [(16, False), (64, large), (160, False)]:
+                assert streams(mb * 512, N, epi, model) == want, (epi, model, mb)
+            for mb, want in [(16, large), (64, False), (160, True)]:
+                assert streams(mb * 512 + 1, N, epi, model) == want, (epi, model, mb)

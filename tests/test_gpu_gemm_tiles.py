@@ -1,4 +1,5 @@
 """The 256-column GEMM kernels at every tile height, at the edges of their tiles, loops and output rules."""
+import numpy as np
 import pytest
 
 import otas_synth as synth
@@ -45,7 +46,7 @@ def test_tile_heights_at_their_edges(lib, kernel, K):
 MB = 1 << 20
 
 
-@pytest.mark.parametrize("epi,N,line", [(0, 1024, 160 * MB), (1, 1024, 16 * MB), (1, 2048, 64 * MB), (1, 2048, 160 * MB)])
+@pytest.mark.parametrize("epi,N,line", [(0, 1024, 160 * MB), (1, 2048, 160 * MB)])
 @pytest.mark.parametrize("kernel", sorted(ROWS))
 def test_outputs_on_both_sides_of_the_streaming_rule(lib, kernel, epi, N, line):
     """Outputs of just the bytes at which the rule changes, one row fewer and one more: stored past the L2's replacement or
@@ -61,3 +62,23 @@ def test_outputs_on_both_sides_of_the_streaming_rule(lib, kernel, epi, N, line):
         ctx.otas_linear_kernel(kernel, x, w, b, None, M, N, K, epi, out)
         assert torch.equal(out, want[:M]), M
     ctx.close()
+
+
+def test_a_large_models_hidden_rows_past_the_caches(lib):
+    """A model of more than 128 MB of weights and one of fewer layers, the same weights layer by layer: the hidden rows of 16 to
+    64 MB are stored past the L2's replacement in the first only.  After its one layer the small model's rows are the large
+    one's after its first, on both sides of both lines."""
+    import torch
+    D, F, n = 768, 3072, 128
+    cfg = synth.Config("stream", L=1, D=D, H=12, F=F, dtype="bf16", B=1, n0=n, seed=3)
+    one, layers = hz.make_context(cfg)
+    many = lib.Context.from_host_weights(10, D, 12, F, lib.OTAS_BF16, cfg.ln_eps, cfg.n_lead, layers * 10)
+    for B in (21, 22, 85, 86):                      # 15.75, 16.5, 63.75 and 64.5 MB
+        assert (2 * B * n * F > 16 * MB) == (B >= 22) and (2 * B * n * F > 64 * MB) == (B == 86)
+        x0 = torch.randn((B * n, D), generator=torch.Generator().manual_seed(B)).to("cuda")
+        off = np.arange(B + 1, dtype=np.int32) * n
+        a = hz.gpu_forward(one, x0, off, [0] * B, trace=False, layer_range=(0, 1))
+        b = hz.gpu_forward(many, x0, off, [0] * B, trace=False, layer_range=(0, 1))
+        assert all(np.array_equal(p, q) for p, q in zip(a["x"], b["x"])), B
+    one.close()
+    many.close()
