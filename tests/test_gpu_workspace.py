@@ -37,13 +37,38 @@ def test_shared_activation_buffer_changes_nothing(lib, dtype, D, H, F, n, B):
     ctx.close()
 
 
-def test_workspace_bytes_never_shrink_as_a_batch_grows(lib):
-    """A workspace sized for a program's largest batch serves its smaller ones, on both sides of the line."""
-    cfg = synth.config("tiny")
+@pytest.mark.parametrize("path", ["merge", "lanes", "grow"])
+@pytest.mark.parametrize("dtype,D,H,F,n", [("bf16", 128, 1, 512, 400), ("bf16", 256, 2, 384, 300), ("f32", 128, 2, 512, 70)])
+def test_a_pass_stays_inside_the_bytes_it_asks_for(lib, dtype, D, H, F, n, path):
+    """Workspaces of exactly the reported size between guard bytes, for batches whose blocks are below, around and above the line
+    at which projection and hidden rows share a buffer, F on both sides of 3 D, metric rows in the spare part of it: no
+    guard byte changes."""
+    import torch
+    cfg = synth.Config("guard", L=3, D=D, H=H, F=F, dtype=dtype, B=1, n0=n, seed=31)
     ctx, _ = hz.make_context(cfg)
-    line = (32 << 20) // (4 * (3 * cfg.D + cfg.F))
-    sizes = [ctx.otas_workspace_bytes(4, T) for T in range(line - 2048, line + 2048, 64)]
-    assert sizes == sorted(sizes)
+    ctx.otas_set_lanes(3 if path == "lanes" else 1)
+    rows = (32 << 20) // ((3 * D + F) * (4 if dtype == "f32" else 2))        # of a block at the line
+    guard = 1 << 16
+    for B in (3, rows // n, rows // n + 1, 2 * rows // n):
+        P = 2 if path == "grow" else 0
+        off = np.arange(B + 1, dtype=np.int32) * (n + P)
+        T = B * (n + 3 * P)                                       # two layers insert P rows each
+        x0 = torch.randn((B * (n + P), D), generator=torch.Generator().manual_seed(B)).to("cuda").to(ctx.torch_dtype)
+        buf = torch.full((ctx.otas_workspace_bytes(B, T) + 2 * guard,), 0xA5, dtype=torch.uint8, device="cuda")
+        ws = buf[guard:-guard]
+        r, left = n // 3, n + 3 * P
+        for _ in range(0 if P else 3):                            # a third of the tokens a layer while the length allows
+            left -= min(r, (left - 1) // 2)
+        x_out = torch.empty((B * left, D), device="cuda")
+        sizes = torch.empty(B * left, dtype=torch.int32, device="cuda")
+        if path == "grow":
+            prompts = torch.randn((3, B * P, D), generator=torch.Generator().manual_seed(1)).to("cuda").to(ctx.torch_dtype)
+            ctx.otas_encoder_forward_deep(x0, off, lib.OTAS_PROMPT_GROW, prompts, np.arange(B + 1, dtype=np.int32) * P, ws,
+                                          x_out, sizes)
+        else:
+            ctx.otas_encoder_forward(x0, off, [r] * B, 0, ws, x_out, sizes)
+        assert bool(torch.isfinite(x_out).all()) and bool((sizes >= 1).all())
+        assert bool((buf[:guard] == 0xA5).all()) and bool((buf[-guard:] == 0xA5).all()), B
     ctx.close()
 
 
