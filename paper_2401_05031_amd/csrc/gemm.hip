@@ -33,6 +33,16 @@ namespace otas {
 #define OTAS_WAIT_LOADS_AND_LDS() __builtin_amdgcn_s_waitcnt(7 << 4)
 // lgkmcnt(0) only (vmcnt, expcnt at their maxima).
 #define OTAS_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14))
+// A barrier that no LDS read of this wave's is still under way at: what the reads were of may be overwritten after it, by
+// loads or by another wave's stores.  The barrier alone does not wait, and the instructions that use what was read, with
+// the compiler's wait for it, may be scheduled behind it.
+__device__ __forceinline__ void lds_reads_barrier() {
+  asm volatile("" ::: "memory");
+  OTAS_WAIT_LDS();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 #define OTAS_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define OTAS_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
@@ -851,9 +861,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
 
   int st = 0, st_new = NS - 1;
   auto tile = [&](int kt, auto more) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    lds_reads_barrier();
     bf16x8 af[RB], wf[CB];
     wf[0] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + wn * WN * BK + frag);
 #pragma unroll
@@ -889,9 +897,7 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
   }
   OTAS_VMCNT(0);
   tile(KT - 1, std::bool_constant<false>());
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();   // every wave has read its last fragments: the stages become the epilogue's staging area
-  asm volatile("" ::: "memory");
+  lds_reads_barrier();   // every wave has its last fragments: the stages become the epilogue's staging area
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
     mfma_epilogue_bf16<EPI, 2 * TM, 2 * TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
@@ -1002,9 +1008,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   for (int t = 0; t < NS - 1; ++t) dma(t, t);
   int st = 0, st_new = NS - 1;
   auto tile = [&](int kt, auto more) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    lds_reads_barrier();
     bf16x8 af[KS][2], wf[KS][2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -1044,9 +1048,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   }
   OTAS_VMCNT(0);
   tile(KT - 1, std::bool_constant<false>());
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  lds_reads_barrier();   // every wave has its last fragments: the stages become the epilogue's staging area
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
     mfma_epilogue_bf16<EPI, 2, 2>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias_s + wn * 32, Y, M, N,
                                   m0 + wm * 32, n0 + wn * 32, lane);

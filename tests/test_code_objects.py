@@ -1,6 +1,8 @@
 """What the built library's GPU code says of its kernels (the AMDGPU metadata note of its code objects; no GPU)."""
 import os
+import re
 import struct
+import subprocess
 
 import msgpack
 import pytest
@@ -26,8 +28,8 @@ def _kernels_of_elf(elf):
     return []
 
 
-def built_kernels():
-    """Metadata of every gfx950 kernel in the library."""
+def _code_objects():
+    """Every gfx950 ELF in the library."""
     if not os.path.exists(otas.lib_path()):
         from paper_2401_05031_amd import build
         build.build(verbose=False)
@@ -40,10 +42,15 @@ def built_kernels():
         for _ in range(entries):
             first, size, name = struct.unpack_from("<QQQ", data, p)
             if b"gfx950" in data[p + 24:p + 24 + name]:
-                out += _kernels_of_elf(data[at + first:at + first + size])
+                out.append(data[at + first:at + first + size])
             p += 24 + name
         at = data.find(BUNDLE, at + 1)
     return out
+
+
+def built_kernels():
+    """Metadata of every gfx950 kernel in the library."""
+    return [k for elf in _code_objects() for k in _kernels_of_elf(elf)]
 
 
 @pytest.fixture(scope="module")
@@ -77,3 +84,44 @@ def test_every_kernel_has_its_place_in_the_traffic_figures(kernels, tmp_path):
     csv.write_text("\n".join(rows + ["void otas::renamed_kernel,FETCH_SIZE,4"]))
     with pytest.raises(ValueError, match="renamed_kernel"):
         traffic._load(str(csv), "FETCH_SIZE")
+
+
+def reads_in_flight_at_barriers(lines):
+    """Names of the functions in a disassembly that reach an s_barrier with an LDS read of their own not waited for."""
+    name, out, found, barriers = "", 0, set(), 0
+    for line in lines:
+        if line.endswith(">:\n"):
+            name, out = line[line.index("<") + 1:-3], 0
+            continue
+        op = line.split(None, 1)[0] if line.strip() else ""
+        if op.startswith("ds_read") or op.startswith("ds_load"):
+            out += 1
+        elif op == "s_waitcnt":
+            count = re.search(r"lgkmcnt\((\d+)\)", line)
+            out = min(out, int(count.group(1))) if count else out
+        elif op == "s_barrier":
+            barriers += 1
+            if out:
+                found.add(name)
+    return found, barriers
+
+
+def test_no_lds_read_is_under_way_at_a_barrier(tmp_path):
+    """What a wave reads from LDS before a barrier may be overwritten after it, by loads or by another wave's stores, and the
+    barrier itself waits for nothing: every kernel of the library has its reads back before it.  (In the order of the
+    code: loops and branches are not followed.)"""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no disassembler for the AMD GPU")
+    lines = ["0 <planted>:\n", "\tds_read_b128 v[0:3], v4\n", "\ts_waitcnt lgkmcnt(1)\n", "\ts_barrier\n",
+             "0 <sound>:\n", "\tds_read_b128 v[0:3], v4\n", "\ts_waitcnt vmcnt(0) lgkmcnt(0)\n", "\ts_barrier\n"]
+    assert reads_in_flight_at_barriers(lines) == ({"planted"}, 2)
+    total = 0
+    for i, elf in enumerate(_code_objects()):
+        path = tmp_path / f"{i}.elf"
+        path.write_bytes(elf)
+        with subprocess.Popen([objdump, "-d", "--no-show-raw-insn", str(path)], stdout=subprocess.PIPE, text=True) as p:
+            found, barriers = reads_in_flight_at_barriers(p.stdout)
+        assert p.returncode == 0 and not found, found
+        total += barriers
+    assert total > 300

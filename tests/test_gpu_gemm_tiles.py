@@ -82,3 +82,24 @@ def test_a_large_models_hidden_rows_past_the_caches(lib):
         assert all(np.array_equal(p, q) for p, q in zip(a["x"], b["x"])), B
     one.close()
     many.close()
+
+
+@pytest.mark.parametrize("epi", [0, 1, 2])
+@pytest.mark.parametrize("K", [64, 96, 128, 192, 256, 320, 384])
+def test_small_tiles_whose_last_stage_the_epilogue_takes(lib, K, epi):
+    """64 x 64 tiles, several per CU: the ring's last k-tile lies in each of its four stages, all but the last of which become
+    the epilogue's staging area while other waves may still read.  Twenty launches, each bit for bit the kernel's that
+    walks K in steps of 32 and has no tile smaller than 128 x 128."""
+    import torch
+    ctx, M, N = _context(), 12549, 136
+    g = torch.Generator(device="cuda").manual_seed(K)
+    x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+    res = torch.randn((M, N), generator=g, device="cuda") if epi == 2 else None
+    want = torch.full((M, N), float("nan"), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+    ctx.otas_linear_kernel(2, x, w, b, res, M, N, K, epi, want)
+    got = torch.empty_like(want)
+    for _ in range(20):
+        got.fill_(float("nan"))
+        ctx.otas_linear_kernel(7, x, w, b, res, M, N, K, epi, got)
+        assert torch.equal(got, want)
+    ctx.close()
