@@ -360,8 +360,10 @@ hipError_t launch_layer_norm_widen(const void* x_bf16, const void* g, const void
 
 // Workgroups past the launch's rows read the weight of the next linear, one word of every cache line once.  What that gains is
 // the way from HBM to the last-level cache under a kernel that leaves HBM idle: the lines end up in one XCD's L2, and
-// which one does not matter (each XCD the columns of its own tiles: 0 - 4 % slower from 800 rows on, as those
-// overlap and the weight is read two to four times).
+// which one matters little.  Each XCD the columns of its own tiles: 0 - 4 % slower from 800 rows on, as those overlap and the
+// weight is read two to four times.  Each XCD an eighth, which are its tiles' columns up to 512 rows (us a pass, eighths /
+// plain, MI355X): ViT-B, eight models in turn, one query 508 / 506, two 537 / 533; ViT-L one 1117 / 1108, two 1214 / 1208; ViT-H 50 rows
+// 1454 / 1448, 200 2186 / 2177, 400 2389 / 2399, 430 1576 / 1576.
 __device__ inline void warm_weight(const WarmWeight& w, int first) {
   const int64_t lines = w.bytes >> 7;
   for (int64_t l = (int64_t)((int)blockIdx.x - first) * 256 + threadIdx.x; l < lines; l += (int64_t)w.wgs * 256) {

@@ -33,12 +33,13 @@ namespace otas {
 #define OTAS_WAIT_LOADS_AND_LDS() __builtin_amdgcn_s_waitcnt(7 << 4)
 // lgkmcnt(0) only (vmcnt, expcnt at their maxima).
 #define OTAS_WAIT_LDS() __builtin_amdgcn_s_waitcnt(0xF | (7 << 4) | (3 << 14))
-// A barrier that no LDS read of this wave's is still under way at: what the reads were of may be overwritten after it, by
-// loads or by another wave's stores.  The barrier alone does not wait, and the instructions that use what was read, with
-// the compiler's wait for it, may be scheduled behind it.
-__device__ __forceinline__ void lds_reads_barrier() {
+// A barrier that this wave reaches with at most VM of its loads and none of its LDS reads still under way: what the reads were
+// of may be overwritten after it, by loads or by another wave's stores.  The barrier alone does not wait, and the
+// instructions that use what was read, with the compiler's wait for it, may be scheduled behind it.
+template <int VM>
+__device__ __forceinline__ void wait_barrier() {
   asm volatile("" ::: "memory");
-  OTAS_WAIT_LDS();
+  __builtin_amdgcn_s_waitcnt((VM & 0xF) | (7 << 4) | ((VM >> 4) << 14));   // lgkmcnt(0)
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
@@ -860,8 +861,8 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     for (int d = 0; d < ND; ++d) dma_one(t, t, d);
 
   int st = 0, st_new = NS - 1;
-  auto tile = [&](int kt, auto more) {
-    lds_reads_barrier();
+  auto tile = [&](int kt, auto more, auto in_flight) {
+    wait_barrier<decltype(in_flight)::value>();
     bf16x8 af[RB], wf[CB];
     wf[0] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + wn * WN * BK + frag);
 #pragma unroll
@@ -884,20 +885,15 @@ __global__ __launch_bounds__(256, TM == 2 ? 3 : 2) void gemm_mfma_k32_kernel(
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
   };
   static_assert(NS == 3, "the last two k-tiles below");
-  OTAS_VMCNT(ND * (NS - 2));   // tile 0 landed, and everything requested before it
+  constexpr std::integral_constant<int, ND * (NS - 2)> NEXT;   // tile kt landed; tile kt+1 may still be in flight
+  constexpr std::integral_constant<int, 0> NONE;
+  OTAS_VMCNT(NEXT.value);   // tile 0 landed, and everything requested before it
   bias_stage<BN>(bias_s, bias_v, tid);
-  tile(0, std::bool_constant<true>());   // KT >= 2; for KT == 2 its request repeats the last tile
-  for (int kt = 1; kt < KT - 2; ++kt) {
-    OTAS_VMCNT(ND * (NS - 2));   // tile kt landed; tile kt+1 may still be in flight
-    tile(kt, std::bool_constant<true>());
-  }
-  if (KT > 2) {
-    OTAS_VMCNT(ND * (NS - 2));
-    tile(KT - 2, std::bool_constant<false>());
-  }
-  OTAS_VMCNT(0);
-  tile(KT - 1, std::bool_constant<false>());
-  lds_reads_barrier();   // every wave has its last fragments: the stages become the epilogue's staging area
+  tile(0, std::bool_constant<true>(), NEXT);   // KT >= 2; for KT == 2 its request repeats the last tile
+  for (int kt = 1; kt < KT - 2; ++kt) tile(kt, std::bool_constant<true>(), NEXT);
+  if (KT > 2) tile(KT - 2, std::bool_constant<false>(), NEXT);
+  tile(KT - 1, std::bool_constant<false>(), NONE);
+  wait_barrier<0>();   // every wave has its last fragments: the stages become the epilogue's staging area
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
     mfma_epilogue_bf16<EPI, 2 * TM, 2 * TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
@@ -1007,8 +1003,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) dma(t, t);
   int st = 0, st_new = NS - 1;
-  auto tile = [&](int kt, auto more) {
-    lds_reads_barrier();
+  auto tile = [&](int kt, auto more, auto in_flight) {
+    wait_barrier<decltype(in_flight)::value>();
     bf16x8 af[KS][2], wf[KS][2];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -1028,27 +1024,24 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
   };
   static_assert(NS == 4, "the last three k-tiles below");
-  OTAS_VMCNT(ND * (NS - 2));   // tile 0 landed, and everything requested before it
+  constexpr std::integral_constant<int, ND * (NS - 2)> TWO;   // tile kt landed; the two after it may still be in flight
+  constexpr std::integral_constant<int, ND> ONE;
+  constexpr std::integral_constant<int, 0> NONE;
+  constexpr std::bool_constant<true> MORE;
+  constexpr std::bool_constant<false> LAST;
+  OTAS_VMCNT(TWO.value);   // tile 0 landed, and everything requested before it
   if (EPI != EPI_PARTIAL) bias_stage<BN>(bias_s, bias_v, tid);
   int kt = 0;
   if (KT < NS) {   // up to three k-tiles: the prologue requested more than there are (they repeat the last one)
-    if (KT > 1) tile(kt++, std::bool_constant<false>());
+    if (KT > 1) tile(kt++, LAST, TWO);
   } else {
-    tile(kt++, std::bool_constant<true>());
-    for (; kt < KT - 3; ++kt) {
-      OTAS_VMCNT(ND * (NS - 2));
-      tile(kt, std::bool_constant<true>());
-    }
-    OTAS_VMCNT(ND * (NS - 2));
-    tile(kt++, std::bool_constant<false>());
+    tile(kt++, MORE, TWO);
+    for (; kt < KT - 3; ++kt) tile(kt, MORE, TWO);
+    tile(kt++, LAST, TWO);
   }
-  for (; kt < KT - 1; ++kt) {
-    OTAS_VMCNT(ND);
-    tile(kt, std::bool_constant<false>());
-  }
-  OTAS_VMCNT(0);
-  tile(KT - 1, std::bool_constant<false>());
-  lds_reads_barrier();   // every wave has its last fragments: the stages become the epilogue's staging area
+  for (; kt < KT - 1; ++kt) tile(kt, LAST, ONE);
+  tile(KT - 1, LAST, NONE);
+  wait_barrier<0>();   // every wave has its last fragments: the stages become the epilogue's staging area
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
     mfma_epilogue_bf16<EPI, 2, 2>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias_s + wn * 32, Y, M, N,
                                   m0 + wm * 32, n0 + wn * 32, lane);
