@@ -646,54 +646,86 @@ hipError_t launch_splitk_reduce_ln(const float* part, int S, const void* bias, c
 // (row by row), every patch flattened channel-major into one row of the patch matrix [N, C p p]
 // (the layout of a [D, C, p, p] projection weight); the linear projection is the GEMM kernel;
 // embed_finish then builds [class token | projected patches] + position embedding.
-template <typename T>
-__global__ void patchify_kernel(const T* __restrict__ img, T* __restrict__ out, int C, int Hi, int Wi, int p,
-                                int64_t total) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;   // one element per thread: total = B N C p p
-  const int nw = Wi / p, nh = Hi / p, kp = C * p * p;
-  const int64_t row = t / kp;
-  const int k = (int)(t - row * kp);
-  const int b = (int)(row / (nh * nw)), pi = (int)(row - (int64_t)b * nh * nw);
-  const int py = pi / nw, px = pi - py * nw;
-  const int c = k / (p * p), ij = k - c * p * p, i = ij / p, j = ij - i * p;
-  out[t] = img[(((size_t)b * C + c) * Hi + (size_t)py * p + i) * Wi + (size_t)px * p + j];
+// Both are passes over memory whose time went into the index arithmetic of a thread per element, most of it divisions of 64
+// bits.  Now a thread moves V elements, 16 bytes, where rows and pointers allow it (V = 1 otherwise), and what does not
+// differ inside a workgroup or wave is worked out once for it.  Patchify: `blocks` workgroups for the p rows of one channel that
+// make up a row of patches, threads patch by patch, so that they write runs of p p elements and find the other 2 p bytes
+// of an image row's cache line in their own L1.  Embed_finish: a wave per row.
+// Measured on MI355X (us, an element per thread / 16 bytes): 24 images of 224 x 224 in bf16, patches of 16, D = 768: 17.4 / 6.4 and 10.2 / 5.6; 6 in float 6.1 / 5.1 and 5.1 / 5.2.
+template <typename T, int V>
+__global__ __launch_bounds__(256) void patchify_kernel(const T* __restrict__ img, T* __restrict__ out, int C, int Hi, int Wi, int p,
+                                                       int blocks) {
+  const int pv = p / V;                                   // threads per row of a patch
+  const int band = (int)blockIdx.x / blocks;              // (image, row of patches, channel)
+  const int k = ((int)blockIdx.x - band * blocks) * 256 + (int)threadIdx.x;
+  if (k >= Wi / V * p) return;
+  const int nw = Wi / p, nh = Hi / p;
+  const int px = k / (p * pv), in = k - px * p * pv, i = in / pv, j = (in - i * pv) * V;
+  const int bh = band / C, c = band - bh * C, b = bh / nh, py = bh - b * nh;
+  const T* src = img + (((size_t)b * C + c) * Hi + (size_t)py * p + i) * Wi + (size_t)px * p + j;
+  T* dst = out + (((size_t)bh * nw + px) * C + c) * p * p + (size_t)i * p + j;
+  if constexpr (V == 1) *dst = *src;
+  else store_vec<T>(dst, load_vec<T>(src));
 }
 
+template <typename T, int V>
+__global__ __launch_bounds__(256) void embed_finish_kernel(const T* __restrict__ proj, const T* __restrict__ cls,
+                                                           const T* __restrict__ pos, T* __restrict__ tokens, int N, int D, int n_lead,
+                                                           int rows) {
+  const int row = (int)blockIdx.x * 4 + wave_index(), lane = threadIdx.x & 63;
+  if (row >= rows) return;
+  const int n = n_lead + N, b = row / n, i = row - b * n;
+  const T* src = i < n_lead ? cls : proj + ((size_t)b * N + (i - n_lead)) * D;
+  const T* at = pos + (size_t)i * D;
+  T* dst = tokens + (size_t)row * D;
+  for (int d = lane * V; d < D; d += 64 * V) {
+    if constexpr (V == 1) dst[d] = from_float<T>(to_float(src[d]) + to_float(at[d]));
+    else {
+      const Vec<T> x = load_vec<T>(src + d), y = load_vec<T>(at + d);
+      Vec<T> o;
+#pragma unroll
+      for (int e = 0; e < V; ++e) o.set(e, x.get(e) + y.get(e));
+      store_vec<T>(dst + d, o);
+    }
+  }
+}
+
+static bool on_16_bytes(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
 template <typename T>
-__global__ void embed_finish_kernel(const T* __restrict__ proj, const T* __restrict__ cls, const T* __restrict__ pos,
-                                    T* __restrict__ tokens, int N, int D, int n_lead, int64_t total) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;   // total = B (n_lead + N) D
-  const int n = n_lead + N;
-  const int64_t row = t / D;
-  const int d = (int)(t - row * D);
-  const int b = (int)(row / n), i = (int)(row - (int64_t)b * n);
-  const float v = i < n_lead ? to_float(cls[d]) : to_float(proj[((size_t)b * N + (i - n_lead)) * D + d]);
-  tokens[t] = from_float<T>(v + to_float(pos[(size_t)i * D + d]));
+static hipError_t patchify(const T* img, T* out, int B, int C, int Hi, int Wi, int p, hipStream_t s) {
+  constexpr int V = Vec<T>::N;   // p % V == 0: every row of the image and of the patch matrix begins on 16 bytes
+  const bool wide = p % V == 0 && on_16_bytes(img) && on_16_bytes(out);
+  if (B <= 0 || C <= 0 || Hi / p <= 0 || Wi / p <= 0) return hipSuccess;
+  const int64_t per_band = ((int64_t)Wi * p / (wide ? V : 1) + 255) / 256;
+  const dim3 grid((unsigned)(per_band * B * (Hi / p) * C)), block(256);
+  if (wide) patchify_kernel<T, V><<<grid, block, 0, s>>>(img, out, C, Hi, Wi, p, (int)per_band);
+  else patchify_kernel<T, 1><<<grid, block, 0, s>>>(img, out, C, Hi, Wi, p, (int)per_band);
+  return hipGetLastError();
 }
 
 hipError_t launch_patchify(int dtype, const void* img, void* out, int B, int C, int Hi, int Wi, int p, hipStream_t s) {
-  const int64_t total = (int64_t)B * (Hi / p) * (Wi / p) * C * p * p;
-  if (total <= 0) return hipSuccess;
-  dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  if (dtype == 0) patchify_kernel<float><<<grid, block, 0, s>>>((const float*)img, (float*)out, C, Hi, Wi, p, total);
-  else patchify_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)img, (bf16_t*)out, C, Hi, Wi, p, total);
+  return dtype == 0 ? patchify((const float*)img, (float*)out, B, C, Hi, Wi, p, s)
+                    : patchify((const bf16_t*)img, (bf16_t*)out, B, C, Hi, Wi, p, s);
+}
+
+template <typename T>
+static hipError_t embed_finish(const T* proj, const T* cls, const T* pos, T* tokens, int B, int N, int D, int n_lead,
+                               hipStream_t s) {
+  constexpr int V = Vec<T>::N;
+  const bool wide = D % V == 0 && on_16_bytes(proj) && on_16_bytes(cls) && on_16_bytes(pos) && on_16_bytes(tokens);
+  const int rows = B * (n_lead + N);   // the offsets that the caller gets are 32-bit
+  if (rows <= 0 || D <= 0) return hipSuccess;
+  const dim3 grid((unsigned)(((int64_t)rows + 3) / 4)), block(256);
+  if (wide) embed_finish_kernel<T, V><<<grid, block, 0, s>>>(proj, cls, pos, tokens, N, D, n_lead, rows);
+  else embed_finish_kernel<T, 1><<<grid, block, 0, s>>>(proj, cls, pos, tokens, N, D, n_lead, rows);
   return hipGetLastError();
 }
 
 hipError_t launch_embed_finish(int dtype, const void* proj, const void* cls, const void* pos, void* tokens, int B,
                                int N, int D, int n_lead, hipStream_t s) {
-  const int64_t total = (int64_t)B * (n_lead + N) * D;
-  if (total <= 0) return hipSuccess;
-  dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  if (dtype == 0)
-    embed_finish_kernel<float><<<grid, block, 0, s>>>((const float*)proj, (const float*)cls, (const float*)pos,
-                                                      (float*)tokens, N, D, n_lead, total);
-  else
-    embed_finish_kernel<bf16_t><<<grid, block, 0, s>>>((const bf16_t*)proj, (const bf16_t*)cls, (const bf16_t*)pos,
-                                                       (bf16_t*)tokens, N, D, n_lead, total);
-  return hipGetLastError();
+  return dtype == 0 ? embed_finish((const float*)proj, (const float*)cls, (const float*)pos, (float*)tokens, B, N, D, n_lead, s)
+                    : embed_finish((const bf16_t*)proj, (const bf16_t*)cls, (const bf16_t*)pos, (bf16_t*)tokens, B, N, D, n_lead, s);
 }
 
 // Back end (Sec. III-B: every task has its own head): the first row of a query's output is normalised (final LayerNorm,

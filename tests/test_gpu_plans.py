@@ -267,3 +267,42 @@ def test_fp32_lists_beside_the_projection_where_they_are_said_to_fit(lib, M, D, 
     else:
         assert bool(torch.isnan(got).all()) and bool((lists == -1).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("p,shift", [(16, 0), (8, 0), (4, 0), (16, 1), (6, 0)])
+def test_patches_and_rows_by_16_bytes_and_by_elements(lib, dtype, p, shift):
+    """Patch sizes that are a multiple of 16 bytes' elements and not, pointers that begin on 16 bytes and not (shift in
+    elements): both forms of the two kernels give the tokens of torch's unfold, product and sum; a grid of 5 x 7 patches, 4
+    channels, so that a workgroup's last threads and a band's last patch are partial."""
+    import torch
+    cfg = synth.config("tiny")
+    cfg.dtype = dtype
+    ctx, _ = hz.make_context(cfg)
+    dt, B, C, Hi, Wi = ctx.torch_dtype, 3, 4, 5 * p, 7 * p
+    N, kp = 35, C * p * p
+    g = torch.Generator(device="cuda").manual_seed(p)
+
+    def draw(*shape):                               # begins `shift` elements past a 16-byte boundary
+        n = int(np.prod(shape))
+        buf = torch.empty(n + 8, dtype=dt, device="cuda")
+        buf.copy_(torch.randn(n + 8, generator=g, device="cuda"))
+        return buf[shift:shift + n].view(shape)
+
+    img, cls, pos = draw(B, C, Hi, Wi), draw(cfg.D), draw(1 + N, cfg.D)
+    w = (torch.randn((cfg.D, kp), generator=g, device="cuda") * 0.05).to(dt)
+    b = torch.randn(cfg.D, generator=g, device="cuda").to(dt)
+    ws = torch.empty(ctx.otas_patch_embed_workspace_bytes(B, C, Hi, Wi, p), dtype=torch.uint8, device="cuda")
+    toks = draw(B * (1 + N), cfg.D).fill_(float("nan"))
+    ctx.otas_patch_embed(img, p, w, b, cls, pos, ws, toks)
+    rows = torch.nn.functional.unfold(img.double(), p, stride=p).transpose(1, 2)
+    proj, mag = rows @ w.double().T + b.double(), rows.abs() @ w.double().abs().T + b.double().abs()
+    eps = 2.0 ** -24 if dtype == "f32" else 2.0 ** -8
+    got = toks.double().view(B, 1 + N, cfg.D)
+    # the projection's sum in fp32, its rounding to the model's type, one more addition with its rounding
+    want = proj + pos[1:].double()
+    bound = (kp + 8) * 2.0 ** -24 * mag + eps * (proj.abs() + want.abs()) + 1e-6
+    assert bool(((got[:, 1:] - want).abs() <= bound).all())
+    lead = (cls.float() + pos[0].float()).to(dt)
+    assert all(torch.equal(toks.view(B, 1 + N, cfg.D)[q, 0], lead) for q in range(B))
+    ctx.close()
