@@ -294,9 +294,11 @@ def rooflines(res):
                              "frac_on_method_bytes": round(w["layer_norm_method_bytes"] / (k["layer_norm"][0] * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
                              "avg_launch_us": round(k["layer_norm"][0] * 1e3 / max(k["layer_norm"][1], 1), 2)}
     # one row per GEMM launch of a forward pass: rows, the kernel the library picks (block tile, workgroup
-    # slots on 256 CUs), tiles, rounds of those slots, microseconds, TFLOP/s
-    tiles_of = {1: (64, 64, 2048), 2: (128, 128, 768), 3: (128, 128, 512), 4: (192, 256, 256), 5: (256, 256, 256),
-                6: (320, 256, 256), 7: (64, 64, 512), 8: (160, 256, 256), 9: (224, 256, 256), 10: (288, 256, 256)}
+    # slots on 256 CUs), tiles, rounds of those slots, microseconds, TFLOP/s.  Kernels 3 and 7 have tiles of several sizes and
+    # pick one by the rows: tiles and rounds are not given for them
+    tiles_of = {1: (64, 64, 2048), 2: (128, 128, 768), 4: (192, 256, 256), 5: (256, 256, 256),
+                6: (320, 256, 256), 8: (160, 256, 256), 9: (224, 256, 256), 10: (288, 256, 256)}
+    names = {3: "128|160x128", 7: "small"}
     cfg, ctx = res["cfg"], res.get("ctx")
     if ctx is not None and not cfg.deep:
         table = []
@@ -305,11 +307,11 @@ def rooflines(res):
         for kind, (rows, N, K, epi) in shapes.items():
             for l, (M, ms) in enumerate(zip(rows, res["launches"].get(kind, []))):
                 S = w["splits"][l] if kind == "gemm_fc2" else 1
-                # split products run the partial-output form of the 128 x 128 or the 64 x 64 kernel (not told apart here)
+                # split products run the partial-output form of kernel 3 or 7 (not told apart here)
                 kid = 0 if S > 1 else ctx.otas_linear_choice(M, N, K, epi)
                 bm, bn, slots = tiles_of.get(kid, (0, 0, 1))
                 tiles = -(-M // bm) * -(-N // bn) * S if bm else 0
-                table.append({"kind": kind, "layer": l, "M": int(M), "N": N, "K": K, "kernel": kid, "tile": f"{bm}x{bn}" if bm else "split",
+                table.append({"kind": kind, "layer": l, "M": int(M), "N": N, "K": K, "kernel": kid, "tile": f"{bm}x{bn}" if bm else names.get(kid, "split"),
                               "split_k": S, "tiles": int(tiles), "rounds": round(tiles / slots, 2), "us": round(ms * 1e3, 1),
                               "tflops": round(2.0 * M * N * K / (ms * 1e-3) / 1e12, 1)})
         out["gemm_per_launch"] = table

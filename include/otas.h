@@ -298,9 +298,9 @@ otas_status otas_attention(otas_ctx *ctx, const void *qkv, const int32_t *sizes,
 /* otas_linear with the kernel named by the caller, so that tests and profiles can run every GEMM
  * kernel of the library at every shape (otas_linear and the encoder choose by shape alone).
  * kernel: 0 the library's own choice, 1 fp32 arithmetic (any dtype), and for bf16 models the
- * MFMA kernels named by block tile (rows x columns) and K step: 2 128x128 k32, 3 128x128 k64,
- * 4 192x256 k64, 5 256x256 k64, 6 320x256 k64, 8 160x256 k64, 9 224x256 k64, 10 288x256 k64, 7 64x64 k64 (k32
- * where K % 64 != 0).
+ * MFMA kernels named by block tile (rows x columns) and K step: 2 128x128 k32, 3 128x128 k64 (160x128 at rows
+ * for which that leaves the fullest CU fewer tiles), 4 192x256 k64, 5 256x256 k64, 6 320x256 k64, 8 160x256 k64,
+ * 9 224x256 k64, 10 288x256 k64, 7 64x64 k64 (by the rows 32x32, 32x64 or 96x64; 64x64 k32 where K % 64 != 0).
  * OTAS_EUNSUPPORTED if the kernel does not take the shape (k32 kernels need K % 32 == 0 and K >= 64,
  * k64 kernels K % 64 == 0 and K >= 128) or the dtype. */
 #define OTAS_LINEAR_KERNELS 11

@@ -9,9 +9,10 @@
 //     half the instructions but draws more power per FLOP, and large products run at the clock the power allows (a loop
 //     of nothing but MFMAs on random operands: 1.91 against 1.82 PFLOP/s; 67072 x 3840 x 1280 544 against 573 us).
 //       gemm_mfma_k32_kernel     128 x 128, K step 32, three workgroups per CU (K that is no multiple of 64)
-//       gemm_mfma128k64_kernel   128 x 128, K step 64, two per CU (also split-K)
+//       gemm_mfma128k64_kernel   128 or 160 x 128, K step 64, two per CU (also split-K)
 //       gemm_mfma256w8_kernel    160, 192, 224, 256, 288 or 320 x 256, eight waves, one per CU
-//       gemm_mfma64_kernel       64 x 64, K step 64 or 32, for products of very few rows (also split-K)
+//       gemm_mfma64_kernel       64 x 64, 32 x 32, 32 x 64 or 96 x 64, K step 64 (64 x 64 also 32), for products of very few rows (also
+//                                split-K)
 //     pick_mfma_kernel chooses among them with a cost model fitted to measured launch times; splitk_factor
 //     decides by a rule of its own whether the MLP's second linear is split over K.
 //     Each kernel has a PLAN form for the attention output projection, whose first workgroups write the lists
@@ -930,26 +931,27 @@ static hipError_t linear_mfma_k32(const void* x, const void* w, const void* bias
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------ 64 x 64
+// ------------------------------------------------------------------------------ 64 x 64 and smaller
 // For products of so few rows that 128 x 128 tiles leave most CUs without a workgroup (small serving batches: a
-// ViT-B query is 197 rows): block tile 64 x 64, four waves of 32 x 32 in a 2 x 2 arrangement, the same
-// direct-to-LDS ring with NS = 4 stages.  Four times the workgroups of the 128 x 128 tiling at twice the operand
+// ViT-B query is 197 rows): block tile (32 RB) x (32 CB), four waves of (16 RB) x (16 CB) in a 2 x 2 arrangement, the same
+// direct-to-LDS ring with NS = 4 stages.  64 x 64 is four times the workgroups of the 128 x 128 tiling at twice the operand
 // bytes per FLOP.  Such a launch lasts as long as one workgroup's chain of k-tiles, each a barrier, an LDS round trip
 // and BK / 16 MFMAs that follow one another; K step 64 halves that chain's barriers and fetches whole cache lines (64 KB
 // of LDS, two workgroups per CU); K step 128 (128 KB, one per CU) was no faster with a CU for every tile and slower
-// beyond.  K step 32 remains for K that is no multiple of 64.
+// beyond.  K step 32 remains for K that is no multiple of 64.  The other tiles: pick_small_tile.
 // Stage layout: 16-byte chunk c of row r sits at chunk c ^ swz(r), which puts the 16 rows that are served per clock on all
 // 64 banks once.
-// Measured on MI355X (us, K step 32 / 64 / 128): 197 x 2304 x 768 6.3 / 5.4 / 5.6, 197 x 768 x 768 + residual 6.4 / 5.5 / 5.8,
+// Measured on MI355X (us, 64 x 64, K step 32 / 64 / 128): 197 x 2304 x 768 6.3 / 5.4 / 5.6, 197 x 768 x 768 + residual 6.4 / 5.5 / 5.8,
 // 197 x 3072 x 768 + GELU 6.8 / 5.9 / 6.1, 1400 x 768 x 768 9.3 / 8.5 / 11.4, 600 x 3072 x 1024 11.7 / 9.4 / 12.2.
-template <int EPI, int BK, bool PLAN = false>
+constexpr int kSmallStages = 4;
+template <int EPI, int BK, int RB, int CB, bool PLAN = false>
 __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const bf16_t* __restrict__ bias, const float* res,
     typename OutType<bf16_t, EPI>::type* Y, int64_t M, int N, int K, int k_len, int tiles_m, int tiles_n, PlanTail pt) {
-  constexpr int BM = 64, BN = 64, NS = 4;
+  constexpr int WM = 16 * RB, WN = 16 * CB, BM = 2 * WM, BN = 2 * WN, NS = kSmallStages;
   constexpr int CPR = BK / 8;                    // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;                  // rows per DMA instruction
-  constexpr int NI = 16 / RPI, ND = 2 * NI;      // DMA instructions per wave and operand tile, per k-tile
+  constexpr int NA = BM / 4 / RPI, NW = BN / 4 / RPI, ND = NA + NW;   // DMA instructions per wave and k-tile
   constexpr int KS = BK / 32;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -964,62 +966,77 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   const int64_t m0 = (int64_t)tile_m * BM;
   const int n0 = tile_n * BN;
   auto swz = [](int r) { return BK == 64 ? (r >> 1) & 7 : (r >> 2) & 3; };
-  // DMA: wave w loads rows 16 w .. of the A tile and of the W tile, RPI rows per instruction
-  uint32_t a_off[NI], w_off[NI];
+  // DMA: wave w loads a quarter of the rows of the A tile and of the W tile, RPI rows per instruction
+  uint32_t a_off[NA], w_off[NW];
 #pragma unroll
-  for (int j = 0; j < NI; ++j) {
-    const int row = wave * 16 + j * RPI + lane / CPR;
+  for (int j = 0; j < NA; ++j) {
+    const int row = wave * (BM / 4) + j * RPI + lane / CPR;
     const int c = (lane % CPR) ^ swz(row);
-    const int64_t a_last = M - 1 - m0;
-    const int w_last = N - 1 - n0;
-    const uint32_t ra = (uint32_t)(row < a_last ? row : a_last), rw = (uint32_t)(row < w_last ? row : w_last);
-    a_off[j] = (ra * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
-    w_off[j] = (rw * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
+    const int64_t last = M - 1 - m0;
+    const uint32_t r = (uint32_t)(row < last ? row : last);
+    a_off[j] = (r * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
+  }
+#pragma unroll
+  for (int j = 0; j < NW; ++j) {
+    const int row = wave * (BN / 4) + j * RPI + lane / CPR;
+    const int c = (lane % CPR) ^ swz(row);
+    const int last = N - 1 - n0;
+    const uint32_t r = (uint32_t)(row < last ? row : last);
+    w_off[j] = (r * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
   }
   const char* a_base = reinterpret_cast<const char*>(A + (size_t)m0 * K + (size_t)blockIdx.y * k_len);
   const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K + (size_t)blockIdx.y * k_len);
   if (EPI == EPI_PARTIAL) Y += (size_t)blockIdx.y * M * N;
   const int KT = k_len / BK;
   auto dma = [&](int kt, int st) {
-    const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
+    const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);   // no branch: see the prologue
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      asm volatile("" : "+v"(a_off[j]), "+v"(w_off[j]));   // as in gemm_mfma256w8_kernel
-      __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
-                                       OTAS_LPTR(As + st * STAGE_A + (wave * 16 + j * RPI) * BK), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[j]),
-                                       OTAS_LPTR(Ws + st * STAGE_W + (wave * 16 + j * RPI) * BK), 16, 0, 0);
+    for (int j = 0; j < (NA > NW ? NA : NW); ++j) {
+      if (j < NA) {
+        asm volatile("" : "+v"(a_off[j]));   // as in gemm_mfma256w8_kernel
+        __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
+                                         OTAS_LPTR(As + st * STAGE_A + (wave * (BM / 4) + j * RPI) * BK), 16, 0, 0);
+      }
+      if (j < NW) {
+        asm volatile("" : "+v"(w_off[j]));
+        __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[j]),
+                                         OTAS_LPTR(Ws + st * STAGE_W + (wave * (BN / 4) + j * RPI) * BK), 16, 0, 0);
+      }
     }
   };
-  Acc<2, 2> acc;
+  Acc<RB, CB> acc;
   acc.clear();
   const int fr = lane & 15, fk = lane >> 4;
   const int frag_row = fr * BK, sw = swz(fr);   // swz of 16 w + fr is swz of fr
   bf16_t* bias_s = Ws + NS * STAGE_W;
   bf16x8 bias_v;
   if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
-  ResSlab<1> first;
-  if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * 32, n0 + wn * 32, lane);
+  constexpr bool SLAB = CB % 2 == 0;   // one block of columns has an epilogue of its own
+  ResSlab<SLAB ? CB / 2 : 1> first;
+  if constexpr (EPI == EPI_RESIDUAL && SLAB) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane, RB == 1 ? 16 : 32);
+  // Unconditional: behind a branch the compiler cannot count these and waits for all of them where it uses the bias (a pass of six
+  // ViT-B queries 0.9 % longer).
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t) dma(t, t);
   int st = 0, st_new = NS - 1;
   auto tile = [&](int kt, auto more, auto in_flight) {
     wait_barrier<decltype(in_flight)::value>();
-    bf16x8 af[KS][2], wf[KS][2];
+    bf16x8 af[KS][RB], wf[KS][CB];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int c = (((ks << 2) + fk) ^ sw) * 8;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        af[ks][i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * 32 + 16 * i) * BK + frag_row + c);
-        wf[ks][i] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * 32 + 16 * i) * BK + frag_row + c);
-      }
+      for (int i = 0; i < RB; ++i)
+        af[ks][i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * WM + 16 * i) * BK + frag_row + c);
+#pragma unroll
+      for (int j = 0; j < CB; ++j)
+        wf[ks][j] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * WN + 16 * j) * BK + frag_row + c);
     }
     if constexpr (decltype(more)::value) dma(kt + NS - 1, st_new);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc.mfma(i >> 1, i & 1, wf[ks][i & 1], af[ks][i >> 1]);
+      for (int i = 0; i < RB * CB; ++i) acc.mfma(i / CB, i % CB, wf[ks][i % CB], af[ks][i / CB]);
     st = st + 1 == NS ? 0 : st + 1;
     st_new = st_new + 1 == NS ? 0 : st_new + 1;
   };
@@ -1042,26 +1059,53 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   for (; kt < KT - 1; ++kt) tile(kt, LAST, ONE);
   tile(KT - 1, LAST, NONE);
   wait_barrier<0>();   // every wave has its last fragments: the stages become the epilogue's staging area
-  if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, 2, 2>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (32 + 8), bias_s + wn * 32, Y, M, N,
-                                  m0 + wm * 32, n0 + wn * 32, lane);
+  if constexpr (!SLAB) {
+    // 32 x 32: all waves leave their block in one slab, a thread finishes four columns of a row
+    static_assert(RB == 1 && CB == 1, "256 threads, four outputs each");
+    float* slab = reinterpret_cast<float*>(smem);   // [32][36]
+    *reinterpret_cast<floatx4*>(slab + (wm * 16 + fr) * 36 + wn * 16 + 4 * fk) = acc.v[0][0];
+    __syncthreads();
+    const int r = tid >> 3, c = (tid & 7) * 4;
+    const floatx4 v = *reinterpret_cast<const floatx4*>(slab + r * 36 + c);
+    if (m0 + r < M && n0 + c < N) {
+      typedef typename OutType<bf16_t, EPI>::type OT;
+      const size_t idx = (size_t)(m0 + r) * N + n0 + c;
+      bf16x4 bb = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
+      if (EPI != EPI_PARTIAL) bb = *reinterpret_cast<const bf16x4*>(bias_s + c);
+      floatx4 rr = {0.f, 0.f, 0.f, 0.f};
+      if (EPI == EPI_RESIDUAL) rr = *reinterpret_cast<const floatx4*>(res + idx);
+      Quad<OT> o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float t = EPI == EPI_PARTIAL ? v[e] : v[e] + (float)bb[e];
+        if (EPI == EPI_GELU) t = gelu_bf16(t);
+        if (EPI == EPI_RESIDUAL) t += rr[e];
+        o.x[e] = from_float<OT>(t);
+      }
+      *reinterpret_cast<Quad<OT>*>(Y + idx) = o;
+    }
+  } else if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
+    mfma_epilogue_bf16<EPI, RB, CB>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
+                                    m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, 2, 2, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (32 + 4),
-                                                  bias_s + wn * 32, res, Y, M, N, m0 + wm * 32, n0 + wn * 32, lane, first);
+    mfma_epilogue<EPI, RB, CB, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
+                                                    bias_s + wn * WN, res, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
-template <int BK>
+template <int BK, int RB, int CB>
 static hipError_t linear_mfma64_bk(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
                                    int N, int K, int epi, hipStream_t s, int splits, const PlanTail* pt) {
-  const int tiles_m = (int)((M + 63) / 64), tiles_n = (N + 63) / 64;
-  const size_t lds = ((size_t)4 * (64 + 64) * BK + 64) * sizeof(bf16_t);   // the stages and the tile's bias
-  static_assert(4 * 32 * (32 + 4) * sizeof(float) <= (size_t)4 * (64 + 64) * BK * sizeof(bf16_t), "epilogue slab");
-  static_assert(kPlanListsLdsMax <= (size_t)4 * (64 + 64) * BK * sizeof(bf16_t), "plan lists");
+  constexpr int BM = 32 * RB, BN = 32 * CB;
+  constexpr size_t stages = (size_t)kSmallStages * (BM + BN) * BK * sizeof(bf16_t);
+  const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
+  const size_t lds = stages + BN * sizeof(bf16_t);   // and the tile's bias
+  static_assert(4 * 32 * (16 * CB + 4) * sizeof(float) <= stages, "epilogue slab");
+  static_assert(kPlanListsLdsMax <= stages, "plan lists");
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0)), (unsigned)splits), block(256);
   const int k_len = K / splits;
 #define OTAS_MFMA(E, ...)                                                                                         \
   do {                                                                                                            \
-    auto kern = gemm_mfma64_kernel<E, BK, ##__VA_ARGS__>;                                                         \
+    auto kern = gemm_mfma64_kernel<E, BK, RB, CB, ##__VA_ARGS__>;                                                             \
     hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
@@ -1079,10 +1123,55 @@ static hipError_t linear_mfma64_bk(const void* x, const void* w, const void* bia
   return hipGetLastError();
 }
 
+// Which of its tiles the small-tile kernel runs (the same bits in each).  A launch lasts as long as the fullest CU's chain
+// of k-tiles, and one CU draws its operands at about 75 GB/s whatever the tile: a k-tile costs in proportion to BM + BN.  With
+// a CU for every 32 x 32 or 32 x 64 tile those have the shortest chain; where 64 x 64 just takes a second workgroup per CU,
+// 96 x 64 takes one.  That tile's stages fill more than half a CU's LDS, so that its second workgroup runs after the first.
+// Measured on MI355X, operands from the last-level cache (us, 32 x 32 / 32 x 64 / 64 x 64 / 96 x 64): 197 x 768 x 768 + residual
+// 4.1 / 4.4 / 5.1 / 6.2, 600 4.9 / 4.8 / 5.4 / 6.5, 1406 8.7 / 7.6 / 7.6 / 7.0; 197 x 2304 x 768 4.7 / 4.6 / 5.1 / 5.9, 300 5.7 / 5.7 / 5.2 /
+// 5.9, 500 8.2 / 7.2 / 6.9 / 6.1, 900 12.5 / 10.8 / 10.4 / 10.9; 101 x 3072 x 768 + GELU 4.6 / 4.6 / 5.3 / 6.3, 394 8.6 / 7.5 / 7.3 / 6.6; eight partial
+// products 165 x 768 x 3072 6.0 / 5.8 / 6.2 / 5.3.  32 x 128, 64 x 128, 128 x 64 and rings of six and eight stages win nowhere by
+// more than 0.2 us.
+struct SmallShape { int bm, bn, slots; };   // slots: workgroups on the chip
+static SmallShape small_shape(SmallTile t) {
+  return t == ST_32X32 ? SmallShape{32, 32, 1024} : t == ST_32X64 ? SmallShape{32, 64, 768}
+         : t == ST_96X64 ? SmallShape{96, 64, 256} : SmallShape{64, 64, 512};
+}
+SmallTile pick_small_tile(int64_t M, int N, int K, int splits) {
+  if (K % (splits * 64) != 0) return ST_64X64;   // K step 32: 64 x 64 only
+  struct Cand { SmallTile t; double alpha, first, more; };   // us: launch and epilogue; per column of K, first and later rounds
+  static const Cand cands[] = {{ST_64X64, 2.40, 0.0031, 0.0031}, {ST_32X32, 2.85, 0.00155, 0.00155},
+                               {ST_32X64, 2.80, 0.00233, 0.00233}, {ST_96X64, 3.00, 0.0039, 0.0064}};
+  const int k_len = K / splits;
+  double best = 1e30;
+  SmallTile pick = ST_64X64;
+  for (const Cand& c : cands) {
+    const SmallShape sh = small_shape(c.t);
+    const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn) * splits;
+    const double cost = c.alpha + k_len * (c.first + c.more * (double)((tiles + 255) / 256 - 1));
+    if (cost < best) { best = cost; pick = c.t; }
+  }
+  return pick;
+}
+
+// Whether a launch of `tiles` leaves slots of its last round for B list workgroups.
+static bool lists_fit(int64_t tiles, int slots, int B) { return tiles % slots != 0 && tiles % slots + B <= slots; }
+// The same tile where lists ride along, unless they would not fit beside it and would beside 64 x 64.
+static SmallTile pick_small_tile_with_lists(int64_t M, int N, int K, int B) {
+  const SmallTile t = pick_small_tile(M, N, K, 1);
+  const SmallShape sh = small_shape(t);
+  return lists_fit(((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn), sh.slots, B) ? t : ST_64X64;
+}
+
 static hipError_t linear_mfma64(const void* x, const void* w, const void* bias, const float* res, void* y, int64_t M,
                                 int N, int K, int epi, hipStream_t s, const PlanTail* pt = nullptr, int splits = 1) {
-  return K % (splits * 64) == 0 ? linear_mfma64_bk<64>(x, w, bias, res, y, M, N, K, epi, s, splits, pt)
-                                : linear_mfma64_bk<32>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
+  if (K % (splits * 64) != 0) return linear_mfma64_bk<32, 2, 2>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
+  switch (pt ? pick_small_tile_with_lists(M, N, K, pt->B) : pick_small_tile(M, N, K, splits)) {
+    case ST_32X32: return linear_mfma64_bk<64, 1, 1>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
+    case ST_32X64: return linear_mfma64_bk<64, 1, 2>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
+    case ST_96X64: return linear_mfma64_bk<64, 3, 2>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
+    default: return linear_mfma64_bk<64, 2, 2>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
+  }
 }
 
 // ------------------------------------------------------------------------------ 256x256, 8 waves
@@ -1315,22 +1404,22 @@ static hipError_t linear_mfma256w8(const void* x, const void* w, const void* bia
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------ 128x128, K step 64
-// Block tile 128 x 128, 4 waves of 64 x 64, two LDS stages of K step 64 (rows of 128 B = whole cache
-// lines, 64 KB in all, two workgroups per CU).  Same per-tile protocol as gemm_mfma256w8_kernel.
-template <int EPI, bool PLAN = false>
+// ------------------------------------------------------------------------------ 128 or 160 x 128, K step 64
+// Block tile (32 RB) x 128 with RB = 4 or 5, 4 waves of (16 RB) x 64, two LDS stages of K step 64 (rows of 128 B = whole cache
+// lines, 64 or 72 KB in all, two workgroups per CU).  Same per-tile protocol as gemm_mfma256w8_kernel.
+template <int EPI, int RB, bool PLAN = false>
 __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* __restrict__ A,
                                                                  const bf16_t* __restrict__ W,
                                                                  const bf16_t* __restrict__ bias, const float* res,
                                                                  typename OutType<bf16_t, EPI>::type* Y, int64_t M,
                                                                  int N, int K, int k_len, int tiles_m, int tiles_n,
                                                                  PlanTail pt) {
-  constexpr int BM = 128, BN = 128, BK = 64, WM = 64, WN = 64, TM = 2, TN = 2;
-  constexpr int RB = 2 * TM, CB = 2 * TN, HB = 2;   // as in gemm_mfma256w8_kernel
-  constexpr int STAGE = BM * BK;
+  constexpr int WM = 16 * RB, BM = 2 * WM, BN = 128, BK = 64, WN = 64, TN = 2;
+  constexpr int CB = 2 * TN, HB = 2, ND = RB + 4;   // as in gemm_mfma256w8_kernel
+  constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [2][128][64]
-  bf16_t* Ws = As + 2 * STAGE;                    // [2][128][64]
+  bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [2][BM][64]
+  bf16_t* Ws = As + 2 * STAGE_A;                  // [2][128][64]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: LDS addresses of the DMA stay scalar
@@ -1341,18 +1430,24 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   const int64_t m0 = (int64_t)tile_m * BM;
   const int n0 = tile_n * BN;
 
-  // wave w owns rows w*32 .. w*32+31 of each operand tile, 8 rows (of 128 B) per instruction.
+  // wave w loads rows w*8*RB .. of the A tile and w*32 .. of the W tile, 8 rows (of 128 B) per instruction.
   // Global addresses: uniform base (tile origin + k) plus a constant per-lane 32-bit byte offset.
-  uint32_t a_off[4], w_off[4];
+  uint32_t a_off[RB], w_off[4];
+#pragma unroll
+  for (int j = 0; j < RB; ++j) {
+    const int row = wave * (8 * RB) + j * 8 + (lane >> 3);
+    const int c = (lane & 7) ^ ((row >> 1) & 7);
+    const int64_t last = M - 1 - m0;                  // rows past the end repeat the last row
+    const uint32_t r = (uint32_t)(row < last ? row : last);
+    a_off[j] = (r * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int row = wave * 32 + j * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((row >> 1) & 7);
-    const int64_t a_last = M - 1 - m0;                // rows past the end repeat the last row
-    const int w_last = N - 1 - n0;
-    const uint32_t ra = (uint32_t)(row < a_last ? row : a_last), rw = (uint32_t)(row < w_last ? row : w_last);
-    a_off[j] = (ra * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
-    w_off[j] = (rw * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
+    const int last = N - 1 - n0;
+    const uint32_t r = (uint32_t)(row < last ? row : last);
+    w_off[j] = (r * (uint32_t)K + (uint32_t)c * 8u) * (uint32_t)sizeof(bf16_t);
   }
   // split-K launches: workgroup row blockIdx.y contracts over k_len columns from blockIdx.y * k_len and writes the
   // float partial result [M, N] number blockIdx.y
@@ -1360,19 +1455,20 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   const char* w_base = reinterpret_cast<const char*>(W + (size_t)n0 * K + (size_t)blockIdx.y * k_len);
   if (EPI == EPI_PARTIAL) Y += (size_t)blockIdx.y * M * N;
   const int KT = k_len / BK;
-  auto dma_one = [&](int kt, int st, int d) {   // d = 0..7
+  auto dma_one = [&](int kt, int st, int d) {   // d < 8: A and W rows in turn; then A's other rows
     const size_t kb = (size_t)((kt < KT ? kt : KT - 1) * BK) * sizeof(bf16_t);
-    const int j = d >> 1;
-    asm volatile("" : "+v"((d & 1) == 0 ? a_off[j] : w_off[j]));   // as in gemm_mfma256w8_kernel
-    if ((d & 1) == 0)
-      __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
-                                       OTAS_LPTR(As + st * STAGE + (wave * 32 + j * 8) * BK), 16, 0, 0);
-    else
+    const bool is_w = d < 8 && (d & 1);
+    const int j = d < 8 ? d >> 1 : d - 4;
+    asm volatile("" : "+v"(is_w ? w_off[j] : a_off[j]));   // as in gemm_mfma256w8_kernel
+    if (is_w)
       __builtin_amdgcn_global_load_lds(OTAS_GPTR(w_base + kb + w_off[j]),
-                                       OTAS_LPTR(Ws + st * STAGE + (wave * 32 + j * 8) * BK), 16, 0, 0);
+                                       OTAS_LPTR(Ws + st * STAGE_W + (wave * 32 + j * 8) * BK), 16, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds(OTAS_GPTR(a_base + kb + a_off[j]),
+                                       OTAS_LPTR(As + st * STAGE_A + (wave * (8 * RB) + j * 8) * BK), 16, 0, 0);
   };
 
-  Acc<2 * TM, 2 * TN> acc;
+  Acc<RB, CB> acc;
   acc.clear();
 
   const int fr = lane & 15, fk = lane >> 4;
@@ -1380,11 +1476,11 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   bf16x8 af[RB], wf[2][CB];
   auto read_a = [&](int st, int ks, int i) {
     const int c = (((ks << 2) + fk) ^ sw) * 8;
-    af[i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE + (wm * WM + i * 16) * BK + frag_row + c);
+    af[i] = *reinterpret_cast<const bf16x8*>(As + st * STAGE_A + (wm * WM + i * 16) * BK + frag_row + c);
   };
   auto read_w = [&](int st, int ks, int j) {
     const int c = (((ks << 2) + fk) ^ sw) * 8;
-    wf[ks][j] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE + (wn * WN + j * 16) * BK + frag_row + c);
+    wf[ks][j] = *reinterpret_cast<const bf16x8*>(Ws + st * STAGE_W + (wn * WN + j * 16) * BK + frag_row + c);
   };
   auto rows = [&](int ks, int i0, int i1, int st, auto next, auto load) {
 #pragma unroll
@@ -1404,16 +1500,16 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
   };
   auto no_load = [](int) {};
 
-  bf16_t* bias_s = Ws + 2 * STAGE;
+  bf16_t* bias_s = Ws + 2 * STAGE_W;
   bf16x8 bias_v;
   if (EPI != EPI_PARTIAL) bias_v = bias_fetch<BN>(bias, N, n0, tid);
   ResSlab<TN> first;
   if (EPI == EPI_RESIDUAL) first.load(res, M, N, m0 + wm * WM, n0 + wn * WN, lane);
 #pragma unroll
-  for (int d = 0; d < 8; ++d) dma_one(0, 0, d);
+  for (int d = 0; d < ND; ++d) dma_one(0, 0, d);
 #pragma unroll
-  for (int d = 0; d < 8; ++d) dma_one(1, 1, d);
-  OTAS_VMCNT(8);
+  for (int d = 0; d < ND; ++d) dma_one(1, 1, d);
+  OTAS_VMCNT(ND);
   if (EPI != EPI_PARTIAL) bias_stage<BN>(bias_s, bias_v, tid);
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
@@ -1433,31 +1529,32 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma128k64_kernel(const bf16_t* _
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     rows(1, HB, RB, st ^ 1, next, [&](int t) {
-      if constexpr (LOAD) dma_one(kt + 2, st, t);
+      if constexpr (LOAD) { if (t < ND) dma_one(kt + 2, st, t); }
     });
   };
-  static_assert((RB - HB) * CB == 8, "a load behind each MFMA");
+  static_assert((RB - HB) * CB >= ND, "a load behind each MFMA");
   for (int kt = 0; kt < KT - 2; ++kt) tile(kt, std::true_type(), std::true_type());
   tile(KT - 2, std::false_type(), std::true_type());
   tile(KT - 1, std::false_type(), std::false_type());
   if constexpr (EPI == EPI_NONE || EPI == EPI_GELU)
-    mfma_epilogue_bf16<EPI, 2 * TM, 2 * TN>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
+    mfma_epilogue_bf16<EPI, RB, CB>(acc, reinterpret_cast<bf16_t*>(smem) + wave * 32 * (WN + 8), bias_s + wn * WN, Y, M, N,
                                     m0 + wm * WM, n0 + wn * WN, lane);
   else
-    mfma_epilogue<EPI, 2 * TM, 2 * TN, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
+    mfma_epilogue<EPI, RB, CB, EPI == EPI_RESIDUAL>(acc, reinterpret_cast<float*>(smem) + wave * 32 * (WN + 4),
                                                     bias_s + wn * WN, res, Y, M, N, m0 + wm * WM, n0 + wn * WN, lane, first);
 }
 
-static hipError_t linear_mfma128k64(const void* x, const void* w, const void* bias, const float* res, void* y,
-                                    int64_t M, int N, int K, int epi, hipStream_t s, int splits = 1,
-                                    const PlanTail* pt = nullptr) {
-  const int tiles_m = (int)((M + 127) / 128), tiles_n = (N + 127) / 128;
-  const size_t lds = ((size_t)2 * 2 * 128 * 64 + 128) * sizeof(bf16_t);   // the stages and the tile's bias
+template <int RB>
+static hipError_t linear_mfma128k64_rb(const void* x, const void* w, const void* bias, const float* res, void* y,
+                                       int64_t M, int N, int K, int epi, hipStream_t s, int splits, const PlanTail* pt) {
+  constexpr int BM = 32 * RB;
+  const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + 127) / 128;
+  const size_t lds = ((size_t)2 * (BM + 128) * 64 + 128) * sizeof(bf16_t);   // the stages and the tile's bias
   dim3 grid((unsigned)(tiles_m * tiles_n + (pt ? pt->B : 0)), (unsigned)splits), block(256);
   const int k_len = K / splits;
 #define OTAS_MFMA(E, ...)                                                                                         \
   do {                                                                                                            \
-    auto kern = gemm_mfma128k64_kernel<E, ##__VA_ARGS__>;                                                         \
+    auto kern = gemm_mfma128k64_kernel<E, RB, ##__VA_ARGS__>;                                                        \
     hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
     if (e != hipSuccess) return e;                                                                                \
     kern<<<grid, block, lds, s>>>((const bf16_t*)x, (const bf16_t*)w, (const bf16_t*)bias, res,                   \
@@ -1473,6 +1570,28 @@ static hipError_t linear_mfma128k64(const void* x, const void* w, const void* bi
   else OTAS_MFMA(EPI_RESIDUAL);
 #undef OTAS_MFMA
   return hipGetLastError();
+}
+
+// 128 or 160 rows (the same bits): 160 where that takes the fullest CU a workgroup less.  Two workgroups of a CU share its path to
+// L2, so that the second costs most of a round although it runs beside the first; a tile of 160 rows costs a tenth more.  Up to
+// 768 columns of K: inside a pass, whose operands come from farther away, a long chain of k-tiles wants the second workgroup beside
+// it (us in a pass of 64 / 24 queries with r = 16 / 10, 128 / 160 rows: 6464 x 768 x 3072 52.5 / 61.0, two partial products of 3300 x 768 x
+// 3072 28.0 / 31.6; passes of 28 and 32 queries without merging 0.9 % shorter with 160 rows up to that line).
+// Measured on MI355X (us, 128 / 160 rows, in brackets the workgroups of the fullest CU): 1406 x 3072 x 768 + GELU 14.1 / 13.7 (2 / 1),
+// 2000 x 2304 x 768 12.6 / 12.3 (2 / 1), 3600 22.7 / 16.7 (3 / 2), 6000 x 768 x 768 + residual 17.3 / 15.2 (2 / 1), 6000 x 768 x 3072 42.2 /
+// 40.6 (2 / 1, alone), six partial products of 900 x 768 x 3072 13.1 / 12.1 (2 / 1), 8000 x 2304 x 768 34.8 / 31.4 (5 / 4); with as many either
+// way 10.9 / 11.7 (1300 x 2304 x 768) to 39.8 / 43.6.  192, 224 and 256 rows: one workgroup per CU, faster than both by 0.5 us at most.
+int wide_rows(int64_t M, int N, int K, int splits) {
+  if (K / splits > 768) return 128;
+  const int64_t cols = (int64_t)((N + 127) / 128) * splits;
+  return ((M + 127) / 128 * cols + 255) / 256 > ((M + 159) / 160 * cols + 255) / 256 ? 160 : 128;
+}
+
+static hipError_t linear_mfma128k64(const void* x, const void* w, const void* bias, const float* res, void* y,
+                                    int64_t M, int N, int K, int epi, hipStream_t s, int splits = 1,
+                                    const PlanTail* pt = nullptr) {
+  return wide_rows(M, N, K, splits) == 160 ? linear_mfma128k64_rb<5>(x, w, bias, res, y, M, N, K, epi, s, splits, pt)
+                                        : linear_mfma128k64_rb<4>(x, w, bias, res, y, M, N, K, epi, s, splits, pt);
 }
 
 // Runs one named kernel (gemm_kernel_id in kernels.h); hipErrorInvalidValue if it does not take the shape.
@@ -1627,18 +1746,22 @@ bool linear_plan_tail_fits(int dtype, const void* x, const void* w, int64_t M, i
   if (M <= 0 || B <= 0 || !(K % 32 == 0 && K >= 64 && N % 8 == 0)) return false;
   int bm = 128, bn = 128, slots = 768;
   switch (pick_mfma_kernel(M, N, K, EPI_RESIDUAL)) {
-    case GK_128_K64: slots = 512; break;
+    case GK_128_K64: bm = wide_rows(M, N, K, 1); slots = 512; break;
     case GK_160X256: bm = 160; bn = 256; slots = 256; break;
     case GK_192X256: bm = 192; bn = 256; slots = 256; break;
     case GK_224X256: bm = 224; bn = 256; slots = 256; break;
     case GK_288X256: bm = 288; bn = 256; slots = 256; break;
     case GK_256X256: bm = 256; bn = 256; slots = 256; break;
     case GK_320X256: bm = 320; bn = 256; slots = 256; break;
-    case GK_64X64: bm = 64; bn = 64; slots = K % 64 == 0 ? 512 : 1024; break;
+    case GK_64X64: {
+      const SmallShape sh = small_shape(pick_small_tile_with_lists(M, N, K, B));
+      bm = sh.bm; bn = sh.bn; slots = K % 64 == 0 ? sh.slots : 1024;
+      break;
+    }
     default: break;
   }
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  return tiles % slots + B <= slots && tiles % slots != 0;
+  return lists_fit(tiles, slots, B);
 }
 
 hipError_t launch_linear_plan_tail(int dtype, const void* x, const void* w, const void* bias, const float* res, void* y,

@@ -86,12 +86,16 @@ bool streams_output(int64_t M, int N, int epi, int64_t model_bytes);
 
 // The same with the kernel named by the caller (tests and profiling exercise every kernel at every
 // shape this way): GK_AUTO = launch_linear's own choice, GK_FMA = fp32 arithmetic (any dtype),
-// the others bf16 MFMA kernels named by block tile (rows x columns) and K step.  Returns
+// the others bf16 MFMA kernels named by block tile (rows x columns; of GK_64X64 and GK_128_K64 the first of several) and K step.  Returns
 // hipErrorInvalidValue if the kernel does not take the shape (K % 32 / K % 64, N % 8).
 enum gemm_kernel_id {
   GK_AUTO = 0, GK_FMA = 1, GK_128_K32 = 2, GK_128_K64 = 3, GK_192X256 = 4, GK_256X256 = 5, GK_320X256 = 6,
   GK_64X64 = 7, GK_160X256 = 8, GK_224X256 = 9, GK_288X256 = 10, GK_COUNT = 11
 };
+// The tiles that kernels 7 and 3 run a shape in (pure host): their results are the same bits.
+enum SmallTile { ST_64X64 = 0, ST_32X32 = 1, ST_32X64 = 2, ST_96X64 = 3 };
+SmallTile pick_small_tile(int64_t M, int N, int K, int splits);
+int wide_rows(int64_t M, int N, int K, int splits);   // 128 or 160
 int linear_kernel_choice(int dtype, int64_t M, int N, int K, int epi);   // the id launch_linear runs for this shape
 hipError_t launch_linear_kernel(int kernel, int dtype, const void* x, const void* w, const void* bias,
                                 const float* res, void* y, int64_t M, int N, int K, int epi, hipStream_t s);

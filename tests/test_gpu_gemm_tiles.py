@@ -103,3 +103,93 @@ def test_small_tiles_whose_last_stage_the_epilogue_takes(lib, K, epi):
         ctx.otas_linear_kernel(7, x, w, b, res, M, N, K, epi, got)
         assert torch.equal(got, want)
     ctx.close()
+
+
+def _against_float64(out, x, w, b, res, epi):
+    """K + 8 roundings of 2^-24 on the terms' absolute sum, GELU's slope below 1.13, the rounding of a bf16 output."""
+    import torch
+    xd, wd, bd, K = x.double(), w.double(), b.double(), x.shape[1]
+    lin, mag = xd @ wd.T + bd, xd.abs() @ wd.abs().T + bd.abs()
+    want = torch.nn.functional.gelu(lin) if epi == 1 else lin + res.double() if epi == 2 else lin
+    bound = (K + 8) * 2.0 ** -24 * 1.13 * (mag + (res.double().abs() if epi == 2 else 0))
+    if epi != 2:
+        bound = bound + 2.0 ** -8 * want.abs() + 1e-7
+    return bool(((out.double() - want).abs() <= bound).all())
+
+
+# tile of kernel 7 -> shapes that are run in it, whole tiles and ragged ones; K of five to twelve k-tiles and of 48
+SMALL = {1: [(1, 8, 320), (32, 32, 384), (197, 200, 448), (65, 1000, 768), (33, 40, 3072)],
+         2: [(197, 2304, 768), (220, 2048, 640), (190, 2056, 576)],
+         0: [(64, 64, 128), (250, 2304, 768), (700, 1000, 64), (130, 72, 192)],
+         3: [(576, 2304, 768), (481, 2304, 384), (500, 2360, 320)]}
+
+
+@pytest.mark.parametrize("epi", [0, 1, 2])
+@pytest.mark.parametrize("tile", sorted(SMALL))
+def test_tiles_of_the_small_kernel(lib, tile, epi):
+    """Kernel 7 in each of its tiles (which one a shape takes is asked of the library) against float64, and bit for bit against the
+    K-step-32 kernel, which walks K in the same order in tiles of 128 x 128."""
+    import ctypes
+    import torch
+    pick = ctypes.CDLL(lib.lib_path())._ZN4otas15pick_small_tileEliii
+    pick.argtypes, pick.restype = [ctypes.c_int64] + [ctypes.c_int] * 3, ctypes.c_int
+    ctx = _context()
+    g = torch.Generator(device="cuda").manual_seed(10 * tile + epi)
+    for M, N, K in SMALL[tile]:
+        assert pick(M, N, K, 1) == tile, (M, N, K)
+        x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+        res = torch.randn((M, N), generator=g, device="cuda") if epi == 2 else None
+        out = {}
+        for k in (7, 2):
+            out[k] = torch.full((M, N), float("nan"), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+            ctx.otas_linear_kernel(k, x, w, b, res, M, N, K, epi, out[k])
+        assert _against_float64(out[7], x, w, b, res, epi), (M, N, K)
+        assert torch.equal(out[7], out[2]), (M, N, K)
+    ctx.close()
+
+
+@pytest.mark.parametrize("epi", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K,rows", [(1920, 2304, 128, 160), (1921, 2176, 192, 160), (2079, 2304, 256, 160), (1406, 3072, 768, 160),
+                                        (3599, 2296, 320, 160), (1281, 2304, 192, 128), (159, 136, 128, 128), (1920, 2304, 832, 128)])
+def test_tiles_of_128_and_160_rows(lib, M, N, K, rows, epi):
+    """Kernel 3 where the fullest CU has a tile fewer with 160 rows and where it has not; the last tile of one row, one row short
+    and whole; two k-tiles to twelve."""
+    import ctypes
+    import torch
+    wide = ctypes.CDLL(lib.lib_path())._ZN4otas9wide_rowsEliii
+    wide.argtypes, wide.restype = [ctypes.c_int64] + [ctypes.c_int] * 3, ctypes.c_int
+    assert wide(M, N, K, 1) == rows
+    ctx = _context()
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x, w, b = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K), (N,)))
+    res = torch.randn((M, N), generator=g, device="cuda") if epi == 2 else None
+    out = {}
+    for k in (3, 2):
+        out[k] = torch.full((M, N), float("nan"), dtype=torch.float32 if epi == 2 else torch.bfloat16, device="cuda")
+        ctx.otas_linear_kernel(k, x, w, b, res, M, N, K, epi, out[k])
+    assert _against_float64(out[3], x, w, b, res, epi)
+    assert torch.equal(out[3], out[2])
+    ctx.close()
+
+
+@pytest.mark.parametrize("M,N,K,S", [(21, 768, 3072, 8), (32, 768, 3072, 8), (100, 768, 3072, 8), (165, 768, 3072, 8),
+                                     (400, 768, 3072, 8), (950, 768, 3072, 6), (1406, 768, 3072, 4), (2000, 768, 3072, 4)])
+def test_partial_products_in_every_tile(lib, M, N, K, S):
+    """The partial products of a split, whichever tile they run in, are the products of the pieces of K bit for bit."""
+    import ctypes
+    import torch
+    split = ctypes.CDLL(lib.lib_path())._ZN4otas20launch_linear_splitkEPKvS1_PfliiiP12ihipStream_t
+    vp = ctypes.c_void_p
+    split.argtypes, split.restype = [vp, vp, vp, ctypes.c_int64] + [ctypes.c_int] * 3 + [vp], ctypes.c_int
+    ctx = _context()
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x, w = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K)))
+    part = torch.full((S, M, N), float("nan"), device="cuda")
+    torch.cuda.synchronize()
+    assert split(x.data_ptr(), w.data_ptr(), part.data_ptr(), M, N, K, S, torch.cuda.current_stream().cuda_stream) == 0
+    zero, none = torch.zeros((M, N), device="cuda"), torch.zeros(N, dtype=torch.bfloat16, device="cuda")
+    for i, (xs, ws) in enumerate(zip(x.chunk(S, 1), w.chunk(S, 1))):
+        want = torch.full((M, N), float("nan"), device="cuda")
+        ctx.otas_linear_kernel(2, xs.contiguous(), ws.contiguous(), none, zero, M, N, K // S, 2, want)
+        assert torch.equal(part[i], want), i
+    ctx.close()
