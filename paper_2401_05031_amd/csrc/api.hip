@@ -582,6 +582,7 @@ struct LaneRun {
   int64_t rowL;                  // first packed row of the lane in the output
   std::vector<int64_t> T;        // packed rows of the lane entering layer l (l = 0 .. L)
   std::vector<int> max_n;        // longest query entering layer l
+  std::vector<int> long_blocks;  // attention_long_blocks of layer l
   std::vector<char> any_merge;
   int last_merge;
   // running state
@@ -698,15 +699,18 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
     if ((size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg > kPlanInts - ln.plan_base) return OTAS_ENOMEM;
     ln.T.assign(L + 1, 0);
     ln.max_n.assign(L + 1, 0);
+    ln.long_blocks.assign(L + 1, 0);
     ln.any_merge.assign(L, 0);
     ln.last_merge = -1;
-    for (int l = 0; l <= L; ++l)
+    for (int l = 0; l <= L; ++l) {
       for (int q = ln.q0; q < ln.q1; ++q) {
         const int n = len[(size_t)l * B + q];
         ln.T[l] += n;
         ln.max_n[l] = std::max(ln.max_n[l], n);
         if (l < L && reff[(size_t)l * B + q] > 0) { ln.any_merge[l] = 1; ln.last_merge = l; }
       }
+      ln.long_blocks[l] = attention_long_blocks(&len[(size_t)l * B + ln.q0], Bg, ln.max_n[l]);
+    }
     if (start) continue;
     plan.resize(ln.plan_base + (size_t)(L + 1) * (Bg + 1) + 2 * (size_t)L * Bg);
     int32_t* off = plan.data() + ln.plan_base;
@@ -846,7 +850,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
       int32_t* sel_bcol = (int32_t*)(sel_best + (size_t)how.nb * T);
       if (fuse) {
         OTAS_LAUNCH_ON(K_ATTN, s,
-                       launch_attention_plan(dt, qkv, ln.sizes_now, off_l, off_n, d_reff, d_tr, Bg, ln.max_n[l], D, H,
+                       launch_attention_plan(dt, qkv, ln.sizes_now, off_l, off_n, d_reff, d_tr, Bg, ln.max_n[l], ln.long_blocks[l], D, H,
                                              size_bias, n_lead, hbuf, src_list, row_ptr,
                                              trace ? trace_src : nullptr, trace ? trace_dst : nullptr,
                                              tail ? sel_best : nullptr, tail ? sel_bcol : nullptr, T, s));
@@ -866,7 +870,7 @@ otas_status run_layers(otas_ctx* c, int32_t layer_begin, int32_t layer_end, cons
           if (!plan_inline) OTAS_HIP(hipEventRecord(hw.ev_join, hw.side));
         }
         OTAS_LAUNCH_ON(K_ATTN, s,
-                       launch_attention(dt, qkv, ln.sizes_now, off_l, Bg, ln.max_n[l], D, H, size_bias, hbuf, s));
+                       launch_attention(dt, qkv, ln.sizes_now, off_l, Bg, ln.max_n[l], ln.long_blocks[l], D, H, size_bias, hbuf, s));
       }
       // in-place residual is safe (each element is read then written by the same thread); the
       // caller's x0 is never written, so layer 0 writes into the workspace.
@@ -968,7 +972,7 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
   // Length schedule: constant (replace) or + P_q per layer (grow); x0 holds layer 0's prompts.
   // Plan layout (int32): off[l][B+1] for l = 0..L-1 | prompt offsets [B+1].
   std::vector<int32_t> plan((size_t)(L + 1) * (B + 1));
-  std::vector<int> max_n(L, 0);
+  std::vector<int> max_n(L, 0), long_blocks(L, 0), lens(B);
   int max_p = 0;
   for (int l = 0; l < L; ++l) {
     int32_t* off = &plan[(size_t)l * (B + 1)];
@@ -979,9 +983,11 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
       const int nl = n + (grow ? l * P : 0);
       if (nl > OTAS_MAX_SEQ) return OTAS_EUNSUPPORTED;
       off[q + 1] = off[q] + nl;
+      lens[q] = nl;
       max_n[l] = std::max(max_n[l], nl);
       max_p = std::max(max_p, P);
     }
+    long_blocks[l] = attention_long_blocks(lens.data(), B, max_n[l]);
   }
   std::memcpy(&plan[(size_t)L * (B + 1)], prompt_offsets, (B + 1) * sizeof(int32_t));
   const int32_t* off_last = &plan[(size_t)(L - 1) * (B + 1)];
@@ -1054,7 +1060,7 @@ otas_status otas_encoder_forward_deep(otas_ctx* c, const void* x0, const int32_t
                                                        start && l == 0 ? &job : nullptr));
     ln1_done = false;
     OTAS_LAUNCH(K_QKV, launch_linear(dt, hbuf, wl.w_qkv, wl.b_qkv, nullptr, qkv, T, 3 * D, D, EPI_NONE, s));
-    OTAS_LAUNCH(K_ATTN, launch_attention(dt, qkv, nullptr, off_l, B, max_n[l], D, H, false, hbuf, s));
+    OTAS_LAUNCH(K_ATTN, launch_attention(dt, qkv, nullptr, off_l, B, max_n[l], long_blocks[l], D, H, false, hbuf, s));
     if (cur < 0) cur = 0;   // the caller's x0 is never written: layer 0 of an f32 model writes into the workspace
     OTAS_LAUNCH(K_PROJ, launch_linear(dt, hbuf, wl.w_proj, wl.b_proj, x_cur, x_buf[cur], T, D, D, EPI_RESIDUAL, s));
     x_cur = x_buf[cur];
@@ -1178,13 +1184,15 @@ otas_status otas_attention(otas_ctx* c, const void* qkv, const int32_t* sizes, c
   const bool size_bias = flags & OTAS_FLAG_SIZE_BIAS;
   if (size_bias && !sizes) return OTAS_EINVAL;
   int max_n = 0;
-  for (int q = 0; q < B; ++q) max_n = std::max(max_n, offsets[q + 1] - offsets[q]);
+  std::vector<int> lens(B);
+  for (int q = 0; q < B; ++q) max_n = std::max(max_n, lens[q] = offsets[q + 1] - offsets[q]);
   if (max_n > OTAS_MAX_SEQ) return OTAS_EUNSUPPORTED;
+  const int long_blocks = attention_long_blocks(lens.data(), B, max_n);
   std::vector<int32_t> plan(offsets, offsets + B + 1);
   if (hipSetDevice(c->device) != hipSuccess) return OTAS_EDEVICE;
   otas_status st = upload_plan(c, plan);
   if (st != OTAS_OK) return st;
-  OTAS_LAUNCH(K_ATTN, launch_attention(c->desc.dtype, qkv, sizes, c->d_plan, B, max_n, c->desc.D, c->desc.H, size_bias, o,
+  OTAS_LAUNCH(K_ATTN, launch_attention(c->desc.dtype, qkv, sizes, c->d_plan, B, max_n, long_blocks, c->desc.D, c->desc.H, size_bias, o,
                             c->stream));
   return OTAS_OK;
 }

@@ -208,7 +208,8 @@ static hipError_t attention_f32(const void* qkv, const int32_t* sz, const int32_
 }
 
 // ------------------------------------------------------------------------------ bf16 MFMA
-// grid (ceil(max_n / (32 NW)), H, B), NW waves (4 or 8): each wave owns 32 query rows of one (query, head).
+// grid (ceil(max_n / (32 NW / KG)), H, B), NW waves (4 or 8): each wave owns 32 query rows of one (query, head) and, where KG > 1,
+// every KG-th block of its keys; what the KG waves of a row block hold is added up at the end (attention_combine).
 // The keys and values of the head are staged in LDS in chunks of up to KC rows (rows padded
 // by 16 bytes so that the 16 lanes served per clock fall on distinct banks); every wave then walks
 // the chunk in blocks of 32 keys with an online softmax (running row maximum and sum, fp32).
@@ -226,11 +227,63 @@ static hipError_t attention_f32(const void* qkv, const int32_t* sz, const int32_
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef short short8_t __attribute__((ext_vector_type(8)));
 
-// One (query q, head h, block xblk of 32 NW query rows) on NW waves: tid = thread index among those 64 NW
+// LDS of the partial results of NW waves: O as the accumulators hold it, the rows' maxima and sums.
+constexpr int attention_parts_floats(int DH, int NW) { return NW * (16 * ((DH + 31) / 32) * 64 + 64); }
+
+// Adds up what the KG key groups of a row block hold, each relative to its own maximum m with the sum l: wave (kg, rw) left O in
+// LDS and finishes every KG-th run of four columns.  A group's part counts for exp2(m - the largest m), groups in ascending
+// order.  orow: this lane's output row, or null.
+template <int DH, int NW, int KG>
+__device__ __forceinline__ void attention_combine(const floatx16 (&oacc)[(DH + 31) / 32], float m, float l, float* lds, int wave,
+                                                  int kg, int rw, int lane, bool active, bf16_t* orow) {
+  constexpr int DT = (DH + 31) / 32, NQ = 4 * DT, RW = NW / KG;
+  float* parts = lds;                              // [NW][NQ][64][4]
+  float* ml = lds + NW * NQ * 256;                 // [NW][2][32]
+  const int fr = lane & 31, fk = lane >> 5;
+  __syncthreads();                                 // everyone is done with the keys and values
+  if (active) {
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+      *reinterpret_cast<floatx4*>(parts + ((wave * NQ + i) * 64 + lane) * 4) =
+          floatx4{oacc[i / 4][4 * (i % 4)], oacc[i / 4][4 * (i % 4) + 1], oacc[i / 4][4 * (i % 4) + 2], oacc[i / 4][4 * (i % 4) + 3]};
+    if (fk == 0) {
+      ml[wave * 64 + fr] = m;
+      ml[wave * 64 + 32 + fr] = l;
+    }
+  }
+  __syncthreads();
+  if (!active) return;
+  float f[KG], m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int g = 0; g < KG; ++g) m_all = fmaxf(m_all, f[g] = ml[(g * RW + rw) * 64 + fr]);
+#pragma unroll
+  for (int g = 0; g < KG; ++g) {
+    f[g] = __builtin_amdgcn_exp2f(f[g] - m_all);   // 0 for a group without a key
+    l_all += f[g] * ml[(g * RW + rw) * 64 + 32 + fr];
+  }
+  const float inv = 1.0f / l_all;
+#pragma unroll
+  for (int j = 0; j < NQ / KG; ++j) {
+    const int i = j * KG + kg;
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+      const floatx4 p = *reinterpret_cast<const floatx4*>(parts + (((g * RW + rw) * NQ + i) * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaf(f[g], p[e], v[e]);
+    }
+    const int d = 8 * i + 4 * fk;
+    if (orow && d < DH)
+      *reinterpret_cast<bf16x4*>(orow + d) =
+          bf16x4{(bf16_t)(v[0] * inv), (bf16_t)(v[1] * inv), (bf16_t)(v[2] * inv), (bf16_t)(v[3] * inv)};
+  }
+}
+
+// One (query q, head h, block xblk of 32 NW / KG query rows) on NW waves: tid = thread index among those 64 NW
 // threads, smem = their LDS region.  Every __syncthreads() below is reached by all threads of the workgroup
 // that share q and xblk (the trip counts depend on the query's length and xblk only), so a workgroup may run
 // several heads of one query side by side, each on its own NW waves and LDS region.
-template <int DH, bool BIAS, int KC, int NW>
+template <int DH, bool BIAS, int KC, int NW, int KG>
 __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes,
                                                     const int32_t* __restrict__ off, int D, float scale,
                                                     bf16_t* __restrict__ o, const int q, const int h, const int xblk,
@@ -243,15 +296,16 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
   bf16_t* Vs = Ks + KC * LD;                              // [VROWS][LD]
   float* lnsz = reinterpret_cast<float*>(Vs + VROWS * LD);  // [KC] log2(size) of the chunk's keys
 
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = KG == 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);   // key loops with scalar bounds
   const int base = off[q], n = off[q + 1] - base;
-  constexpr int NT = 64 * NW;             // threads: NW waves of 32 query rows each
-  const int row0 = xblk * (32 * NW);
+  constexpr int NT = 64 * NW, RW = NW / KG;   // threads; waves side by side in the query rows
+  const int row0 = xblk * (32 * RW);
   if (row0 >= n) return;
   const size_t ld = (size_t)3 * D;
   const int fr = lane & 31, fk = lane >> 5;
-  const int my_row = row0 + wave * 32 + fr;
-  const bool wave_active = row0 + wave * 32 < n;
+  const int kg = KG == 1 ? 0 : wave / RW, rw = KG == 1 ? wave : wave % RW;
+  const int my_row = row0 + rw * 32 + fr;
+  const bool wave_active = row0 + rw * 32 < n;
 
   // Q fragments (B operand): lane (row, half) holds Q[row][16 ks + 8 half .. +7]
   bf16x8 qf[KS];
@@ -344,7 +398,8 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
       if (!BIAS) mx *= scale2;
       if (__any(mx > m_run)) {   // some row's maximum moved: rescale what has been accumulated
         const float m_new = fmaxf(m_run, mx);
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
+        // 0 on a row's first block (m_run = -inf); a row whose keys all had no weight so far has nothing to rescale
+        const float alpha = KG > 1 && m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
         l_part *= alpha;
 #pragma unroll
@@ -352,11 +407,13 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
 #pragma unroll
           for (int e = 0; e < 16; ++e) oacc[t][e] *= alpha;
       }
+      // a key group may begin with keys of no weight (sizes 0) where the whole sequence does not
+      const float m_ref = KG > 1 && m_run == -INFINITY ? 0.f : m_run;
       float psum = 0.f;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const float pv = BIAS ? __builtin_amdgcn_exp2f(sacc[e] - m_run)
-                              : __builtin_amdgcn_exp2f(fmaf(sacc[e], scale2, -m_run));
+        const float pv = BIAS ? __builtin_amdgcn_exp2f(sacc[e] - m_ref)
+                              : __builtin_amdgcn_exp2f(fmaf(sacc[e], scale2, -m_ref));
         sacc[e] = pv;
         psum += pv;
       }
@@ -387,17 +444,22 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
     };
     const int nblk = nc_pad >> 5;
     floatx16 s_even, s_odd;
-    s_block(s_even, 0);
-    for (int b = 0; b < nblk; b += 2) {
-      if (b + 1 < nblk) s_block(s_odd, (b + 1) * 32);
+    s_block(s_even, KG == 1 ? 0 : min(kg, nblk - 1) * 32);
+    for (int b = kg; b < nblk; b += 2 * KG) {
+      if (b + KG < nblk) s_block(s_odd, (b + KG) * 32);
       __builtin_amdgcn_sched_barrier(0);
       softmax_pv(s_even, b * 32);
-      if (b + 1 < nblk) {
-        if (b + 2 < nblk) s_block(s_even, (b + 2) * 32);
+      if (b + KG < nblk) {
+        if (b + 2 * KG < nblk) s_block(s_even, (b + 2 * KG) * 32);
         __builtin_amdgcn_sched_barrier(0);
-        softmax_pv(s_odd, (b + 1) * 32);
+        softmax_pv(s_odd, (b + KG) * 32);
       }
     }
+  }
+  if constexpr (KG > 1) {
+    attention_combine<DH, NW, KG>(oacc, m_run, xor32_sum(l_part), reinterpret_cast<float*>(smem), wave, kg, rw, lane, wave_active,
+                                  my_row < n ? o + (size_t)(base + my_row) * D + h * DH : nullptr);
+    return;
   }
   if (!wave_active) return;
   const float l_tot = xor32_sum(l_part);
@@ -418,13 +480,13 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
   }
 }
 
-template <int DH, bool BIAS, int KC, int NW>
+template <int DH, bool BIAS, int KC, int NW, int KG>
 __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kernel(const bf16_t* __restrict__ qkv,
                                                              const int32_t* __restrict__ sizes,
                                                              const int32_t* __restrict__ off, int D, float scale,
                                                              bf16_t* __restrict__ o) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  attention_mfma_body<DH, BIAS, KC, NW>(qkv, sizes, off, D, scale, o, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x,
+  attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x,
                                         smem, (int)threadIdx.x);
 }
 
@@ -440,7 +502,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kern
 // only (four waves per SIMD leave 128 registers per lane).
 // grid.x = B * na * nb + xblks * (H / G) * B with G = 8 / NW (na = nb = 1 for the whole plan).
 constexpr int kFusedThreads = 512;
-template <bool BIAS, int KC, int NW>
+template <bool BIAS, int KC, int NW, int KG>
 __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
     const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes, const int32_t* __restrict__ off, int D, int H,
     float scale, bf16_t* __restrict__ o, int B, int xblks, const int32_t* __restrict__ out_off,
@@ -468,50 +530,88 @@ __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
   id /= xblks;
   const int hgrp = id % hg, q = id / hg;
   const int unit = (int)threadIdx.x / (64 * NW), tid = (int)threadIdx.x % (64 * NW);
-  attention_mfma_body<DH, BIAS, KC, NW>(qkv, sizes, off, D, scale, o, q, hgrp * G + unit, xblk, smem + (size_t)unit * unit_lds,
+  attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, hgrp * G + unit, xblk, smem + (size_t)unit * unit_lds,
                                         tid);
 }
 
+// How a launch cuts up its work: keys staged at a time, waves per head and row block, key groups.
+struct AttnShape { int kc, nw, kg; };
+constexpr size_t attention_lds_bytes(int dh, int kc, int nw, int kg) {
+  const size_t staged = (size_t)(kc + kc + 4) * (dh + 8) * sizeof(bf16_t) + kc * sizeof(float);
+  const size_t parts = kg > 1 ? sizeof(float) * attention_parts_floats(dh, nw) : 0;
+  return ((staged > parts ? staged : parts) + 15) & ~(size_t)15;
+}
+
+// Without key groups: sequences of up to 128 rows (and those beyond 256) take four waves per workgroup, keys and values
+// staged 128 at a time ((128 + 132) rows of DH + 8 bf16 = 37 KB at DH = 64, so four workgroups share
+// a CU and cover each other's MFMA-dependency and barrier waits).  Sequences of 129 .. 256 rows: one
+// workgroup of eight waves per (query, head) instead of two of four, with the head's keys and values
+// staged once and in one piece (75 KB at DH = 64, two workgroups per CU): one load phase per
+// workgroup instead of two (measured on MI355X, batch 64, 12 heads: 26.3 us against 27.2 at n = 197,
+// 18.2 against 20.6 at n = 133).  At DH = 64 the same form takes longer sequences whose last block of 256 rows is more than half full
+// (16 / 32 / 64 queries of 400 tokens 23.4 / 41.2 / 72.8 -> 24.7 / 37.1 / 65.6 us; of 320, where it is not, 18.3 / 27.9 / 45.5 and 20.2 /
+// 32.1 / 53.3; 577 37.0 / 64.2 / 115.8 and 41.5 / 67.1 / 121.4).
+// With key groups, for launches that leave CUs idle: a wave's chain of key blocks (load, logits, softmax, product, 0.6 us each) is what
+// such a launch lasts, so the waves of a row block share it.  Four groups while every block of 32 rows finds a CU of its own,
+// or every block of 64; two while those of 128 do.  Measured, us without and with (12 heads): one query of 101 / 197 / 256 / 577 tokens
+// 5.0 / 7.9 / 9.1 / 14.1 -> 4.0 / 4.9 / 5.0 / 8.5; four of 101 / 197 / 256 / 400 5.1 / 8.2 / 9.5 / 11.6 -> 4.1 / 6.2 / 6.3 / 10.3 (the 101 in
+// blocks of 32, the 400 of 128); seven of 197 8.3 -> 7.2, of 165 7.3 -> 6.1; ten of 577 and 197 in turn 26.6 -> 22.8, with sizes 30.2 ->
+// 23.7.  Past those lines the groups' extra staging and sums cost more: twelve of 197 8.5 and 10.5, seven of 577 22.1 and 22.0, of 400
+// 14.0 and 16.8.
+// long_blocks: blocks of 128 rows of the queries longer than half the longest, which last longest.  pairs: an even number of heads
+// can be dealt in twos.  others: workgroups beside attention's, those of the plan's selection.  Up to 256 rows such a launch lasts as
+// long as the selection, and attention's own workgroups slow it: no more than the CUs left over, in blocks of 32 (passes of one / four /
+// seven queries of 197 tokens with r = 16, us, without groups, by this rule, by the rule for attention alone: 472 / 567 / 665, 469 / 567 /
+// 665, 469 / 568 / 672); beyond 256 rows attention lasts longest.
+static AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, bool bias, bool pairs, int others) {
+  const bool shared = others > 0 && max_n <= 256;
+  auto blocks = [&](int rows) { return (int64_t)B * H * ((max_n + rows - 1) / rows); };
+  if (dh <= 80 && max_n > 64 && pairs && blocks(32) <= (shared ? 256 - others : 256)) return AttnShape{128, 4, 4};
+  if (dh == 64 && max_n > 128 && !shared && blocks(64) <= 256) return AttnShape{128, 8, 4};
+  if (dh == 64 && max_n > 192 && !shared && (int64_t)H * long_blocks <= (max_n > 512 ? 320 : 256)) return AttnShape{bias ? 128 : 256, 8, 2};
+  const int last = (max_n - 1) % 256 + 1;   // rows of the last block of 256
+  if (max_n > 128 && last > 128 && (max_n <= 256 || dh == 64)) return AttnShape{dh <= 64 ? 256 : 128, 8, 1};
+  return AttnShape{128, 4, 1};
+}
+
 template <int DH, bool BIAS>
-static hipError_t attention_mfma_b(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int D,
-                                 int H, float scale, void* o, hipStream_t s) {
-  constexpr int LD = DH + 8;
-  // Sequences of up to 128 rows (and those beyond 256): four waves per workgroup, keys and values
-  // staged 128 at a time ((128 + 132) rows of DH + 8 bf16 = 37 KB at DH = 64, so four workgroups share
-  // a CU and cover each other's MFMA-dependency and barrier waits).  Sequences of 129 .. 256 rows: one
-  // workgroup of eight waves per (query, head) instead of two of four, with the head's keys and values
-  // staged once and in one piece (75 KB at DH = 64, two workgroups per CU): one load phase per
-  // workgroup instead of two (measured on MI355X, batch 64, 12 heads: 26.3 us against 27.2 at n = 197,
-  // 18.2 against 20.6 at n = 133).
-#define OTAS_ATTN(KC, NWV)                                                                                        \
-  do {                                                                                                            \
-    const size_t lds = (size_t)(KC + KC + 4) * LD * sizeof(bf16_t) + KC * sizeof(float);                          \
-    auto kern = attention_mfma_kernel<DH, BIAS, KC, NWV>;                                                         \
+static hipError_t attention_mfma_b(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int long_blocks,
+                                   int D, int H, float scale, void* o, hipStream_t s) {
+  const AttnShape sh = attention_shape(DH, H, B, max_n, long_blocks, BIAS, true, 0);
+#define OTAS_ATTN(KC, NWV, KG)                                                                                    \
+  if (sh.kc == KC && sh.nw == NWV && sh.kg == KG) {                                                               \
+    constexpr size_t lds = attention_lds_bytes(DH, KC, NWV, KG);                                                  \
+    constexpr int rows = 32 * NWV / KG;                                                                           \
+    auto kern = attention_mfma_kernel<DH, BIAS, KC, NWV, KG>;                                                     \
     hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
     if (e != hipSuccess) return e;                                                                                \
-    dim3 grid((max_n + 32 * NWV - 1) / (32 * NWV), H, B), block(64 * NWV);                                        \
+    dim3 grid((max_n + rows - 1) / rows, H, B), block(64 * NWV);                                                  \
     kern<<<grid, block, lds, s>>>((const bf16_t*)qkv, sz, d_off, D, scale, (bf16_t*)o);                           \
-  } while (0)
-  if (max_n > 128 && max_n <= 256) OTAS_ATTN((DH <= 64 ? 256 : 128), 8);   // wider heads: two pieces, as before
-  else OTAS_ATTN(128, 4);
+    return hipGetLastError();                                                                                     \
+  }
+  OTAS_ATTN(128, 4, 1)
+  if constexpr (DH <= 80) { OTAS_ATTN(128, 4, 4) }
+  OTAS_ATTN((DH <= 64 ? 256 : 128), 8, 1)   // wider heads: two pieces
+  if constexpr (DH == 64) {
+    OTAS_ATTN(128, 8, 4)
+    OTAS_ATTN((BIAS ? 128 : 256), 8, 2)
+  }
 #undef OTAS_ATTN
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <int DH>
-static hipError_t attention_mfma(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int D,
-                                 int H, float scale, void* o, hipStream_t s) {
-  return sz ? attention_mfma_b<DH, true>(qkv, sz, d_off, B, max_n, D, H, scale, o, s)
-            : attention_mfma_b<DH, false>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
+static hipError_t attention_mfma(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int long_blocks,
+                                 int D, int H, float scale, void* o, hipStream_t s) {
+  return sz ? attention_mfma_b<DH, true>(qkv, sz, d_off, B, max_n, long_blocks, D, H, scale, o, s)
+            : attention_mfma_b<DH, false>(qkv, sz, d_off, B, max_n, long_blocks, D, H, scale, o, s);
 }
 
-// LDS of the fused kernel's attention workgroups: one head of eight waves with all keys staged for 129 .. 256 rows, else
-// two heads of four waves with 128 keys each.
-static size_t fused_attention_lds(int max_n, size_t* unit) {
-  const bool one = max_n > 128 && max_n <= 256;
-  const int kc = one ? 256 : 128;
-  *unit = ((size_t)(kc + kc + 4) * (64 + 8) * sizeof(bf16_t) + kc * sizeof(float) + 15) & ~(size_t)15;
-  return one ? *unit : 2 * *unit;
+// LDS of the fused kernel's attention workgroups as the number of the selection's is chosen by: one head of eight waves with
+// all keys staged for 129 .. 256 rows, else two heads of four waves with 128 keys each (75 KB either way; key groups and
+// longer sequences in pieces of 256 take no more).
+static size_t fused_attention_lds(int max_n) {
+  return max_n > 128 && max_n <= 256 ? attention_lds_bytes(64, 256, 8, 1) : 2 * attention_lds_bytes(64, 128, 4, 1);
 }
 
 // How launch_attention_plan runs this case (pure host; not at all: na = 0).  Below two tokens there is nothing to select.
@@ -528,9 +628,8 @@ FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lis
   if (D != 64 * H) return how;
   const int G = (max_n > 128 && max_n <= 256) ? 1 : 2;   // heads per workgroup: 8 waves / (8 or 4 waves per head)
   if (H % G != 0) return how;
-  size_t unit;
   if (lists_elsewhere) {
-    const PlanParts p = plan_parts(B, max_n, 64, fused_attention_lds(max_n, &unit));
+    const PlanParts p = plan_parts(B, max_n, 64, fused_attention_lds(max_n));
     if (plan_select_lds_bytes(max_n, 64, p.a, p.b) > 160 * 1024) return how;
     how.na = p.a;
     how.nb = p.b;
@@ -544,7 +643,7 @@ FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lis
 // workgroup takes); hipErrorInvalidValue for what attention_plan_how does not take -- the caller then launches
 // the two kernels one after the other.
 hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
-                                 const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int D, int H,
+                                 const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int long_blocks, int D, int H,
                                  bool size_bias, int n_lead, void* o, int32_t* src_list, int32_t* row_ptr,
                                  int32_t* trace_src, int32_t* trace_dst, float* sel_best, int32_t* sel_bcol,
                                  int64_t sel_stride, hipStream_t s) {
@@ -575,40 +674,47 @@ hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* size
   const size_t plan_lds = sel_best ? plan_select_lds_bytes(max_n, 64, how.na, how.nb) : merge_plan_lds_bytes(max_n, 64);
   const float scale = 1.0f / sqrtf(64.0f);
   const int32_t* sz = size_bias ? sizes : nullptr;
-  size_t unit;
-  const size_t attn_lds = fused_attention_lds(max_n, &unit), lds = attn_lds > plan_lds ? attn_lds : plan_lds;
-#define OTAS_FUSED(BIASV, KC, NWV)                                                                                \
-  do {                                                                                                            \
-    constexpr int G = kFusedThreads / 64 / NWV;                                                                   \
-    auto kern = attention_plan_kernel<BIASV, KC, NWV>;                                                            \
+  const AttnShape sh = attention_shape(64, H, B, max_n, long_blocks, size_bias, H % 2 == 0, B * how.na * how.nb);
+#define OTAS_FUSED(BIASV, KC, NWV, KG)                                                                            \
+  if ((sz != nullptr) == BIASV && sh.kc == KC && sh.nw == NWV && sh.kg == KG) {                                   \
+    constexpr int G = kFusedThreads / 64 / NWV, rows = 32 * NWV / KG;                                             \
+    constexpr size_t unit = attention_lds_bytes(64, KC, NWV, KG), attn_lds = G * unit;                            \
+    const size_t lds = attn_lds > plan_lds ? attn_lds : plan_lds;                                                 \
+    if (H % G != 0) return hipErrorInvalidValue;                                                                  \
+    auto kern = attention_plan_kernel<BIASV, KC, NWV, KG>;                                                        \
     hipError_t e = set_max_dynamic_lds((const void*)kern, 160 * 1024);                                            \
     if (e != hipSuccess) return e;                                                                                \
-    const int xblks = (max_n + 32 * NWV - 1) / (32 * NWV);                                                        \
+    const int xblks = (max_n + rows - 1) / rows;                                                                  \
     dim3 grid((unsigned)(B * how.na * how.nb + xblks * (H / G) * B)), block(kFusedThreads);                       \
     kern<<<grid, block, lds, s>>>((const bf16_t*)qkv, sz, d_off, D, H, scale, (bf16_t*)o, B, xblks, d_out_off,    \
                                   d_reff, d_troff, n_lead, src_list, row_ptr, trace_src, trace_dst, sel_best,     \
                                   sel_bcol, sel_stride, how.na, how.nb, (int)unit);                               \
-  } while (0)
-  if (max_n > 128 && max_n <= 256) {
-    if (sz) OTAS_FUSED(true, 256, 8); else OTAS_FUSED(false, 256, 8);
-  } else {
-    if (sz) OTAS_FUSED(true, 128, 4); else OTAS_FUSED(false, 128, 4);
+    return hipGetLastError();                                                                                     \
   }
+#define OTAS_FUSED_BIAS(BIASV)              \
+  OTAS_FUSED(BIASV, 128, 4, 1)              \
+  OTAS_FUSED(BIASV, 128, 4, 4)              \
+  OTAS_FUSED(BIASV, 256, 8, 1)              \
+  OTAS_FUSED(BIASV, 128, 8, 4)              \
+  OTAS_FUSED(BIASV, (BIASV ? 128 : 256), 8, 2)
+  OTAS_FUSED_BIAS(true)
+  OTAS_FUSED_BIAS(false)
+#undef OTAS_FUSED_BIAS
 #undef OTAS_FUSED
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes, const int32_t* d_off, int B,
-                            int max_n, int D, int H, bool size_bias, void* o, hipStream_t s) {
+                            int max_n, int long_blocks, int D, int H, bool size_bias, void* o, hipStream_t s) {
   if (B <= 0 || max_n <= 0) return hipSuccess;
   const int dh = D / H;
   const float scale = 1.0f / sqrtf((float)dh);
   const int32_t* sz = size_bias ? sizes : nullptr;
   if (dtype != 0) {
-    if (dh == 64) return attention_mfma<64>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
-    if (dh == 80) return attention_mfma<80>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
-    if (dh == 96) return attention_mfma<96>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
-    if (dh == 128) return attention_mfma<128>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);
+    if (dh == 64) return attention_mfma<64>(qkv, sz, d_off, B, max_n, long_blocks, D, H, scale, o, s);
+    if (dh == 80) return attention_mfma<80>(qkv, sz, d_off, B, max_n, long_blocks, D, H, scale, o, s);
+    if (dh == 96) return attention_mfma<96>(qkv, sz, d_off, B, max_n, long_blocks, D, H, scale, o, s);
+    if (dh == 128) return attention_mfma<128>(qkv, sz, d_off, B, max_n, long_blocks, D, H, scale, o, s);
   }
   return dtype == 0 ? attention_f32<float>(qkv, sz, d_off, B, max_n, D, H, scale, o, s)
                     : attention_f32<bf16_t>(qkv, sz, d_off, B, max_n, D, H, scale, o, s);

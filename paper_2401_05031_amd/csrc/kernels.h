@@ -114,8 +114,15 @@ hipError_t launch_splitk_reduce_ln(const float* part, int S, const void* bias, c
                                    hipStream_t s, const WarmWeight& warm = WarmWeight{});
 
 hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
-                            const int32_t* d_off, int B, int max_n, int D, int H, bool size_bias,
+                            const int32_t* d_off, int B, int max_n, int long_blocks, int D, int H, bool size_bias,
                             void* o, hipStream_t s);
+// long_blocks of these launches: blocks of 128 rows of the queries that are longer than half the longest one, max_n.
+inline int attention_long_blocks(const int* n, int B, int max_n) {
+  int blocks = 0;
+  for (int q = 0; q < B; ++q)
+    if (2 * n[q] > max_n) blocks += (n[q] + 127) / 128;
+  return blocks;
+}
 
 // Attention and the merge plan of one layer in a single launch (bf16 models of head width 64, and f32 models, whose launch
 // takes the selection only; the plan's metric is the head mean of the keys in qkv).  Returns hipErrorInvalidValue, having launched nothing, for what attention_plan_how
@@ -127,7 +134,7 @@ hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
 struct FusedPlan { int na, nb; };   // na = 0: not taken
 FusedPlan attention_plan_how(int dtype, int B, int max_n, int D, int H, bool lists_elsewhere);
 hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* sizes, const int32_t* d_off, const int32_t* d_out_off,
-                                 const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int D, int H,
+                                 const int32_t* d_reff, const int32_t* d_troff, int B, int max_n, int long_blocks, int D, int H,
                                  bool size_bias, int n_lead, void* o, int32_t* src_list, int32_t* row_ptr,
                                  int32_t* trace_src, int32_t* trace_dst, float* sel_best, int32_t* sel_bcol,
                                  int64_t sel_stride, hipStream_t s);
