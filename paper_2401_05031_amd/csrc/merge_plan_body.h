@@ -226,9 +226,57 @@ __device__ __forceinline__ void merge_plan_select(
   // in ascending B order plus one exchange with lane ^ 32.  Wave w owns the workgroup's A block w % nAl and every
   // G-th of its B blocks; the G partial results per A token are combined through LDS.  Ties go to the
   // lowest B position at every step.
+  // With few blocks for the waves (a small batch's workgroup has one of either kind) they are cut into tiles of 16 x 16, so that one
+  // wave's chain of 32 MFMAs of 64 clocks becomes one of 16 of 32 clocks in each of four waves.  Either instruction adds the
+  // products of its columns one after the other, in ascending order, so the similarities are the same bits.  16 x 16 tiles
+  // take twice the operand reads, so only where there is a wave for each (four blocks in eight waves: otas_token_merge of one query of
+  // 197 tokens 14.7 -> 15.1 us).  ViT-B passes of 1 / 4 / 8 / 16 queries of 197 tokens with r = 16 451 / 563 / 690 / 922 -> 443 / 557 / 687 / 918
+  // us, of 101 with r = 8 419 / 485 / 553 / 687 -> 409 / 480 / 548 / 679; ViT-L, four of 197 with r = 8, 1378 -> 1362.
   constexpr int NWV = NT / 64;
-  const int G = max(1, NWV / nAl);
-  {
+  const bool fine = NT < kPlanThreads && 4 * nAl * nBl <= NWV;
+  const int nAs = (nAv + 15) >> 4, nBs = (nBv + 15) >> 4;
+  const int G = max(1, NWV / (fine ? nAs : nAl)), part_rows = fine ? nAs * 16 : nAl * 32;
+  if (fine) {
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 15, fk = lane >> 4;   // accumulator: A token fr, B tokens 4 fk .. + 3 of the tile
+    const int al = w % nAs, grp = w / nAs;      // nAs <= NWV
+    if (grp < G) {
+      // lane group fk feeds column 4 u + fk to MFMA u: every second float of the even or the odd columns
+      const float* pa = mh + (size_t)(nBv + min(al * 16 + fr, nAv - 1)) * ldm + (fk & 1) * hp + (fk >> 1);
+      float bv = -FLT_MAX;   // as below
+      int bc = 0;
+      for (int bl = grp; bl < nBs; bl += G) {
+        const float* pb = mh + (size_t)min(bl * 16 + fr, nBv - 1) * ldm + (fk & 1) * hp + (fk >> 1);
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < hp; k0 += 16) {   // 8 MFMAs per batch, their operand reads issued first (hp % 4 == 0)
+          float ra[8], rb[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int k = k0 + 2 * (u & ~1) < hp ? k0 + 2 * u : 0;
+            ra[u] = pa[k];
+            rb[u] = pb[k];
+          }
+#pragma unroll
+          for (int u = 0; u < 8; u += 2)
+            if (k0 + 2 * u < hp) {
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[u], ra[u], acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rb[u + 1], ra[u + 1], acc, 0, 0, 0);
+            }
+        }
+        const int b0 = (pt.b + pt.nb * (bl >> 1)) * 32 + 16 * (bl & 1) + 4 * fk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (b0 + e < nB && acc[e] > bv) { bv = acc[e]; bc = b0 + e; }
+      }
+      auto take = [&](float ov, int oc) { if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; } };
+      take(__shfl_xor(bv, 16, kWave), __shfl_xor(bc, 16, kWave));
+      take(wave_halves(bv).hi, __float_as_int(wave_halves(__int_as_float(bc)).hi));   // the first 16 lanes decide
+      if (fk == 0) {
+        part_v[grp * part_rows + al * 16 + fr] = bv;
+        part_c[grp * part_rows + al * 16 + fr] = bc;
+      }
+    }
+  } else {
     const int lane = tid & 63, w = tid >> 6;
     const int fr = lane & 31, fk = lane >> 5;
     // nAl <= NWV: one (A block, B group) per wave, groups beyond G idle; more A blocks than waves: one group, the
@@ -273,20 +321,19 @@ __device__ __forceinline__ void merge_plan_select(
       const int oc = __float_as_int(wave_halves(__int_as_float(bc)).hi);
       if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
       if (fk == 0) {
-        part_v[grp * (nAl * 32) + al * 32 + fr] = bv;
-        part_c[grp * (nAl * 32) + al * 32 + fr] = bc;
+        part_v[grp * part_rows + al * 32 + fr] = bv;
+        part_c[grp * part_rows + al * 32 + fr] = bc;
       }
     }
   }
   __syncthreads();
-  for (int t = tid; t < nAl * 32; t += NT) {
+  for (int t = tid; t < nAv; t += NT) {
     const int a = (pt.a + pt.na * (t >> 5)) * 32 + (t & 31);
-    if (a >= nA) continue;
     float bv = part_v[t];
     int bc = part_c[t];
     for (int g = 1; g < G; ++g) {
-      const float v = part_v[g * (nAl * 32) + t];
-      const int c = part_c[g * (nAl * 32) + t];
+      const float v = part_v[g * part_rows + t];
+      const int c = part_c[g * part_rows + t];
       if (v > bv || (v == bv && c < bc)) { bv = v; bc = c; }
     }
     const float v = (2 * a < n_lead) ? -INFINITY : bv;   // protected leading token: never a merge source

@@ -306,3 +306,37 @@ def test_patches_and_rows_by_16_bytes_and_by_elements(lib, dtype, p, shift):
     lead = (cls.float() + pos[0].float()).to(dt)
     assert all(torch.equal(toks.view(B, 1 + N, cfg.D)[q, 0], lead) for q in range(B))
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [2, 3, 16, 17, 31, 32, 33, 34, 49, 63, 64, 65, 100])
+def test_selection_in_tiles_of_16_and_of_32(lib, n):
+    """Queries of up to 64 tokens have one block of 32 tokens of either kind, which the selection beside attention (eight waves)
+    compares in tiles of 16 x 16; otas_token_merge (sixteen waves) in tiles of 32 x 32.  The same edges from the same keys: both
+    heads are given the same ones, whose mean is that of one."""
+    import torch
+    D, dh = 128, 64
+    cfg = synth.Config("tiles", L=1, D=D, H=2, F=128, dtype="bf16", B=1, n0=n, seed=n)
+    layers = synth.all_weights(cfg)
+    layers[0]["w_qkv"][D + dh:2 * D] = layers[0]["w_qkv"][D:D + dh]
+    layers[0]["b_qkv"][D + dh:2 * D] = layers[0]["b_qkv"][D:D + dh]
+    ctx, _ = hz.make_context(cfg, layers)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x0 = torch.randn((n, D), generator=g, device="cuda").to(torch.bfloat16)
+    r = max(1, n // 3)
+    got = hz.gpu_forward(ctx, x0, [0, n], [r])
+    w = {k: torch.from_numpy(np.ascontiguousarray(v)).to("cuda").to(torch.bfloat16) for k, v in layers[0].items()}
+    h = torch.empty((n, D), dtype=torch.bfloat16, device="cuda")
+    qkv = torch.empty((n, 3 * D), dtype=torch.bfloat16, device="cuda")
+    ctx.otas_layer_norm(x0, w["ln1_g"], w["ln1_b"], n, h)
+    ctx.otas_linear(h, w["w_qkv"], w["b_qkv"], None, n, 3 * D, D, 0, qkv)
+    metric = qkv[:, D:D + dh].contiguous()
+    assert torch.equal(metric, qkv[:, D + dh:2 * D])
+    ws = torch.empty(ctx.otas_merge_workspace_bytes(1, n), dtype=torch.uint8, device="cuda")
+    xo, so = torch.empty((n, D), dtype=torch.bfloat16, device="cuda"), torch.zeros(n, dtype=torch.int32, device="cuda")
+    src, dst = (torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    off = ctx.otas_token_merge(x0, metric, dh, None, [0, n], [r], ws, xo, so, src, dst)
+    k = n - int(off[1])
+    assert k == min(r, (n - cfg.n_lead) // 2)
+    s, d = got["trace"][0][0]
+    assert np.array_equal(np.asarray(s), src[:k].cpu().numpy()) and np.array_equal(np.asarray(d), dst[:k].cpu().numpy())
+    ctx.close()
