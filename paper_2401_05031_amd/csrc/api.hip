@@ -484,6 +484,14 @@ otas_status token_merge_impl(otas_ctx* c, const void* x, const void* metric, int
   const bool was_timing = c->timing;
   if (!timed) c->timing = false;
   st = [&]() -> otas_status {
+    if (token_merge_in_two(B, max_n, dm)) {   // the lists stay in LDS: their arrays hold the selection
+      float* best = (float*)src_list;
+      OTAS_LAUNCH(K_PLAN, launch_merge_select_host(c->desc.dtype, metric, dm, plan, count, c->d_plan, B, max_n, n_lead, best, row_ptr,
+                                                   c->stream));
+      OTAS_LAUNCH(K_APPLY, launch_merge_lists_apply_host(c->desc.dtype, x, sizes, dm, best, row_ptr, plan, count, c->d_plan, B,
+                                                         max_n, c->desc.D, x_out, sizes_out, trace_src, trace_dst, c->stream));
+      return OTAS_OK;
+    }
     OTAS_LAUNCH(K_PLAN, launch_merge_plan_host(c->desc.dtype, metric, dm, plan, count, c->d_plan, B, max_n, n_lead,
                                                src_list, row_ptr, trace_src, trace_dst, rows, c->stream));
     OTAS_LAUNCH(K_APPLY, launch_merge_apply(c->desc.dtype, x, sizes, src_list, row_ptr, T, T_out, c->desc.D, x_out,
@@ -538,7 +546,8 @@ otas_status otas_token_merge_static(otas_ctx* c, const void* x, const void* metr
   if (!c->d_scratch) return OTAS_EDEVICE;
   int32_t plan[4 * kStaticMergeQueries + 2];   // on the stack: no host allocation either
   // Nothing in the lists has to start at zero: the plan kernel writes every entry of src_list [0, T)
-  // and row_ptr [0, T_out) that the apply kernel reads, whatever an earlier call left there.
+  // and row_ptr [0, T_out) that the apply kernel reads, whatever an earlier call left there; likewise the selection
+  // every A token's entry.
   // (no room for metric rows here: a query too long for the plan kernel's LDS is refused, EUNSUPPORTED)
   return token_merge_impl(c, x, metric, dm, sizes, offsets, r, B, plan, c->d_scratch,
                           c->d_scratch + kStaticRowPtrAt, nullptr, x_out, sizes_out, offsets_out, trace_src,

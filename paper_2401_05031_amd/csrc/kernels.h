@@ -171,6 +171,16 @@ hipError_t launch_merge_plan(int dtype, const void* src, int64_t row_stride, int
 hipError_t launch_merge_plan_host(int dtype, const void* metric, int dm, const int32_t* plan, size_t count,
                                   const int32_t* d_plan, int B, int max_n, int n_lead, int32_t* src_list,
                                   int32_t* row_ptr, int32_t* trace_src, int32_t* trace_dst, float* rows, hipStream_t s);
+// The merging module as an operator of its own in two launches that share out a query's work between workgroups: the selection
+// (every A token's best match into best / bcol, an entry per packed token row), then the lists, in LDS, with the averages.
+// Arguments as above; D columns of x.  token_merge_in_two: whether B queries of up to max_n tokens are run this way (pure host);
+// if not, the two launchers return hipErrorInvalidValue.
+bool token_merge_in_two(int B, int max_n, int dm);
+hipError_t launch_merge_select_host(int dtype, const void* metric, int dm, const int32_t* plan, size_t count, const int32_t* d_plan,
+                                    int B, int max_n, int n_lead, float* best, int32_t* bcol, hipStream_t s);
+hipError_t launch_merge_lists_apply_host(int dtype, const void* x, const int32_t* sizes, int dm, const float* best, const int32_t* bcol,
+                                         const int32_t* plan, size_t count, const int32_t* d_plan, int B, int max_n, int D,
+                                         void* x_out, int32_t* sizes_out, int32_t* trace_src, int32_t* trace_dst, hipStream_t s);
 size_t merge_plan_lds_bytes(int max_n, int dm);
 size_t merge_plan_rows_bytes(int64_t T, int dm);
 

@@ -16,9 +16,9 @@ CAL_BYTES = 256 << 20
 FAMILIES = {
     "gemm": ("gemm_mfma", "gemm_f32"),               # bf16 and fp32
     "attention": ("attention_",),
-    "merge_apply": ("merge_apply_ln_kernel", "merge_apply_kernel"),
+    "merge_apply": ("merge_apply_ln_kernel", "merge_apply_kernel", "merge_lists_apply_kernel"),
     "splitk_reduce_ln": ("splitk_reduce_ln_kernel",),
-    "merge_plan": ("merge_plan_kernel",),
+    "merge_plan": ("merge_plan_kernel", "merge_select_kernel"),
     "layer_norm": ("layer_norm_kernel",),
 }
 # The library's kernels outside those families: the ends of the model, small integer work, the clock and timing probes.

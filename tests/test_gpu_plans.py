@@ -201,6 +201,49 @@ def test_merge_of_tokens_that_compare_with_none(lib, dtype, n):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,D,dm", [("bf16", 768, 64), ("bf16", 136, 100), ("f32", 192, 128), ("f32", 104, 4)])
+@pytest.mark.parametrize("ns", [[129], [128, 129, 1], [0, 197, 2, 196, 0, 33, 130], [577, 400], [1024], [131] * 64])
+def test_merge_shared_out_equals_one_workgroup_a_query(lib, dtype, D, dm, ns):
+    """Up to 64 queries with one of 129 tokens or more share their work between workgroups; with more queries each has one.
+    Rows, sizes, offsets and edges bit for bit, with and without sizes and edges, some queries removing nothing."""
+    import torch
+    cfg = synth.Config("op", L=1, D=D, H=8 if D == 768 else 2, F=128, dtype=dtype, B=1, n0=2, seed=17)
+    ctx, _ = hz.make_context(cfg)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    more = ns + [3] * (65 - len(ns))
+    off = np.concatenate([[0], np.cumsum(more)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(len(ns) + ns[0])
+    x = torch.randn((int(off[-1]), D), generator=g, device="cuda").to(dt)
+    metric = torch.randn((int(off[-1]), dm), generator=g, device="cuda").to(dt)
+    sizes = torch.randint(1, 5, (int(off[-1]),), generator=g, device="cuda", dtype=torch.int32)
+    r = [(0, n // 3, n, 1)[(q + len(ns)) % 4] for q, n in enumerate(more)]
+
+    def run(B, sz, traced, static=False):
+        T = int(off[B])
+        out = torch.full((T, D), float("nan"), device="cuda", dtype=dt)
+        so, src, dst = (torch.full((T,), -1, dtype=torch.int32, device="cuda") for _ in range(3))
+        ws = torch.full((ctx.otas_merge_workspace_bytes(B, T),), 0xff, dtype=torch.uint8, device="cuda")
+        args = (x[:T].contiguous(), metric[:T].contiguous(), dm, sz[:T].contiguous() if sz is not None else None, off[:B + 1], r[:B])
+        tr = (src, dst) if traced else (None, None)
+        o = ctx.otas_token_merge_static(*args, out, so, *tr) if static else ctx.otas_token_merge(*args, ws, out, so, *tr)
+        return out, so, src, dst, np.asarray(o)
+
+    B = len(ns)
+    for sz in (None, sizes):
+        want = run(65, sz, True)
+        end, edges = int(want[4][B]), int(off[B]) - int(want[4][B])
+        # (without a workspace a query whose metric rows do not fit in LDS is refused)
+        for traced, static in ((True, False), (False, False), (True, True))[:3 if max(ns) * (dm + 4) * 4 < 150 * 1024 else 2]:
+            got = run(B, sz, traced, static)
+            assert np.array_equal(got[4], want[4][:B + 1])
+            assert torch.equal(got[0][:end], want[0][:end]) and torch.equal(got[1][:end], want[1][:end])
+            assert bool((got[1][end:] == -1).all()) and bool(got[0][end:].isnan().all())
+            for a, b in zip(got[2:4], want[2:4]):
+                assert torch.equal(a[:edges], b[:edges] if traced else torch.full_like(a[:edges], -1))
+                assert bool((a[edges:] == -1).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("D,H", [(192, 3), (200, 2)])
 def test_fp32_selection_beside_attention_equals_the_plan_kernel(lib, D, H):
     """f32 models: a query alone runs its selection beside attention, in as many workgroups as its tokens have blocks, and
