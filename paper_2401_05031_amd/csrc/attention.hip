@@ -480,14 +480,34 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
   }
 }
 
-template <int DH, bool BIAS, int KC, int NW, int KG>
+// Which head (counted through all queries) and row block workgroup id has.  Workgroups go to the eight XCDs in turn: BY_HEAD gives
+// the xblks row blocks of a head, which read the same keys and values, to one XCD and so to one L2, eight heads at a time (the
+// heads past the last eight are dealt out).  The eight change places from group to group: lengths that alternate would
+// otherwise leave the long queries to half of the XCDs (32 of 577 and 197 tokens in turn 2632 us a pass, 2672 without).
+struct HeadBlock { int head, x; };
+template <bool BY_HEAD>
+__device__ __forceinline__ HeadBlock head_block(unsigned id, unsigned xblks, unsigned heads) {
+  if (!BY_HEAD) return HeadBlock{(int)(id / xblks), (int)(id % xblks)};
+  const unsigned eights = heads & ~7u;
+  const bool whole = id < eights * xblks;
+  const unsigned k = whole ? id >> 3 : id - eights * xblks, p = k / xblks;
+  return HeadBlock{(int)(whole ? p * 8 + ((id + p) & 7) : eights + p), (int)(k - p * xblks)};
+}
+
+template <int DH, bool BIAS, int KC, int NW, int KG, bool BY_HEAD>
 __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kernel(const bf16_t* __restrict__ qkv,
                                                              const int32_t* __restrict__ sizes,
                                                              const int32_t* __restrict__ off, int D, float scale,
                                                              bf16_t* __restrict__ o) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, (int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x,
-                                        smem, (int)threadIdx.x);
+  int q = (int)blockIdx.z, h = (int)blockIdx.y, x = (int)blockIdx.x;
+  if constexpr (BY_HEAD) {
+    const HeadBlock b = head_block<true>(x + gridDim.x * (h + gridDim.y * q), gridDim.x, gridDim.y * gridDim.z);
+    q = b.head / (int)gridDim.y;
+    h = b.head - q * (int)gridDim.y;
+    x = b.x;
+  }
+  attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, h, x, smem, (int)threadIdx.x);
 }
 
 // Attention and the merge plan of a layer in ONE launch (both only read the layer's QKV projection, and
@@ -502,7 +522,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kern
 // only (four waves per SIMD leave 128 registers per lane).
 // grid.x = B * na * nb + xblks * (H / G) * B with G = 8 / NW (na = nb = 1 for the whole plan).
 constexpr int kFusedThreads = 512;
-template <bool BIAS, int KC, int NW, int KG>
+template <bool BIAS, int KC, int NW, int KG, bool BY_HEAD>
 __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
     const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes, const int32_t* __restrict__ off, int D, int H,
     float scale, bf16_t* __restrict__ o, int B, int xblks, const int32_t* __restrict__ out_off,
@@ -524,18 +544,19 @@ __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
                                         trace_dst, nullptr, reinterpret_cast<float*>(smem), (int)threadIdx.x);
     return;
   }
-  int id = (int)blockIdx.x - B * na * nb;
   const int hg = H / G;
-  const int xblk = id % xblks;
-  id /= xblks;
-  const int hgrp = id % hg, q = id / hg;
+  const HeadBlock b = head_block<BY_HEAD>(blockIdx.x - B * na * nb, xblks, B * hg);
+  const int hgrp = b.head % hg, q = b.head / hg, xblk = b.x;
   const int unit = (int)threadIdx.x / (64 * NW), tid = (int)threadIdx.x % (64 * NW);
   attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, hgrp * G + unit, xblk, smem + (size_t)unit * unit_lds,
                                         tid);
 }
 
 // How a launch cuts up its work: keys staged at a time, waves per head and row block, key groups.
-struct AttnShape { int kc, nw, kg; };
+struct AttnShape {
+  int kc, nw, kg;
+  bool by_head;   // head_block
+};
 constexpr size_t attention_lds_bytes(int dh, int kc, int nw, int kg) {
   const size_t staged = (size_t)(kc + kc + 4) * (dh + 8) * sizeof(bf16_t) + kc * sizeof(float);
   const size_t parts = kg > 1 ? sizeof(float) * attention_parts_floats(dh, nw) : 0;
@@ -563,15 +584,30 @@ constexpr size_t attention_lds_bytes(int dh, int kc, int nw, int kg) {
 // long as the selection, and attention's own workgroups slow it: no more than the CUs left over, in blocks of 32 (passes of one / four /
 // seven queries of 197 tokens with r = 16, us, without groups, by this rule, by the rule for attention alone: 472 / 567 / 665, 469 / 567 /
 // 665, 469 / 568 / 672); beyond 256 rows attention lasts longest.
+//
+// Row blocks of a head beyond 256 rows go to one XCD (us a pass, dealt out -> by head; ViT-B unless said): beside a
+// selection (10 / 32 / 64 queries of 577 and 197 tokens in turn with r = 23 1291 / 2660 / 4744 -> 1282 / 2632 / 4659);
+// with key groups, where the launch is less than one round of the CUs (two / four of 257 549 / 762 -> 539 / 750, of 325
+// 622 / 821 -> 613 / 814), though not for a lone query (257 448.4 -> 451.8), nor in the smaller blocks of up to 256 rows
+// (seven / ten of 197 824 / 924 -> 832 / 936, three of 101 and 4 prompts 428 -> 432), nor without groups (six of 401
+// 1103 -> 1114); and from 448 blocks of 128 rows of long queries on (8 / 64 of 577 1652 / 8555 -> 1627 / 8432, 64 of 325
+// 4560 -> 4499, ViT-H 32 of 257 10837 -> 10679). Between, a chip of 1 to 2 workgroups a CU lasts as long as its fullest
+// XCD: 5 of 513 tokens (300 blocks) 1222 -> 1238, 10 of 325 (360) 1255 -> 1265, 24 of 325 and 50 in turn (432) 1579 ->
+// 1583, but 8 of 513 (480) 1624 -> 1610, 14 of 257 (504) 1357 -> 1354.
 static AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, bool bias, bool pairs, int others) {
   const bool shared = others > 0 && max_n <= 256;
+  auto shape = [&](int kc, int nw, int kg) {
+    const int rows = 32 * nw / kg, xblks = (max_n + rows - 1) / rows;
+    const bool few = kg > 1 && (int64_t)B * H * xblks <= 256, many = (int64_t)H * long_blocks >= 448;
+    return AttnShape{kc, nw, kg, max_n > 256 && B > 1 && (others > 0 || few || many)};
+  };
   auto blocks = [&](int rows) { return (int64_t)B * H * ((max_n + rows - 1) / rows); };
-  if (dh <= 80 && max_n > 64 && pairs && blocks(32) <= (shared ? 256 - others : 256)) return AttnShape{128, 4, 4};
-  if (dh == 64 && max_n > 128 && !shared && blocks(64) <= 256) return AttnShape{128, 8, 4};
-  if (dh == 64 && max_n > 192 && !shared && (int64_t)H * long_blocks <= (max_n > 512 ? 320 : 256)) return AttnShape{bias ? 128 : 256, 8, 2};
+  if (dh <= 80 && max_n > 64 && pairs && blocks(32) <= (shared ? 256 - others : 256)) return shape(128, 4, 4);
+  if (dh == 64 && max_n > 128 && !shared && blocks(64) <= 256) return shape(128, 8, 4);
+  if (dh == 64 && max_n > 192 && !shared && (int64_t)H * long_blocks <= (max_n > 512 ? 320 : 256)) return shape(bias ? 128 : 256, 8, 2);
   const int last = (max_n - 1) % 256 + 1;   // rows of the last block of 256
-  if (max_n > 128 && last > 128 && (max_n <= 256 || dh == 64)) return AttnShape{dh <= 64 ? 256 : 128, 8, 1};
-  return AttnShape{128, 4, 1};
+  if (max_n > 128 && last > 128 && (max_n <= 256 || dh == 64)) return shape(dh <= 64 ? 256 : 128, 8, 1);
+  return shape(128, 4, 1);
 }
 
 template <int DH, bool BIAS>
@@ -582,7 +618,9 @@ static hipError_t attention_mfma_b(const void* qkv, const int32_t* sz, const int
   if (sh.kc == KC && sh.nw == NWV && sh.kg == KG) {                                                               \
     constexpr size_t lds = attention_lds_bytes(DH, KC, NWV, KG);                                                  \
     constexpr int rows = 32 * NWV / KG;                                                                           \
-    auto kern = attention_mfma_kernel<DH, BIAS, KC, NWV, KG>;                                                     \
+    constexpr bool longer = DH <= 64 || NWV == 4;   /* whether the form takes more than 256 rows */                 \
+    auto kern = sh.by_head ? attention_mfma_kernel<DH, BIAS, KC, NWV, KG, longer>                                 \
+                           : attention_mfma_kernel<DH, BIAS, KC, NWV, KG, false>;                                 \
     hipError_t e = set_max_dynamic_lds((const void*)kern, (int)lds);                                              \
     if (e != hipSuccess) return e;                                                                                \
     dim3 grid((max_n + rows - 1) / rows, H, B), block(64 * NWV);                                                  \
@@ -681,7 +719,8 @@ hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* size
     constexpr size_t unit = attention_lds_bytes(64, KC, NWV, KG), attn_lds = G * unit;                            \
     const size_t lds = attn_lds > plan_lds ? attn_lds : plan_lds;                                                 \
     if (H % G != 0) return hipErrorInvalidValue;                                                                  \
-    auto kern = attention_plan_kernel<BIASV, KC, NWV, KG>;                                                        \
+    auto kern = sh.by_head ? attention_plan_kernel<BIASV, KC, NWV, KG, true>                                      \
+                           : attention_plan_kernel<BIASV, KC, NWV, KG, false>;                                    \
     hipError_t e = set_max_dynamic_lds((const void*)kern, 160 * 1024);                                            \
     if (e != hipSuccess) return e;                                                                                \
     const int xblks = (max_n + rows - 1) / rows;                                                                  \
