@@ -208,8 +208,8 @@ static hipError_t attention_f32(const void* qkv, const int32_t* sz, const int32_
 }
 
 // ------------------------------------------------------------------------------ bf16 MFMA
-// grid (ceil(max_n / (32 NW / KG)), H, B), NW waves (4 or 8): each wave owns 32 query rows of one (query, head) and, where KG > 1,
-// every KG-th block of its keys; what the KG waves of a row block hold is added up at the end (attention_combine).
+// grid (ceil(max_n / (32 NW / KG)), H, B), NW waves (4 or 8): each wave owns 32 query rows of one (query, head), or, where KG > 1, KG
+// waves share 32 rows (attention_shared_body).
 // The keys and values of the head are staged in LDS in chunks of up to KC rows (rows padded
 // by 16 bytes so that the 16 lanes served per clock fall on distinct banks); every wave then walks
 // the chunk in blocks of 32 keys with an online softmax (running row maximum and sum, fp32).
@@ -227,63 +227,147 @@ static hipError_t attention_f32(const void* qkv, const int32_t* sz, const int32_
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef short short8_t __attribute__((ext_vector_type(8)));
 
-// LDS of the partial results of NW waves: O as the accumulators hold it, the rows' maxima and sums.
-constexpr int attention_parts_floats(int DH, int NW) { return NW * (16 * ((DH + 31) / 32) * 64 + 64); }
-
-// Adds up what the KG key groups of a row block hold, each relative to its own maximum m with the sum l: wave (kg, rw) left O in
-// LDS and finishes every KG-th run of four columns.  A group's part counts for exp2(m - the largest m), groups in ascending
-// order.  orow: this lane's output row, or null.
-template <int DH, int NW, int KG>
-__device__ __forceinline__ void attention_combine(const floatx16 (&oacc)[(DH + 31) / 32], float m, float l, float* lds, int wave,
-                                                  int kg, int rw, int lane, bool active, bf16_t* orow) {
-  constexpr int DT = (DH + 31) / 32, NQ = 4 * DT, RW = NW / KG;
-  float* parts = lds;                              // [NW][NQ][64][4]
-  float* ml = lds + NW * NQ * 256;                 // [NW][2][32]
-  const int fr = lane & 31, fk = lane >> 5;
-  __syncthreads();                                 // everyone is done with the keys and values
-  if (active) {
+// The steps of a chunk, which the two bodies below share: they are the same arithmetic in the same order in both.
+// Stages K and V rows c0 .. c0 + nc_pad - 1 of a head (zero beyond nc) with NT threads.
+template <int DH, bool BIAS, int NT>
+__device__ __forceinline__ void attention_stage(const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes, size_t ld, int D, int h,
+                                                int first, int nc, int nc_pad, bf16_t* Ks, bf16_t* Vs, float* lnsz, int tid) {
+  constexpr int LD = DH + 8, CPR = DH / 8;    // 16-byte chunks per row
+  // batches of 4 chunk pairs per thread: all eight loads of a batch are issued before the first
+  // LDS store waits for them, so their latencies overlap
+  const int n_chunks = nc_pad * CPR;
+  for (int t0 = 0; t0 < n_chunks; t0 += 4 * NT) {
+    bf16x8 kv[4], vv[4];
 #pragma unroll
-    for (int i = 0; i < NQ; ++i)
-      *reinterpret_cast<floatx4*>(parts + ((wave * NQ + i) * 64 + lane) * 4) =
-          floatx4{oacc[i / 4][4 * (i % 4)], oacc[i / 4][4 * (i % 4) + 1], oacc[i / 4][4 * (i % 4) + 2], oacc[i / 4][4 * (i % 4) + 3]};
-    if (fk == 0) {
-      ml[wave * 64 + fr] = m;
-      ml[wave * 64 + 32 + fr] = l;
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + u * NT + tid;
+      const int r = t / CPR, c = (t - r * CPR) * 8;
+      const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+      kv[u] = zero;
+      vv[u] = zero;
+      if (t < n_chunks && r < nc) {
+        const bf16_t* src = qkv + (size_t)(first + r) * ld + D + h * DH + c;
+        kv[u] = *reinterpret_cast<const bf16x8*>(src);
+        vv[u] = *reinterpret_cast<const bf16x8*>(src + D);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + u * NT + tid;
+      const int r = t / CPR, c = (t - r * CPR) * 8;
+      if (t < n_chunks) {
+        *reinterpret_cast<bf16x8*>(Ks + r * LD + c) = kv[u];
+        *reinterpret_cast<bf16x8*>(Vs + r * LD + c) = vv[u];
+      }
     }
   }
-  __syncthreads();
-  if (!active) return;
-  float f[KG], m_all = -INFINITY, l_all = 0.f;
-#pragma unroll
-  for (int g = 0; g < KG; ++g) m_all = fmaxf(m_all, f[g] = ml[(g * RW + rw) * 64 + fr]);
-#pragma unroll
-  for (int g = 0; g < KG; ++g) {
-    f[g] = __builtin_amdgcn_exp2f(f[g] - m_all);   // 0 for a group without a key
-    l_all += f[g] * ml[(g * RW + rw) * 64 + 32 + fr];
-  }
-  const float inv = 1.0f / l_all;
-#pragma unroll
-  for (int j = 0; j < NQ / KG; ++j) {
-    const int i = j * KG + kg;
-    floatx4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int g = 0; g < KG; ++g) {
-      const floatx4 p = *reinterpret_cast<const floatx4*>(parts + (((g * RW + rw) * NQ + i) * 64 + lane) * 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = fmaf(f[g], p[e], v[e]);
-    }
-    const int d = 8 * i + 4 * fk;
-    if (orow && d < DH)
-      *reinterpret_cast<bf16x4*>(orow + d) =
-          bf16x4{(bf16_t)(v[0] * inv), (bf16_t)(v[1] * inv), (bf16_t)(v[2] * inv), (bf16_t)(v[3] * inv)};
+  if (BIAS) {
+    for (int t = tid; t < nc_pad; t += NT) lnsz[t] = t < nc ? log2f((float)sizes[first + t]) : 0.f;
   }
 }
 
-// One (query q, head h, block xblk of 32 NW / KG query rows) on NW waves: tid = thread index among those 64 NW
+// Q fragments (B operand): lane (row, half) holds Q[row][16 ks + 8 half .. +7]
+template <int DH>
+__device__ __forceinline__ void attention_query(bf16x8 (&qf)[DH / 16], const bf16_t* qrow) {
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
+}
+
+// S^T block: logits of keys kb .. kb + 31
+template <int DH>
+__device__ __forceinline__ void attention_logits(floatx16& sacc, const bf16_t* Ks, const bf16x8 (&qf)[DH / 16], int kb, int fr, int fk) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < DH / 16; ++ks) {
+    const bf16x8 kf = *reinterpret_cast<const bf16x8*>(Ks + (kb + fr) * (DH + 8) + ks * 16 + fk * 8);
+    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sacc, 0, 0, 0);
+  }
+}
+
+// The block's largest logit per row.
+// Logits in base-2 units, t = s * (scale * log2 e) [+ log2(size)], so that exp(s - m) is one
+// v_exp_f32.  Without the size bias the scaling is folded into the exponent's argument,
+// exp2(fma(s, scale2, -m)): the maximum is taken over the raw products (scale2 > 0) and scaled
+// once per row.  Only the chunk's last block can hold keys past the end.
+template <bool BIAS>
+__device__ __forceinline__ float attention_block_max(floatx16& sacc, const float* lnsz, float scale2, int kb, int nc, int fk) {
+  float mx = -INFINITY;
+  if (BIAS) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      sacc[e] = sacc[e] * scale2 + lnsz[kb + 8 * (e >> 2) + 4 * fk + (e & 3)];
+  }
+  if (kb + 32 > nc) {   // wave-uniform: keys past the end of the sequence
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      sacc[e] = (kb + 8 * (e >> 2) + 4 * fk + (e & 3)) < nc ? sacc[e] : -INFINITY;
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[e]);
+  mx = xor32_max(mx);
+  if (!BIAS) mx *= scale2;
+  return mx;
+}
+
+// The block's weights in place of its logits, and their sum over the lane's keys.
+template <bool BIAS>
+__device__ __forceinline__ float attention_weights(floatx16& sacc, float scale2, float m) {
+  float psum = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const float pv = BIAS ? __builtin_amdgcn_exp2f(sacc[e] - m) : __builtin_amdgcn_exp2f(fmaf(sacc[e], scale2, -m));
+    sacc[e] = pv;
+    psum += pv;
+  }
+  return psum;
+}
+
+// V^T fragment (A operand) of tile t of O^T for the 16 keys from kb + 16 kk on.
+// transposing reads: lane s of each 16-lane group points at V[k0 + s/4][d0 + 4 (s & 3)]
+template <int DH>
+__device__ __forceinline__ bf16x8 attention_values(const bf16_t* Vs, int kb, int kk, int t, int lane) {
+  constexpr int LD = DH + 8;
+  const int s16 = lane & 15, d0 = ((lane >> 4) & 1) * 16, k0 = kb + 16 * kk + 4 * (lane >> 5);
+  const bf16_t* vp = Vs + (k0 + (s16 >> 2)) * LD + t * 32 + d0 + 4 * (s16 & 3);
+  const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t*)(vp));
+  const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4_t*)(vp + 8 * LD));
+  const short8_t both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  bf16x8 vf;
+  __builtin_memcpy(&vf, &both, 16);
+  return vf;
+}
+
+// Tile t of the lane's output row.
+template <int DH>
+__device__ __forceinline__ void attention_store(bf16_t* orow, const floatx16& oacc, float inv, int t, int fk) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int d = t * 32 + g * 8 + fk * 4;
+    if (d < DH) {
+      bf16x4 ov = {(bf16_t)(oacc[g * 4 + 0] * inv), (bf16_t)(oacc[g * 4 + 1] * inv),
+                   (bf16_t)(oacc[g * 4 + 2] * inv), (bf16_t)(oacc[g * 4 + 3] * inv)};
+      *reinterpret_cast<bf16x4*>(orow + d) = ov;
+    }
+  }
+}
+
+// LDS of a head on NW waves: keys (and, in their place, weights: shared body) | values | log2 sizes | block maxima, sums and factors.
+// The reads of V^T's last tile may run past DH: four more rows keep them in bounds.
+constexpr size_t attention_keys_bytes(int dh, int kc, int nw, int kg) {
+  const size_t keys = (size_t)kc * (dh + 8) * sizeof(bf16_t), weights = kg > 1 ? (size_t)nw / kg * kc * 32 * sizeof(bf16_t) : 0;
+  return keys > weights ? keys : weights;
+}
+constexpr size_t attention_lds_bytes(int dh, int kc, int nw, int kg) {
+  const size_t stats = kg > 1 ? (size_t)nw / kg * kc * 4 * sizeof(float) : 0;
+  return (attention_keys_bytes(dh, kc, nw, kg) + (size_t)(kc + 4) * (dh + 8) * sizeof(bf16_t) + kc * sizeof(float) + stats + 15) & ~(size_t)15;
+}
+
+// One (query q, head h, block xblk of 32 NW query rows) on NW waves: tid = thread index among those 64 NW
 // threads, smem = their LDS region.  Every __syncthreads() below is reached by all threads of the workgroup
 // that share q and xblk (the trip counts depend on the query's length and xblk only), so a workgroup may run
 // several heads of one query side by side, each on its own NW waves and LDS region.
-template <int DH, bool BIAS, int KC, int NW, int KG>
+template <int DH, bool BIAS, int KC, int NW>
 __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes,
                                                     const int32_t* __restrict__ off, int D, float scale,
                                                     bf16_t* __restrict__ o, const int q, const int h, const int xblk,
@@ -291,29 +375,22 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
   constexpr int KS = DH / 16;             // k-steps of Q K^T
   constexpr int DT = (DH + 31) / 32;      // 32-row tiles of O^T
   constexpr int LD = DH + 8;              // LDS row stride in elements (16 bytes of padding)
-  constexpr int VROWS = KC + 4;           // V^T reads of the last d tile may run past DH: keep them in bounds
   bf16_t* Ks = reinterpret_cast<bf16_t*>(smem);           // [KC][LD]
-  bf16_t* Vs = Ks + KC * LD;                              // [VROWS][LD]
-  float* lnsz = reinterpret_cast<float*>(Vs + VROWS * LD);  // [KC] log2(size) of the chunk's keys
+  bf16_t* Vs = Ks + KC * LD;                              // [KC + 4][LD]
+  float* lnsz = reinterpret_cast<float*>(Vs + (KC + 4) * LD);  // [KC] log2(size) of the chunk's keys
 
-  const int lane = tid & 63, wave = KG == 1 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);   // key loops with scalar bounds
+  const int lane = tid & 63, wave = tid >> 6;
   const int base = off[q], n = off[q + 1] - base;
-  constexpr int NT = 64 * NW, RW = NW / KG;   // threads; waves side by side in the query rows
-  const int row0 = xblk * (32 * RW);
+  constexpr int NT = 64 * NW;             // threads: NW waves of 32 query rows each
+  const int row0 = xblk * (32 * NW);
   if (row0 >= n) return;
   const size_t ld = (size_t)3 * D;
   const int fr = lane & 31, fk = lane >> 5;
-  const int kg = KG == 1 ? 0 : wave / RW, rw = KG == 1 ? wave : wave % RW;
-  const int my_row = row0 + rw * 32 + fr;
-  const bool wave_active = row0 + rw * 32 < n;
+  const int my_row = row0 + wave * 32 + fr;
+  const bool wave_active = row0 + wave * 32 < n;
 
-  // Q fragments (B operand): lane (row, half) holds Q[row][16 ks + 8 half .. +7]
   bf16x8 qf[KS];
-  {
-    const bf16_t* qrow = qkv + (size_t)(base + (my_row < n ? my_row : n - 1)) * ld + h * DH + fk * 8;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16);
-  }
+  attention_query<DH>(qf, qkv + (size_t)(base + (my_row < n ? my_row : n - 1)) * ld + h * DH + fk * 8);
 
   floatx16 oacc[DT];
 #pragma unroll
@@ -327,39 +404,7 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
     const int nc = min(KC, n - c0);
     const int nc_pad = (nc + 31) & ~31;
     if (c0 > 0) __syncthreads();   // everyone is done with the previous chunk
-    // stage K and V rows c0 .. c0 + nc_pad - 1 (zero beyond n)
-    constexpr int CPR = DH / 8;    // 16-byte chunks per row
-    // batches of 4 chunk pairs per thread: all eight loads of a batch are issued before the first
-    // LDS store waits for them, so their latencies overlap
-    const int n_chunks = nc_pad * CPR;
-    for (int t0 = 0; t0 < n_chunks; t0 += 4 * NT) {
-      bf16x8 kv[4], vv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = t0 + u * NT + tid;
-        const int r = t / CPR, c = (t - r * CPR) * 8;
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-        kv[u] = zero;
-        vv[u] = zero;
-        if (t < n_chunks && r < nc) {
-          const bf16_t* src = qkv + (size_t)(base + c0 + r) * ld + D + h * DH + c;
-          kv[u] = *reinterpret_cast<const bf16x8*>(src);
-          vv[u] = *reinterpret_cast<const bf16x8*>(src + D);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = t0 + u * NT + tid;
-        const int r = t / CPR, c = (t - r * CPR) * 8;
-        if (t < n_chunks) {
-          *reinterpret_cast<bf16x8*>(Ks + r * LD + c) = kv[u];
-          *reinterpret_cast<bf16x8*>(Vs + r * LD + c) = vv[u];
-        }
-      }
-    }
-    if (BIAS) {
-      for (int t = tid; t < nc_pad; t += NT) lnsz[t] = t < nc ? log2f((float)sizes[base + c0 + t]) : 0.f;
-    }
+    attention_stage<DH, BIAS, NT>(qkv, sizes, ld, D, h, base + c0, nc, nc_pad, Ks, Vs, lnsz, tid);
     __syncthreads();
     if (!wave_active) continue;
 
@@ -367,39 +412,12 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
     // issued before the softmax arithmetic of block b starts, so the matrix pipe works under the VALU
     // instructions of the same wave (the kernel runs at two to four waves per SIMD and is bound by
     // these dependency waits, not by VALU or MFMA throughput).
-    auto s_block = [&](floatx16& sacc, int kb) {   // S^T block: logits of keys kb .. kb + 31
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sacc[e] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(Ks + (kb + fr) * LD + ks * 16 + fk * 8);
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sacc, 0, 0, 0);
-      }
-    };
+    auto s_block = [&](floatx16& sacc, int kb) { attention_logits<DH>(sacc, Ks, qf, kb, fr, fk); };
     auto softmax_pv = [&](floatx16& sacc, int kb) {
-      // Logits in base-2 units, t = s * (scale * log2 e) [+ log2(size)], so that exp(s - m) is one
-      // v_exp_f32.  Without the size bias the scaling is folded into the exponent's argument,
-      // exp2(fma(s, scale2, -m)): the maximum is taken over the raw products (scale2 > 0) and scaled
-      // once per row.  Only the chunk's last block can hold keys past the end.
-      float mx = -INFINITY;
-      if (BIAS) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          sacc[e] = sacc[e] * scale2 + lnsz[kb + 8 * (e >> 2) + 4 * fk + (e & 3)];
-      }
-      if (kb + 32 > nc) {   // wave-uniform: keys past the end of the sequence
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          sacc[e] = (kb + 8 * (e >> 2) + 4 * fk + (e & 3)) < nc ? sacc[e] : -INFINITY;
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[e]);
-      mx = xor32_max(mx);
-      if (!BIAS) mx *= scale2;
+      const float mx = attention_block_max<BIAS>(sacc, lnsz, scale2, kb, nc, fk);
       if (__any(mx > m_run)) {   // some row's maximum moved: rescale what has been accumulated
         const float m_new = fmaxf(m_run, mx);
-        // 0 on a row's first block (m_run = -inf); a row whose keys all had no weight so far has nothing to rescale
-        const float alpha = KG > 1 && m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first block (m_run = -inf)
         m_run = m_new;
         l_part *= alpha;
 #pragma unroll
@@ -407,59 +425,30 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
 #pragma unroll
           for (int e = 0; e < 16; ++e) oacc[t][e] *= alpha;
       }
-      // a key group may begin with keys of no weight (sizes 0) where the whole sequence does not
-      const float m_ref = KG > 1 && m_run == -INFINITY ? 0.f : m_run;
-      float psum = 0.f;
+      l_part += attention_weights<BIAS>(sacc, scale2, m_run);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pv = BIAS ? __builtin_amdgcn_exp2f(sacc[e] - m_ref)
-                              : __builtin_amdgcn_exp2f(fmaf(sacc[e], scale2, -m_ref));
-        sacc[e] = pv;
-        psum += pv;
-      }
-      l_part += psum;
-      // O^T += V^T P^T, two k-steps of 16 keys
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
+      for (int kk = 0; kk < 2; ++kk) {   // two k-steps of 16 keys
         bf16x8 pf;
 #pragma unroll
         for (int i = 0; i < 8; ++i) pf[i] = (bf16_t)sacc[8 * kk + i];
-        // transposing reads: lane s of each 16-lane group points at V[k0 + s/4][d0 + 4 (s & 3)]
-        const int s16 = lane & 15;
-        const int d0 = ((lane >> 4) & 1) * 16;
-        const int k0 = kb + 16 * kk + 4 * fk;
 #pragma unroll
-        for (int t = 0; t < DT; ++t) {
-          const bf16_t* vp = Vs + (k0 + (s16 >> 2)) * LD + t * 32 + d0 + 4 * (s16 & 3);
-          const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (__attribute__((address_space(3))) short4_t*)(vp));
-          const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (__attribute__((address_space(3))) short4_t*)(vp + 8 * LD));
-          const short8_t both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          bf16x8 vf;
-          __builtin_memcpy(&vf, &both, 16);
-          oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, oacc[t], 0, 0, 0);
-        }
+        for (int t = 0; t < DT; ++t)
+          oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(attention_values<DH>(Vs, kb, kk, t, lane), pf, oacc[t], 0, 0, 0);
       }
     };
     const int nblk = nc_pad >> 5;
     floatx16 s_even, s_odd;
-    s_block(s_even, KG == 1 ? 0 : min(kg, nblk - 1) * 32);
-    for (int b = kg; b < nblk; b += 2 * KG) {
-      if (b + KG < nblk) s_block(s_odd, (b + KG) * 32);
+    s_block(s_even, 0);
+    for (int b = 0; b < nblk; b += 2) {
+      if (b + 1 < nblk) s_block(s_odd, (b + 1) * 32);
       __builtin_amdgcn_sched_barrier(0);
       softmax_pv(s_even, b * 32);
-      if (b + KG < nblk) {
-        if (b + 2 * KG < nblk) s_block(s_even, (b + 2 * KG) * 32);
+      if (b + 1 < nblk) {
+        if (b + 2 < nblk) s_block(s_even, (b + 2) * 32);
         __builtin_amdgcn_sched_barrier(0);
-        softmax_pv(s_odd, (b + KG) * 32);
+        softmax_pv(s_odd, (b + 1) * 32);
       }
     }
-  }
-  if constexpr (KG > 1) {
-    attention_combine<DH, NW, KG>(oacc, m_run, xor32_sum(l_part), reinterpret_cast<float*>(smem), wave, kg, rw, lane, wave_active,
-                                  my_row < n ? o + (size_t)(base + my_row) * D + h * DH : nullptr);
-    return;
   }
   if (!wave_active) return;
   const float l_tot = xor32_sum(l_part);
@@ -467,17 +456,162 @@ __device__ __forceinline__ void attention_mfma_body(const bf16_t* __restrict__ q
     const float inv = 1.0f / l_tot;
     bf16_t* orow = o + (size_t)(base + my_row) * D + h * DH;
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
+    for (int t = 0; t < DT; ++t) attention_store<DH>(orow, oacc[t], inv, t, fk);
+  }
+}
+
+// The same with a row block's 32 rows on KG waves, of which NW / KG are side by side in the rows: wave kg has every KG-th block of a
+// chunk's keys (logits, maximum; then, knowing the maxima of the blocks in front, weights, their sum and the factor that rescales
+// what came before, all left in LDS) and tile kg of O^T, to which it adds the chunk's products block by block.  What depends on the
+// order of the keys, the running maximum, the rescaling, the row sum and the products, is done block after block as by the one wave
+// above: the same bits.  The next chunk's keys and values are on their way while this one is worked on.
+template <int DH, bool BIAS, int KC, int NW, int KG>
+__device__ __forceinline__ void attention_shared_body(const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes,
+                                                      const int32_t* __restrict__ off, int D, float scale,
+                                                      bf16_t* __restrict__ o, const int q, const int h, const int xblk,
+                                                      unsigned char* smem, const int tid) {
+  constexpr int KS = DH / 16, DT = (DH + 31) / 32, LD = DH + 8, NT = 64 * NW, RW = NW / KG;
+  constexpr int NB = KC / 32, OWN = NB / KG;   // blocks of a chunk, and of them a wave's
+  constexpr int CPR = DH / 8, PIECES = KC * CPR / NT;   // 16-byte pieces of a row; of a chunk's keys, a thread's
+  static_assert(DT <= KG && NB % KG == 0, "a tile of O^T to a wave, the same number of blocks to each");
+  static_assert(KC * CPR % NT == 0 && KC <= NT, "the same number of pieces to each thread, one size at most");
+  bf16_t* Ks = reinterpret_cast<bf16_t*>(smem);                                                      // [KC][LD]
+  bf16_t* Vs = reinterpret_cast<bf16_t*>(smem + attention_keys_bytes(DH, KC, NW, KG));               // [KC + 4][LD]
+  float* lnsz = reinterpret_cast<float*>(Vs + (KC + 4) * LD);                                        // [KC]
+
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave / RW, rw = wave % RW;
+  bf16x8* weights = reinterpret_cast<bf16x8*>(smem) + rw * NB * 2 * 64;   // [NB][2][64], in place of the keys
+  float* maxima = lnsz + KC + rw * NB * 32;                               // [NB][32]
+  float* sums = lnsz + KC + RW * NB * 32 + rw * NB * 64;                  // [NB][64]
+  float* factors = lnsz + KC + RW * NB * 96 + rw * NB * 32;               // [NB][32]
+  const int base = off[q], n = off[q + 1] - base;
+  const int row0 = xblk * (32 * RW);
+  if (row0 >= n) return;
+  const size_t ld = (size_t)3 * D;
+  const int fr = lane & 31, fk = lane >> 5;
+  const int my_row = row0 + rw * 32 + fr;
+  const bool wave_active = row0 + rw * 32 < n;
+
+  bf16x8 kv[PIECES], vv[PIECES];
+  int sz = 0;
+  auto fetch = [&](int c0) {   // rows past the end are zero
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int d = t * 32 + g * 8 + fk * 4;
-        if (d < DH) {
-          bf16x4 ov = {(bf16_t)(oacc[t][g * 4 + 0] * inv), (bf16_t)(oacc[t][g * 4 + 1] * inv),
-                       (bf16_t)(oacc[t][g * 4 + 2] * inv), (bf16_t)(oacc[t][g * 4 + 3] * inv)};
-          *reinterpret_cast<bf16x4*>(orow + d) = ov;
+    for (int u = 0; u < PIECES; ++u) {
+      const int t = u * NT + tid, r = t / CPR, c = (t - r * CPR) * 8;
+      const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+      kv[u] = zero;
+      vv[u] = zero;
+      if (c0 + r < n) {
+        const bf16_t* src = qkv + (size_t)(base + c0 + r) * ld + D + h * DH + c;
+        kv[u] = *reinterpret_cast<const bf16x8*>(src);
+        vv[u] = *reinterpret_cast<const bf16x8*>(src + D);
+      }
+    }
+    if (BIAS) sz = tid < KC && c0 + tid < n ? sizes[base + c0 + tid] : 1;
+  };
+  fetch(0);
+  bf16x8 qf[KS];
+  attention_query<DH>(qf, qkv + (size_t)(base + (my_row < n ? my_row : n - 1)) * ld + h * DH + fk * 8);
+
+  floatx16 oacc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) oacc[e] = 0.f;
+  float m_run = -INFINITY, l_part = 0.f;
+  const float scale2 = scale * 1.44269504088896340736f;
+
+  for (int c0 = 0; c0 < n; c0 += KC) {
+    const int nc = min(KC, n - c0), nblk = (nc + 31) >> 5;
+    if (c0 > 0) __syncthreads();   // everyone is done with the previous chunk
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) {
+      const int t = u * NT + tid, r = t / CPR, c = (t - r * CPR) * 8;
+      *reinterpret_cast<bf16x8*>(Ks + r * LD + c) = kv[u];
+      *reinterpret_cast<bf16x8*>(Vs + r * LD + c) = vv[u];
+    }
+    if (BIAS && tid < KC) lnsz[tid] = log2f((float)sz);
+    __syncthreads();
+    if (c0 + KC < n) fetch(c0 + KC);
+    floatx16 sacc[OWN];
+    if (wave_active) {
+#pragma unroll
+      for (int j = 0; j < OWN; ++j) {
+        const int b = kg + j * KG;
+        if (b < nblk) {
+          attention_logits<DH>(sacc[j], Ks, qf, b * 32, fr, fk);
+          const float mx = attention_block_max<BIAS>(sacc[j], lnsz, scale2, b * 32, nc, fk);
+          if (fk == 0) maxima[b * 32 + fr] = mx;
         }
       }
+    }
+    __syncthreads();   // the maxima are there, and the keys no longer needed
+    if (wave_active) {
+      float mx[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) mx[b] = b < nblk ? maxima[b * 32 + fr] : -INFINITY;
+      float m = m_run, before[OWN], mine[OWN];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        if (b % KG == kg) before[b / KG] = m;
+        m = fmaxf(m, mx[b]);
+        if (b % KG == kg) mine[b / KG] = m;
+      }
+      m_run = m;
+#pragma unroll
+      for (int j = 0; j < OWN; ++j) {
+        const int b = kg + j * KG;
+        if (b < nblk) {
+          if (fk == 0) factors[b * 32 + fr] = __builtin_amdgcn_exp2f(before[j] - mine[j]);   // 0 on the first block
+          sums[b * 64 + lane] = attention_weights<BIAS>(sacc[j], scale2, mine[j]);
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk) {
+            bf16x8 pf;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) pf[i] = (bf16_t)sacc[j][8 * kk + i];
+            weights[(b * 2 + kk) * 64 + lane] = pf;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (wave_active && kg < DT) {
+      struct Block { bf16x8 w[2], v[2]; float factor, sum; } cur, next;   // operands are read a block ahead
+      auto read = [&](Block& x, int b) {
+        x.factor = factors[b * 32 + fr];
+        x.sum = sums[b * 64 + lane];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          x.w[kk] = weights[(b * 2 + kk) * 64 + lane];
+          x.v[kk] = attention_values<DH>(Vs, b * 32, kk, kg, lane);
+        }
+      };
+      read(cur, 0);
+      for (int b = 0; b < nblk; ++b) {
+        read(next, min(b + 1, nblk - 1));
+        if (__any(cur.factor != 1.f)) {
+          l_part *= cur.factor;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[e] *= cur.factor;
+        }
+        l_part += cur.sum;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) oacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.v[kk], cur.w[kk], oacc, 0, 0, 0);
+        cur = next;
+      }
+    }
   }
+  if (wave_active && kg < DT) {
+    const float l_tot = xor32_sum(l_part);
+    if (my_row < n) attention_store<DH>(o + (size_t)(base + my_row) * D + h * DH, oacc, 1.0f / l_tot, kg, fk);
+  }
+}
+
+template <int DH, bool BIAS, int KC, int NW, int KG>
+__device__ __forceinline__ void attention_head(const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes,
+                                               const int32_t* __restrict__ off, int D, float scale, bf16_t* __restrict__ o, int q,
+                                               int h, int xblk, unsigned char* smem, int tid) {
+  if constexpr (KG == 1) attention_mfma_body<DH, BIAS, KC, NW>(qkv, sizes, off, D, scale, o, q, h, xblk, smem, tid);
+  else attention_shared_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, h, xblk, smem, tid);
 }
 
 // Which head (counted through all queries) and row block workgroup id has.  Workgroups go to the eight XCDs in turn: BY_HEAD gives
@@ -495,7 +629,7 @@ __device__ __forceinline__ HeadBlock head_block(unsigned id, unsigned xblks, uns
 }
 
 template <int DH, bool BIAS, int KC, int NW, int KG, bool BY_HEAD>
-__global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kernel(const bf16_t* __restrict__ qkv,
+__global__ __launch_bounds__(64 * NW, DH <= 64 && KG == 1 ? 4 : 2) void attention_mfma_kernel(const bf16_t* __restrict__ qkv,
                                                              const int32_t* __restrict__ sizes,
                                                              const int32_t* __restrict__ off, int D, float scale,
                                                              bf16_t* __restrict__ o) {
@@ -507,7 +641,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kern
     h = b.head - q * (int)gridDim.y;
     x = b.x;
   }
-  attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, h, x, smem, (int)threadIdx.x);
+  attention_head<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, h, x, smem, (int)threadIdx.x);
 }
 
 // Attention and the merge plan of a layer in ONE launch (both only read the layer's QKV projection, and
@@ -519,11 +653,12 @@ __global__ __launch_bounds__(64 * NW, DH <= 64 ? 4 : 2) void attention_mfma_kern
 // attention then has the shape of the stand-alone kernel (one head of eight waves, or two of four: heads in one
 // workgroup share its barriers, and four heads in lock-step in 1024-thread workgroups cost attention a fifth of its
 // speed), and a plan workgroup shares its CU with an attention workgroup instead of taking the CU.  Head width 64
-// only (four waves per SIMD leave 128 registers per lane).
+// only (four waves per SIMD leave 128 registers per lane; two where waves share row blocks, of launches with a CU for nearly every
+// workgroup).
 // grid.x = B * na * nb + xblks * (H / G) * B with G = 8 / NW (na = nb = 1 for the whole plan).
 constexpr int kFusedThreads = 512;
 template <bool BIAS, int KC, int NW, int KG, bool BY_HEAD>
-__global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
+__global__ __launch_bounds__(kFusedThreads, KG == 1 ? 4 : 2) void attention_plan_kernel(
     const bf16_t* __restrict__ qkv, const int32_t* __restrict__ sizes, const int32_t* __restrict__ off, int D, int H,
     float scale, bf16_t* __restrict__ o, int B, int xblks, const int32_t* __restrict__ out_off,
     const int32_t* __restrict__ reff_arr, const int32_t* __restrict__ troff, int n_lead,
@@ -548,22 +683,10 @@ __global__ __launch_bounds__(kFusedThreads, 4) void attention_plan_kernel(
   const HeadBlock b = head_block<BY_HEAD>(blockIdx.x - B * na * nb, xblks, B * hg);
   const int hgrp = b.head % hg, q = b.head / hg, xblk = b.x;
   const int unit = (int)threadIdx.x / (64 * NW), tid = (int)threadIdx.x % (64 * NW);
-  attention_mfma_body<DH, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, hgrp * G + unit, xblk, smem + (size_t)unit * unit_lds,
-                                        tid);
+  attention_head<64, BIAS, KC, NW, KG>(qkv, sizes, off, D, scale, o, q, hgrp * G + unit, xblk, smem + (size_t)unit * unit_lds, tid);
 }
 
-// How a launch cuts up its work: keys staged at a time, waves per head and row block, key groups.
-struct AttnShape {
-  int kc, nw, kg;
-  bool by_head;   // head_block
-};
-constexpr size_t attention_lds_bytes(int dh, int kc, int nw, int kg) {
-  const size_t staged = (size_t)(kc + kc + 4) * (dh + 8) * sizeof(bf16_t) + kc * sizeof(float);
-  const size_t parts = kg > 1 ? sizeof(float) * attention_parts_floats(dh, nw) : 0;
-  return ((staged > parts ? staged : parts) + 15) & ~(size_t)15;
-}
-
-// Without key groups: sequences of up to 128 rows (and those beyond 256) take four waves per workgroup, keys and values
+// Without shared keys: sequences of up to 128 rows (and those beyond 256) take four waves per workgroup, keys and values
 // staged 128 at a time ((128 + 132) rows of DH + 8 bf16 = 37 KB at DH = 64, so four workgroups share
 // a CU and cover each other's MFMA-dependency and barrier waits).  Sequences of 129 .. 256 rows: one
 // workgroup of eight waves per (query, head) instead of two of four, with the head's keys and values
@@ -572,39 +695,36 @@ constexpr size_t attention_lds_bytes(int dh, int kc, int nw, int kg) {
 // 18.2 against 20.6 at n = 133).  At DH = 64 the same form takes longer sequences whose last block of 256 rows is more than half full
 // (16 / 32 / 64 queries of 400 tokens 23.4 / 41.2 / 72.8 -> 24.7 / 37.1 / 65.6 us; of 320, where it is not, 18.3 / 27.9 / 45.5 and 20.2 /
 // 32.1 / 53.3; 577 37.0 / 64.2 / 115.8 and 41.5 / 67.1 / 121.4).
-// With key groups, for launches that leave CUs idle: a wave's chain of key blocks (load, logits, softmax, product, 0.6 us each) is what
-// such a launch lasts, so the waves of a row block share it.  Four groups while every block of 32 rows finds a CU of its own,
-// or every block of 64; two while those of 128 do.  Measured, us without and with (12 heads): one query of 101 / 197 / 256 / 577 tokens
-// 5.0 / 7.9 / 9.1 / 14.1 -> 4.0 / 4.9 / 5.0 / 8.5; four of 101 / 197 / 256 / 400 5.1 / 8.2 / 9.5 / 11.6 -> 4.1 / 6.2 / 6.3 / 10.3 (the 101 in
-// blocks of 32, the 400 of 128); seven of 197 8.3 -> 7.2, of 165 7.3 -> 6.1; ten of 577 and 197 in turn 26.6 -> 22.8, with sizes 30.2 ->
-// 23.7.  Past those lines the groups' extra staging and sums cost more: twelve of 197 8.5 and 10.5, seven of 577 22.1 and 22.0, of 400
-// 14.0 and 16.8.
-// long_blocks: blocks of 128 rows of the queries longer than half the longest, which last longest.  pairs: an even number of heads
-// can be dealt in twos.  others: workgroups beside attention's, those of the plan's selection.  Up to 256 rows such a launch lasts as
-// long as the selection, and attention's own workgroups slow it: no more than the CUs left over, in blocks of 32 (passes of one / four /
-// seven queries of 197 tokens with r = 16, us, without groups, by this rule, by the rule for attention alone: 472 / 567 / 665, 469 / 567 /
-// 665, 469 / 568 / 672); beyond 256 rows attention lasts longest.
+//
+// Launches that leave CUs idle last as long as a wave's chain of key blocks (logits, softmax, product, 0.6 us each): four waves share a
+// row block (attention_shared_body), in blocks of 32 rows while each of these finds a CU of its own, in blocks of 64 while those do.
+// Measured, us without and with (12 heads): one query of 101 / 197 / 256 / 577 tokens 5.0 / 8.0 / 9.1 / 14.2 -> 4.0 / 5.3 / 5.4 / 10.7, with sizes
+// of 197 8.6 -> 5.5; three of 197 8.1 -> 5.6; blocks of 64, five of 197 8.2 -> 6.5, seven of 165 7.2 -> 5.9, three of 400 11.4 -> 9.7.  Past those
+// lines a CU's second workgroup waits for its registers: seven of 197 8.3 and 11.2, four of 400 11.5 and 19.0, ten of 577 and 197 in
+// turn 27.0 and 41.5.  Two waves a row block are nowhere faster than the better of the two.  Keys 256 at a time beyond 128 rows: one query
+// of 197 / 400 5.6 / 8.5 -> 5.3 / 8.1, but of 101 4.0 -> 4.5 and at DH = 80 no faster.  Beside a selection of up to 256 rows, which is what such a
+// launch lasts, sharing gains nothing (passes of one / two / four queries of 197 tokens with r = 16 448 / 492 / 557 us and 448 / 490 / 557; ViT-L,
+// one with r = 8, 1026 and 1031); beyond 256 rows attention lasts longest (one of 577
+// 785 -> 732, of 401 633 -> 592, two of 577 and 197 795 -> 696: blocks of 64 whether or not the selection leaves each a CU, 770 where it must).
+// others: workgroups beside attention's, those of the plan's selection.
 //
 // Row blocks of a head beyond 256 rows go to one XCD (us a pass, dealt out -> by head; ViT-B unless said): beside a
 // selection (10 / 32 / 64 queries of 577 and 197 tokens in turn with r = 23 1291 / 2660 / 4744 -> 1282 / 2632 / 4659);
-// with key groups, where the launch is less than one round of the CUs (two / four of 257 549 / 762 -> 539 / 750, of 325
-// 622 / 821 -> 613 / 814), though not for a lone query (257 448.4 -> 451.8), nor in the smaller blocks of up to 256 rows
-// (seven / ten of 197 824 / 924 -> 832 / 936, three of 101 and 4 prompts 428 -> 432), nor without groups (six of 401
-// 1103 -> 1114); and from 448 blocks of 128 rows of long queries on (8 / 64 of 577 1652 / 8555 -> 1627 / 8432, 64 of 325
-// 4560 -> 4499, ViT-H 32 of 257 10837 -> 10679). Between, a chip of 1 to 2 workgroups a CU lasts as long as its fullest
-// XCD: 5 of 513 tokens (300 blocks) 1222 -> 1238, 10 of 325 (360) 1255 -> 1265, 24 of 325 and 50 in turn (432) 1579 ->
-// 1583, but 8 of 513 (480) 1624 -> 1610, 14 of 257 (504) 1357 -> 1354.
-static AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, bool bias, bool pairs, int others) {
-  const bool shared = others > 0 && max_n <= 256;
-  auto shape = [&](int kc, int nw, int kg) {
-    const int rows = 32 * nw / kg, xblks = (max_n + rows - 1) / rows;
-    const bool few = kg > 1 && (int64_t)B * H * xblks <= 256, many = (int64_t)H * long_blocks >= 448;
-    return AttnShape{kc, nw, kg, max_n > 256 && B > 1 && (others > 0 || few || many)};
-  };
+// with shared row blocks, whose launch is less than one round of the CUs (two / three of 325 and 3 prompts 636 / 738 -> 628 /
+// 730), though not for a lone query (257 448.4 -> 451.8); and from 448 blocks of 128 rows of long queries (long_blocks: those
+// longer than half the longest) on (8 / 64 of 577 1652 / 8555 -> 1627 / 8432, 64 of 325 4560 -> 4499, ViT-H 32 of 257 10837 ->
+// 10679). Between, a chip of 1 to 2 workgroups a CU lasts as long as its fullest XCD: 5 of 513 tokens (300 blocks) 1222 -> 1238,
+// 10 of 325 (360) 1255 -> 1265, 24 of 325 and 50 in turn (432) 1579 -> 1583, but 8 of 513 (480) 1624 -> 1610, 14 of 257 (504)
+// 1357 -> 1354.
+AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, int others) {
   auto blocks = [&](int rows) { return (int64_t)B * H * ((max_n + rows - 1) / rows); };
-  if (dh <= 80 && max_n > 64 && pairs && blocks(32) <= (shared ? 256 - others : 256)) return shape(128, 4, 4);
-  if (dh == 64 && max_n > 128 && !shared && blocks(64) <= 256) return shape(128, 8, 4);
-  if (dh == 64 && max_n > 192 && !shared && (int64_t)H * long_blocks <= (max_n > 512 ? 320 : 256)) return shape(bias ? 128 : 256, 8, 2);
+  auto shape = [&](int kc, int nw, int kg) {
+    return AttnShape{kc, nw, kg, max_n > 256 && B > 1 && (others > 0 || kg > 1 || (int64_t)H * long_blocks >= 448)};
+  };
+  if (dh <= 80 && max_n > (others > 0 ? 256 : 64)) {
+    if (blocks(32) <= 256) return shape(dh == 64 && max_n > 128 ? 256 : 128, 4, 4);
+    if (dh == 64 && max_n > 128 && blocks(64) <= 256) return shape(256, 8, 4);
+  }
   const int last = (max_n - 1) % 256 + 1;   // rows of the last block of 256
   if (max_n > 128 && last > 128 && (max_n <= 256 || dh == 64)) return shape(dh <= 64 ? 256 : 128, 8, 1);
   return shape(128, 4, 1);
@@ -613,7 +733,7 @@ static AttnShape attention_shape(int dh, int H, int B, int max_n, int long_block
 template <int DH, bool BIAS>
 static hipError_t attention_mfma_b(const void* qkv, const int32_t* sz, const int32_t* d_off, int B, int max_n, int long_blocks,
                                    int D, int H, float scale, void* o, hipStream_t s) {
-  const AttnShape sh = attention_shape(DH, H, B, max_n, long_blocks, BIAS, true, 0);
+  const AttnShape sh = attention_shape(DH, H, B, max_n, long_blocks, 0);
 #define OTAS_ATTN(KC, NWV, KG)                                                                                    \
   if (sh.kc == KC && sh.nw == NWV && sh.kg == KG) {                                                               \
     constexpr size_t lds = attention_lds_bytes(DH, KC, NWV, KG);                                                  \
@@ -631,8 +751,8 @@ static hipError_t attention_mfma_b(const void* qkv, const int32_t* sz, const int
   if constexpr (DH <= 80) { OTAS_ATTN(128, 4, 4) }
   OTAS_ATTN((DH <= 64 ? 256 : 128), 8, 1)   // wider heads: two pieces
   if constexpr (DH == 64) {
-    OTAS_ATTN(128, 8, 4)
-    OTAS_ATTN((BIAS ? 128 : 256), 8, 2)
+    OTAS_ATTN(256, 4, 4)
+    OTAS_ATTN(256, 8, 4)
   }
 #undef OTAS_ATTN
   return hipErrorInvalidValue;
@@ -646,8 +766,8 @@ static hipError_t attention_mfma(const void* qkv, const int32_t* sz, const int32
 }
 
 // LDS of the fused kernel's attention workgroups as the number of the selection's is chosen by: one head of eight waves with
-// all keys staged for 129 .. 256 rows, else two heads of four waves with 128 keys each (75 KB either way; key groups and
-// longer sequences in pieces of 256 take no more).
+// all keys staged for 129 .. 256 rows, else two heads of four waves with 128 keys each (75 KB either way; longer
+// sequences in pieces of 256 take no more, two heads of shared row blocks 155 KB, with a CU for every workgroup).
 static size_t fused_attention_lds(int max_n) {
   return max_n > 128 && max_n <= 256 ? attention_lds_bytes(64, 256, 8, 1) : 2 * attention_lds_bytes(64, 128, 4, 1);
 }
@@ -712,7 +832,7 @@ hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* size
   const size_t plan_lds = sel_best ? plan_select_lds_bytes(max_n, 64, how.na, how.nb) : merge_plan_lds_bytes(max_n, 64);
   const float scale = 1.0f / sqrtf(64.0f);
   const int32_t* sz = size_bias ? sizes : nullptr;
-  const AttnShape sh = attention_shape(64, H, B, max_n, long_blocks, size_bias, H % 2 == 0, B * how.na * how.nb);
+  const AttnShape sh = attention_shape(64, H, B, max_n, long_blocks, B * how.na * how.nb);
 #define OTAS_FUSED(BIASV, KC, NWV, KG)                                                                            \
   if ((sz != nullptr) == BIASV && sh.kc == KC && sh.nw == NWV && sh.kg == KG) {                                   \
     constexpr int G = kFusedThreads / 64 / NWV, rows = 32 * NWV / KG;                                             \
@@ -732,10 +852,9 @@ hipError_t launch_attention_plan(int dtype, const void* qkv, const int32_t* size
   }
 #define OTAS_FUSED_BIAS(BIASV)              \
   OTAS_FUSED(BIASV, 128, 4, 1)              \
-  OTAS_FUSED(BIASV, 128, 4, 4)              \
   OTAS_FUSED(BIASV, 256, 8, 1)              \
-  OTAS_FUSED(BIASV, 128, 8, 4)              \
-  OTAS_FUSED(BIASV, (BIASV ? 128 : 256), 8, 2)
+  OTAS_FUSED(BIASV, 256, 4, 4)              \
+  OTAS_FUSED(BIASV, 256, 8, 4)
   OTAS_FUSED_BIAS(true)
   OTAS_FUSED_BIAS(false)
 #undef OTAS_FUSED_BIAS

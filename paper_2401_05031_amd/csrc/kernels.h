@@ -116,6 +116,13 @@ hipError_t launch_splitk_reduce_ln(const float* part, int S, const void* bias, c
 hipError_t launch_attention(int dtype, const void* qkv, const int32_t* sizes,
                             const int32_t* d_off, int B, int max_n, int long_blocks, int D, int H, bool size_bias,
                             void* o, hipStream_t s);
+// How a launch of the bf16 attention cuts up its work (pure host): keys staged at a time, waves per head and row block, of which kg share
+// 32 rows, whether the row blocks of a head go to one XCD.  The results are the same bits in every shape.
+struct AttnShape {
+  int kc, nw, kg;
+  bool by_head;
+};
+AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, int others);
 // long_blocks of these launches: blocks of 128 rows of the queries that are longer than half the longest one, max_n.
 inline int attention_long_blocks(const int* n, int B, int max_n) {
   int blocks = 0;
