@@ -690,6 +690,16 @@ __global__ __launch_bounds__(256) void embed_finish_kernel(const T* __restrict__
   }
 }
 
+// Launches work on B images in as many pieces as it takes to keep a grid of 256 threads a workgroup below the 2^32 threads it can
+// have: short rows (4 x 4 pixels in one patch: 16 threads of 256 have an element) reach that before the elements do.
+template <typename F>
+static hipError_t launch_images(int64_t B, int64_t workgroups_per_image, F&& launch) {
+  int64_t most = ((1 << 24) - 1) / workgroups_per_image;
+  if (most < 1) most = 1;
+  for (int64_t b = 0; b < B; b += most) launch(b, (int)(B - b < most ? B - b : most));
+  return hipGetLastError();
+}
+
 static bool on_16_bytes(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <typename T>
@@ -697,11 +707,13 @@ static hipError_t patchify(const T* img, T* out, int B, int C, int Hi, int Wi, i
   constexpr int V = Vec<T>::N;   // p % V == 0: every row of the image and of the patch matrix begins on 16 bytes
   const bool wide = p % V == 0 && on_16_bytes(img) && on_16_bytes(out);
   if (B <= 0 || C <= 0 || Hi / p <= 0 || Wi / p <= 0) return hipSuccess;
-  const int64_t per_band = ((int64_t)Wi * p / (wide ? V : 1) + 255) / 256;
-  const dim3 grid((unsigned)(per_band * B * (Hi / p) * C)), block(256);
-  if (wide) patchify_kernel<T, V><<<grid, block, 0, s>>>(img, out, C, Hi, Wi, p, (int)per_band);
-  else patchify_kernel<T, 1><<<grid, block, 0, s>>>(img, out, C, Hi, Wi, p, (int)per_band);
-  return hipGetLastError();
+  const int64_t per_band = ((int64_t)Wi * p / (wide ? V : 1) + 255) / 256, per_image = per_band * (Hi / p) * C;
+  const int64_t pixels = (int64_t)C * Hi * Wi;
+  return launch_images(B, per_image, [&](int64_t b, int images) {
+    const dim3 grid((unsigned)(per_image * images)), block(256);
+    if (wide) patchify_kernel<T, V><<<grid, block, 0, s>>>(img + b * pixels, out + b * pixels, C, Hi, Wi, p, (int)per_band);
+    else patchify_kernel<T, 1><<<grid, block, 0, s>>>(img + b * pixels, out + b * pixels, C, Hi, Wi, p, (int)per_band);
+  });
 }
 
 hipError_t launch_patchify(int dtype, const void* img, void* out, int B, int C, int Hi, int Wi, int p, hipStream_t s) {
@@ -714,12 +726,16 @@ static hipError_t embed_finish(const T* proj, const T* cls, const T* pos, T* tok
                                hipStream_t s) {
   constexpr int V = Vec<T>::N;
   const bool wide = D % V == 0 && on_16_bytes(proj) && on_16_bytes(cls) && on_16_bytes(pos) && on_16_bytes(tokens);
-  const int rows = B * (n_lead + N);   // the offsets that the caller gets are 32-bit
-  if (rows <= 0 || D <= 0) return hipSuccess;
-  const dim3 grid((unsigned)(((int64_t)rows + 3) / 4)), block(256);
-  if (wide) embed_finish_kernel<T, V><<<grid, block, 0, s>>>(proj, cls, pos, tokens, N, D, n_lead, rows);
-  else embed_finish_kernel<T, 1><<<grid, block, 0, s>>>(proj, cls, pos, tokens, N, D, n_lead, rows);
-  return hipGetLastError();
+  const int n = n_lead + N;
+  if (B <= 0 || n <= 0 || D <= 0) return hipSuccess;
+  return launch_images(B, (n + 3) / 4, [&](int64_t b, int images) {
+    const int rows = images * n;
+    const T* from = proj + b * N * D;
+    T* to = tokens + b * n * D;
+    const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+    if (wide) embed_finish_kernel<T, V><<<grid, block, 0, s>>>(from, cls, pos, to, N, D, n_lead, rows);
+    else embed_finish_kernel<T, 1><<<grid, block, 0, s>>>(from, cls, pos, to, N, D, n_lead, rows);
+  });
 }
 
 hipError_t launch_embed_finish(int dtype, const void* proj, const void* cls, const void* pos, void* tokens, int B,

@@ -351,6 +351,29 @@ def test_patches_and_rows_by_16_bytes_and_by_elements(lib, dtype, p, shift):
     ctx.close()
 
 
+def test_more_images_than_a_grid_has_threads_for(lib):
+    """A launch has fewer than 2^32 threads, 256 for the rows of a band of patches however short they are: 2^23 + 3 images of two channels
+    of 4 x 4 pixels in one patch are more.  So are 2^26 + 6 token rows with a wave each.  (One patch an image: the patch matrix is the images.)"""
+    import ctypes
+    import torch
+    so, vp, i32 = ctypes.CDLL(lib.lib_path()), ctypes.c_void_p, ctypes.c_int
+    patchify, finish = so._ZN4otas15launch_patchifyEiPKvPviiiiiP12ihipStream_t, so._ZN4otas19launch_embed_finishEiPKvS1_S1_PviiiiP12ihipStream_t
+    patchify.argtypes, finish.argtypes = [i32, vp, vp] + [i32] * 5 + [vp], [i32] + [vp] * 4 + [i32] * 4 + [vp]
+    stream = torch.cuda.current_stream().cuda_stream
+    B = (1 << 23) + 3
+    img = torch.randint(-9, 9, (B, 32), dtype=torch.int8, device="cuda").to(torch.bfloat16)
+    out = torch.full_like(img, float("nan"))
+    assert patchify(1, img.data_ptr(), out.data_ptr(), B, 2, 4, 4, 4, stream) == 0
+    assert torch.equal(out, img)
+    del img, out
+    B, D = (1 << 25) + 3, 8
+    proj = torch.randint(-9, 9, (B, D), dtype=torch.int8, device="cuda").to(torch.bfloat16)
+    cls, pos = (torch.randint(-9, 9, s, dtype=torch.int8, device="cuda").to(torch.bfloat16) for s in ((D,), (2, D)))
+    toks = torch.full((B, 2, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert finish(1, proj.data_ptr(), cls.data_ptr(), pos.data_ptr(), toks.data_ptr(), B, 1, D, 1, stream) == 0
+    assert bool((toks[:, 0] == cls + pos[0]).all()) and torch.equal(toks[:, 1], proj + pos[1])
+
+
 @pytest.mark.parametrize("n", [2, 3, 16, 17, 31, 32, 33, 34, 49, 63, 64, 65, 100])
 def test_selection_in_tiles_of_16_and_of_32(lib, n):
     """Queries of up to 64 tokens have one block of 32 tokens of either kind, which the selection beside attention (eight waves)
