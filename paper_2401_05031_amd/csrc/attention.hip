@@ -693,8 +693,12 @@ __global__ __launch_bounds__(kFusedThreads, KG == 1 ? 4 : 2) void attention_plan
 // staged once and in one piece (75 KB at DH = 64, two workgroups per CU): one load phase per
 // workgroup instead of two (measured on MI355X, batch 64, 12 heads: 26.3 us against 27.2 at n = 197,
 // 18.2 against 20.6 at n = 133).  At DH = 64 the same form takes longer sequences whose last block of 256 rows is more than half full
-// (16 / 32 / 64 queries of 400 tokens 23.4 / 41.2 / 72.8 -> 24.7 / 37.1 / 65.6 us; of 320, where it is not, 18.3 / 27.9 / 45.5 and 20.2 /
-// 32.1 / 53.3; 577 37.0 / 64.2 / 115.8 and 41.5 / 67.1 / 121.4).
+// (of 320, where it is not, 16 / 32 / 64 queries 18.3 / 27.9 / 45.5 -> 20.2 / 32.1 / 53.3): beside a selection always (passes of 10 / 24 of 485
+// and 197 tokens with r = 23 1148 / 1829 -> 1137 / 1799, 16 of 650 with r = 16 2663 -> 2645), on its own where it halves the rounds of the
+// CUs, all queries having as many blocks.  us, four waves / eight (12 heads): 400 tokens, rounds 1 / 1 (5 queries) 12.7 / 13.7, 2 / 1 (8) 17.0 /
+// 14.3, 3 / 2 (13) 23.1 / 23.8, 4 / 2 (19) 29.3 / 25.9, 5 / 3 (24) 35.8 / 36.0, 8 / 4 (42) 52.0 / 46.7; 900 tokens, 2 / 1 (4) 31.3 / 29.3, 3 / 2 (7) 41.9 / 44.0, 4 / 2 (9)
+// 53.1 / 46.1, 5 / 3 (12) 66.3 / 69.2, 7 / 4 (18) 87.7 / 91.6.  With workgroups that have no rows it depends on where these fall: 650 and 197 in turn, 16
+// heads, 5 queries 24.4 / 21.1, 8 27.6 / 33.5, 20 48.8 / 52.7.
 //
 // Launches that leave CUs idle last as long as a wave's chain of key blocks (logits, softmax, product, 0.6 us each): four waves share a
 // row block (attention_shared_body), in blocks of 32 rows while each of these finds a CU of its own, in blocks of 64 while those do.
@@ -726,7 +730,9 @@ AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, int 
     if (dh == 64 && max_n > 128 && blocks(64) <= 256) return shape(256, 8, 4);
   }
   const int last = (max_n - 1) % 256 + 1;   // rows of the last block of 256
-  if (max_n > 128 && last > 128 && (max_n <= 256 || dh == 64)) return shape(dh <= 64 ? 256 : 128, 8, 1);
+  auto rounds = [&](int rows) { return (blocks(rows) + 255) / 256; };
+  const bool halves = long_blocks == (int64_t)B * ((max_n + 127) / 128) && rounds(128) >= 2 * rounds(256);
+  if (max_n > 128 && last > 128 && (max_n <= 256 || (dh == 64 && (others > 0 || halves)))) return shape(dh <= 64 ? 256 : 128, 8, 1);
   return shape(128, 4, 1);
 }
 

@@ -49,6 +49,32 @@ def test_workgroups_of_the_selection():
             assert 1 <= p.na <= ((max_n + 1) // 2 + 31) // 32 and 1 <= p.nb <= (max_n // 2 + 31) // 32
 
 
+class AttnShape(ctypes.Structure):
+    _fields_ = [("kc", ctypes.c_int), ("nw", ctypes.c_int), ("kg", ctypes.c_int), ("by_head", ctypes.c_bool)]
+
+
+def test_how_attention_is_cut_up():
+    """Waves share row blocks while every block has a CU of its own; 256 rows a workgroup beyond 256 rows, on its own, where every
+    query has as many blocks and the rounds of the CUs are halved.  12 heads of width 64."""
+    shape = _library()._ZN4otas15attention_shapeEiiiiii
+    shape.argtypes, shape.restype = [ctypes.c_int] * 6, AttnShape
+
+    def form(ns, others=0, H=12, dh=64):
+        s = shape(dh, H, len(ns), max(ns), sum(-(-n // 128) for n in ns if 2 * n > max(ns)), others)
+        return s.kc, s.nw, s.kg
+
+    rows128, rows256 = (128, 4, 1), (256, 8, 1)
+    assert [form([n]) for n in (64, 65, 128, 129, 577)] == [rows128] + [(128, 4, 4)] * 2 + [(256, 4, 4)] * 2
+    assert [form([197] * B) for B in (3, 4, 5, 6)] == [(256, 4, 4)] + [(256, 8, 4)] * 2 + [rows256]
+    assert [form([577] * B) for B in (1, 2, 3)] == [(256, 4, 4), (256, 8, 4), rows128]
+    assert [form([400] * B) for B in (4, 5, 6, 10, 11, 16, 17, 21, 22, 26, 27, 32)] == \
+        [rows128] * 2 + [rows256] * 2 + [rows128] * 2 + [rows256] * 2 + [rows128] * 2 + [rows256] * 2
+    assert form([400] * 7 + [384]) == form([400, 197] * 4) == rows128 and form([400] * 7 + [385]) == rows256
+    assert form([577] + [128] * 32) == form([197] + [98] * 64, H=16, dh=80)[:1] + (4, 1) == rows128   # few long ones in a full chip
+    # beside a selection: not up to 256 rows
+    assert form([197], 16) == rows256 and form([101], 16) == rows128 and form([577], 16) == (256, 4, 4) and form([400] * 5, 64) == rows256
+
+
 def _choice():
     choice = _library()._ZN4otas20linear_kernel_choiceEiliii
     choice.argtypes = [ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 3
