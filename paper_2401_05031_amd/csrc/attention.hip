@@ -692,7 +692,9 @@ __global__ __launch_bounds__(kFusedThreads, KG == 1 ? 4 : 2) void attention_plan
 // workgroup of eight waves per (query, head) instead of two of four, with the head's keys and values
 // staged once and in one piece (75 KB at DH = 64, two workgroups per CU): one load phase per
 // workgroup instead of two (measured on MI355X, batch 64, 12 heads: 26.3 us against 27.2 at n = 197,
-// 18.2 against 20.6 at n = 133).  At DH = 64 the same form takes longer sequences whose last block of 256 rows is more than half full
+// 18.2 against 20.6 at n = 133).  On its own and at DH = 64 two
+// workgroups of four are faster where every one finds a CU (7 / 10 queries, 12 heads, 165 tokens 7.2 / 7.3 -> 7.0 / 7.3, 197 8.3 / 8.4 -> 7.5 / 7.8, 256 9.5 /
+// 9.7 -> 8.0 / 8.5; 133 6.3 / 6.4 -> 6.5 / 7.0).  At DH = 64 the same form takes longer sequences whose last block of 256 rows is more than half full
 // (of 320, where it is not, 16 / 32 / 64 queries 18.3 / 27.9 / 45.5 -> 20.2 / 32.1 / 53.3): beside a selection always (passes of 10 / 24 of 485
 // and 197 tokens with r = 23 1148 / 1829 -> 1137 / 1799, 16 of 650 with r = 16 2663 -> 2645), on its own where it halves the rounds of the
 // CUs, all queries having as many blocks.  us, four waves / eight (12 heads): 400 tokens, rounds 1 / 1 (5 queries) 12.7 / 13.7, 2 / 1 (8) 17.0 /
@@ -731,6 +733,7 @@ AttnShape attention_shape(int dh, int H, int B, int max_n, int long_blocks, int 
   }
   const int last = (max_n - 1) % 256 + 1;   // rows of the last block of 256
   auto rounds = [&](int rows) { return (blocks(rows) + 255) / 256; };
+  if (others == 0 && dh == 64 && max_n > 160 && rounds(128) == 1) return shape(128, 4, 1);
   const bool halves = long_blocks == (int64_t)B * ((max_n + 127) / 128) && rounds(128) >= 2 * rounds(256);
   if (max_n > 128 && last > 128 && (max_n <= 256 || (dh == 64 && (others > 0 || halves)))) return shape(dh <= 64 ? 256 : 128, 8, 1);
   return shape(128, 4, 1);

@@ -955,8 +955,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma64_kernel(
   constexpr int KS = BK / 32;
   constexpr int STAGE_A = BM * BK, STAGE_W = BN * BK;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][64][BK]
-  bf16_t* Ws = As + NS * STAGE_A;                 // [NS][64][BK]
+  bf16_t* As = reinterpret_cast<bf16_t*>(smem);   // [NS][BM][BK]
+  bf16_t* Ws = As + NS * STAGE_A;                 // [NS][BN][BK]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -1625,6 +1625,8 @@ static hipError_t linear_mfma_kernel(int kernel, const void* x, const void* w, c
 // differences between kernels are fitted: the absolute figures are those of neither kind of launch.  Over these the picks
 // take 0.30 % longer than the best kernel of each shape in the same pass, 0.42 % by the first fit; on row counts left out
 // of the fit 0.31 and 0.32 against 0.41 and 0.43 (two halves).  At widths of 128 to 512, not fitted to: 2.3 against 2.9 %.
+// Kernels 7 and 3 are priced as what they were fitted as, 64 x 64 and 128 x 128 tiles; pick_small_tile and wide_rows then take a faster
+// tile of theirs where there is one, which the model does not know of: 3600 x 2304 x 768, 16.7 us in 160 x 128 tiles on its own, runs 160 x 256.
 // The choice depends on the shape only, so a shape always runs the same kernel.  The K-step-32 kernel is nowhere the
 // fastest where K is a multiple of 64, and not among the candidates.
 static double rounds_cost(double tiles, int slots, double p) {

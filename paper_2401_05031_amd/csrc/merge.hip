@@ -10,7 +10,8 @@
 //   merge_apply_kernel -- one or two 16-byte chunks of one output row per thread: gathers the listed rows,
 //       accumulates size * x in fp32 in list order, divides by the summed size.  Reads every input
 //       row once and writes every output row once, with no atomics, so results are deterministic.
-// The merging module as an operator of its own runs both in other proportions (launch_token_merge):
+// The merging module as an operator of its own runs both in other proportions where token_merge_in_two says so
+// (launch_merge_select_host, then launch_merge_lists_apply_host):
 //   merge_select_kernel      -- the plan's selection, a query's A tokens dealt to several workgroups.
 //   merge_lists_apply_kernel -- several workgroups per query, each of which works out the query's lists for itself, in
 //       LDS, and averages its share of the output rows.
@@ -169,7 +170,9 @@ __global__ __launch_bounds__(256) void merge_apply_kernel(const T* __restrict__ 
 // applies them: nothing but the selection goes through memory.  The lists and sums are what the two other kernels make.
 // Measured on MI355X (us a call, bf16, D = 768, merge_plan_kernel and merge_apply_kernel / these two): one query of 50 / 197 / 401 / 577
 // tokens 13.0 / 13.1, 16.6 / 14.7, 30.8 / 19.2, 57.9 / 23.1; 16 of them 13.1 / 13.6, 18.0 / 16.2, 34.1 / 21.2, 66.0 / 26.5; 64 14.0 / 14.6, 22.4 /
-// 20.1, 43.1 / 34.3, 81.2 / 62.7; 128 14.9 / 15.5, 28.8 / 27.5, 54.2 / 56.6, 100.7 / 102.9.  Workgroups of 256, 512 and 1024 threads that
+// 20.1, 43.1 / 34.3, 81.2 / 62.7.  Up to 64 queries, which have four workgroups each that apply.  With three (66 ... 85 queries of 129 ... 577
+// tokens, 45 calls at each of three widths) bf16 gains 8 % in the mean (0.96 ... 1.46 times) and float 1 % (0.87 ... 1.33: 85 of 401 at
+// D = 1280 loses most); with two (96 ... 128) 0.94 ... 1.10 and 0.85 ... 1.01 times; with one (144) 0.70 ... 0.95.  Workgroups of 256, 512 and 1024 threads that
 // apply, 1024, 256 and 256 of them in all: 64 of 197 22.5, 21.6, 20.1.
 constexpr int kSelectThreads = 512, kListsApplyThreads = 1024;
 constexpr int kOperatorQueries = 64, kOperatorTokens = 129;   // up to so many queries, from so many tokens on

@@ -65,7 +65,8 @@ def test_how_attention_is_cut_up():
 
     rows128, rows256 = (128, 4, 1), (256, 8, 1)
     assert [form([n]) for n in (64, 65, 128, 129, 577)] == [rows128] + [(128, 4, 4)] * 2 + [(256, 4, 4)] * 2
-    assert [form([197] * B) for B in (3, 4, 5, 6)] == [(256, 4, 4)] + [(256, 8, 4)] * 2 + [rows256]
+    assert [form([197] * B) for B in (3, 4, 5, 6, 10, 11)] == [(256, 4, 4)] + [(256, 8, 4)] * 2 + [rows128] * 2 + [rows256]
+    assert [form([160] * B) for B in (4, 5, 7, 8, 10)] == [(256, 4, 4)] + [(256, 8, 4)] * 2 + [rows256] * 2 and form([161] * 8) == rows128
     assert [form([577] * B) for B in (1, 2, 3)] == [(256, 4, 4), (256, 8, 4), rows128]
     assert [form([400] * B) for B in (4, 5, 6, 10, 11, 16, 17, 21, 22, 26, 27, 32)] == \
         [rows128] * 2 + [rows256] * 2 + [rows128] * 2 + [rows256] * 2 + [rows128] * 2 + [rows256] * 2

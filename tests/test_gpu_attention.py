@@ -31,10 +31,10 @@ CASES = {
     (256, 4, 4, True): [(64, 4, [700, 2]), (64, 2, [513, 1, 257, 256]), (64, 3, [300, 270, 301])],
     (256, 8, 4, False): [(64, 12, [197, 65, 64, 1, 129]), (64, 4, [161, 160, 129, 128, 2, 97, 63, 130, 191, 150, 1, 140, 256, 31])],
     (256, 8, 4, True): [(64, 12, [257, 1, 129, 65]), (64, 12, [400, 193, 2])],
-    (256, 8, 1, False): [(64, 12, [197, 193, 256, 1, 225, 32, 33, 100]), (64, 12, [400, 385, 512, 511, 480, 450])],
+    (256, 8, 1, False): [(64, 12, [197, 193, 256, 1, 225, 32, 33, 100, 129, 160, 161]), (64, 12, [160, 129, 1, 31, 64, 97, 128, 65]), (64, 12, [400, 385, 512, 511, 480, 450])],
     (256, 8, 1, True): [(64, 4, [1000, 897, 1024, 998] * 4)],
     (128, 8, 1, False): [(80, 4, [197, 129, 256, 1, 33, 200] * 2), (96, 2, [130, 256]), (128, 1, [200, 3])],
-    (128, 4, 1, False): [(64, 4, [300, 257, 384, 290, 31, 1] * 8), (64, 3, [100, 128, 1, 65, 33] * 20), (64, 2, [64, 1, 32]),
+    (128, 4, 1, False): [(64, 12, [197, 193, 256, 1, 225, 32, 33, 100]), (64, 12, [161, 160] * 4), (64, 4, [300, 257, 384, 290, 31, 1] * 8), (64, 3, [100, 128, 1, 65, 33] * 20), (64, 2, [64, 1, 32]),
                          (64, 4, [400, 385, 512, 511, 257, 1, 129, 480] * 3),                          (80, 4, [267, 257, 100, 5] * 12)],
     (128, 4, 1, True): [(64, 4, [770, 1000, 1024, 897] * 4), (64, 3, [300, 257, 129, 1] * 51 + [300]), (80, 4, [300, 257, 1] * 21)],
 }

@@ -206,6 +206,7 @@ def test_merge_of_tokens_that_compare_with_none(lib, dtype, n):
 def test_merge_shared_out_equals_one_workgroup_a_query(lib, dtype, D, dm, ns):
     """Up to 64 queries with one of 129 tokens or more share their work between workgroups; with more queries each has one.
     Rows, sizes, offsets and edges bit for bit, with and without sizes and edges, some queries removing nothing."""
+    import ctypes
     import torch
     cfg = synth.Config("op", L=1, D=D, H=8 if D == 768 else 2, F=128, dtype=dtype, B=1, n0=2, seed=17)
     ctx, _ = hz.make_context(cfg)
@@ -229,6 +230,9 @@ def test_merge_shared_out_equals_one_workgroup_a_query(lib, dtype, D, dm, ns):
         return out, so, src, dst, np.asarray(o)
 
     B = len(ns)
+    in_two = ctypes.CDLL(lib.lib_path())._ZN4otas18token_merge_in_twoEiii
+    in_two.argtypes, in_two.restype = [ctypes.c_int] * 3, ctypes.c_bool
+    assert (in_two(B, max(ns), dm) or max(ns) * dm > 64 * 1024) and not in_two(65, max(ns), dm)   # (B tokens that LDS does not hold)
     for sz in (None, sizes):
         want = run(65, sz, True)
         end, edges = int(want[4][B]), int(off[B]) - int(want[4][B])
